@@ -12,7 +12,7 @@
 // 4 consecutive columns of a row of C: the epilogue (bias, residual, rounding to bf16) writes 8 bytes
 // per store.
 //
-// fp32: plain LDS-tiled FMA kernel (used by the small fp32 configurations, which are launch bound).
+// fp32: kernels_gemm_f32.hip.
 #include <cstdlib>
 #include <stdexcept>
 
@@ -223,67 +223,6 @@ __global__ void __launch_bounds__(256) splitk_reduce_k(const float *__restrict__
     }
 }
 
-// ---------------------------------------------------------------- fp32
-template <bool AKM, bool BKM>
-__global__ void __launch_bounds__(256) gemm_f32_k(const float *__restrict__ A, int64_t lda, const float *__restrict__ B,
-                                                  int64_t ldb, const float *__restrict__ bias,
-                                                  const float *__restrict__ resid, int64_t ldr, float *__restrict__ C,
-                                                  int64_t ldc, int64_t M, int64_t N, int64_t K,
-                                                  float *__restrict__ rowsum, int rowsum_acc) {
-    constexpr int BT = 64, BKK = 16;
-    __shared__ float As[BKK][BT + 1];
-    __shared__ float Bs[BKK][BT + 1];
-    const int tid = threadIdx.x;
-    const int64_t m0 = (int64_t)blockIdx.y * BT, n0 = (int64_t)blockIdx.x * BT;
-    const int ty = tid / 16, tx = tid % 16;             // thread computes rows ty*4.., cols tx*4..
-    float acc[4][4] = {};
-    float rsum = 0.f;                                     // fused row sums of A (first tile column, thread = row)
-    const bool do_rowsum = rowsum != nullptr && blockIdx.x == 0 && tid < BT;
-    for (int64_t k0 = 0; k0 < K; k0 += BKK) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = tid + i * 256;                 // 0..1023
-            int r, kk;
-            if (AKM) { r = e % BT; kk = e / BT; } else { kk = e % BKK; r = e / BKK; }
-            const int64_t gm = m0 + r, gk = k0 + kk;
-            As[kk][r] = (gm < M && gk < K) ? (AKM ? A[gk * lda + gm] : A[gm * lda + gk]) : 0.f;
-            if (BKM) { r = e % BT; kk = e / BT; } else { kk = e % BKK; r = e / BKK; }
-            const int64_t gn = n0 + r, gkb = k0 + kk;
-            Bs[kk][r] = (gn < N && gkb < K) ? (BKM ? B[gkb * ldb + gn] : B[gn * ldb + gkb]) : 0.f;
-        }
-        __syncthreads();
-        if (do_rowsum)
-#pragma unroll
-            for (int kk = 0; kk < BKK; ++kk) rsum += As[kk][tid];
-#pragma unroll
-        for (int kk = 0; kk < BKK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    if (do_rowsum && m0 + tid < M) rowsum[m0 + tid] = rsum + (rowsum_acc ? rowsum[m0 + tid] : 0.f);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float x = acc[i][j];
-            if (bias) x += bias[n];
-            if (resid) x += resid[m * ldr + n];
-            C[m * ldc + n] = x;
-        }
-    }
-}
-
 }  // namespace
 
 template <int BM, int BN, int BK, int WGM, int WGN, int NBUF>
@@ -371,13 +310,7 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
         // operands too large for 32-bit buffer offsets: plain kernel with 64-bit addressing
         launch_bf16<128, 128, 64, 2, 2, 1>(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, workspace, splits, accumulate);
     } else {
-        const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-#define TIO_GEMM_ARGS (const float *)A, lda, (const float *)B, ldb, (const float *)bias, (const float *)resid, ldr, (float *)C, ldc, M, N, K, (float *)rowsum, (int)accumulate
-        if (!a_km && !b_km) gemm_f32_k<false, false><<<grid, 256, 0, s>>>(TIO_GEMM_ARGS);
-        else if (!a_km && b_km) gemm_f32_k<false, true><<<grid, 256, 0, s>>>(TIO_GEMM_ARGS);
-        else if (a_km && b_km) gemm_f32_k<true, true><<<grid, 256, 0, s>>>(TIO_GEMM_ARGS);
-        else gemm_f32_k<true, false><<<grid, 256, 0, s>>>(TIO_GEMM_ARGS);
-#undef TIO_GEMM_ARGS
+        gemm_f32(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, accumulate);
     }
 }
 

@@ -1,0 +1,260 @@
+// fp32 GEMM for gfx950 on the fp32 matrix instruction: C[M,N] = A . B^T (+bias) (+residual), for every combination of
+// operand layouts, with the row sums of A from the same launch.
+//
+// v_mfma_f32_32x32x2_f32 multiplies and adds in fp32 like a chain of fused multiply-adds, at 256 flops per clock and
+// compute unit: twice what scalar (not packed) vector instructions reach, from one register per operand instead of
+// an LDS read per multiply-add.  Bound: the matrix cores (157 TFLOP/s) for products that fill the chip, launch and memory
+// latency for the tiny ones.
+//
+//  * a contraction tile of BK elements goes global -> registers (two tiles ahead) -> one of two LDS stages; one barrier a tile;
+//  * contraction index contiguous: LDS [row][BK + 4], read 16 bytes at a time (rows 4 banks apart modulo 64: no conflicts);
+//    contraction index slow: LDS [k][rows + 8], read 4 bytes at a time (the two lane halves are 4 k-rows = 32 banks apart);
+//  * a lane half takes k = 8c + 4 half + j in product j of chunk c, on both operands alike;
+//  * small outputs have too few tiles to fill 256 compute units and too short a contraction to hide a memory latency, so
+//    their tile is 32x32 and the four wavefronts of a workgroup split every contraction tile between them; the four
+//    partial tiles are added in wavefront order.
+// Measured figures stand at the choice of the tile in gemm_f32.
+#include "../../include/teraio.h"
+#include "device_common.h"
+#include "kernels.h"
+#include "mfma_tiles.h"
+
+namespace tio {
+namespace k {
+
+namespace {
+
+template <int ROWS, int BK, int NT, bool KM> struct F32Operand {
+    static constexpr int PITCH = KM ? ROWS + 8 : BK + 4;
+    static constexpr int FLOATS = KM ? BK * PITCH : ROWS * PITCH;
+    static constexpr int PER = ROWS * BK / 4 / NT;                // 16-byte chunks per thread and tile
+    static constexpr int CPR = KM ? ROWS / 4 : BK / 4;            // chunks per LDS row
+    static_assert(PER >= 1 && PER * NT * 4 == ROWS * BK, "chunks divide over the threads");
+    const float *p[PER];
+    int64_t step;                                                // floats from one contraction tile to the next
+    int rows, slow_rows;                                          // rows of the operand in this tile; some chunk holds both valid and other rows
+    __device__ __forceinline__ void init(const float *base, int64_t ld, int rows_valid, int tid) {
+        rows = rows_valid;
+        slow_rows = KM && rows_valid < ROWS && (rows_valid & 3);
+        step = KM ? (int64_t)BK * ld : BK;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = i * NT + tid, o = c / CPR, q = c % CPR;
+            // rows past the end read a valid row: what comes out of them is never stored
+            if (KM) p[i] = base + (int64_t)o * ld + (q * 4 + 4 <= rows_valid ? q * 4 : 0);
+            else p[i] = base + (int64_t)(o < rows_valid ? o : rows_valid - 1) * ld + q * 4;
+        }
+    }
+    __device__ __forceinline__ void load(float4 (&r)[PER], int kt) const {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) r[i] = *reinterpret_cast<const float4 *>(p[i] + kt * step);
+    }
+    // the last tile of a contraction that is no multiple of BK, and tiles with a partly valid chunk: element by element,
+    // nothing at or past the end is read
+    __device__ void load_edge(float4 (&r)[PER], const float *base, int64_t ld, int kt, int kvalid, int tid) const {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = i * NT + tid, o = c / CPR, q = c % CPR;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = KM ? q * 4 + e : o, k = KM ? o : q * 4 + e;
+                const bool ok = row < rows && k < kvalid;
+                v[e] = ok ? base[kt * step + (KM ? (int64_t)k * ld + row : (int64_t)row * ld + k)] : 0.f;
+            }
+            r[i] = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    }
+    static __device__ __forceinline__ void store(float *lds, const float4 (&r)[PER], int tid) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int c = i * NT + tid;
+            *reinterpret_cast<float4 *>(lds + (c / CPR) * PITCH + (c % CPR) * 4) = r[i];
+        }
+    }
+    // the four values of chunk c for row `row`: k = 8c + 4 lhi + 0..3
+    static __device__ __forceinline__ void frag(float (&f)[4], const float *lds, int row, int c, int lhi) {
+        if (KM) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = lds[(c * 8 + lhi * 4 + j) * PITCH + row];
+        } else {
+            const float4 v = *reinterpret_cast<const float4 *>(lds + row * PITCH + c * 8 + lhi * 4);
+            f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+        }
+    }
+    static __device__ __forceinline__ float at(const float *lds, int row, int k) { return KM ? lds[k * PITCH + row] : lds[row * PITCH + k]; }
+};
+
+template <int BM, int BN, int BK, int WGM, int WGN, int KG, bool AKM, bool BKM>
+__global__ void __launch_bounds__(WGM *WGN *KG * 64)
+    gemm_f32_mfma_k(const float *__restrict__ A, int64_t lda, const float *__restrict__ B, int64_t ldb,
+                    const float *__restrict__ bias, const float *resid, int64_t ldr, float *C, int64_t ldc, int64_t M,
+                    int64_t N, int64_t K, int tiles_m, int tiles_n, float *__restrict__ rowsum, int rowsum_acc) {
+    constexpr int NT = WGM * WGN * KG * 64, TPR = NT / BM;
+    constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
+    constexpr int CH = BK / 8 / KG;                               // chunks of eight k per wavefront and tile
+    static_assert(TPR <= 64 && (TPR & (TPR - 1)) == 0 && BK % TPR == 0 && CH >= 1, "row-sum mapping, chunks per wavefront");
+    using OpA = F32Operand<BM, BK, NT, AKM>;
+    using OpB = F32Operand<BN, BK, NT, BKM>;
+    constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
+    constexpr int RED = (KG - 1) * BM * BN;
+    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE > RED ? 2 * STAGE : RED];
+
+    const int total = tiles_m * tiles_n;
+    const int bid = (int)(blockIdx.x % 8) * ((total + 7) / 8) + (int)(blockIdx.x / 8);      // neighbouring tiles on one XCD
+    if (bid >= total) return;
+    const int tm = bid % tiles_m, tn = bid / tiles_m;
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
+    const int kg = wave % KG, wt = wave / KG, wm = wt / WGN, wn = wt % WGN;
+
+    const float *baseA = AKM ? A + m0 : A + m0 * lda, *baseB = BKM ? B + n0 : B + n0 * ldb;
+    OpA oa;
+    OpB ob;
+    oa.init(baseA, lda, (int)(M - m0 < BM ? M - m0 : BM), tid);
+    ob.init(baseB, ldb, (int)(N - n0 < BN ? N - n0 : BN), tid);
+    const int nk = (int)((K + BK - 1) / BK), nkf = (int)(K / BK), rem = (int)(K - (int64_t)nkf * BK);
+    const bool edge_rows = oa.slow_rows || ob.slow_rows;
+
+    float4 ra[2][OpA::PER], rb[2][OpB::PER];
+    auto load = [&](int set, int kt) {
+        if (kt < nkf && !edge_rows) {
+            oa.load(ra[set], kt);
+            ob.load(rb[set], kt);
+        } else {
+            const int kv = kt < nkf ? BK : rem;
+            oa.load_edge(ra[set], baseA, lda, kt, kv, tid);
+            ob.load_edge(rb[set], baseB, ldb, kt, kv, tid);
+        }
+    };
+    auto store = [&](int set) {
+        OpA::store(smem + set * STAGE, ra[set], tid);
+        OpB::store(smem + set * STAGE + OpA::FLOATS, rb[set], tid);
+    };
+
+    floatx16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    const bool do_rowsum = rowsum != nullptr && tn == 0;
+    float rsum = 0.f;
+
+    load(0, 0);
+    if (nk > 1) load(1, 1);
+    store(0);
+    __syncthreads();
+    auto tile = [&](int set, int kt) {                // stage `set` holds tile kt, the other register set tile kt + 1
+        if (kt + 2 < nk) load(set, kt + 2);
+        const float *As = smem + set * STAGE, *Bs = As + OpA::FLOATS;
+        if (do_rowsum) {
+#pragma unroll 4
+            for (int j = 0; j < BK / TPR; ++j) rsum += OpA::at(As, tid / TPR, (tid % TPR) * (BK / TPR) + j);
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            float fa[TM][4], fb[TN][4];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) OpA::frag(fa[i], As, wm * WM + i * 32 + l32, kg * CH + c, lhi);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) OpB::frag(fb[j], Bs, wn * WN + j * 32 + l32, kg * CH + c, lhi);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+        }
+        if (kt + 1 < nk) store(set ^ 1);
+        __syncthreads();
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+        tile(0, kt);
+        if (kt + 1 < nk) tile(1, kt + 1);
+    }
+
+    if (do_rowsum) {
+#pragma unroll
+        for (int o = 1; o < TPR; o <<= 1) rsum += __shfl_xor(rsum, o, 64);
+        const int64_t m = m0 + tid / TPR;
+        if (tid % TPR == 0 && m < M) rowsum[m] = rsum + (rowsum_acc ? rowsum[m] : 0.f);
+    }
+    if (KG > 1) {                                     // the last barrier came after every read of the stages
+        if (kg > 0) {
+            float *dst = smem + ((kg - 1) * (WGM * WGN) + wt) * (WM * WN) + lane;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) dst[((i * TN + j) * 16 + r) * 64] = acc[i][j][r];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int g = 1; g < KG; ++g) {
+            const float *src = smem + ((g - 1) * (WGM * WGN) + wt) * (WM * WN) + lane;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] += src[((i * TN + j) * 16 + r) * 64];
+        }
+    }
+    // lane l holds column l % 32: every store instruction writes two full 128-byte row pieces
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int64_t n = n0 + wn * WN + j * 32 + l32;
+        if (n >= N) continue;
+        const float bn = bias ? bias[n] : 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t m = m0 + wm * WM + i * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
+                if (m < M) C[m * ldc + n] = acc[i][j][r] + bn + (resid ? resid[m * ldr + n] : 0.f);
+            }
+    }
+}
+
+template <int BM, int BN, int BK, int WGM, int WGN, int KG>
+void launch(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const float *B,
+            int64_t ldb, const float *bias, const float *resid, int64_t ldr, float *C, int64_t ldc, float *rowsum, bool accumulate) {
+    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
+    const unsigned grid = 8 * (((unsigned)tiles_m * tiles_n + 7) / 8);
+    constexpr int NT = WGM * WGN * KG * 64;
+#define TIO_F32(AKM, BKM) gemm_f32_mfma_k<BM, BN, BK, WGM, WGN, KG, AKM, BKM><<<grid, NT, 0, s>>>(A, lda, B, ldb, bias, resid, ldr, \
+                                                                                  C, ldc, M, N, K, tiles_m, tiles_n, rowsum, (int)accumulate)
+    if (!a_km && !b_km) TIO_F32(false, false);
+    else if (!a_km && b_km) TIO_F32(false, true);
+    else if (a_km && b_km) TIO_F32(true, true);
+    else TIO_F32(true, false);
+#undef TIO_F32
+}
+
+}  // namespace
+
+void gemm_f32(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
+              int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, bool accumulate) {
+    // 32x32 tiles while 64x64 ones would leave compute units without work.  Microseconds, 32 / 64 / (not kept) 128 square, both
+    // operands contraction-contiguous:
+    //   128 x 512 x 128      5.5 /   7.2 /  20        1024 x  768 x 3072 (192 tiles of 64)   57 /  74 / 253
+    //   128 x 128 x 1024    12.4 /  27   /  91         896 x 1024 x 2048 (224)                55 /  52 / 173
+    //   512 x 512 x 512      8.7 /  15.7 /  50        1024 x 1280 x 2048 (320)                75 /  79 / 172
+    //  2048 x 2048 x 2048  203   / 160   / 174        1024 x 1792 x 2048 (448)                96 /  80 / 172
+    // The first kernel here (64x64 tiles on the vector ALU) took 62 us for 128 x 128 x 1024 and about 300 us for 1024 x 3072 x 768,
+    // now 53.  128x128 tiles leave one wavefront per SIMD where the others leave three, and lose everywhere.
+#define TIO_F32_ARGS s, a_km, b_km, M, N, K, (const float *)A, lda, (const float *)B, ldb, (const float *)bias, (const float *)resid, ldr, \
+                     (float *)C, ldc, (float *)rowsum, accumulate
+    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    if (tiles64 >= 224) launch<64, 64, 32, 2, 2, 1>(TIO_F32_ARGS);
+    else launch<32, 32, 64, 1, 1, 4>(TIO_F32_ARGS);
+#undef TIO_F32_ARGS
+}
+
+}  // namespace k
+}  // namespace tio

@@ -1,0 +1,45 @@
+"""GPU: fp32 products at the sizes where the dispatch changes its tile (32 or 64 square) and at the edges of tiles and of
+contraction tiles, against numpy in 64 bits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # M, N, K: 32x32 tiles, then 64x64 tiles; whole, one short, one over
+    (32, 32, 64), (1, 1, 1), (31, 33, 63), (65, 97, 200),
+    (896, 1024, 32), (1024, 1024, 64), (1021, 1019, 97),
+]
+
+
+@pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", CASES)
+def test_fp32_products(M, N, K, a_km, b_km):
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"fp32 gemm M={M} N={N} K={K} a_km={a_km} b_km={b_km}", flush=True)
+    r8 = lambda n: (n + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    A = torch.randn((M, K), device="cuda", generator=g)
+    B = torch.randn((N, K), device="cuda", generator=g)
+
+    def stored(X, km):                      # padding is NaN: it must never leak
+        X = X.t() if km else X
+        t = torch.full((X.shape[0], r8(X.shape[1])), float("nan"), device="cuda")
+        t[:, :X.shape[1]] = X
+        return t
+    dA, dB = stored(A, a_km), stored(B, b_km)
+    bias = torch.randn(r8(N), device="cuda", generator=g)
+    R = torch.randn((M, r8(N)), device="cuda", generator=g)
+    C, rs = torch.full((M, r8(N)), 7.0, device="cuda"), torch.full((r8(M) + 8,), 7.0, device="cuda")
+    tio.tio_op_gemm(0, "fp32", a_km, b_km, M, N, K, dA.data_ptr(), dA.shape[1], dB.data_ptr(), dB.shape[1], bias.data_ptr(),
+                    R.data_ptr(), r8(N), C.data_ptr(), r8(N), rs.data_ptr())
+    torch.cuda.synchronize()
+    ref = (A.double() @ B.double().t() + bias[:N].double() + R[:, :N].double()).cpu().numpy()
+    mag = (A.abs().double() @ B.abs().double().t()).cpu().numpy() + np.abs(ref)
+    got = C.cpu().numpy().astype(np.float64)
+    # one rounding of 2^-24 per addition of a chain of K products and two epilogue terms
+    assert np.all(np.abs(got[:, :N] - ref) <= (K + 3) * 2.0 ** -24 * mag)
+    assert np.all(got[:, N:] == 7.0)
+    sums = rs.cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(sums[:M] - A.double().sum(1).cpu().numpy()) <= (K + 3) * 2.0 ** -24 * A.abs().double().sum(1).cpu().numpy() + 1e-30)
+    assert np.all(sums[M:] == 7.0)
