@@ -1,9 +1,8 @@
 // Dense contractions of the training step: C[M,N] = A . B^T (+bias) (+residual).
 //
-// bf16: the MFMA kernel of kernels_gemm_dl.hip (operand tiles loaded straight into LDS) does the work, the pipelined
-// kernel of kernels_gemm_pipe.hip (tiles staged through registers) where that one does not apply; this file holds the dispatch,
-// the split-K reduction and a plain MFMA kernel with 64-bit addressing that takes over when an operand is
-// too large for the pipelined kernel's 32-bit buffer offsets.  In the plain kernel a workgroup owns a
+// bf16: the MFMA kernel of kernels_gemm_dl.hip (operand tiles loaded straight into LDS) does the work; this file holds the
+// dispatch, the split-K reduction and a plain MFMA kernel with 64-bit addressing that takes over when an operand is
+// too large for the first one's 32-bit buffer offsets.  In the plain kernel a workgroup owns a
 // BM x BN tile of C; both operand tiles are staged through LDS in [row][k] order with a 16-byte row
 // pad, so that every MFMA operand is one 16-byte LDS read.  Operands that are stored with the
 // contraction index as the slow dimension ("k-major": the weight in dX = dY.W, both operands in
@@ -13,7 +12,6 @@
 // per store.
 //
 // fp32: kernels_gemm_f32.hip.
-#include <cstdlib>
 #include <stdexcept>
 
 #include "../../include/teraio.h"
@@ -256,18 +254,6 @@ static void launch_bf16(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t 
     }
 }
 
-static int gemm_cfg_override() {
-    static int v = -2;
-    if (v == -2) { const char *e = getenv("TIO_GEMM_CFG"); v = e ? atoi(e) : -1; }
-    return v;
-}
-
-static bool gemm_direct_enabled() {
-    static int v = -1;
-    if (v < 0) { const char *e = getenv("TIO_GEMM_DIRECT"); v = e ? (atoi(e) != 0) : 1; }
-    return v != 0;
-}
-
 void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
           const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc,
           void *rowsum, void *workspace, int splits, bool accumulate) {
@@ -283,24 +269,14 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
         ldr = ldc;
     }
     if (dtype == TIO_PREC_BF16) {
-        // The pipelined kernel is the default.  Its 256x256 tiles (eight wavefronts, 128x64 each: fewer LDS
-        // bytes per MFMA) run one per CU, its 128x128 tiles two per CU at about 0.8 of the large tile's rate
-        // (measured on 768- to 5120-wide products); the choice goes to the one that loses less to the last,
-        // partly filled round over the 256 CUs.  TIO_GEMM_CFG forces a choice: 0 plain kernel, 1 pipelined 128x128,
-        // 2 pipelined 256x256.
+        // 256x256 tiles run one per CU, 128x128 tiles two per CU at about 0.8 of the large tile's rate (measured on 768- to
+        // 5120-wide products); the choice goes to the one that loses less to the last, partly filled round over the 256 CUs.
         const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
         const int64_t small_tiles = ((M + 127) / 128) * ((N + 127) / 128) * (splits > 1 ? splits : 1);
         auto fill = [](int64_t tiles, int64_t slots) { return (double)tiles / (double)((tiles + slots - 1) / slots * slots); };
-        const bool large = splits <= 1 && fill(big_tiles, 256) >= 0.8 * fill(small_tiles, 512);
-        const int ov = gemm_cfg_override();
-        const int pipe_cfg = ov == 1 ? 0 : ov == 2 ? 1 : (large ? 1 : 0);
-        // first choice: operand tiles straight from global memory into LDS; the kernel that stages them through
-        // registers takes the products it refuses (K not a multiple of 8); TIO_GEMM_DIRECT=0 switches the first one off
+        const bool large = splits <= 1 && big_tiles >= 128 && fill(big_tiles, 256) >= 0.8 * fill(small_tiles, 512);
         float *const wsp = splits > 1 ? (float *)workspace : nullptr;
-        if (ov != 0 && ((gemm_direct_enabled() && gemm_bf16_direct(s, pipe_cfg, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C,
-                                                                   ldc, rowsum, wsp, splits, accumulate)) ||
-                        gemm_bf16_pipelined(s, pipe_cfg, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, wsp,
-                                            splits, accumulate))) {
+        if (gemm_bf16_direct(s, large ? 1 : 0, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, wsp, splits, accumulate)) {
             if (splits > 1) {
                 const int64_t n = M * (N / 4) + (rowsum ? M : 0);
                 splitk_reduce_k<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const float *)workspace, (uint16_t *)C, ldc, (uint16_t *)rowsum, M, N, splits, (int)accumulate);

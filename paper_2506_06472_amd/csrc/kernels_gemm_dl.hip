@@ -11,9 +11,19 @@
 //      contraction index slow ("k-major"): LDS row k holds ROWS elements, chunk c at slot c ^ ((k & 3) << 2):
 //      the four k-rows a transposing read touches together fall into different 64-byte bank groups, and
 //      the 32 consecutive bytes four lanes read stay consecutive;
-//  * two stages in LDS; the loads of tile t+2 are issued right after the barrier that retires tile t, so they have
-//    a whole tile of MFMAs to land; MFMA fragments are double-buffered in registers across contraction steps and
-//    across the barrier.
+//  * four wavefronts, one per SIMD, with a quarter of the output tile each (128x128 of 256x256): a third less LDS traffic
+//    per flop than eight.  One wavefront per SIMD hides nothing by switching, so the order of every product, fragment read and
+//    tile load is pinned: a tile of 64 is two contraction steps, fragments double-buffered in registers across steps and across
+//    the one barrier a tile has;
+//  * LDS holds D and a half contraction tiles (a ring per operand, 2.5 of 256x256), so that the loads are spread evenly over a tile
+//    and are issued D - 1 to D - 0.5 tiles before they are waited for.
+// Bound: the power limit on operands with many set bits (the clock follows it), the matrix cores otherwise.  Measured, 4096 x
+// 4096 x 8192, contraction-contiguous operands, TFLOP/s on normal values / on zeros: eight wavefronts of 128x64 with 32x32x16
+// products and two stages 1333 / 1775; four wavefronts with 16x16x32 products 1435 / 1795; with the loads spread over the tile
+// 1492 / 2049 (without any loads 2146 on zeros: issued in a burst they fill the queue and stall the wavefront's products).
+// Prefetching lines into the L2 four tiles ahead as well: 1406 / 1795, the extra traffic costs more clock than it saves.
+#include <type_traits>
+
 #include "../../include/teraio.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -25,14 +35,36 @@ namespace k {
 namespace {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-template <int ROWS, int BK, int NT, bool KM> struct DlOperand;
+constexpr int BK = 64;                                          // contraction tile
+
+// c += a . b with the accumulator held in an accumulation register, where it stays: left to itself the compiler moves
+// accumulators between the two register files around almost every product of a kernel that uses most of both.  It does not
+// know the instruction's hazards from here: settle() stands wherever an accumulator is written or read by something else.
+__device__ __forceinline__ void mfma_acc(floatx4 &c, const bf16x8 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// The same with a tile load (see load_to_lds_b128) behind it: the product fills the wait state that M0 needs.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void mfma_acc_load(floatx4 &c, const bf16x8 &a, const bf16x8 &b, i32x4 rsrc, uint32_t lds_addr, uint32_t voff,
+                                              uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %3\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tbuffer_load_dwordx4 %4, %5, %6 offen lds"
+                 : "+a"(c)
+                 : "v"(a), "v"(b), "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+#pragma clang diagnostic pop
+__device__ __forceinline__ void settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+template <int ROWS, int NT, bool KM> struct DlOperand;
 
 // ---- contraction index contiguous
-template <int ROWS, int BK, int NT> struct DlOperand<ROWS, BK, NT, false> {
-    static_assert(BK == 64, "one LDS row is eight 16-byte chunks");
-    static constexpr int BYTES = ROWS * 128;
+template <int ROWS, int NT> struct DlOperand<ROWS, NT, false> {
+    static constexpr int BYTES = ROWS * BK * 2;
     static constexpr int BLOCKS = BYTES / 1024, NW = NT / 64, PER = BLOCKS / NW;     // 1 KiB blocks per wavefront
+    static constexpr int READS = 1;                             // LDS read instructions per fragment
     static_assert(BLOCKS % NW == 0, "blocks divide over the wavefronts");
     uint32_t voff[PER];
     __device__ __forceinline__ void init(int64_t ld, int rows_valid, int kvalid, int wave, int lane) {
@@ -43,112 +75,84 @@ template <int ROWS, int BK, int NT> struct DlOperand<ROWS, BK, NT, false> {
         }
     }
     static __device__ __forceinline__ uint32_t tile_step(int64_t) { return BK * 2; }
-    __device__ __forceinline__ void load(i32x4 rsrc, uint32_t kb, uint32_t stage, int wave) const {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) load_to_lds_b128(rsrc, stage + (i * NW + wave) * 1024, voff[i], kb);
-    }
     __device__ __forceinline__ void load_one(int i, i32x4 rsrc, uint32_t kb, uint32_t stage, int wave) const {
         load_to_lds_b128(rsrc, stage + (i * NW + wave) * 1024, voff[i], kb);
     }
-    // fragments: lane (l32, lhi) reads chunk 2 ks + lhi of row row0 + sub*32 + l32 (row0 a multiple of 32)
-    uint32_t foff[BK / 16];
+    // fragment: lane l reads chunk 4 ks + l/16 of row row0 + sub*16 + l%16 (row0 a multiple of 16)
+    uint32_t foff[BK / 32];
     __device__ __forceinline__ void init_frag(int row0, int lane) {
-        const int l32 = lane & 31, lhi = lane >> 5, x = (l32 >> 1) & 7;
+        const int l16 = lane & 15, lq = lane >> 4;
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) foff[ks] = (uint32_t)((row0 + l32) * 128 + (((ks * 2 + lhi) ^ x) << 4));
+        for (int ks = 0; ks < BK / 32; ++ks) foff[ks] = (uint32_t)((row0 + l16) * 128 + (((ks * 4 + lq) ^ (l16 >> 1)) << 4));
     }
     __device__ __forceinline__ bf16x8 frag(const unsigned char *stage, int sub, int ks) const {
         Frag f;
-        f.u = *reinterpret_cast<const uint4 *>(stage + foff[ks] + sub * 4096);
+        f.u = *reinterpret_cast<const uint4 *>(stage + foff[ks] + sub * 2048);
         return f.v;
     }
-    template <int TPR> static __device__ __forceinline__ float row_partial(const unsigned char *stage, int row, int part) {
-        float s = 0.f;
-        const int x = (row >> 1) & 7;
-#pragma unroll
-        for (int c = 0; c < 8 / TPR; ++c) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * 128 + (((part * (8 / TPR) + c) ^ x) << 4));
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
+    // zeroes elements kvalid .. of a landed tile (kvalid not a multiple of eight: a load brings whole chunks)
+    static __device__ __forceinline__ void clear_tail(unsigned char *stage, int kvalid, int tid) {
+        for (int r = tid; r < ROWS; r += NT) {
+            unsigned char *chunk = stage + r * 128 + (((kvalid >> 3) ^ ((r >> 1) & 7)) << 4);
+            for (int e = kvalid & 7; e < 8; ++e) reinterpret_cast<uint16_t *>(chunk)[e] = 0;
         }
-        return s;
     }
 };
 
 // ---- contraction index slow: LDS row k = ROWS elements
-template <int ROWS, int BK, int NT> struct DlOperand<ROWS, BK, NT, true> {
+template <int ROWS, int NT> struct DlOperand<ROWS, NT, true> {
     static constexpr int BYTES = ROWS * BK * 2;
     static constexpr int CPK = ROWS / 8;                        // chunks per k-row
     static constexpr int KPB = 64 / CPK;                        // k-rows per 1 KiB block
     static constexpr int BLOCKS = BYTES / 1024, NW = NT / 64, PER = BLOCKS / NW;
+    static constexpr int READS = 2;
     static_assert(BLOCKS % NW == 0 && CPK >= 16 && 64 % CPK == 0, "blocks divide over the wavefronts");
+    static __device__ __forceinline__ int swz(int k) { return ((k & 3) << 2) ^ (((k >> 3) & 1) << 1); }
     uint32_t voff[PER];
     __device__ __forceinline__ void init(int64_t ld, int rows_valid, int kvalid, int wave, int lane) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int b = i * NW + wave, kk = b * KPB + lane / CPK, c = (lane % CPK) ^ ((kk & 3) << 2);
+            const int b = i * NW + wave, kk = b * KPB + lane / CPK, c = (lane % CPK) ^ swz(kk);
             voff[i] = (c * 8 < rows_valid && kk < kvalid) ? (uint32_t)(((int64_t)kk * ld + c * 8) * 2) : DL_OOB;
         }
     }
     static __device__ __forceinline__ uint32_t tile_step(int64_t ld) { return (uint32_t)(BK * ld * 2); }
-    __device__ __forceinline__ void load(i32x4 rsrc, uint32_t kb, uint32_t stage, int wave) const {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) load_to_lds_b128(rsrc, stage + (i * NW + wave) * 1024, voff[i], kb);
-    }
     __device__ __forceinline__ void load_one(int i, i32x4 rsrc, uint32_t kb, uint32_t stage, int wave) const {
         load_to_lds_b128(rsrc, stage + (i * NW + wave) * 1024, voff[i], kb);
     }
     // transposing read: within 16 lanes, lanes 4j..4j+3 address k-row j (32 consecutive bytes); lane i receives
     // column i of four consecutive k
-    static constexpr int SUBS = ROWS / 32 > 4 ? 4 : ROWS / 32;
-    uint32_t foff[4];                                           // per 32-row group of the wavefront's tile
+    uint32_t foff[8];                                           // per 16-row group of the wavefront's tile
     __device__ __forceinline__ void init_frag(int row0, int lane) {
-        const int kk = (lane >> 5) * 8 + ((lane & 15) >> 2);
+        const int kk = (lane >> 4) * 8 + ((lane & 15) >> 2);
 #pragma unroll
-        for (int sub = 0; sub < 4; ++sub) {
-            const int col = row0 + sub * 32 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-            const int c = (col >> 3) ^ ((kk & 3) << 2);
-            foff[sub] = (uint32_t)(kk * (ROWS * 2) + c * 16 + (col & 7) * 2);
+        for (int sub = 0; sub < 8; ++sub) {
+            const int col = row0 + sub * 16 + (lane & 3) * 4;
+            foff[sub] = (uint32_t)(kk * (ROWS * 2) + (((col >> 3) ^ swz(kk)) << 4) + (col & 7) * 2);
         }
     }
     __device__ __forceinline__ bf16x8 frag(const unsigned char *stage, int sub, int ks) const {
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-        const unsigned char *p = stage + foff[sub] + ks * 16 * (ROWS * 2);
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (ROWS * 2)));
+        const unsigned char *p = stage + foff[sub] + ks * 32 * (ROWS * 2);
         union { s16x4 h[2]; bf16x8 v; } f;
-        f.h[0] = lo;
-        f.h[1] = hi;
+        f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p));
+        f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (ROWS * 2)));
         return f.v;
     }
-    template <int TPR> static __device__ __forceinline__ float row_partial(const unsigned char *stage, int row, int part) {
-        float s = 0.f;
-#pragma unroll 8
-        for (int j = 0; j < BK / TPR; ++j) {
-            const int kk = part * (BK / TPR) + j;
-            const int c = (row >> 3) ^ ((kk & 3) << 2);
-            s += bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(stage + kk * (ROWS * 2) + c * 16 + (row & 7) * 2));
-        }
-        return s;
-    }
+    static __device__ __forceinline__ void clear_tail(unsigned char *, int, int) {}       // whole k-rows: masked on their way in
 };
 
-template <int BM, int BN, int BK, int WGM, int WGN, bool AKM, bool BKM>
+template <int BM, int BN, int WGM, int WGN, int D, bool AKM, bool BKM, bool ROWSUM>
 __global__ void __launch_bounds__(WGM *WGN * 64)
     gemm_bf16_dl_k(const uint16_t *__restrict__ A, int64_t lda, const uint16_t *__restrict__ B, int64_t ldb,
                    const uint16_t *__restrict__ bias, const uint16_t *__restrict__ resid, int64_t ldr,
                    uint16_t *__restrict__ C, int64_t ldc, int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n,
                    uint16_t *__restrict__ rowsum, float *__restrict__ ws, int64_t k_chunk, int rowsum_acc, int xsplits) {
     constexpr int NT = WGM * WGN * 64;
-    constexpr int TPR = NT / BM;
-    static_assert(NT % BM == 0 && (TPR & (TPR - 1)) == 0 && TPR <= 8, "row-sum mapping");
-    constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32, KS = BK / 16;
-    static_assert(KS % 2 == 0 && TM <= 4 && TN <= 4, "fragment double buffering needs an even number of contraction steps");
-    constexpr int NREADS = TM * (AKM ? 2 : 1) + TN * (BKM ? 2 : 1);     // LDS read instructions per contraction step
-    using OpA = DlOperand<BM, BK, NT, AKM>;
-    using OpB = DlOperand<BN, BK, NT, BKM>;
-    constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+    constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
+    static_assert(TM <= 8 && TN <= 8 && BK == 64, "two contraction steps of 32 per tile");
+    using OpA = DlOperand<BM, NT, AKM>;
+    using OpB = DlOperand<BN, NT, BKM>;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_dl[];
 
     const int tid = threadIdx.x;
@@ -180,7 +184,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wm = wave / WGN, wn = wave % WGN;
-    const int l32 = lane & 31, lhi = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
 
     const int64_t kbeg = (int64_t)split * k_chunk;
     const int64_t kend = (ws != nullptr && kbeg + k_chunk < K) ? kbeg + k_chunk : K;
@@ -204,133 +208,183 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     oa.init_frag(wm * WM, lane);
     ob.init_frag(wn * WN, lane);
 
-    floatx16 acc[TM][TN];
+    // acc[i][j]: lane l holds C row 16 i + l%16, columns 16 j + 4 (l/16) + 0..3
+    floatx4 acc[TM][TN];
+    float rs[TM];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        rs[i] = 0.f;
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    }
+    // row sums of A: the wavefronts of the first tile column's first column add up their A fragments
+    const bool do_rowsum = ROWSUM && tn == 0 && wn == 0;
 
-    auto load_tile = [&](int kt, int buf) {          // kt < nk
-        const uint32_t st = lds0 + buf * STAGE;
+    // LDS: a ring of D + 1 A tiles, then one of D B tiles.  While tile t is multiplied, the tiles up to t + D - 1 sit there or
+    // are landing; A's spare slot takes A of tile t + D in the first half of the tile, and B's slot of tile t itself takes B of
+    // tile t + D in the second half, when its last fragments are in registers.
+    constexpr uint32_t RINGA = (D + 1) * OpA::BYTES, RINGB = D * OpB::BYTES;
+    auto next_a = [&](uint32_t at) __attribute__((always_inline)) { return at + OpA::BYTES >= RINGA ? 0u : at + OpA::BYTES; };
+    auto next_b = [&](uint32_t at) __attribute__((always_inline)) { return at + OpB::BYTES >= RINGA + RINGB ? RINGA : at + OpB::BYTES; };
+    auto load_tile = [&](int kt, uint32_t at, auto OP) __attribute__((always_inline)) {      // kt < nk; OP 0: A, 1: B
+        constexpr bool isA = OP() == 0;
         if (kt < nkf) {
-            oa.load(rsA, (uint32_t)kt * stepA, st, wave);
-            ob.load(rsB, (uint32_t)kt * stepB, st + OpA::BYTES, wave);
-        } else {                                     // the last, partial tile: chunks beyond the contraction read as zero
-            OpA ta;
-            OpB tb;
-            ta.init(lda, rows_a, rem, wave, lane);
-            tb.init(ldb, rows_b, rem, wave, lane);
-            ta.load(rsA, (uint32_t)kt * stepA, st, wave);
-            tb.load(rsB, (uint32_t)kt * stepB, st + OpA::BYTES, wave);
+#pragma unroll
+            for (int l = 0; l < (isA ? OpA::PER : OpB::PER); ++l) {
+                if (isA) oa.load_one(l, rsA, (uint32_t)kt * stepA, lds0 + at, wave);
+                else ob.load_one(l, rsB, (uint32_t)kt * stepB, lds0 + at, wave);
+            }
+        } else if (isA) {                            // the last, partial tile: chunks beyond the contraction read as zero
+            OpA t;
+            t.init(lda, rows_a, rem, wave, lane);
+#pragma unroll
+            for (int l = 0; l < OpA::PER; ++l) t.load_one(l, rsA, (uint32_t)kt * stepA, lds0 + at, wave);
+        } else {
+            OpB t;
+            t.init(ldb, rows_b, rem, wave, lane);
+#pragma unroll
+            for (int l = 0; l < OpB::PER; ++l) t.load_one(l, rsB, (uint32_t)kt * stepB, lds0 + at, wave);
+        }
+    };
+    // tile kt has landed for every wavefront: what a partial chunk brought from behind the contraction's end goes to zero
+    auto clear_tail = [&](int kt, uint32_t atA, uint32_t atB) __attribute__((always_inline)) {
+        if (kt == nkf && (rem & 7)) {
+            OpA::clear_tail(smem_dl + atA, rem, tid);
+            OpB::clear_tail(smem_dl + atB, rem, tid);
+            __syncthreads();
         }
     };
 
     bf16x8 fa[2][TM], fb[2][TN];
-    auto read_frags = [&](int set, int buf, int ks) {
-        const unsigned char *As = smem_dl + buf * STAGE, *Bs = As + OpA::BYTES;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[set][i] = oa.frag(As, i, ks);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[set][j] = ob.frag(Bs, j, ks);
+    // fragment r of a step in the order the products need them: A row group 0, every B column group, the other A row groups
+    auto read_one = [&](int set, uint32_t atA, uint32_t atB, int ks, int r) __attribute__((always_inline)) {
+        if (r == 0) fa[set][0] = oa.frag(smem_dl + atA, 0, ks);
+        else if (r <= TN) fb[set][r - 1] = ob.frag(smem_dl + atB, r - 1, ks);
+        else fa[set][r - TN] = oa.frag(smem_dl + atA, r - TN, ks);
     };
-    auto mfmas = [&](int set) {
+    constexpr int NQ = TM * TN, NR = TM + TN;
+    // The products of one contraction step from register set S, with the next step's fragment reads and the loads of one
+    // operand tile between them in a pinned order: the reads over the first three quarters, so that the last one has landed
+    // when the step ends; the loads evenly over the whole step (LOADS 0: none, 1: A, 2: B): a compute unit takes sixteen
+    // clocks for each, and a wavefront whose load finds the queue full stalls with its products.
+    auto step = [&](auto S, uint32_t rA, uint32_t rB, auto RKS, auto LOADS, int lkt, uint32_t at) __attribute__((always_inline)) {
+        constexpr int NL = LOADS() == 1 ? OpA::PER : LOADS() == 2 ? OpB::PER : 0;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int i = q / TN, j = q % TN, l = q * NL / NQ;
+            if (NL > 0 && (q == 0 || (q - 1) * NL / NQ != l)) {
+                if (LOADS() == 1) mfma_acc_load(acc[i][j], fb[S()][j], fa[S()][i], rsA, lds0 + at + (l * OpA::NW + wave) * 1024, oa.voff[l % OpA::PER], (uint32_t)lkt * stepA);
+                else mfma_acc_load(acc[i][j], fb[S()][j], fa[S()][i], rsB, lds0 + at + (l * OpB::NW + wave) * 1024, ob.voff[l % OpB::PER], (uint32_t)lkt * stepB);
+            } else {
+                mfma_acc(acc[i][j], fb[S()][j], fa[S()][i]);
+            }
+            if (ROWSUM && j == 0 && do_rowsum) {
+                const Frag f{.v = fa[S()][i]};
+                const uint32_t w[4] = {f.u.x, f.u.y, f.u.z, f.u.w};
+                float t = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
+                rs[i] += t;
+            }
+#pragma unroll
+            for (int r = q * NR * 4 / (NQ * 3); r < (q + 1) * NR * 4 / (NQ * 3) && r < NR; ++r) read_one(S() ^ 1, rA, rB, RKS(), r);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, 2> c2{};
+    constexpr auto wait_vm = [](int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); };      // s_waitcnt vmcnt(n)
+    constexpr int PA = OpA::PER, PB = OpB::PER;
+    static_assert((D - 1) * (PA + PB) < 64, "loads in flight fit the counter");
+
+    // prologue: tiles 0 .. D - 1 on their way, tile 0 landed, fragments of its step 0 in registers
+#pragma unroll
+    for (int t = 0; t < D; ++t)
+        if (t < nk) {
+            load_tile(t, t * OpA::BYTES, c0);
+            load_tile(t, RINGA + t * OpB::BYTES, c1);
+        }
+    if (nk >= D) __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * (PA + PB)));       // the later tiles' loads may be outstanding
+    else __builtin_amdgcn_s_waitcnt(wait_vm(0));
+    __builtin_amdgcn_s_barrier();
+    clear_tail(0, 0, RINGA);
+    if (nk > 0) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) read_one(0, 0, RINGA, 0, r);
+    }
+    auto pin = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
     };
+    pin();
+    settle();
 
-    const bool do_rowsum = rowsum != nullptr && tn == 0;
-    float rsum = 0.f;
-
-    // prologue: tiles 0 and 1 on their way, tile 0 landed, fragments of its step 0 in registers
-    if (nk > 0) load_tile(0, 0);
-    if (nk > 1) load_tile(1, 1);
-    if (nk > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | (OpA::PER + OpB::PER));      // vmcnt: tile 1's loads may be outstanding
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
-    __builtin_amdgcn_s_barrier();
-    if (nk > 0) read_frags(0, 0, 0);
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1, nxt = cur ^ 1;
-        if (do_rowsum) rsum += OpA::template row_partial<TPR>(smem_dl + cur * STAGE, tid / TPR, tid % TPR);
-#pragma unroll
-        for (int ks = 0; ks + 1 < KS; ++ks) {
-            read_frags((ks + 1) & 1, cur, ks + 1);
-            mfmas(ks & 1);
-            // one MFMA, two reads, one MFMA, ...: the reads of the next step are issued under the first MFMAs of this one
-#pragma unroll
-            for (int q = 0; q < NREADS / 2; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - NREADS / 2, 0);
-            __builtin_amdgcn_sched_barrier(0);
+    uint32_t atA = 0, atB = RINGA, spareA = D * OpA::BYTES;      // ring offsets: tile kt's operands, A's spare slot
+    auto tile = [&](int kt, auto FULL) __attribute__((always_inline)) {      // FULL: tile kt + D is a full tile
+        const uint32_t nxA = next_a(atA), nxB = next_b(atB);
+        if (FULL()) {
+            step(c0, atA, atB, c1, c1, kt + D, spareA);
+        } else {
+            if (kt + D < nk) load_tile(kt + D, spareA, c0);
+            step(c0, atA, atB, c1, c0, 0, 0);
         }
-        // tile kt+1 (issued a tile ago) has landed for this wavefront; after the barrier it has landed for all, and
-        // nobody reads stage `cur` any more
-        __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0)
+        // tile kt+1 has landed for this wavefront (later tiles' loads may be outstanding); after the barrier it has landed for
+        // all, and nobody reads tile kt's slots any more
+        if (FULL()) __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * PA + (D - 2) * PB) & 0xC0FF);     // and lgkmcnt(0)
+        else __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
-        if (kt + 1 < nk) read_frags(0, nxt, 0);
-        // the loads of tile kt+2 go out one by one between the MFMAs of the last step
-        const bool full = kt + 2 < nkf;
-        if (!full && kt + 2 < nk) load_tile(kt + 2, cur);
-        {
-            const uint32_t st = lds0 + cur * STAGE;
-            const uint32_t kbA = full ? (uint32_t)(kt + 2) * stepA : DL_OOB, kbB = full ? (uint32_t)(kt + 2) * stepB : DL_OOB;
-#pragma unroll
-            for (int q = 0; q < TM * TN; ++q) {
-                const int i = q / TN, j = q % TN;
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[(KS - 1) & 1][j], fa[(KS - 1) & 1][i], acc[i][j], 0, 0, 0);
-                constexpr int NL = OpA::PER + OpB::PER;
-                if (full) {
-#pragma unroll
-                    for (int l = q * NL / (TM * TN); l < (q + 1) * NL / (TM * TN); ++l) {
-                        if (l < OpA::PER) oa.load_one(l, rsA, kbA, st, wave);
-                        else ob.load_one(l - OpA::PER, rsB, kbB, st + OpA::BYTES, wave);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
         __builtin_amdgcn_sched_barrier(0);
-    }
+        if (FULL()) {
+            step(c1, nxA, nxB, c0, c2, kt + D, atB);
+        } else {
+            if (kt + 1 < nk) clear_tail(kt + 1, nxA, nxB);
+            if (kt + D < nk) load_tile(kt + D, atB, c1);
+            step(c1, nxA, nxB, c0, c0, 0, 0);        // after the last tile these reads fetch nothing that is used
+        }
+        spareA = atA;
+        atA = nxA;
+        atB = nxB;
+    };
+    int kt = 0;
+    for (; kt + D < nkf; ++kt) tile(kt, c1);
+    for (; kt < nk; ++kt) tile(kt, c0);
+    settle();
+    pin();
 
     if (do_rowsum) {
 #pragma unroll
-        for (int o = 1; o < TPR; o <<= 1) rsum += __shfl_xor(rsum, o, 64);
-        const int64_t m = m0 + tid / TPR;
-        if (tid % TPR == 0 && m < M) {
-            if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rsum;
-            else rowsum[m] = (uint16_t)f32_to_bf16_bits(rsum + (rowsum_acc ? bf16_bits_to_f32(rowsum[m]) : 0.f));
+        for (int i = 0; i < TM; ++i) {
+            rs[i] += __shfl_xor(rs[i], 16, 64);
+            rs[i] += __shfl_xor(rs[i], 32, 64);
+            const int64_t m = m0 + wm * WM + i * 16 + l16;
+            if (lq == 0 && m < M) {
+                if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rs[i];
+                else rowsum[m] = (uint16_t)f32_to_bf16_bits(rs[i] + (rowsum_acc ? bf16_bits_to_f32(rowsum[m]) : 0.f));
+            }
         }
     }
-    // epilogue through LDS, 32 rows of a wavefront's tile at a time as fp32 (both stages are free: the last barrier of
+    // epilogue through LDS, 16 rows of a wavefront's tile at a time as fp32 (the rings are free: the last barrier of
     // the loop came after every fragment read)
     {
-        constexpr int SPF = WN + 4, CPR = WN / 8, PASSES = 32 * CPR / 64;
-        static_assert((32 * CPR) % 64 == 0, "a 32-row block is a whole number of wavefront passes");
+        constexpr int SPF = WN + 4, CPR = WN / 8, PASSES = 16 * CPR / 64;
+        static_assert((16 * CPR) % 64 == 0, "a 16-row block is a whole number of wavefront passes");
         const bool wide = (ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0);
-        static_assert((size_t)2 * STAGE >= (size_t)WGM * WGN * 32 * SPF * 4, "the staging blocks fit the two stages");
-        float *stage = reinterpret_cast<float *>(smem_dl) + wave * (32 * SPF);
+        static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * 16 * SPF * 4, "the staging blocks fit the rings");
+        float *stage = reinterpret_cast<float *>(smem_dl) + wave * (16 * SPF);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4 *>(stage + l32 * SPF + j * 32 + q * 8 + lhi * 4) =
-                        make_float4(acc[i][j][q * 4 + 0], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]);
+            for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(stage + l16 * SPF + j * 16 + lq * 4) = acc[i][j];
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int p = 0; p < PASSES; ++p) {
                 const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
                 const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
                 const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
-                const int64_t m = m0 + wm * WM + i * 32 + row, n = n0 + wn * WN + ch * 8;
+                const int64_t m = m0 + wm * WM + i * 16 + row, n = n0 + wn * WN + ch * 8;
                 if (m >= M || n >= N) continue;
                 if (ws) {
                     float *dst = ws + ((int64_t)split * M + m) * N + n;
@@ -372,21 +426,10 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     }
 }
 
-#define TIO_DL_INSTANCE(BM, BN, WGM, WGN, AKM, BKM)                                                                         \
-    template __global__ void gemm_bf16_dl_k<BM, BN, 64, WGM, WGN, AKM, BKM>(                                                \
-        const uint16_t *, int64_t, const uint16_t *, int64_t, const uint16_t *, const uint16_t *, int64_t, uint16_t *, int64_t, \
-        int64_t, int64_t, int64_t, int, int, uint16_t *, float *, int64_t, int, int);
-TIO_DL_INSTANCE(256, 256, 2, 4, false, false) TIO_DL_INSTANCE(256, 256, 2, 4, false, true)
-TIO_DL_INSTANCE(256, 256, 2, 4, true, true) TIO_DL_INSTANCE(256, 256, 2, 4, true, false)
-TIO_DL_INSTANCE(128, 128, 2, 2, false, false) TIO_DL_INSTANCE(128, 128, 2, 2, false, true)
-TIO_DL_INSTANCE(128, 128, 2, 2, true, true) TIO_DL_INSTANCE(128, 128, 2, 2, true, false)
-#undef TIO_DL_INSTANCE
-
-template <int BM, int BN, int BK, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, int D>
 bool launch_dl(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc,
                void *rowsum, float *ws, int splits, bool rowsum_acc) {
-    if (K % 8) return false;                 // a partly valid 16-byte chunk cannot be masked on its way into LDS
     const int64_t k_chunk = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
     const int64_t kspan = splits > 1 ? k_chunk : K;
     const int64_t spanA = a_km ? (kspan + 3 * BK) * lda * 2 : ((int64_t)BM * lda + kspan + 3 * BK) * 2;
@@ -399,22 +442,29 @@ bool launch_dl(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_
     const dim3 grid = xsplits ? dim3((unsigned)(8 * ((tiles + 8 / xsplits - 1) / (8 / xsplits))))
                               : dim3((unsigned)(8 * ((tiles + 7) / 8)), (unsigned)(splits > 1 ? splits : 1));
     const dim3 block(WGM * WGN * 64);
-    constexpr size_t lds = (size_t)2 * (BM + BN) * BK * 2;
-    static bool attr_done = false;
-    if (!attr_done) {
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        (void)hipFuncSetAttribute((const void *)gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        attr_done = true;
+    constexpr size_t lds = (size_t)((D + 1) * BM + D * BN) * BK * 2;
+    static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+#define TIO_DL(AKM, BKM, RS)                                                                                              \
+    do {                                                                                                                  \
+        static const hipError_t raised = hipFuncSetAttribute((const void *)gemm_bf16_dl_k<BM, BN, WGM, WGN, D, AKM, BKM, RS>,  \
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);      \
+        (void)raised;                                                                                                     \
+        gemm_bf16_dl_k<BM, BN, WGM, WGN, D, AKM, BKM, RS><<<grid, block, lds, s>>>(                                          \
+            (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid, ldr,      \
+            (uint16_t *)C, ldc, M, N, K, tiles_m, tiles_n, (uint16_t *)rowsum, ws, k_chunk, (int)rowsum_acc, xsplits);     \
+    } while (0)
+    if (rowsum) {
+        if (!a_km && !b_km) TIO_DL(false, false, true);
+        else if (!a_km && b_km) TIO_DL(false, true, true);
+        else if (a_km && b_km) TIO_DL(true, true, true);
+        else TIO_DL(true, false, true);
+    } else {
+        if (!a_km && !b_km) TIO_DL(false, false, false);
+        else if (!a_km && b_km) TIO_DL(false, true, false);
+        else if (a_km && b_km) TIO_DL(true, true, false);
+        else TIO_DL(true, false, false);
     }
-#define TIO_GEMM_ARGS (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid, ldr, \
-                      (uint16_t *)C, ldc, M, N, K, tiles_m, tiles_n, (uint16_t *)rowsum, ws, k_chunk, (int)rowsum_acc, xsplits
-    if (!a_km && !b_km) gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, false, false><<<grid, block, lds, s>>>(TIO_GEMM_ARGS);
-    else if (!a_km && b_km) gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, false, true><<<grid, block, lds, s>>>(TIO_GEMM_ARGS);
-    else if (a_km && b_km) gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, true, true><<<grid, block, lds, s>>>(TIO_GEMM_ARGS);
-    else gemm_bf16_dl_k<BM, BN, BK, WGM, WGN, true, false><<<grid, block, lds, s>>>(TIO_GEMM_ARGS);
-#undef TIO_GEMM_ARGS
+#undef TIO_DL
     return true;
 }
 
@@ -423,9 +473,13 @@ bool launch_dl(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_
 bool gemm_bf16_direct(hipStream_t s, int cfg, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A,
                       int64_t lda, const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr,
                       void *C, int64_t ldc, void *rowsum, float *ws, int splits, bool rowsum_accumulate) {
-#define TIO_P(BM, BN, BK, WGM, WGN) launch_dl<BM, BN, BK, WGM, WGN>(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, ws, splits, rowsum_accumulate)
-    if (cfg == 1) return TIO_P(256, 256, 64, 2, 4);
-    return TIO_P(128, 128, 64, 2, 2);
+#define TIO_P(BM, BN, WGM, WGN, D) launch_dl<BM, BN, WGM, WGN, D>(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, ws, splits, rowsum_accumulate)
+    if (cfg == 1) return TIO_P(256, 256, 2, 2, 2);
+    // with at most one 128x128 tile per compute unit there is room for a deeper ring: a tile is then 512 clocks long, far less
+    // than a memory latency
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128) * (splits > 1 ? splits : 1);
+    if (tiles <= 256) return TIO_P(128, 128, 2, 2, 4);
+    return TIO_P(128, 128, 2, 2, 2);
 #undef TIO_P
 }
 
