@@ -17,10 +17,10 @@ void norm_fwd(hipStream_t s, int dtype, bool rms, const void *x, const void *g, 
 // rowsum (optional, [M]): sum over k of A[m][k], produced by the same launch (bias gradient of dW);
 // workspace/splits: with splits > 1 and an fp32 workspace of splits*(M*N+M) floats the contraction is
 // cut into `splits` ranges whose partial results are added in order by a second launch
-// bf16 MFMA GEMM whose operand tiles are loaded from global memory straight into LDS (kernels_gemm_dl.hip); cfg 0: 128x128
-// tiles, 1: 256x256 tiles.  Returns false without launching when an operand is too large for 32-bit buffer offsets.  With
+// bf16 MFMA GEMM whose operand tiles are loaded from global memory straight into LDS (kernels_gemm_dl.hip), which
+// also chooses the tile.  Returns false without launching when an operand is too large for 32-bit buffer offsets.  With
 // ws != nullptr the fp32 split-K partials go to ws and the caller runs the reduction.
-bool gemm_bf16_direct(hipStream_t s, int cfg, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A,
+bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A,
                       int64_t lda, const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr,
                       void *C, int64_t ldc, void *rowsum, float *ws, int splits, bool rowsum_accumulate);
 // fp32 products on the fp32 matrix instruction (kernels_gemm_f32.hip); accumulate adds to rowsum (the caller passes C as resid)

@@ -269,14 +269,8 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
         ldr = ldc;
     }
     if (dtype == TIO_PREC_BF16) {
-        // 256x256 tiles run one per CU, 128x128 tiles two per CU at about 0.8 of the large tile's rate (measured on 768- to
-        // 5120-wide products); the choice goes to the one that loses less to the last, partly filled round over the 256 CUs.
-        const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
-        const int64_t small_tiles = ((M + 127) / 128) * ((N + 127) / 128) * (splits > 1 ? splits : 1);
-        auto fill = [](int64_t tiles, int64_t slots) { return (double)tiles / (double)((tiles + slots - 1) / slots * slots); };
-        const bool large = splits <= 1 && big_tiles >= 128 && fill(big_tiles, 256) >= 0.8 * fill(small_tiles, 512);
         float *const wsp = splits > 1 ? (float *)workspace : nullptr;
-        if (gemm_bf16_direct(s, large ? 1 : 0, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, wsp, splits, accumulate)) {
+        if (gemm_bf16_direct(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, wsp, splits, accumulate)) {
             if (splits > 1) {
                 const int64_t n = M * (N / 4) + (rowsum ? M : 0);
                 splitk_reduce_k<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const float *)workspace, (uint16_t *)C, ldc, (uint16_t *)rowsum, M, N, splits, (int)accumulate);

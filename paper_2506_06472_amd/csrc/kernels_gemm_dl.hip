@@ -8,9 +8,9 @@
 //      contraction index contiguous ("k-contig"): LDS row r holds the eight chunks of operand row r, chunk c at
 //      slot c ^ ((r >> 1) & 7): the sixteen rows read together by a quarter wavefront fall into sixteen
 //      different 16-byte bank groups;
-//      contraction index slow ("k-major"): LDS row k holds ROWS elements, chunk c at slot c ^ ((k & 3) << 2):
-//      the four k-rows a transposing read touches together fall into different 64-byte bank groups, and
-//      the 32 consecutive bytes four lanes read stay consecutive;
+//      contraction index slow ("k-major"): LDS row k holds ROWS elements, chunk c at slot c ^ swz(k): the eight
+//      k-rows half a wavefront's transposing read touches fall into different 32-byte bank groups, and the 32 consecutive
+//      bytes four lanes read stay consecutive;
 //  * four wavefronts, one per SIMD, with a quarter of the output tile each (128x128 of 256x256): a third less LDS traffic
 //    per flop than eight.  One wavefront per SIMD hides nothing by switching, so the order of every product, fragment read and
 //    tile load is pinned: a tile of 64 is two contraction steps, fragments double-buffered in registers across steps and across
@@ -90,6 +90,7 @@ template <int ROWS, int NT> struct DlOperand<ROWS, NT, false> {
         f.u = *reinterpret_cast<const uint4 *>(stage + foff[ks] + sub * 2048);
         return f.v;
     }
+    __device__ __forceinline__ void second_step() { foff[0] = foff[1]; }
     // zeroes elements kvalid .. of a landed tile (kvalid not a multiple of eight: a load brings whole chunks)
     static __device__ __forceinline__ void clear_tail(unsigned char *stage, int kvalid, int tid) {
         for (int r = tid; r < ROWS; r += NT) {
@@ -103,16 +104,19 @@ template <int ROWS, int NT> struct DlOperand<ROWS, NT, false> {
 template <int ROWS, int NT> struct DlOperand<ROWS, NT, true> {
     static constexpr int BYTES = ROWS * BK * 2;
     static constexpr int CPK = ROWS / 8;                        // chunks per k-row
-    static constexpr int KPB = 64 / CPK;                        // k-rows per 1 KiB block
     static constexpr int BLOCKS = BYTES / 1024, NW = NT / 64, PER = BLOCKS / NW;
     static constexpr int READS = 2;
-    static_assert(BLOCKS % NW == 0 && CPK >= 16 && 64 % CPK == 0, "blocks divide over the wavefronts");
-    static __device__ __forceinline__ int swz(int k) { return ((k & 3) << 2) ^ (((k >> 3) & 1) << 1); }
+    static_assert(BLOCKS % NW == 0 && ROWS % 64 == 0, "blocks divide over the wavefronts; rows of an even number of 128 bytes");
+    // what the chunk index of k-row k is XORed with: k-rows 0..3 and 8..11 are read together, 32 bytes of each, and have to
+    // fall into eight different 32-byte bank groups; where a row is an odd number of 128 bytes odd rows are 128 bytes off already
+    static __device__ __forceinline__ int swz(int k) {
+        return (ROWS % 128 == 0 ? (k & 3) << 2 : ((k >> 1) & 1) << 2) ^ (((k >> 3) & 1) << 1);
+    }
     uint32_t voff[PER];
     __device__ __forceinline__ void init(int64_t ld, int rows_valid, int kvalid, int wave, int lane) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int b = i * NW + wave, kk = b * KPB + lane / CPK, c = (lane % CPK) ^ swz(kk);
+            const int at = (i * NW + wave) * 64 + lane, kk = at / CPK, c = (at % CPK) ^ swz(kk);
             voff[i] = (c * 8 < rows_valid && kk < kvalid) ? (uint32_t)(((int64_t)kk * ld + c * 8) * 2) : DL_OOB;
         }
     }
@@ -139,8 +143,127 @@ template <int ROWS, int NT> struct DlOperand<ROWS, NT, true> {
         f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * (ROWS * 2)));
         return f.v;
     }
+    __device__ __forceinline__ void second_step() {
+#pragma unroll
+        for (int sub = 0; sub < 8; ++sub) foff[sub] += 32 * ROWS * 2;
+    }
     static __device__ __forceinline__ void clear_tail(unsigned char *, int, int) {}       // whole k-rows: masked on their way in
 };
+
+// Workgroup -> output tile and contraction range; each XCD's L2 sees one contiguous part of the tile sequence (and, where the
+// number of ranges allows it, one range).  false: a padding workgroup.
+__device__ __forceinline__ bool place(int tiles_m, int tiles_n, int xsplits, int &split, int &nsplit, int &tm, int &tn) {
+    const int total_tiles = tiles_m * tiles_n;
+    int bid;
+    if (xsplits) {
+        const int x = (int)(blockIdx.x % 8), i = (int)(blockIdx.x / 8);
+        const int parts = 8 / xsplits, chunk = (total_tiles + parts - 1) / parts;
+        nsplit = xsplits;
+        split = x % xsplits;
+        if (i >= chunk) return false;
+        bid = (x / xsplits) * chunk + i;
+    } else {
+        nsplit = (int)gridDim.y;
+        split = (int)blockIdx.y;
+        bid = (int)(blockIdx.x % 8) * ((total_tiles + 7) / 8) + (int)(blockIdx.x / 8);
+    }
+    if (bid >= total_tiles) return false;
+    // consecutive workgroups walk down GROUP tile rows before moving to the next tile column; products with very many tile
+    // rows (weight gradients of the wide layers) do better with the narrower band (measured: +3..5 % there, -2 % elsewhere)
+    const int GROUP = tiles_m > 64 ? 4 : 8;
+    const int per_group = GROUP * tiles_n;
+    const int g = bid / per_group;
+    const int gm0 = g * GROUP;
+    const int gsz = tiles_m - gm0 < GROUP ? tiles_m - gm0 : GROUP;
+    tm = gm0 + (bid % per_group) % gsz;
+    tn = (bid % per_group) / gsz;
+    return true;
+}
+
+__device__ __forceinline__ float sum_frag(const bf16x8 &v) {
+    const Frag f{.v = v};
+    const uint32_t w[4] = {f.u.x, f.u.y, f.u.z, f.u.w};
+    float t = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
+    return t;
+}
+// row sums of A: lane l's rs[i] is its quarter of the sum of row mw + 16 i + l%16
+template <int TM>
+__device__ __forceinline__ void store_rowsum(float (&rs)[TM], int lane, int64_t mw, int64_t M, int64_t N, uint16_t *rowsum, int accumulate,
+                                             float *ws, int split, int nsplit) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        rs[i] += __shfl_xor(rs[i], 16, 64);
+        rs[i] += __shfl_xor(rs[i], 32, 64);
+        const int64_t m = mw + i * 16 + (lane & 15);
+        if (lane < 16 && m < M) {
+            if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rs[i];
+            else rowsum[m] = (uint16_t)f32_to_bf16_bits(rs[i] + (accumulate ? bf16_bits_to_f32(rowsum[m]) : 0.f));
+        }
+    }
+}
+
+// A wavefront's part of the output tile through LDS, 16 rows at a time as fp32, so that a lane ends up with eight consecutive
+// columns of one row: bias, residual and output (or the fp32 partial tile of a split product) move as whole 16-byte chunks.
+template <int TM, int TN>
+__device__ __forceinline__ void store_tile(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
+                                           const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
+                                           float *__restrict__ ws, int split) {
+    constexpr int WN = TN * 16, SPF = WN + 4, CPR = WN / 8, PASSES = 16 * CPR / 64;
+    static_assert((16 * CPR) % 64 == 0, "a 16-row block is a whole number of wavefront passes");
+    const bool wide = (ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0);
+    const int l16 = lane & 15, lq = lane >> 4;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(stage + l16 * SPF + j * 16 + lq * 4) = acc[i][j];
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int p = 0; p < PASSES; ++p) {
+                    const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
+                    const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
+                    const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
+                    const int64_t m = mw + i * 16 + row, n = nw + ch * 8;
+                    if (m >= M || n >= N) continue;
+                    if (ws) {
+                        float *dst = ws + ((int64_t)split * M + m) * N + n;
+                        *reinterpret_cast<float4 *>(dst) = x0;
+                        if (n + 4 < N) *reinterpret_cast<float4 *>(dst + 4) = x1;
+                        continue;
+                    }
+                    float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                    if (n + 8 <= N && wide) {
+                        if (bias) {
+                            const uint4 t = *reinterpret_cast<const uint4 *>(bias + n);
+                            const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
+                        }
+                        if (resid) {
+                            const uint4 t = *reinterpret_cast<const uint4 *>(resid + m * ldr + n);
+                            const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
+                        }
+                        uint4 o;
+                        o.x = pack_bf16x2(v[0], v[1]);
+                        o.y = pack_bf16x2(v[2], v[3]);
+                        o.z = pack_bf16x2(v[4], v[5]);
+                        o.w = pack_bf16x2(v[6], v[7]);
+                        *reinterpret_cast<uint4 *>(C + m * ldc + n) = o;
+                    } else {
+                        for (int e = 0; e < 8 && n + e < N; ++e) {
+                            float x = v[e];
+                            if (bias) x += bf16_bits_to_f32(bias[n + e]);
+                            if (resid) x += bf16_bits_to_f32(resid[m * ldr + n + e]);
+                            C[m * ldc + n + e] = (uint16_t)f32_to_bf16_bits(x);
+                        }
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+}
 
 template <int BM, int BN, int WGM, int WGN, int D, bool AKM, bool BKM, bool ROWSUM>
 __global__ void __launch_bounds__(WGM *WGN * 64)
@@ -156,35 +279,12 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_dl[];
 
     const int tid = threadIdx.x;
-    const int total_tiles = tiles_m * tiles_n;
-    int split, nsplit, bid;
-    if (xsplits) {
-        const int x = (int)(blockIdx.x % 8), i = (int)(blockIdx.x / 8);
-        const int parts = 8 / xsplits, chunk = (total_tiles + parts - 1) / parts;
-        nsplit = xsplits;
-        split = x % xsplits;
-        if (i >= chunk) return;
-        bid = (x / xsplits) * chunk + i;
-    } else {
-        nsplit = (int)gridDim.y;
-        split = (int)blockIdx.y;
-        bid = (int)(blockIdx.x % 8) * ((total_tiles + 7) / 8) + (int)(blockIdx.x / 8);
-    }
-    if (bid >= total_tiles) return;
-    // consecutive workgroups walk down GROUP tile rows before moving to the next tile column; products with very many tile
-    // rows (weight gradients of the wide layers) do better with the narrower band (measured: +3..5 % there, -2 % elsewhere)
-    const int GROUP = tiles_m > 64 ? 4 : 8;
-    const int per_group = GROUP * tiles_n;
-    const int g = bid / per_group;
-    const int gm0 = g * GROUP;
-    const int gsz = tiles_m - gm0 < GROUP ? tiles_m - gm0 : GROUP;
-    const int tm = gm0 + (bid % per_group) % gsz;
-    const int tn = (bid % per_group) / gsz;
+    int split, nsplit, tm, tn;
+    if (!place(tiles_m, tiles_n, xsplits, split, nsplit, tm, tn)) return;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wm = wave / WGN, wn = wave % WGN;
-    const int l16 = lane & 15, lq = lane >> 4;
 
     const int64_t kbeg = (int64_t)split * k_chunk;
     const int64_t kend = (ws != nullptr && kbeg + k_chunk < K) ? kbeg + k_chunk : K;
@@ -279,12 +379,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
                 mfma_acc(acc[i][j], fb[S()][j], fa[S()][i]);
             }
             if (ROWSUM && j == 0 && do_rowsum) {
-                const Frag f{.v = fa[S()][i]};
-                const uint32_t w[4] = {f.u.x, f.u.y, f.u.z, f.u.w};
-                float t = 0.f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) t += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
-                rs[i] += t;
+                rs[i] += sum_frag(fa[S()][i]);
             }
 #pragma unroll
             for (int r = q * NR * 4 / (NQ * 3); r < (q + 1) * NR * 4 / (NQ * 3) && r < NR; ++r) read_one(S() ^ 1, rA, rB, RKS(), r);
@@ -354,133 +449,286 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     settle();
     pin();
 
-    if (do_rowsum) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            rs[i] += __shfl_xor(rs[i], 16, 64);
-            rs[i] += __shfl_xor(rs[i], 32, 64);
-            const int64_t m = m0 + wm * WM + i * 16 + l16;
-            if (lq == 0 && m < M) {
-                if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rs[i];
-                else rowsum[m] = (uint16_t)f32_to_bf16_bits(rs[i] + (rowsum_acc ? bf16_bits_to_f32(rowsum[m]) : 0.f));
-            }
-        }
-    }
-    // epilogue through LDS, 16 rows of a wavefront's tile at a time as fp32 (the rings are free: the last barrier of
-    // the loop came after every fragment read)
-    {
-        constexpr int SPF = WN + 4, CPR = WN / 8, PASSES = 16 * CPR / 64;
-        static_assert((16 * CPR) % 64 == 0, "a 16-row block is a whole number of wavefront passes");
-        const bool wide = (ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0);
-        static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * 16 * SPF * 4, "the staging blocks fit the rings");
-        float *stage = reinterpret_cast<float *>(smem_dl) + wave * (16 * SPF);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(stage + l16 * SPF + j * 16 + lq * 4) = acc[i][j];
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int p = 0; p < PASSES; ++p) {
-                const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
-                const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
-                const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
-                const int64_t m = m0 + wm * WM + i * 16 + row, n = n0 + wn * WN + ch * 8;
-                if (m >= M || n >= N) continue;
-                if (ws) {
-                    float *dst = ws + ((int64_t)split * M + m) * N + n;
-                    *reinterpret_cast<float4 *>(dst) = x0;
-                    if (n + 4 < N) *reinterpret_cast<float4 *>(dst + 4) = x1;
-                    continue;
-                }
-                float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                if (n + 8 <= N && wide) {
-                    if (bias) {
-                        const uint4 t = *reinterpret_cast<const uint4 *>(bias + n);
-                        const uint32_t u[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
-                    }
-                    if (resid) {
-                        const uint4 t = *reinterpret_cast<const uint4 *>(resid + m * ldr + n);
-                        const uint32_t u[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
-                    }
-                    uint4 o;
-                    o.x = pack_bf16x2(v[0], v[1]);
-                    o.y = pack_bf16x2(v[2], v[3]);
-                    o.z = pack_bf16x2(v[4], v[5]);
-                    o.w = pack_bf16x2(v[6], v[7]);
-                    *reinterpret_cast<uint4 *>(C + m * ldc + n) = o;
-                } else {
-                    for (int e = 0; e < 8 && n + e < N; ++e) {
-                        float x = v[e];
-                        if (bias) x += bf16_bits_to_f32(bias[n + e]);
-                        if (resid) x += bf16_bits_to_f32(resid[m * ldr + n + e]);
-                        C[m * ldc + n + e] = (uint16_t)f32_to_bf16_bits(x);
-                    }
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
+    if (do_rowsum) store_rowsum<TM>(rs, lane, m0 + wm * WM, M, N, rowsum, rowsum_acc, ws, split, nsplit);
+    store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl) + wave * (16 * (WN + 4)), lane, m0 + wm * WM, n0 + wn * WN, M, N, bias, resid,
+                       ldr, C, ldc, ws, split);      // the rings are free: the last barrier came after every fragment read
+    static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * 16 * (WN + 4) * 4, "the staging blocks fit the rings");
 }
 
-template <int BM, int BN, int WGM, int WGN, int D>
-bool launch_dl(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
-               const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc,
-               void *rowsum, float *ws, int splits, bool rowsum_acc) {
-    const int64_t k_chunk = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
-    const int64_t kspan = splits > 1 ? k_chunk : K;
-    const int64_t spanA = a_km ? (kspan + 3 * BK) * lda * 2 : ((int64_t)BM * lda + kspan + 3 * BK) * 2;
-    const int64_t spanB = b_km ? (kspan + 3 * BK) * ldb * 2 : ((int64_t)BN * ldb + kspan + 3 * BK) * 2;
-    constexpr int64_t LIMIT = (int64_t)1 << 30;
-    if (spanA >= LIMIT || spanB >= LIMIT) return false;
-    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
-    const int tiles = tiles_m * tiles_n;
-    const int xsplits = (splits == 2 || splits == 4 || splits == 8) ? splits : 0;
+// 64x64 tiles for products with too few larger ones: eight wavefronts in two groups, each with one of the two contraction steps
+// of every tile, so that two wavefronts per SIMD cover each other's LDS latency; the groups' sums are added in order.  A tile
+// is 256 clocks of loads and 128 of products, so the ring is D tiles deep.
+template <int D, bool AKM, bool BKM, bool ROWSUM>
+__global__ void __launch_bounds__(512)
+    gemm_bf16_small_k(const uint16_t *__restrict__ A, int64_t lda, const uint16_t *__restrict__ B, int64_t ldb,
+                      const uint16_t *__restrict__ bias, const uint16_t *__restrict__ resid, int64_t ldr,
+                      uint16_t *__restrict__ C, int64_t ldc, int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n,
+                      uint16_t *__restrict__ rowsum, float *__restrict__ ws, int64_t k_chunk, int rowsum_acc, int xsplits) {
+    constexpr int BM = 64, BN = 64, NT = 512, TM = 2, TN = 2;
+    using OpA = DlOperand<BM, NT, AKM>;
+    using OpB = DlOperand<BN, NT, BKM>;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem_dl[];
+
+    const int tid = threadIdx.x;
+    int split, nsplit, tm, tn;
+    if (!place(tiles_m, tiles_n, xsplits, split, nsplit, tm, tn)) return;
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int kg = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+
+    const int64_t kbeg = (int64_t)split * k_chunk;
+    const int64_t kend = (ws != nullptr && kbeg + k_chunk < K) ? kbeg + k_chunk : K;
+    const int kspan = kend > kbeg ? (int)(kend - kbeg) : 0;
+    const int nkf = kspan / BK, rem = kspan % BK, nk = nkf + (rem ? 1 : 0);
+
+    const int rows_a = (int)(M - m0 < BM ? M - m0 : BM), rows_b = (int)(N - n0 < BN ? N - n0 : BN);
+    const uint16_t *baseA = AKM ? A + kbeg * lda + m0 : A + m0 * lda + kbeg;
+    const uint16_t *baseB = BKM ? B + kbeg * ldb + n0 : B + n0 * ldb + kbeg;
+    const int k8 = (kspan + 7) / 8 * 8;
+    const int64_t recA = kspan == 0 ? 0 : AKM ? ((int64_t)(kspan - 1) * lda + (rows_a + 7) / 8 * 8) * 2 : ((int64_t)(rows_a - 1) * lda + k8) * 2;
+    const int64_t recB = kspan == 0 ? 0 : BKM ? ((int64_t)(kspan - 1) * ldb + (rows_b + 7) / 8 * 8) * 2 : ((int64_t)(rows_b - 1) * ldb + k8) * 2;
+    const i32x4 rsA = make_rsrc(baseA, (uint32_t)recA), rsB = make_rsrc(baseB, (uint32_t)recB);
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem_dl));
+    const uint32_t stepA = OpA::tile_step(lda), stepB = OpB::tile_step(ldb);
+
+    OpA oa;
+    OpB ob;
+    oa.init(lda, rows_a, BK, wave, lane);
+    ob.init(ldb, rows_b, BK, wave, lane);
+    oa.init_frag(wm * 32, lane);
+    ob.init_frag(wn * 32, lane);
+    if (kg) {                                        // this wavefront's contraction step is the second one
+        oa.second_step();
+        ob.second_step();
+    }
+
+    floatx4 acc[TM][TN];
+    float rs[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        rs[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    }
+    const bool do_rowsum = ROWSUM && tn == 0 && wn == 0;
+
+    constexpr uint32_t TILE = OpA::BYTES + OpB::BYTES;
+    constexpr int PL = OpA::PER + OpB::PER;
+    auto load_tile = [&](int kt, uint32_t at) __attribute__((always_inline)) {      // kt < nk
+        if (kt < nkf) {
+#pragma unroll
+            for (int l = 0; l < OpA::PER; ++l) oa.load_one(l, rsA, (uint32_t)kt * stepA, lds0 + at, wave);
+#pragma unroll
+            for (int l = 0; l < OpB::PER; ++l) ob.load_one(l, rsB, (uint32_t)kt * stepB, lds0 + at + OpA::BYTES, wave);
+        } else {                                     // the last, partial tile: chunks beyond the contraction read as zero
+            OpA ta;
+            OpB tb;
+            ta.init(lda, rows_a, rem, wave, lane);
+            tb.init(ldb, rows_b, rem, wave, lane);
+#pragma unroll
+            for (int l = 0; l < OpA::PER; ++l) ta.load_one(l, rsA, (uint32_t)kt * stepA, lds0 + at, wave);
+#pragma unroll
+            for (int l = 0; l < OpB::PER; ++l) tb.load_one(l, rsB, (uint32_t)kt * stepB, lds0 + at + OpA::BYTES, wave);
+        }
+    };
+    auto clear_tail = [&](int kt, uint32_t at) __attribute__((always_inline)) {
+        if (kt == nkf && (rem & 7)) {
+            OpA::clear_tail(smem_dl + at, rem, tid);
+            OpB::clear_tail(smem_dl + at + OpA::BYTES, rem, tid);
+            __syncthreads();
+        }
+    };
+    bf16x8 fa[2][TM], fb[2][TN];
+    auto read_frags = [&](auto S, uint32_t at) __attribute__((always_inline)) {
+        const unsigned char *As = smem_dl + at, *Bs = As + OpA::BYTES;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[S()][i] = oa.frag(As, i, 0);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[S()][j] = ob.frag(Bs, j, 0);
+    };
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr auto wait_vm = [](int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); };      // s_waitcnt vmcnt(n)
+    static_assert(D * PL < 64, "loads in flight fit the counter");
+
+#pragma unroll
+    for (int t = 0; t < D; ++t)
+        if (t < nk) load_tile(t, t * TILE);
+    if (nk >= D) __builtin_amdgcn_s_waitcnt(wait_vm((D - 1) * PL));
+    else __builtin_amdgcn_s_waitcnt(wait_vm(0));
+    __builtin_amdgcn_s_barrier();
+    clear_tail(0, 0);
+    if (nk > 0) read_frags(c0, 0);
+
+    uint32_t at = 0;                                 // ring offset of tile kt, whose fragments are in set S or on their way there
+    auto tile = [&](int kt, auto S, auto FULL) __attribute__((always_inline)) {
+        constexpr std::integral_constant<int, (S() ^ 1)> other{};
+        const uint32_t nx = at + TILE >= D * TILE ? 0u : at + TILE;
+        // tile kt+1 has landed; tile kt's fragments are in everybody's registers, its slot is free
+        if (FULL()) __builtin_amdgcn_s_waitcnt(wait_vm((D - 2) * PL) & 0xC0FF);
+        else __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (!FULL() && kt + 1 < nk) clear_tail(kt + 1, nx);
+        read_frags(other, nx);                       // after the last tile these reads fetch nothing that is used
+        if (FULL() || kt + D < nk) load_tile(kt + D, at);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[S()][j], fa[S()][i], acc[i][j], 0, 0, 0);
+            if (ROWSUM && do_rowsum) rs[i] += sum_frag(fa[S()][i]);
+        }
+        at = nx;
+    };
+    int kt = 0;
+    for (; kt + 1 + D < nkf; kt += 2) {
+        tile(kt, c0, c1);
+        tile(kt + 1, c1, c1);
+    }
+    for (; kt < nk; kt += 2) {
+        tile(kt, c0, c0);
+        if (kt + 1 < nk) tile(kt + 1, c1, c0);
+    }
+
+    // the second group's sums join the first's
+    float *red = reinterpret_cast<float *>(smem_dl) + (wave & 3) * (TM * TN * 4 + TM) * 64 + lane;
+    __syncthreads();
+    if (kg) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) red[((i * TN + j) * 4 + e) * 64] = acc[i][j][e];
+            red[(TM * TN * 4 + i) * 64] = rs[i];
+        }
+    }
+    __syncthreads();
+    if (kg) return;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] += red[((i * TN + j) * 4 + e) * 64];
+        rs[i] += red[(TM * TN * 4 + i) * 64];
+    }
+    if (do_rowsum) store_rowsum<TM>(rs, lane, m0 + wm * 32, M, N, rowsum, rowsum_acc, ws, split, nsplit);
+    constexpr size_t RED = 4 * (TM * TN * 4 + TM) * 64 * 4;
+    static_assert(D * TILE >= RED + 4 * 16 * 36 * 4, "reduction and staging blocks fit the ring");
+    store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl + RED) + wave * (16 * 36), lane, m0 + wm * 32, n0 + wn * 32, M, N, bias, resid, ldr,
+                       C, ldc, ws, split);
+}
+struct Product {
+    hipStream_t s;
+    bool a_km, b_km;
+    int64_t M, N, K;
+    const uint16_t *A;
+    int64_t lda;
+    const uint16_t *B;
+    int64_t ldb;
+    const uint16_t *bias, *resid;
+    int64_t ldr;
+    uint16_t *C;
+    int64_t ldc;
+    uint16_t *rowsum;
+    float *ws;
+    int splits, rowsum_acc;
+};
+
+template <auto *KERNEL> void launch(const Product &p, int BM, int BN, int threads, size_t lds) {
+    static const hipError_t raised = hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)raised;
+    const int64_t k_chunk = p.splits > 1 ? ((p.K + p.splits - 1) / p.splits + BK - 1) / BK * BK : p.K;
+    const int tiles_m = (int)((p.M + BM - 1) / BM), tiles_n = (int)((p.N + BN - 1) / BN), tiles = tiles_m * tiles_n;
+    const int xsplits = (p.splits == 2 || p.splits == 4 || p.splits == 8) ? p.splits : 0;
     const dim3 grid = xsplits ? dim3((unsigned)(8 * ((tiles + 8 / xsplits - 1) / (8 / xsplits))))
-                              : dim3((unsigned)(8 * ((tiles + 7) / 8)), (unsigned)(splits > 1 ? splits : 1));
-    const dim3 block(WGM * WGN * 64);
+                              : dim3((unsigned)(8 * ((tiles + 7) / 8)), (unsigned)(p.splits > 1 ? p.splits : 1));
+    KERNEL<<<grid, threads, lds, p.s>>>(p.A, p.lda, p.B, p.ldb, p.bias, p.resid, p.ldr, p.C, p.ldc, p.M, p.N, p.K, tiles_m, tiles_n,
+                                        p.rowsum, p.ws, k_chunk, p.rowsum_acc, xsplits);
+}
+
+// With row sums only the layout of a weight gradient (both operands k-major) has every tile; the others have the 128x128 one.
+template <int BM, int BN, int D> void launch_dl(const Product &p) {
     constexpr size_t lds = (size_t)((D + 1) * BM + D * BN) * BK * 2;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-#define TIO_DL(AKM, BKM, RS)                                                                                              \
-    do {                                                                                                                  \
-        static const hipError_t raised = hipFuncSetAttribute((const void *)gemm_bf16_dl_k<BM, BN, WGM, WGN, D, AKM, BKM, RS>,  \
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);      \
-        (void)raised;                                                                                                     \
-        gemm_bf16_dl_k<BM, BN, WGM, WGN, D, AKM, BKM, RS><<<grid, block, lds, s>>>(                                          \
-            (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid, ldr,      \
-            (uint16_t *)C, ldc, M, N, K, tiles_m, tiles_n, (uint16_t *)rowsum, ws, k_chunk, (int)rowsum_acc, xsplits);     \
-    } while (0)
-    if (rowsum) {
-        if (!a_km && !b_km) TIO_DL(false, false, true);
-        else if (!a_km && b_km) TIO_DL(false, true, true);
-        else if (a_km && b_km) TIO_DL(true, true, true);
-        else TIO_DL(true, false, true);
-    } else {
-        if (!a_km && !b_km) TIO_DL(false, false, false);
-        else if (!a_km && b_km) TIO_DL(false, true, false);
-        else if (a_km && b_km) TIO_DL(true, true, false);
-        else TIO_DL(true, false, false);
-    }
+    constexpr bool EVERY = BM == 128 && BN == 128;
+#define TIO_DL(AKM, BKM, RS) launch<gemm_bf16_dl_k<BM, BN, 2, 2, D, AKM, BKM, RS>>(p, BM, BN, 256, lds)
+    if (p.rowsum) {
+        if (p.a_km && p.b_km) TIO_DL(true, true, true);
+        else if constexpr (EVERY) {
+            if (p.a_km) TIO_DL(true, false, true);
+            else if (p.b_km) TIO_DL(false, true, true);
+            else TIO_DL(false, false, true);
+        }
+    } else if (!p.a_km && !p.b_km) TIO_DL(false, false, false);
+    else if (!p.a_km && p.b_km) TIO_DL(false, true, false);
+    else if (p.a_km && p.b_km) TIO_DL(true, true, false);
+    else TIO_DL(true, false, false);
 #undef TIO_DL
-    return true;
 }
+template <int D> void launch_small(const Product &p) {
+    constexpr size_t lds = (size_t)D * 128 * BK * 2;
+#define TIO_SMALL(AKM, BKM, RS) launch<gemm_bf16_small_k<D, AKM, BKM, RS>>(p, 64, 64, 512, lds)
+    if (p.rowsum) TIO_SMALL(true, true, true);
+    else if (!p.a_km && !p.b_km) TIO_SMALL(false, false, false);
+    else if (!p.a_km && p.b_km) TIO_SMALL(false, true, false);
+    else if (p.a_km && p.b_km) TIO_SMALL(true, true, false);
+    else TIO_SMALL(true, false, false);
+#undef TIO_SMALL
+}
+
+// The tiles and what they take, in microseconds: `tile` per contraction tile of 64 with the chip full (the clock follows the
+// power drawn: 0.6 of it with few compute units busy), `fixed` per output tile (first loads, epilogue).  per_cu = 2: two
+// workgroups share a compute unit; `solo` / `solo_fixed` where there are no more workgroups than units.  Fitted to 37 products of
+// the GPT-2-small, Llama-7B and ragged shapes, every tile measured on each (operands in no cache); the choice below takes the
+// fastest tile or one within 4 % of it on 34 of them, 20 % slower on the worst.  Some of them, 256x256 / 256x192 / 128x192 / 128x128 /
+// 64x64, us (before, choosing between the first and the fourth by the fill of the last round: 8192 x 768 x 3072 40, head 1021 x 768
+// x 50257 540, 768 x 768 x 8192 62, 1024^3 11):
+//    8192 x  768 x  3072   60 /  47 /  36 /  40 /  61      1021 x  768 x 50257  1097 / 1000 / 638 /  540 / 264
+//    8192 x 3072 x   768   48 /  44 /  54 /  43            1000 x 5120 x  5120    88 /   70 /  50 /   62 /  81
+//     768 x  768 x  8192  137 / 109 /  65 /  62 /  30      8192 x 22016 x 4096  1027 / 1101 / 1404 / 1381
+struct TileChoice {
+    int bm, bn, per_cu;
+    double tile, fixed, solo, solo_fixed;
+    void (*launch)(const Product &);
+    double cost(int64_t groups, int64_t nk) const {
+        if (per_cu == 2 && groups <= 256) return (double)nk * solo + solo_fixed;
+        const int64_t rounds = (groups + 255) / 256;
+        if (per_cu == 2) return 0.5 * (double)rounds * ((double)nk * tile + fixed);
+        const double busy = groups < 256 ? (double)groups / 256 : 1.0;
+        return (double)rounds * ((double)nk * tile * (0.6 + 0.4 * busy) + fixed);
+    }
+};
+const TileChoice TILES[] = {
+    {256, 256, 1, 1.33, 10, 0, 0, launch_dl<256, 256, 2>}, {256, 192, 1, 1.03, 10, 0, 0, launch_dl<256, 192, 2>},
+    {128, 192, 1, 0.60, 8, 0, 0, launch_dl<128, 192, 3>},  {128, 128, 2, 0.88, 5, 0.5, 4, launch_dl<128, 128, 2>},
+    {64, 64, 2, 0.42, 3, 0.2, 3.5, launch_small<4>},
+};
 
 }  // namespace
 
-bool gemm_bf16_direct(hipStream_t s, int cfg, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A,
-                      int64_t lda, const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr,
-                      void *C, int64_t ldc, void *rowsum, float *ws, int splits, bool rowsum_accumulate) {
-#define TIO_P(BM, BN, WGM, WGN, D) launch_dl<BM, BN, WGM, WGN, D>(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, ws, splits, rowsum_accumulate)
-    if (cfg == 1) return TIO_P(256, 256, 2, 2, 2);
-    // with at most one 128x128 tile per compute unit there is room for a deeper ring: a tile is then 512 clocks long, far less
-    // than a memory latency
-    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128) * (splits > 1 ? splits : 1);
-    if (tiles <= 256) return TIO_P(128, 128, 2, 2, 4);
-    return TIO_P(128, 128, 2, 2, 2);
-#undef TIO_P
+bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
+                      int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, float *ws,
+                      int splits, bool rowsum_accumulate) {
+    // 32-bit buffer offsets: what one workgroup addresses of an operand has to lie within 1 GiB
+    const int64_t kspan = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
+    const int64_t spanA = a_km ? (kspan + 3 * BK) * lda * 2 : ((int64_t)256 * lda + kspan + 3 * BK) * 2;
+    const int64_t spanB = b_km ? (kspan + 3 * BK) * ldb * 2 : ((int64_t)256 * ldb + kspan + 3 * BK) * 2;
+    constexpr int64_t LIMIT = (int64_t)1 << 30;
+    if (spanA >= LIMIT || spanB >= LIMIT) return false;
+    const Product p{s, a_km, b_km, M, N, K, (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid,
+                    ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate};
+    const int64_t nk = (kspan + BK - 1) / BK;
+    const TileChoice *best = nullptr;
+    double best_cost = 0;
+    for (const TileChoice &t : TILES) {
+        if (rowsum && !(a_km && b_km) && !(t.bm == 128 && t.bn == 128)) continue;
+        const double cost = t.cost(((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1), nk);
+        if (!best || cost < best_cost) { best = &t; best_cost = cost; }
+    }
+    best->launch(p);
+    return true;
 }
 
 }  // namespace k

@@ -45,10 +45,12 @@ def test_contraction_remainders(K, a_km, b_km):
     _run(127, 129, K, a_km, b_km, rowsum=K % 2 == 1)
 
 
+# output sizes that get each of the tiles: 256x256, 256x192, 128x192, 128x128, 64x64
 @pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 1), (1, 0)])
-@pytest.mark.parametrize("M,N,K", [(4096, 4096, 65), (4095, 3841, 200), (3841, 4090, 131)])
-def test_large_tiles(M, N, K, a_km, b_km):
-    _run(M, N, K, a_km, b_km, rowsum=True)
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031), (8192, 3072, 768), (8100, 3070, 777), (2047, 3072, 3000),
+                                   (4000, 1500, 640), (3100, 1000, 200), (2048, 2048, 300), (500, 700, 391), (1021, 768, 5025)])
+def test_every_tile(M, N, K, a_km, b_km):
+    _run(M, N, K, a_km, b_km, rowsum=a_km == b_km == 1)
 
 
 @pytest.mark.parametrize("M,N,K,splits", [(256, 128, 1000, 3), (129, 68, 517, 2), (200, 136, 64, 8), (130, 64, 4097, 4)])
