@@ -45,7 +45,17 @@ constexpr int BK = 64;                                          // contraction t
 __device__ __forceinline__ void mfma_acc(floatx4 &c, const bf16x8 &a, const bf16x8 &b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
-// The same with a tile load (see load_to_lds_b128) behind it: the product fills the wait state that M0 needs.
+// c += a . b0 or a . b1 as `which` says (uniform; anything but 0 and 1: nothing).  One block, so that c stays in one place: the
+// compiler would move it from branch to branch without the wait a product's result needs.
+__device__ __forceinline__ void mfma_pick(floatx4 &c, const bf16x8 &a, const bf16x8 &b0, const bf16x8 &b1, int which) {
+    asm volatile("s_cmp_eq_u32 %4, 0\n\ts_cbranch_scc1 .Lpick0_%=\n\ts_cmp_eq_u32 %4, 1\n\ts_cbranch_scc0 .Lpick_end_%=\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %1, %3, %0\n\ts_branch .Lpick_end_%=\n"
+                 ".Lpick0_%=:\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n.Lpick_end_%=:"
+                 : "+v"(c)
+                 : "v"(a), "v"(b0), "v"(b1), "s"(which)
+                 : "scc");
+}
+// The first with a tile load (see load_to_lds_b128) behind it: the product fills the wait state that M0 needs.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void mfma_acc_load(floatx4 &c, const bf16x8 &a, const bf16x8 &b, i32x4 rsrc, uint32_t lds_addr, uint32_t voff,
@@ -180,26 +190,22 @@ __device__ __forceinline__ bool place(int tiles_m, int tiles_n, int xsplits, int
     return true;
 }
 
-__device__ __forceinline__ float sum_frag(const bf16x8 &v) {
-    const Frag f{.v = v};
-    const uint32_t w[4] = {f.u.x, f.u.y, f.u.z, f.u.w};
-    float t = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t += __uint_as_float(w[e] << 16) + __uint_as_float(w[e] & 0xffff0000u);
-    return t;
+// Row sums of A as products with a vector of ones: rs[u] belongs to the 16-row group 2u + wn of the wavefront (the two
+// wavefronts that share A's rows take every other group), lane l holds the sum of its row l%16.
+__device__ __forceinline__ bf16x8 ones8() {
+    Frag f;
+    f.u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    return f.v;
 }
-// row sums of A: lane l's rs[i] is its quarter of the sum of row mw + 16 i + l%16
 template <int TM>
-__device__ __forceinline__ void store_rowsum(float (&rs)[TM], int lane, int64_t mw, int64_t M, int64_t N, uint16_t *rowsum, int accumulate,
-                                             float *ws, int split, int nsplit) {
+__device__ __forceinline__ void store_rowsum(const floatx4 (&rs)[TM / 2], int lane, int wn, int64_t mw, int64_t M, int64_t N, uint16_t *rowsum,
+                                             int accumulate, float *ws, int split, int nsplit) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        rs[i] += __shfl_xor(rs[i], 16, 64);
-        rs[i] += __shfl_xor(rs[i], 32, 64);
-        const int64_t m = mw + i * 16 + (lane & 15);
+    for (int u = 0; u < TM / 2; ++u) {
+        const int64_t m = mw + (2 * u + wn) * 16 + lane;
         if (lane < 16 && m < M) {
-            if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rs[i];
-            else rowsum[m] = (uint16_t)f32_to_bf16_bits(rs[i] + (accumulate ? bf16_bits_to_f32(rowsum[m]) : 0.f));
+            if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rs[u][0];
+            else rowsum[m] = (uint16_t)f32_to_bf16_bits(rs[u][0] + (accumulate ? bf16_bits_to_f32(rowsum[m]) : 0.f));
         }
     }
 }
@@ -212,57 +218,96 @@ __device__ __forceinline__ void store_tile(const floatx4 (&acc)[TM][TN], float *
                                            float *__restrict__ ws, int split) {
     constexpr int WN = TN * 16, SPF = WN + 4, CPR = WN / 8, PASSES = 16 * CPR / 64;
     static_assert((16 * CPR) % 64 == 0, "a 16-row block is a whole number of wavefront passes");
-    const bool wide = (ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0);
     const int l16 = lane & 15, lq = lane >> 4;
+    auto to_lds = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(stage + l16 * SPF + j * 16 + lq * 4) = acc[i][j];
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto add8 = [](float (&v)[8], const uint4 &t) __attribute__((always_inline)) {
+        const uint32_t u[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-                for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(stage + l16 * SPF + j * 16 + lq * 4) = acc[i][j];
-                __builtin_amdgcn_wave_barrier();
+        for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
+    };
+    if (mw + TM * 16 <= M && nw + WN <= N && (ws || ((ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0)))) {
+        // the whole part lies inside: no tests per chunk, the bias read once, the residual one 16-row block ahead
+        int64_t out[PASSES], res[PASSES];
+        uint4 b[PASSES], r[PASSES];
 #pragma unroll
-                for (int p = 0; p < PASSES; ++p) {
-                    const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
-                    const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
-                    const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
-                    const int64_t m = mw + i * 16 + row, n = nw + ch * 8;
-                    if (m >= M || n >= N) continue;
-                    if (ws) {
-                        float *dst = ws + ((int64_t)split * M + m) * N + n;
-                        *reinterpret_cast<float4 *>(dst) = x0;
-                        if (n + 4 < N) *reinterpret_cast<float4 *>(dst + 4) = x1;
-                        continue;
-                    }
-                    float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                    if (n + 8 <= N && wide) {
-                        if (bias) {
-                            const uint4 t = *reinterpret_cast<const uint4 *>(bias + n);
-                            const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+        for (int p = 0; p < PASSES; ++p) {
+            const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
+            out[p] = ws ? ((int64_t)split * M + mw + row) * N + nw + ch * 8 : (mw + row) * ldc + nw + ch * 8;
+            res[p] = (mw + row) * ldr + nw + ch * 8;
+            if (bias) b[p] = *reinterpret_cast<const uint4 *>(bias + nw + ch * 8);
+            if (resid) r[p] = *reinterpret_cast<const uint4 *>(resid + res[p]);
+        }
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
-                        }
-                        if (resid) {
-                            const uint4 t = *reinterpret_cast<const uint4 *>(resid + m * ldr + n);
-                            const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+        for (int i = 0; i < TM; ++i) {
+            to_lds(i);
+            uint4 next[PASSES];
+            if (resid && i + 1 < TM) {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
-                        }
-                        uint4 o;
-                        o.x = pack_bf16x2(v[0], v[1]);
-                        o.y = pack_bf16x2(v[2], v[3]);
-                        o.z = pack_bf16x2(v[4], v[5]);
-                        o.w = pack_bf16x2(v[6], v[7]);
-                        *reinterpret_cast<uint4 *>(C + m * ldc + n) = o;
-                    } else {
-                        for (int e = 0; e < 8 && n + e < N; ++e) {
-                            float x = v[e];
-                            if (bias) x += bf16_bits_to_f32(bias[n + e]);
-                            if (resid) x += bf16_bits_to_f32(resid[m * ldr + n + e]);
-                            C[m * ldc + n + e] = (uint16_t)f32_to_bf16_bits(x);
-                        }
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
+                for (int p = 0; p < PASSES; ++p) next[p] = *reinterpret_cast<const uint4 *>(resid + res[p] + (int64_t)(i + 1) * 16 * ldr);
             }
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) {
+                const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
+                const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
+                const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
+                if (ws) {
+                    float *dst = ws + out[p] + (int64_t)i * 16 * N;
+                    *reinterpret_cast<float4 *>(dst) = x0;
+                    *reinterpret_cast<float4 *>(dst + 4) = x1;
+                } else {
+                    float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                    if (bias) add8(v, b[p]);
+                    if (resid) add8(v, r[p]);
+                    *reinterpret_cast<uint4 *>(C + out[p] + (int64_t)i * 16 * ldc) =
+                        make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+                }
+            }
+            if (resid && i + 1 < TM) {
+#pragma unroll
+                for (int p = 0; p < PASSES; ++p) r[p] = next[p];
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        return;
+    }
+    const bool wide = (ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        to_lds(i);
+#pragma unroll 1
+        for (int p = 0; p < PASSES; ++p) {
+            const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
+            const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
+            const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
+            const int64_t m = mw + i * 16 + row, n = nw + ch * 8;
+            if (m >= M || n >= N) continue;
+            if (ws) {
+                float *dst = ws + ((int64_t)split * M + m) * N + n;
+                *reinterpret_cast<float4 *>(dst) = x0;
+                if (n + 4 < N) *reinterpret_cast<float4 *>(dst + 4) = x1;
+                continue;
+            }
+            float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+            if (n + 8 <= N && wide) {
+                if (bias) add8(v, *reinterpret_cast<const uint4 *>(bias + n));
+                if (resid) add8(v, *reinterpret_cast<const uint4 *>(resid + m * ldr + n));
+                *reinterpret_cast<uint4 *>(C + m * ldc + n) =
+                    make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+            } else {
+                for (int e = 0; e < 8 && n + e < N; ++e) {
+                    float x = v[e];
+                    if (bias) x += bf16_bits_to_f32(bias[n + e]);
+                    if (resid) x += bf16_bits_to_f32(resid[m * ldr + n + e]);
+                    C[m * ldc + n + e] = (uint16_t)f32_to_bf16_bits(x);
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 template <int BM, int BN, int WGM, int WGN, int D, bool AKM, bool BKM, bool ROWSUM>
@@ -309,16 +354,18 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     ob.init_frag(wn * WN, lane);
 
     // acc[i][j]: lane l holds C row 16 i + l%16, columns 16 j + 4 (l/16) + 0..3
-    floatx4 acc[TM][TN];
-    float rs[TM];
+    floatx4 acc[TM][TN], rs[TM / 2];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-        rs[i] = 0.f;
+        rs[i / 2] = (floatx4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
     }
-    // row sums of A: the wavefronts of the first tile column's first column add up their A fragments
-    const bool do_rowsum = ROWSUM && tn == 0 && wn == 0;
+    static_assert(WGN == 2 && TM % 2 == 0, "row sums: two wavefronts share A's rows");
+    const bool do_rowsum = ROWSUM && tn == 0;
+    const int rs_group = do_rowsum ? wn : 2;
+    bf16x8 ones = ones8();
+    if (ROWSUM) asm volatile("" : "+v"(ones));       // written once, here: not right before a product that reads it
 
     // LDS: a ring of D + 1 A tiles, then one of D B tiles.  While tile t is multiplied, the tiles up to t + D - 1 sit there or
     // are landing; A's spare slot takes A of tile t + D in the first half of the tile, and B's slot of tile t itself takes B of
@@ -378,9 +425,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
             } else {
                 mfma_acc(acc[i][j], fb[S()][j], fa[S()][i]);
             }
-            if (ROWSUM && j == 0 && do_rowsum) {
-                rs[i] += sum_frag(fa[S()][i]);
-            }
+            if (ROWSUM && j == 0 && i % 2 == 1) mfma_pick(rs[i / 2], ones, fa[S()][i - 1], fa[S()][i], rs_group);
 #pragma unroll
             for (int r = q * NR * 4 / (NQ * 3); r < (q + 1) * NR * 4 / (NQ * 3) && r < NR; ++r) read_one(S() ^ 1, rA, rB, RKS(), r);
             __builtin_amdgcn_sched_barrier(0);
@@ -413,6 +458,10 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+        if (ROWSUM) {
+#pragma unroll
+            for (int u = 0; u < TM / 2; ++u) asm volatile("" : "+v"(rs[u]));
+        }
     };
     pin();
     settle();
@@ -449,7 +498,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     settle();
     pin();
 
-    if (do_rowsum) store_rowsum<TM>(rs, lane, m0 + wm * WM, M, N, rowsum, rowsum_acc, ws, split, nsplit);
+    if (do_rowsum) store_rowsum<TM>(rs, lane, wn, m0 + wm * WM, M, N, rowsum, rowsum_acc, ws, split, nsplit);
     store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl) + wave * (16 * (WN + 4)), lane, m0 + wm * WM, n0 + wn * WN, M, N, bias, resid,
                        ldr, C, ldc, ws, split);      // the rings are free: the last barrier came after every fragment read
     static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * 16 * (WN + 4) * 4, "the staging blocks fit the rings");
@@ -502,15 +551,13 @@ __global__ void __launch_bounds__(512)
         ob.second_step();
     }
 
-    floatx4 acc[TM][TN];
-    float rs[TM];
+    floatx4 acc[TM][TN], rs[1] = {(floatx4){0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        rs[i] = 0.f;
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    }
-    const bool do_rowsum = ROWSUM && tn == 0 && wn == 0;
+    const bool do_rowsum = ROWSUM && tn == 0;
+    const bf16x8 ones = ones8();
 
     constexpr uint32_t TILE = OpA::BYTES + OpB::BYTES;
     constexpr int PL = OpA::PER + OpB::PER;
@@ -573,11 +620,10 @@ __global__ void __launch_bounds__(512)
         read_frags(other, nx);                       // after the last tile these reads fetch nothing that is used
         if (FULL() || kt + D < nk) load_tile(kt + D, at);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[S()][j], fa[S()][i], acc[i][j], 0, 0, 0);
-            if (ROWSUM && do_rowsum) rs[i] += sum_frag(fa[S()][i]);
-        }
+        if (ROWSUM && do_rowsum) rs[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, wn ? fa[S()][1] : fa[S()][0], rs[0], 0, 0, 0);
         at = nx;
     };
     int kt = 0;
@@ -591,7 +637,7 @@ __global__ void __launch_bounds__(512)
     }
 
     // the second group's sums join the first's
-    float *red = reinterpret_cast<float *>(smem_dl) + (wave & 3) * (TM * TN * 4 + TM) * 64 + lane;
+    float *red = reinterpret_cast<float *>(smem_dl) + (wave & 3) * (TM * TN * 4 + 1) * 64 + lane;
     __syncthreads();
     if (kg) {
 #pragma unroll
@@ -600,8 +646,8 @@ __global__ void __launch_bounds__(512)
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) red[((i * TN + j) * 4 + e) * 64] = acc[i][j][e];
-            red[(TM * TN * 4 + i) * 64] = rs[i];
         }
+        red[TM * TN * 4 * 64] = rs[0][0];
     }
     __syncthreads();
     if (kg) return;
@@ -611,10 +657,10 @@ __global__ void __launch_bounds__(512)
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[i][j][e] += red[((i * TN + j) * 4 + e) * 64];
-        rs[i] += red[(TM * TN * 4 + i) * 64];
     }
-    if (do_rowsum) store_rowsum<TM>(rs, lane, m0 + wm * 32, M, N, rowsum, rowsum_acc, ws, split, nsplit);
-    constexpr size_t RED = 4 * (TM * TN * 4 + TM) * 64 * 4;
+    rs[0][0] += red[TM * TN * 4 * 64];
+    if (do_rowsum) store_rowsum<TM>(rs, lane, wn, m0 + wm * 32, M, N, rowsum, rowsum_acc, ws, split, nsplit);
+    constexpr size_t RED = 4 * (TM * TN * 4 + 1) * 64 * 4;
     static_assert(D * TILE >= RED + 4 * 16 * 36 * 4, "reduction and staging blocks fit the ring");
     store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl + RED) + wave * (16 * 36), lane, m0 + wm * 32, n0 + wn * 32, M, N, bias, resid, ldr,
                        C, ldc, ws, split);
