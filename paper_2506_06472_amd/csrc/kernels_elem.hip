@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(TPB) embed_bwd_k(const T *__restrict__ dx, con
                                                    T *__restrict__ dw, int64_t S, int64_t d, bool accumulate) {
     constexpr int V = Vec16<T>::N;
     constexpr int CAP = 1024;                              // occurrences handled per round
-    __shared__ int cnt[TPB + 1];
+    __shared__ int cnt[TPB / 64];
     __shared__ int list[CAP];
     const int64_t cpr = d / V;
     const int64_t blk = blockIdx.x;
@@ -71,15 +71,21 @@ __global__ void __launch_bounds__(TPB) embed_bwd_k(const T *__restrict__ dx, con
             if (tok[i] == id) { ++n; earlier |= (i < blk); }
     }
     if (__syncthreads_or(earlier)) return;
-    cnt[tid] = n;
-    __syncthreads();
-    if (tid == 0) {                                        // exclusive prefix over the threads' counts
-        int run = 0;
-        for (int t = 0; t < TPB; ++t) { const int c = cnt[t]; cnt[t] = run; run += c; }
-        cnt[TPB] = run;
+    // exclusive prefix over the threads' counts: within the wavefront by shuffles, then over the wavefronts
+    int incl = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if ((tid & 63) >= o) incl += up;
     }
+    if ((tid & 63) == 63) cnt[tid >> 6] = incl;
     __syncthreads();
-    const int total = cnt[TPB], first = cnt[tid];
+    int first = incl - n, total = 0;
+#pragma unroll
+    for (int w = 0; w < TPB / 64; ++w) {
+        if (w < (tid >> 6)) first += cnt[w];
+        total += cnt[w];
+    }
     constexpr int NC = 2;                                  // column chunks a thread owns per pass
     for (int64_t cb0 = 0; cb0 < cpr; cb0 += (int64_t)NC * TPB) {
         float acc[NC][V];
@@ -94,7 +100,7 @@ __global__ void __launch_bounds__(TPB) embed_bwd_k(const T *__restrict__ dx, con
             if (total > CAP || cb0 == 0) {                 // (re)build the list of this round's occurrences
                 __syncthreads();
                 int rank = first;
-                for (int64_t i = lo; i < hi; ++i)
+                for (int64_t i = lo; i < hi && rank < first + n; ++i)
                     if (tok[i] == id) {
                         if (rank >= base && rank < base + CAP) list[rank - base] = (int)i;
                         ++rank;
@@ -316,7 +322,8 @@ __global__ void __launch_bounds__(TPB) norm_bwd_k(const T *__restrict__ dy, cons
 // keeps it in registers between the statistics pass and the output pass (one read of dy and x, no
 // barriers per row); the wavefronts of a workgroup take its rows round-robin, each adds its rows'
 // contributions to the gain / bias gradients in registers in row order, and the four register sets
-// are then added through LDS in wavefront order.
+// are then added through LDS in wavefront order (each set written once, 16 bytes at a time, and summed column by column:
+// adding them in place one wavefront after the other, a float at a time, took longer than the rows themselves).
 template <typename T, bool RMS, int NCH>
 __global__ void __launch_bounds__(TPB) norm_bwd_wave_k(const T *__restrict__ dy, const T *__restrict__ x,
                                                        const float *__restrict__ stats, const T *__restrict__ g,
@@ -324,7 +331,7 @@ __global__ void __launch_bounds__(TPB) norm_bwd_wave_k(const T *__restrict__ dy,
                                                        float *__restrict__ part, int64_t S, int64_t d, int rows_per_blk) {
     constexpr int V = Vec16<T>::N;
     constexpr int NP = RMS ? 1 : 2, NW = TPB / 64;
-    extern __shared__ float lds[];          // NP*d accumulators
+    extern __shared__ __attribute__((aligned(16))) float lds[];          // NW*NP*d sums
     const int cpr = (int)(d / V);
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_blk;
     const int64_t r1 = r0 + rows_per_blk < S ? r0 + rows_per_blk : S;
@@ -384,24 +391,26 @@ __global__ void __launch_bounds__(TPB) norm_bwd_wave_k(const T *__restrict__ dy,
             }
         }
     }
-    for (int ww = 0; ww < NW; ++ww) {
-        if (w == ww) {
+    // each wavefront's sums to its own part of LDS, then column by column in wavefront order
+    float *mine = lds + (int64_t)w * NP * d;
 #pragma unroll
-            for (int i = 0; i < NCH; ++i) {
-                if (l + 64 * i < cpr) {
+    for (int i = 0; i < NCH; ++i) {
+        if (l + 64 * i < cpr) {
 #pragma unroll
-                    for (int e = 0; e < V; ++e) {
-                        const int col = (l + 64 * i) * V + e;
-                        lds[col] = (ww ? lds[col] : 0.f) + cg[i][e];
-                        if (!RMS) lds[d + col] = (ww ? lds[d + col] : 0.f) + cb[i][e];
-                    }
-                }
+            for (int e = 0; e < V; e += 4) {
+                *reinterpret_cast<float4 *>(mine + (l + 64 * i) * V + e) = make_float4(cg[i][e], cg[i][e + 1], cg[i][e + 2], cg[i][e + 3]);
+                if (!RMS) *reinterpret_cast<float4 *>(mine + d + (l + 64 * i) * V + e) = make_float4(cb[i][e], cb[i][e + 1], cb[i][e + 2], cb[i][e + 3]);
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
     float *p = part + (int64_t)blockIdx.x * NP * d;
-    for (int64_t i = threadIdx.x; i < NP * d; i += TPB) p[i] = lds[i];
+    for (int64_t i = threadIdx.x; i < NP * d; i += TPB) {
+        float t = lds[i];
+#pragma unroll
+        for (int ww = 1; ww < NW; ++ww) t += lds[ww * NP * d + i];
+        p[i] = t;
+    }
 }
 
 // Same contract as norm_bwd_k (one partial row of gain / bias gradient sums per workgroup, ROWS rows per workgroup),
@@ -769,21 +778,21 @@ __global__ void __launch_bounds__(TPB) ce_k(T *__restrict__ logits, const int32_
     }
 }
 
-// Same contract as ce_k, for rows of at most TPB*NCH 16-byte chunks: the workgroup keeps its row in registers, so
+// Same contract as ce_k, for rows of at most NT*NCH 16-byte chunks: the workgroup keeps its row in registers, so
 // the logits are read once with all of a thread's loads in flight together, and maximum, sum and gradient are three
 // passes over registers.
-template <typename T, int NCH>
-__global__ void __launch_bounds__(TPB) ce_reg_k(T *__restrict__ logits, const int32_t *__restrict__ labels,
+template <typename T, int NCH, int NT>
+__global__ void __launch_bounds__(NT) ce_reg_k(T *__restrict__ logits, const int32_t *__restrict__ labels,
                                                 float *__restrict__ losses, int64_t S, int64_t Vn, int64_t ld, int64_t S_total) {
     constexpr int V = Vec16<T>::N;
-    __shared__ float red[8];
+    __shared__ float red[NT / 64];
     const int64_t row = blockIdx.x;
     T *xr = logits + row * ld;
     const int nchunk = (int)(ld / V), nv = (int)Vn;
     Vec16<T> a[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = threadIdx.x + TPB * i;
+        const int c = threadIdx.x + NT * i;
         if (c < nchunk) a[i].load(xr + (int64_t)c * V);
     }
     const int32_t lab = labels[row];
@@ -793,7 +802,7 @@ __global__ void __launch_bounds__(TPB) ce_reg_k(T *__restrict__ logits, const in
     float m = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = threadIdx.x + TPB * i;
+        const int c = threadIdx.x + NT * i;
         if (c < nchunk) {
             float f[V]; a[i].get(f);
             if ((c + 1) * V <= nv) {
@@ -805,12 +814,12 @@ __global__ void __launch_bounds__(TPB) ce_reg_k(T *__restrict__ logits, const in
             }
         }
     }
-    const float M = block_max<TPB / 64>(m, red);
+    const float M = block_max<NT / 64>(m, red);
     const float kM = -M * L2E;
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = threadIdx.x + TPB * i;
+        const int c = threadIdx.x + NT * i;
         if (c < nchunk) {
             float f[V]; a[i].get(f);
             if ((c + 1) * V <= nv) {
@@ -822,7 +831,7 @@ __global__ void __launch_bounds__(TPB) ce_reg_k(T *__restrict__ logits, const in
             }
         }
     }
-    const float tot = block_sum<TPB / 64>(sum, red);
+    const float tot = block_sum<NT / 64>(sum, red);
     const float lse = M + logf(tot);
     if (threadIdx.x == 0) losses[row] = lse - x_lab;
     // gradient of the mean loss over the whole batch: exp(x - lse) / S_total as one exponential, the 1/S_total folded
@@ -831,7 +840,7 @@ __global__ void __launch_bounds__(TPB) ce_reg_k(T *__restrict__ logits, const in
     const float kL = -lse * L2E - log2f((float)S_total);
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = threadIdx.x + TPB * i;
+        const int c = threadIdx.x + NT * i;
         if (c < nchunk) {
             float f[V]; a[i].get(f);
 #pragma unroll
@@ -998,8 +1007,9 @@ void norm_bwd(hipStream_t s, int dtype, bool rms, const void *dy, const void *x,
         const int64_t chunks = d / Vec16<T>::N;          // 16-byte chunks per row
         const bool block_ok = rows == NORM_BLOCK_ROWS;
         if (chunks <= 64 * 2) {                          // a wavefront per row
-            if (rms) norm_bwd_wave_k<T, true, 2><<<(unsigned)nb, TPB, lds, s>>>(TIO_NORM_BWD_ARGS);
-            else norm_bwd_wave_k<T, false, 2><<<(unsigned)nb, TPB, lds, s>>>(TIO_NORM_BWD_ARGS);
+            const size_t sums = (size_t)(TPB / 64) * (rms ? 1 : 2) * d * sizeof(float);       // at most 32 KiB
+            if (rms) norm_bwd_wave_k<T, true, 2><<<(unsigned)nb, TPB, sums, s>>>(TIO_NORM_BWD_ARGS);
+            else norm_bwd_wave_k<T, false, 2><<<(unsigned)nb, TPB, sums, s>>>(TIO_NORM_BWD_ARGS);
         }
         else if (block_ok && chunks <= TPB) TIO_NORM_BWD_BLOCK(1, 4);         // a workgroup per row, rows in flight: 4
         else if (block_ok && chunks <= TPB * 2) TIO_NORM_BWD_BLOCK(2, 4);
@@ -1058,13 +1068,16 @@ void rope(hipStream_t s, int dtype, void *qkv, int64_t B, int64_t Tn, int64_t H,
 
 void ce_fwd_bwd(hipStream_t s, int dtype, void *logits, const int32_t *labels, float *losses, int64_t S, int64_t V,
                 int64_t ld, int64_t S_total) {
-#define TIO_CE_REG(NCH) ce_reg_k<T, NCH><<<(unsigned)S, TPB, 0, s>>>((T *)logits, labels, losses, S, V, ld, S_total)
+#define TIO_CE_REG(NCH, NT) ce_reg_k<T, NCH, NT><<<(unsigned)S, NT, 0, s>>>((T *)logits, labels, losses, S, V, ld, S_total)
     TIO_DISPATCH(dtype, {
-        const int64_t chunks = ld / Vec16<T>::N;         // 16-byte chunks per row; TPB threads take NCH each
-        if (chunks <= TPB * 4) TIO_CE_REG(4);
-        else if (chunks <= TPB * 8) TIO_CE_REG(8);
-        else if (chunks <= TPB * 16) TIO_CE_REG(16);
-        else if (chunks <= TPB * 32) TIO_CE_REG(32);
+        // 16-byte chunks per row; NT threads take NCH each.  Long rows are spread over 1024 threads: with 32 chunks in the
+        // registers of each of 256, too few workgroups fit a compute unit for one row's exponentials to overlap another's loads
+        // (8192 rows of 50257 in bf16: 476 us, 3.5 TB/s; with 1024 threads 355 us, 4.6 TB/s)
+        const int64_t chunks = ld / Vec16<T>::N;
+        if (chunks <= 256 * 4) TIO_CE_REG(4, 256);
+        else if (chunks <= 256 * 8) TIO_CE_REG(8, 256);
+        else if (chunks <= 256 * 16) TIO_CE_REG(16, 256);
+        else if (chunks <= 1024 * 8) TIO_CE_REG(8, 1024);
         else ce_k<T><<<(unsigned)S, TPB, 0, s>>>((T *)logits, labels, losses, S, V, ld, S_total);
     });
 #undef TIO_CE_REG

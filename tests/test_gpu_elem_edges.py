@@ -1,0 +1,43 @@
+"""GPU: cross entropy at the vocabulary sizes where its kernel changes (rows of 4096 and 8192 chunks of 16 bytes, one chunk more),
+and the embedding gradient with one token id in most or all positions, through one fp32 training step against the oracle."""
+import numpy as np
+import pytest
+
+from gpulib import make_inputs, plans_for
+from oracle import model as om
+
+pytestmark = pytest.mark.gpu
+
+
+def _step_matches(cfg, tokens=None):
+    import paper_2506_06472_amd as tio
+    params, tok, lab = make_inputs(cfg, seed=1)
+    if tokens is not None:
+        tok = tokens(tok)
+    pe = plans_for(cfg)[2].export()
+    ctx = tio.tio_ctx_create(cfg, pe["arena_needed"], pe["host_needed"] + (1 << 20), 0)
+    ctx.tio_params_load(params)
+    loss = ctx.tio_train_step(tok, lab, None, capture_grads=True)["loss"]
+    ref, grads = om.forward_backward(cfg, params, tok, lab)
+    assert abs(loss - ref) <= 1e-5 * abs(ref), (loss, ref)
+    for n in ("w_head", "wte", "lnf_g"):            # the bars of the fp32 parity tests
+        g, r = ctx.tio_grads_read(n).astype(np.float64).ravel(), grads[n].ravel()
+        assert np.abs(g - r).max() <= 1e-4 * np.abs(r).max(), (n, np.abs(g - r).max() / np.abs(r).max())
+    ctx.close()
+
+
+@pytest.mark.parametrize("V", [16384, 16385, 32768, 32769])
+def test_cross_entropy_kernels_meet(V):
+    print(f"vocabulary {V}", flush=True)
+    _step_matches(dict(arch="gpt", L=1, d=64, H=2, f=128, V=V, T=24, B=1, precision="fp32", lr=1e-3))
+
+
+@pytest.mark.parametrize("B,keep", [(1, 0), (1, 3), (20, 7), (20, 0)])
+def test_embedding_gradient_of_repeated_tokens(B, keep):
+    print(f"repeated tokens B={B} keep={keep}", flush=True)
+
+    def repeat(tok):
+        t = np.full_like(tok, 5)
+        t.ravel()[:keep] = tok.ravel()[:keep]
+        return t
+    _step_matches(dict(arch="gpt", L=1, d=64, H=2, f=128, V=300, T=64, B=B, precision="fp32", lr=1e-3), repeat)
