@@ -107,15 +107,16 @@ template <int DH> __device__ __forceinline__ int swz(int r) {
     return DH == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3));
 }
 // per-lane parts of the fragment addresses (element offsets into a tile), computed once per kernel: the XOR makes
-// them non-additive in the contraction step, so each step has its own
-template <int DH> struct TileLanes {
+// them non-additive in the contraction step, so each step has its own; with LEAN only the first step's is kept and a step's
+// is one more XOR away (for the kernel that has no registers to spare)
+template <int DH, bool LEAN = false> struct TileLanes {
     static constexpr int CPR = DH / 8, KS = DH / 16, DT = DH / 32;
-    int roff[KS];          // row-wise fragment of contraction step ks: row lane%32, chunk 2 ks + lane/32
+    int roff[LEAN ? 1 : KS];          // row-wise fragment of contraction step ks: row lane%32, chunk 2 ks + lane/32
     int troff[DT][2];      // transposing fragment of column block i: rows 4 (lane/32) + (lane%16)/4 (+ 8), columns by lane
     __device__ __forceinline__ TileLanes(int lane) {
         const int l32 = lane & 31, lhi = lane >> 5;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) roff[ks] = (l32 * CPR + ((ks * 2 + lhi) ^ swz<DH>(l32 & 15))) * 8;
+        for (int ks = 0; ks < (LEAN ? 1 : KS); ++ks) roff[ks] = (l32 * CPR + ((ks * 2 + lhi) ^ swz<DH>(l32 & 15))) * 8;
 #pragma unroll
         for (int i = 0; i < DT; ++i)
 #pragma unroll
@@ -128,7 +129,7 @@ template <int DH> struct TileLanes {
     // A operand, rows row0 + lane%32 (row0 a multiple of 16), contraction step ks
     __device__ __forceinline__ bf16x8 row(const uint16_t *lds, int row0, int ks) const {
         Frag f;
-        f.u = *reinterpret_cast<const uint4 *>(lds + row0 * DH + roff[ks]);
+        f.u = *reinterpret_cast<const uint4 *>(lds + row0 * DH + (LEAN ? roff[0] ^ (ks * 16) : roff[LEAN ? 0 : ks]));
         return f.v;
     }
     // A operand "column 32 i + lane%32, contraction over rows r0 .. r0+15 in the slot order of pack8" (r0 a multiple of 16)
@@ -144,21 +145,21 @@ template <int DH> struct TileLanes {
 // (lane i writes bytes 16 i ..), so which chunk a lane fetches decides where it lands: lane i of block b fetches, for
 // row b*RPB + i/CPR, the logical chunk (i%CPR) ^ swz(row).  Rows past the sequence lie outside the descriptor and
 // arrive as zeros.
-template <int DH> struct DmaTile {
-    static constexpr int CPR = DH / 8, RPB = 64 / CPR, BLOCKS = 64 * DH * 2 / 1024, PER = BLOCKS / (NT / 64);
-    static_assert(BLOCKS % (NT / 64) == 0, "blocks divide over the wavefronts");
-    static_assert(((NT / 64) * RPB) % 16 == 0, "the permutation repeats from one load of a wavefront to its next");
+template <int DH, int NW = NT / 64> struct DmaTile {
+    static constexpr int CPR = DH / 8, RPB = 64 / CPR, BLOCKS = 64 * DH * 2 / 1024, PER = BLOCKS / NW;
+    static_assert(BLOCKS % NW == 0, "blocks divide over the wavefronts");
+    static_assert((NW * RPB) % 16 == 0, "the permutation repeats from one load of a wavefront to its next");
     uint32_t voff, step;           // byte offset of this lane's chunk in the wavefront's first block; bytes between its blocks (uniform)
     __device__ __forceinline__ DmaTile(uint32_t ld_bytes, int wave, int lane) {
         const int row = wave * RPB + lane / CPR;
         voff = (uint32_t)row * ld_bytes + (uint32_t)(((lane % CPR) ^ swz<DH>(row & 15)) * 16);
-        step = __builtin_amdgcn_readfirstlane((uint32_t)((NT / 64) * RPB) * ld_bytes);
+        step = __builtin_amdgcn_readfirstlane((uint32_t)(NW * RPB) * ld_bytes);
     }
     // load i of the PER that make up this wavefront's share of a tile (soff = row0 * ld_bytes, uniform): rows
-    // i * (NT / 64) * RPB further down, which only moves the uniform part of the address (the scalar offset takes part
+    // i * NW * RPB further down, which only moves the uniform part of the address (the scalar offset takes part
     // in the descriptor's range check like the per-lane one: checked on the hardware)
     __device__ __forceinline__ void load_one(int i, i32x4 rsrc, uint32_t soff, uint32_t lds_addr, int wave) const {
-        load_to_lds_b128(rsrc, lds_addr + (uint32_t)(i * (NT / 64) + wave) * 1024u, voff, soff + (uint32_t)i * step);
+        load_to_lds_b128(rsrc, lds_addr + (uint32_t)(i * NW + wave) * 1024u, voff, soff + (uint32_t)i * step);
     }
     // rows row0 .. row0+63 of the head behind rsrc to the tile at LDS address lds_addr
     __device__ __forceinline__ void load(i32x4 rsrc, uint32_t row0, uint32_t ld_bytes, uint32_t lds_addr, int wave) const {
@@ -456,52 +457,63 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
-// MODE 0 produces both gradients in one pass.  With head dimension 128 the two accumulators, the K and V
-// fragments and the prefetch registers do not fit the 256 registers that two wavefronts per SIMD allow, so
-// there the work is split: MODE 1 computes dV only (needs S), MODE 2 dK only (needs S and dP).
-template <int DH, int MODE>
-__global__ void __launch_bounds__(NT, 2) attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
-                                                          const float *__restrict__ lse, const float *__restrict__ delta,
-                                                          uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale) {
-    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4;
+// Both gradients in one launch: S and dP are computed once for the two of them, and the Q and dO tiles are loaded once.  A
+// wavefront's accumulators and K fragments take 160 of the 256 registers that two wavefronts per SIMD allow at head size 128,
+// so its V fragments are not kept in registers there but read from LDS (the workgroup's V rows, loaded once); to have room for
+// them, and half the tile loads per product, a workgroup is eight wavefronts with 256 key rows.  Bound: latency between the
+// products of two wavefronts per SIMD (the matrix cores are busy for a third of the time).  Measured at 4 x 2048 tokens, 32 heads
+// of 128: 482 us where two launches with four wavefronts each (dV, then dK) took 620 (18 % of that was tile loads); whole
+// backward pass faster at every size tried, from 1 x 64 x 2 heads (forward and backward 25.4 -> 21.5 us) to 1 x 4096 x 52 (1457 ->
+// 1233).  Transposed fragments four ahead in registers: 525 us, for want of the registers.
+template <int DH> constexpr int dkv_waves() { return DH == 128 ? 8 : 4; }
+template <int DH>
+__global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
+    attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
+                        const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale) {
+    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4, NW = dkv_waves<DH>(), KEYS = NW * 32;
+    constexpr bool VLDS = DH == 128;
     constexpr int BUF = 2 * TE;                                          // Q tile | dO tile, filled as in the forward kernel
-    extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];    // [2 buffers][Q | dO], then [2][64 lse | 64 delta] floats
+    // [2 buffers][Q | dO], [KEYS][DH] V rows if VLDS, then [2][64 lse | 64 delta] floats
+    extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int64_t d = H * DH, ld = 3 * d;
     const uint32_t ldb = (uint32_t)(ld * 2), ldg = (uint32_t)(d * 2);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, (int)((Tn + 127) / 128), bh, blk)) return;
+    if (!head_and_block(Bn * H, (int)((Tn + KEYS - 1) / KEYS), bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
-    const int kv0 = blk * 128;                                            // earliest keys see the most queries: first
+    const int kv0 = blk * KEYS;                                           // earliest keys see the most queries: first
     const int kv0w = kv0 + wave * 32, kv = kv0w + l32;
     const uint16_t *qb = qkv + b * Tn * ld + h * DH;
+    const uint32_t head_bytes = (uint32_t)(((Tn - 1) * ld + DH) * 2);
     const __amdgpu_buffer_rsrc_t rsK = head_rsrc(qb + d, Tn, ld, DH), rsV = head_rsrc(qb + 2 * d, Tn, ld, DH);
-    const i32x4 rsQ = make_rsrc(qb, (uint32_t)(((Tn - 1) * ld + DH) * 2));
+    const i32x4 rsQ = make_rsrc(qb, head_bytes);
     const i32x4 rsG = make_rsrc(dO + b * Tn * d + h * DH, (uint32_t)(((Tn - 1) * d + DH) * 2));
     const float c = scale * LOG2E;
     const bool live = kv < Tn;
-    const TileLanes<DH> L(lane);
-    const DmaTile<DH> dmaQ(ldb, wave, lane), dmaG(ldg, wave, lane);
+    const TileLanes<DH, VLDS> L(lane);
+    const DmaTile<DH, NW> dmaQ(ldb, wave, lane), dmaG(ldg, wave, lane);
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
-    constexpr bool DO_DV = MODE != 2, DO_DK = MODE != 1;
-    constexpr int NDK = DO_DK ? DT : 1, NDV = DO_DV ? DT : 1, NVF = DO_DK ? KS : 1;
+    const uint16_t *Vs = smem + 2 * BUF;
 
-    bf16x8 kf[KS], vf[NVF];
+    bf16x8 kf[KS], vf[VLDS ? 1 : KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         kf[ks] = buf_frag(rsK, (uint32_t)kv * ldb + (ks * 16 + lhi * 8) * 2);
-        if (DO_DK) vf[ks] = buf_frag(rsV, (uint32_t)kv * ldb + (ks * 16 + lhi * 8) * 2);
+        if (!VLDS) vf[VLDS ? 0 : ks] = buf_frag(rsV, (uint32_t)kv * ldb + (ks * 16 + lhi * 8) * 2);
     }
-    floatx16 dk[NDK], dv[NDV];
+    if (VLDS) {
+        const i32x4 rs = make_rsrc(qb + 2 * d, head_bytes);
 #pragma unroll
-    for (int i = 0; i < NDK; ++i) dk[i] = zero16();
+        for (int i = 0; i < KEYS / 64; ++i) dmaQ.load(rs, (uint32_t)(kv0 + 64 * i), ldb, lds0 + (2 * BUF + i * TE) * 2, wave);
+    }
+    floatx16 dk[DT], dv[DT];
 #pragma unroll
-    for (int i = 0; i < NDV; ++i) dv[i] = zero16();
+    for (int i = 0; i < DT; ++i) { dk[i] = zero16(); dv[i] = zero16(); }
     const int ntiles = ((int)Tn - kv0 + 63) / 64;
 
     float st_l = 0.f, st_d = 0.f;                       // statistics of row i0 + tid (threads 0..63), one tile ahead
-    float *stats = reinterpret_cast<float *>(smem + 2 * BUF);
+    float *stats = reinterpret_cast<float *>(smem + 2 * BUF + (VLDS ? KEYS * DH : 0));
     auto load_stats = [&](int i0) {
         if (tid < 64) {
             const bool ok = i0 + tid < Tn;
@@ -524,7 +536,7 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dkv_mfma_k(const uint16_t *__r
     load_stats(kv0);
     store_stats(0);
     if (ntiles > 1) load_stats(kv0 + 64);
-    __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): this wavefront's part of tile 0 has landed
+    __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): this wavefront's part of tile 0 (and of V) has landed
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
         const int i0 = kv0 + t * 64;
@@ -546,58 +558,53 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dkv_mfma_k(const uint16_t *__r
             for (int qt = 0; qt < 2; ++qt) {
                 floatx16 s = zero16(), dp = zero16();
                 {
-                    // S^T = Q.K^T (and dP^T = dO.V^T); the Q and dO fragments run RING ahead of their products
-                    constexpr int PERK = DO_DK ? 2 : 1, N = PERK * KS;
-                    bf16x8 ring[RING];
-                    auto frag = [&](int idx) { return L.row((PERK == 2 && (idx & 1)) ? Gs : Qs, qt * 32, idx / PERK); };
+                    // S^T = Q.K^T, then dP^T = dO.V^T; the Q and dO fragments run RING ahead of their products, V's VR ahead
+                    constexpr int N = 2 * KS, VR = 2;
+                    bf16x8 ring[RING], vr[VLDS ? VR : 1];
+                    auto frag = [&](int idx) { return L.row(idx < KS ? Qs : Gs, qt * 32, idx % KS); };
 #pragma unroll
                     for (int i = 0; i < RING; ++i) ring[i] = frag(i);
 #pragma unroll
                     for (int idx = 0; idx < N; ++idx) {
-                        const int ks = idx / PERK;
-                        if (PERK == 2 && (idx & 1)) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[idx % RING], vf[ks % NVF], dp, 0, 0, 0);
-                        else s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[idx % RING], kf[ks], s, 0, 0, 0);
+                        if (idx < KS) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[idx % RING], kf[idx % KS], s, 0, 0, 0);
+                        else dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[idx % RING], VLDS ? vr[VLDS ? idx % VR : 0] : vf[VLDS ? 0 : idx % KS], dp, 0, 0, 0);
                         if (idx + RING < N) ring[idx % RING] = frag(idx + RING);
+                        if (VLDS && idx + VR >= KS && idx + VR < N) vr[VLDS ? idx % VR : 0] = L.row(Vs, wave * 32, (idx + VR) % KS);
                     }
                     __builtin_amdgcn_sched_group_barrier(0x100, RING, 0);
 #pragma unroll
-                    for (int idx = 0; idx < N - RING; ++idx) {
+                    for (int idx = 0; idx < N; ++idx) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        const int reads = (idx + RING < N ? 1 : 0) + (VLDS && idx + VR >= KS && idx + VR < N ? 1 : 0);
+                        if (reads == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                        else if (reads == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                     }
-                    __builtin_amdgcn_sched_group_barrier(0x008, RING, 0);
                 }
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     // rows 8*r4 + 4*lhi + 0..3 of this 32-row group: their statistics are 16 contiguous bytes
                     const int ql = qt * 32 + 8 * r4 + 4 * lhi;
-                    const float4 l4 = *reinterpret_cast<const float4 *>(L2s + ql);
-                    const float4 d4 = DO_DK ? *reinterpret_cast<const float4 *>(Ds + ql) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const float4 l4 = *reinterpret_cast<const float4 *>(L2s + ql), d4 = *reinterpret_cast<const float4 *>(Ds + ql);
                     const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dvv[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int r = 4 * r4 + e;
                         float p = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lv[e]));
                         if (edge && (i0 + ql + e < kv || i0 + ql + e >= (int)Tn)) p = 0.0f;
-                        if (DO_DK) dp[r] = p * (dp[r] - dvv[e]);     // the 1/sqrt(dh) factor is applied once, to the sums
+                        dp[r] = p * (dp[r] - dvv[e]);        // the 1/sqrt(dh) factor is applied once, to the sums
                         s[r] = p;
                     }
                 }
-                if (DO_DV) {
-                    const bf16x8 p0 = pack8<0>(s), p1 = pack8<8>(s);
+                const bf16x8 p0 = pack8<0>(s), p1 = pack8<8>(s), d0 = pack8<0>(dp), d1 = pack8<8>(dp);
 #pragma unroll
-                    for (int i = 0; i < NDV; ++i) {
-                        dv[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Gs, qt * 32, i), p0, dv[i], 0, 0, 0);
-                        dv[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Gs, qt * 32 + 16, i), p1, dv[i], 0, 0, 0);
-                    }
+                for (int i = 0; i < DT; ++i) {
+                    dv[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Gs, qt * 32, i), p0, dv[i], 0, 0, 0);
+                    dv[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Gs, qt * 32 + 16, i), p1, dv[i], 0, 0, 0);
                 }
-                if (DO_DK) {
-                    const bf16x8 d0 = pack8<0>(dp), d1 = pack8<8>(dp);
 #pragma unroll
-                    for (int i = 0; i < NDK; ++i) {
-                        dk[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Qs, qt * 32, i), d0, dk[i], 0, 0, 0);
-                        dk[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Qs, qt * 32 + 16, i), d1, dk[i], 0, 0, 0);
-                    }
+                for (int i = 0; i < DT; ++i) {
+                    dk[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Qs, qt * 32, i), d0, dk[i], 0, 0, 0);
+                    dk[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(L.tr(Qs, qt * 32 + 16, i), d1, dk[i], 0, 0, 0);
                 }
             }
         }
@@ -611,22 +618,20 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dkv_mfma_k(const uint16_t *__r
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 uint2 w;
-                if (DO_DK) {
-                    w.x = pack2(dk[i % NDK][4 * g] * scale, dk[i % NDK][4 * g + 1] * scale);
-                    w.y = pack2(dk[i % NDK][4 * g + 2] * scale, dk[i % NDK][4 * g + 3] * scale);
-                    *reinterpret_cast<uint2 *>(krow + i * 32 + 8 * g + 4 * lhi) = w;
-                }
-                if (DO_DV) {
-                    w.x = pack2(dv[i % NDV][4 * g], dv[i % NDV][4 * g + 1]);
-                    w.y = pack2(dv[i % NDV][4 * g + 2], dv[i % NDV][4 * g + 3]);
-                    *reinterpret_cast<uint2 *>(vrow + i * 32 + 8 * g + 4 * lhi) = w;
-                }
+                w.x = pack2(dk[i][4 * g] * scale, dk[i][4 * g + 1] * scale);
+                w.y = pack2(dk[i][4 * g + 2] * scale, dk[i][4 * g + 3] * scale);
+                *reinterpret_cast<uint2 *>(krow + i * 32 + 8 * g + 4 * lhi) = w;
+                w.x = pack2(dv[i][4 * g], dv[i][4 * g + 1]);
+                w.y = pack2(dv[i][4 * g + 2], dv[i][4 * g + 3]);
+                *reinterpret_cast<uint2 *>(vrow + i * 32 + 8 * g + 4 * lhi) = w;
             }
     }
 }
 
 template <int DH> constexpr size_t kv_smem() { return (size_t)2 * 2 * 64 * DH * 2; }       // two buffers of two tiles
-template <int DH> constexpr size_t dkv_smem() { return (size_t)2 * 2 * 64 * DH * 2 + 2 * 128 * 4; }      // tiles, then statistics
+template <int DH> constexpr size_t dkv_smem() {         // tiles, V rows, then statistics
+    return (size_t)2 * 2 * 64 * DH * 2 + (DH == 128 ? (size_t)dkv_waves<DH>() * 32 * DH * 2 : 0) + 2 * 128 * 4;
+}
 
 // 32-bit buffer offsets: one head's rows must span less than 2 GiB
 bool fits(int64_t Tn, int64_t H, int64_t dh) { return (Tn + 192) * 3 * H * dh * 2 < ((int64_t)1 << 31); }
@@ -656,17 +661,17 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const float *
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void *)attn_bwd_dq_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kv_smem<128>());
-        (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128>());
-        (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128>());
         attr_set = true;
     }
     if (dh == 64) {
         attn_bwd_dq_mfma_k<64><<<grid, NT, kv_smem<64>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
-        attn_bwd_dkv_mfma_k<64, 0><<<grid, NT, dkv_smem<64>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
+        attn_bwd_dkv_mfma_k<64><<<grid, NT, dkv_smem<64>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
     } else {
         attn_bwd_dq_mfma_k<128><<<grid, NT, kv_smem<128>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
-        attn_bwd_dkv_mfma_k<128, 1><<<grid, NT, dkv_smem<128>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
-        attn_bwd_dkv_mfma_k<128, 2><<<grid, NT, dkv_smem<128>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
+        constexpr int KEYS = dkv_waves<128>() * 32;
+        const dim3 kgrid((unsigned)(((Tn + KEYS - 1) / KEYS) * ((B * H + 7) / 8) * 8));
+        attn_bwd_dkv_mfma_k<128><<<kgrid, dkv_waves<128>() * 64, dkv_smem<128>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
     }
 }
 
