@@ -221,6 +221,101 @@ __global__ void __launch_bounds__(WGM *WGN *KG * 64)
     }
 }
 
+// 16x16 tiles on v_mfma_f32_16x16x4_f32 for outputs of a few thousand elements: four times the workgroups, and a quarter of the
+// chain of dependent products per contraction element (8 clocks against 32).  Four wavefronts split every contraction tile; lane
+// quarter q takes k = 16c + 4q + j in product j of chunk c.
+template <bool AKM, bool BKM>
+__global__ void __launch_bounds__(256)
+    gemm_f32_tiny_k(const float *__restrict__ A, int64_t lda, const float *__restrict__ B, int64_t ldb, const float *__restrict__ bias,
+                    const float *resid, int64_t ldr, float *C, int64_t ldc, int64_t M, int64_t N, int64_t K, int tiles_m,
+                    float *__restrict__ rowsum, int rowsum_acc) {
+    constexpr int T = 16, BK = 128, NT = 256, KG = 4, CH = BK / 16 / KG, TPR = NT / T;
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
+    using OpA = F32Operand<T, BK, NT, AKM>;
+    using OpB = F32Operand<T, BK, NT, BKM>;
+    constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
+    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
+    __shared__ float red[KG - 1][4][64];
+
+    const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
+    const int64_t m0 = (int64_t)tm * T, n0 = (int64_t)tn * T;
+    const int tid = threadIdx.x, kg = tid >> 6, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+    const float *baseA = AKM ? A + m0 : A + m0 * lda, *baseB = BKM ? B + n0 : B + n0 * ldb;
+    OpA oa;
+    OpB ob;
+    oa.init(baseA, lda, (int)(M - m0 < T ? M - m0 : T), tid);
+    ob.init(baseB, ldb, (int)(N - n0 < T ? N - n0 : T), tid);
+    const int nk = (int)((K + BK - 1) / BK), nkf = (int)(K / BK), rem = (int)(K - (int64_t)nkf * BK);
+    const bool edge_rows = oa.slow_rows || ob.slow_rows;
+    float4 ra[2][OpA::PER], rb[2][OpB::PER];
+    auto load = [&](int set, int kt) {
+        if (kt < nkf && !edge_rows) {
+            oa.load(ra[set], kt);
+            ob.load(rb[set], kt);
+        } else {
+            const int kv = kt < nkf ? BK : rem;
+            oa.load_edge(ra[set], baseA, lda, kt, kv, tid);
+            ob.load_edge(rb[set], baseB, ldb, kt, kv, tid);
+        }
+    };
+    auto store = [&](int set) {
+        OpA::store(smem + set * STAGE, ra[set], tid);
+        OpB::store(smem + set * STAGE + OpA::FLOATS, rb[set], tid);
+    };
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    const bool do_rowsum = rowsum != nullptr && tn == 0;
+    float rsum = 0.f;
+    load(0, 0);
+    if (nk > 1) load(1, 1);
+    store(0);
+    __syncthreads();
+    auto tile = [&](int set, int kt) {                // stage `set` holds tile kt, the other register set tile kt + 1
+        if (kt + 2 < nk) load(set, kt + 2);
+        const float *As = smem + set * STAGE, *Bs = As + OpA::FLOATS;
+        if (do_rowsum) {
+#pragma unroll
+            for (int j = 0; j < BK / TPR; ++j) rsum += OpA::at(As, tid / TPR, (tid % TPR) * (BK / TPR) + j);
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            float fa[4], fb[4];
+            OpA::frag(fa, As, l16, 2 * (kg * CH + c), lq);
+            OpB::frag(fb, Bs, l16, 2 * (kg * CH + c), lq);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e], fb[e], acc, 0, 0, 0);
+        }
+        if (kt + 1 < nk) store(set ^ 1);
+        __syncthreads();
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+        tile(0, kt);
+        if (kt + 1 < nk) tile(1, kt + 1);
+    }
+    if (do_rowsum) {
+#pragma unroll
+        for (int o = 1; o < TPR; o <<= 1) rsum += __shfl_xor(rsum, o, 64);
+        const int64_t m = m0 + tid / TPR;
+        if (tid % TPR == 0 && m < M) rowsum[m] = rsum + (rowsum_acc ? rowsum[m] : 0.f);
+    }
+    if (kg > 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[kg - 1][r][lane] = acc[r];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+    const int64_t n = n0 + l16;
+    if (n >= N) return;
+    const float bn = bias ? bias[n] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t m = m0 + 4 * lq + r;
+        float x = acc[r];
+#pragma unroll
+        for (int g = 0; g < KG - 1; ++g) x += red[g][r][lane];
+        if (m < M) C[m * ldc + n] = x + bn + (resid ? resid[m * ldr + n] : 0.f);
+    }
+}
+
 template <int BM, int BN, int BK, int WGM, int WGN, int KG>
 void launch(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const float *B,
             int64_t ldb, const float *bias, const float *resid, int64_t ldr, float *C, int64_t ldc, float *rowsum, bool accumulate) {
@@ -250,7 +345,21 @@ void gemm_f32(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t
     // now 53.  128x128 tiles leave one wavefront per SIMD where the others leave three, and lose everywhere.
 #define TIO_F32_ARGS s, a_km, b_km, M, N, K, (const float *)A, lda, (const float *)B, ldb, (const float *)bias, (const float *)resid, ldr, \
                      (float *)C, ldc, (float *)rowsum, accumulate
-    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64), tiles32 = ((M + 31) / 32) * ((N + 31) / 32);
+    // 16x16 tiles up to 160 tiles of 32x32: 128 x 128 x 1024 (16 tiles) 12.5 -> 6.0 us, 256 x 512 x 512 (128) 8.5 -> 5.6,
+    // 300 x 500 x 1000 (160) 13.2 -> 11.5, but 64 x 3000 x 512 (188) 8.7 -> 10.2 with a k-major operand
+    if (tiles32 <= 160) {
+        const int tiles_m = (int)((M + 15) / 16);
+        const unsigned grid = (unsigned)(tiles_m * ((N + 15) / 16));
+#define TIO_F32_TINY(AKM, BKM) gemm_f32_tiny_k<AKM, BKM><<<grid, 256, 0, s>>>((const float *)A, lda, (const float *)B, ldb, (const float *)bias, \
+                                   (const float *)resid, ldr, (float *)C, ldc, M, N, K, tiles_m, (float *)rowsum, (int)accumulate)
+        if (!a_km && !b_km) TIO_F32_TINY(false, false);
+        else if (!a_km && b_km) TIO_F32_TINY(false, true);
+        else if (a_km && b_km) TIO_F32_TINY(true, true);
+        else TIO_F32_TINY(true, false);
+#undef TIO_F32_TINY
+        return;
+    }
     if (tiles64 >= 224) launch<64, 64, 32, 2, 2, 1>(TIO_F32_ARGS);
     else launch<32, 32, 64, 1, 1, 4>(TIO_F32_ARGS);
 #undef TIO_F32_ARGS

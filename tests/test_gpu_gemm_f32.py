@@ -1,12 +1,13 @@
-"""GPU: fp32 products at the sizes where the dispatch changes its tile (32 or 64 square) and at the edges of tiles and of
+"""GPU: fp32 products at the sizes where the dispatch changes its tile (16, 32 or 64 square) and at the edges of tiles and of
 contraction tiles, against numpy in 64 bits."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # M, N, K: 32x32 tiles, then 64x64 tiles; whole, one short, one over
-    (32, 32, 64), (1, 1, 1), (31, 33, 63), (65, 97, 200),
+CASES = [  # M, N, K: 16x16, 32x32, then 64x64 tiles; whole, one short, one over
+    (32, 32, 128), (1, 1, 1), (31, 33, 127), (65, 97, 300), (17, 15, 129),
+    (512, 512, 64), (509, 423, 63), (64, 3000, 200),
     (896, 1024, 32), (1024, 1024, 64), (1021, 1019, 97),
 ]
 
