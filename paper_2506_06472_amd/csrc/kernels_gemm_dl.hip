@@ -757,12 +757,10 @@ const TileChoice TILES[] = {
 bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
                       int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, float *ws,
                       int splits, bool rowsum_accumulate) {
-    // 32-bit buffer offsets: what one workgroup addresses of an operand has to lie within 1 GiB
     const int64_t kspan = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
-    const int64_t spanA = a_km ? (kspan + 3 * BK) * lda * 2 : ((int64_t)256 * lda + kspan + 3 * BK) * 2;
-    const int64_t spanB = b_km ? (kspan + 3 * BK) * ldb * 2 : ((int64_t)256 * ldb + kspan + 3 * BK) * 2;
+    // 32-bit buffer offsets: what one workgroup addresses of an operand has to lie within 1 GiB
+    auto span = [&](bool km, int64_t rows, int64_t ld) { return (km ? (kspan + 3 * BK) * ld : rows * ld + kspan + 3 * BK) * 2; };
     constexpr int64_t LIMIT = (int64_t)1 << 30;
-    if (spanA >= LIMIT || spanB >= LIMIT) return false;
     const Product p{s, a_km, b_km, M, N, K, (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid,
                     ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate};
     const int64_t nk = (kspan + BK - 1) / BK;
@@ -770,9 +768,11 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
     double best_cost = 0;
     for (const TileChoice &t : TILES) {
         if (rowsum && !(a_km && b_km) && !(t.bm == 128 && t.bn == 128)) continue;
+        if (span(a_km, t.bm, lda) >= LIMIT || span(b_km, t.bn, ldb) >= LIMIT) continue;
         const double cost = t.cost(((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1), nk);
         if (!best || cost < best_cost) { best = &t; best_cost = cost; }
     }
+    if (!best) return false;
     best->launch(p);
     return true;
 }
