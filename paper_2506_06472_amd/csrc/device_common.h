@@ -69,6 +69,9 @@ __device__ __forceinline__ void buffer_load16(Vec16<bf16_t> &v, __amdgpu_buffer_
     const tio_u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
     v.raw = make_uint4(t.x, t.y, t.z, t.w);
 }
+__device__ __forceinline__ float buffer_load4(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
 __device__ __forceinline__ void buffer_store16(const Vec16<float> &v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
     const tio_u32x4 t = {__float_as_uint(v.raw.x), __float_as_uint(v.raw.y), __float_as_uint(v.raw.z), __float_as_uint(v.raw.w)};
     __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)off, 0, 0);

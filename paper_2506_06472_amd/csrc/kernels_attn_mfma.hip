@@ -461,10 +461,13 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
 // wavefront's accumulators and K fragments take 160 of the 256 registers that two wavefronts per SIMD allow at head size 128,
 // so its V fragments are not kept in registers there but read from LDS (the workgroup's V rows, loaded once); to have room for
 // them, and half the tile loads per product, a workgroup is eight wavefronts with 256 key rows.  Bound: latency between the
-// products of two wavefronts per SIMD (the matrix cores are busy for a third of the time).  Measured at 4 x 2048 tokens, 32 heads
-// of 128: 482 us where two launches with four wavefronts each (dV, then dK) took 620 (18 % of that was tile loads); whole
-// backward pass faster at every size tried, from 1 x 64 x 2 heads (forward and backward 25.4 -> 21.5 us) to 1 x 4096 x 52 (1457 ->
-// 1233).  Transposed fragments four ahead in registers: 525 us, for want of the registers.
+// products of two wavefronts per SIMD.  Measured at 4 x 2048 tokens, 32 heads of 128 (kernel trace): 393 us, where two launches with
+// four wavefronts each (dV, then dK) took 227 + 302; whole backward pass faster at every size tried, from 1 x 64 x 2 heads (forward and
+// backward 25.4 -> 21.5 us) to 1 x 4096 x 52 (1457 -> 1233).  Head size 64, 8 x 1024 tokens, 12 heads: 60 us.
+// Every one of the 256 registers is in use at head size 128, and nothing may spill: a reload from scratch in the loop waits for the
+// tile loads in flight, and wavefront 0 with it keeps the other seven at the barrier (six spilled registers, and the statistics
+// multiplied where they are loaded: 418 us, and 70 at head size 64).  Transposed fragments four ahead in registers: slower by 9 %,
+// for want of the registers.
 template <int DH> constexpr int dkv_waves() { return DH == 128 ? 8 : 4; }
 template <int DH>
 __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
@@ -490,7 +493,7 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
     const i32x4 rsQ = make_rsrc(qb, head_bytes);
     const i32x4 rsG = make_rsrc(dO + b * Tn * d + h * DH, (uint32_t)(((Tn - 1) * d + DH) * 2));
     const float c = scale * LOG2E;
-    const bool live = kv < Tn;
+    const bool live = kv < (int)Tn;
     const TileLanes<DH, VLDS> L(lane);
     const DmaTile<DH, NW> dmaQ(ldb, wave, lane), dmaG(ldg, wave, lane);
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
@@ -512,19 +515,21 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
     for (int i = 0; i < DT; ++i) { dk[i] = zero16(); dv[i] = zero16(); }
     const int ntiles = ((int)Tn - kv0 + 63) / 64;
 
-    float st_l = 0.f, st_d = 0.f;                       // statistics of row i0 + tid (threads 0..63), one tile ahead
+    // Statistics of row i0 + lane, one tile ahead, in wavefront 0: through descriptors of the head's rows (rows past the
+    // sequence read zero; no addresses to keep in registers), used only where they go to LDS, a tile after their fetch.
+    const __amdgpu_buffer_rsrc_t rsL = buffer_over(lse + bh * Tn, (uint32_t)Tn * 4), rsD = buffer_over(delta + bh * Tn, (uint32_t)Tn * 4);
+    float st_l = 0.f, st_d = 0.f;
     float *stats = reinterpret_cast<float *>(smem + 2 * BUF + (VLDS ? KEYS * DH : 0));
     auto load_stats = [&](int i0) {
-        if (tid < 64) {
-            const bool ok = i0 + tid < Tn;
-            st_l = ok ? lse[bh * Tn + i0 + tid] * LOG2E : 0.f;
-            st_d = ok ? delta[bh * Tn + i0 + tid] : 0.f;
+        if (wave == 0) {
+            st_l = buffer_load4(rsL, (uint32_t)(i0 + lane) * 4);
+            st_d = buffer_load4(rsD, (uint32_t)(i0 + lane) * 4);
         }
     };
     auto store_stats = [&](int buf) {
-        if (tid < 64) {
-            stats[buf * 128 + tid] = st_l;
-            stats[buf * 128 + 64 + tid] = st_d;
+        if (wave == 0) {
+            stats[buf * 128 + lane] = st_l * LOG2E;
+            stats[buf * 128 + 64 + lane] = st_d;
         }
     };
     auto load_tile = [&](int i0, int buf) {
@@ -613,6 +618,7 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
     }
     if (live) {
         uint16_t *krow = dqkv + (b * Tn + kv) * ld + d + h * DH, *vrow = krow + d;
+        const int half = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) >> 5;      // lhi, not kept over the loop
 #pragma unroll
         for (int i = 0; i < DT; ++i)
 #pragma unroll
@@ -620,10 +626,10 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
                 uint2 w;
                 w.x = pack2(dk[i][4 * g] * scale, dk[i][4 * g + 1] * scale);
                 w.y = pack2(dk[i][4 * g + 2] * scale, dk[i][4 * g + 3] * scale);
-                *reinterpret_cast<uint2 *>(krow + i * 32 + 8 * g + 4 * lhi) = w;
+                *reinterpret_cast<uint2 *>(krow + i * 32 + 8 * g + 4 * half) = w;
                 w.x = pack2(dv[i][4 * g], dv[i][4 * g + 1]);
                 w.y = pack2(dv[i][4 * g + 2], dv[i][4 * g + 3]);
-                *reinterpret_cast<uint2 *>(vrow + i * 32 + 8 * g + 4 * lhi) = w;
+                *reinterpret_cast<uint2 *>(vrow + i * 32 + 8 * g + 4 * half) = w;
             }
     }
 }
