@@ -639,8 +639,12 @@ template <int DH> constexpr size_t dkv_smem() {         // tiles, V rows, then s
     return (size_t)2 * 2 * 64 * DH * 2 + (DH == 128 ? (size_t)dkv_waves<DH>() * 32 * DH * 2 : 0) + 2 * 128 * 4;
 }
 
-// 32-bit buffer offsets: one head's rows must span less than 2 GiB
-bool fits(int64_t Tn, int64_t H, int64_t dh) { return (Tn + 192) * 3 * H * dh * 2 < ((int64_t)1 << 31); }
+// Unsigned 32-bit buffer offsets: one head's rows, and PAST more, span less than 2 GiB.  A block's rows past the sequence (up to
+// its size less one) are addressed too and refused by the descriptor, so their offsets must not wrap around 4 GiB: as many rows as
+// twice PAST keep Tn + rows below twice Tn + PAST.
+constexpr int64_t PAST = 192;
+static_assert(dkv_waves<64>() * 32 <= 2 * PAST && dkv_waves<128>() * 32 <= 2 * PAST && 128 <= 2 * PAST, "offsets past the sequence do not wrap");
+bool fits(int64_t Tn, int64_t H, int64_t dh) { return (Tn + PAST) * 3 * H * dh * 2 < ((int64_t)1 << 31); }
 
 }  // namespace
 
