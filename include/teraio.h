@@ -334,6 +334,10 @@ int tio_op_gemm(void *stream, int32_t dtype, int32_t a_kmajor, int32_t b_kmajor,
                 const void *A, int64_t lda, const void *B, int64_t ldb,
                 const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum,
                 void *workspace, int32_t splits);
+/* Measuring aid, host only: the output tile (rows x columns) that tio_op_gemm takes for a bf16 product, with or without row sums and
+ * with its contraction in `splits` ranges (workspace given, no bias / resid); 0 x 0: the kernel with 64-bit addressing. */
+int tio_op_gemm_tile(int32_t a_kmajor, int32_t b_kmajor, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int32_t rowsum,
+                     int32_t splits, int32_t *out_rows, int32_t *out_cols);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): tio_op_gemm without bias / residual, whose split-contraction partial tiles go to a
  * fixed 64 MiB (67108864-byte) array in the library's device image instead of a caller workspace.  It allocates

@@ -450,6 +450,14 @@ def tio_op_gemm(stream_handle, dtype, a_kmajor, b_kmajor, M, N, K, A_ptr, lda, B
                              vp(resid_ptr), C.c_int64(ldr), vp(C_ptr), C.c_int64(ldc), vp(rowsum_ptr), vp(workspace_ptr), int(splits)))
 
 
+def tio_op_gemm_tile(a_kmajor, b_kmajor, M, N, K, lda, ldb, rowsum=False, splits=1):
+    """(rows, columns) of the output tile tio_op_gemm takes for a bf16 product; host only."""
+    rows, cols = C.c_int32(), C.c_int32()
+    _check(lib().tio_op_gemm_tile(int(a_kmajor), int(b_kmajor), C.c_int64(M), C.c_int64(N), C.c_int64(K), C.c_int64(lda),
+                                  C.c_int64(ldb), int(rowsum), int(splits), C.byref(rows), C.byref(cols)))
+    return rows.value, cols.value
+
+
 def tio_op_gemm_static_ws(stream_handle, dtype, a_kmajor, b_kmajor, M, N, K, A_ptr, lda, B_ptr, ldb, C_ptr, ldc,
                           rowsum_ptr=0, splits=1):
     """tio_op_gemm with the split-contraction partials in the library's fixed device array; allocates nothing."""

@@ -23,6 +23,9 @@ void norm_fwd(hipStream_t s, int dtype, bool rms, const void *x, const void *g, 
 bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A,
                       int64_t lda, const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr,
                       void *C, int64_t ldc, void *rowsum, float *ws, int splits, bool rowsum_accumulate);
+// the output tile gemm_bf16_direct takes, 0 x 0 where it refuses; host only
+void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits, int *rows,
+                    int *cols);
 // fp32 products on the fp32 matrix instruction (kernels_gemm_f32.hip); accumulate adds to rowsum (the caller passes C as resid)
 void gemm_f32(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
               int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, bool accumulate);

@@ -694,15 +694,17 @@ template <auto *KERNEL> void launch(const Product &p, int BM, int BN, int thread
                                         p.rowsum, p.ws, k_chunk, p.rowsum_acc, xsplits);
 }
 
-// With row sums only the layout of a weight gradient (both operands k-major) has every tile; the others have the 128x128 one.
+// With row sums the layout of a weight gradient (both operands k-major) has every tile, the others the two square ones above 64:
+// the large one for outputs that fill the chip with it (8192 x 22016 x 4096, A and B contraction-contiguous: 1050 us, 1385 with 128x128
+// alone; the kernel with eight wavefronts before took 1182).
+constexpr bool row_sums_in_every_layout(int bm, int bn) { return bm == bn && bm >= 128; }
 template <int BM, int BN, int D> void launch_dl(const Product &p) {
     constexpr size_t lds = (size_t)((D + 1) * BM + D * BN) * BK * 2;
     static_assert(lds <= 160 * 1024, "LDS of a compute unit");
-    constexpr bool EVERY = BM == 128 && BN == 128;
 #define TIO_DL(AKM, BKM, RS) launch<gemm_bf16_dl_k<BM, BN, 2, 2, D, AKM, BKM, RS>>(p, BM, BN, 256, lds)
     if (p.rowsum) {
         if (p.a_km && p.b_km) TIO_DL(true, true, true);
-        else if constexpr (EVERY) {
+        else if constexpr (row_sums_in_every_layout(BM, BN)) {
             if (p.a_km) TIO_DL(true, false, true);
             else if (p.b_km) TIO_DL(false, true, true);
             else TIO_DL(false, false, true);
@@ -752,29 +754,41 @@ const TileChoice TILES[] = {
     {64, 64, 2, 0.42, 3, 0.2, 3.5, launch_small<4>},
 };
 
+// the tile with the lowest cost among those that can address the operands and have the layout; nullptr: none can
+const TileChoice *choose(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits) {
+    const int64_t kspan = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
+    // 32-bit buffer offsets: what one workgroup addresses of an operand has to lie within 1 GiB
+    auto span = [&](bool km, int64_t rows, int64_t ld) { return (km ? (kspan + 3 * BK) * ld : rows * ld + kspan + 3 * BK) * 2; };
+    constexpr int64_t LIMIT = (int64_t)1 << 30;
+    const int64_t nk = (kspan + BK - 1) / BK;
+    const TileChoice *best = nullptr;
+    double best_cost = 0;
+    for (const TileChoice &t : TILES) {
+        if (rowsum && !(a_km && b_km) && !row_sums_in_every_layout(t.bm, t.bn)) continue;
+        if (span(a_km, t.bm, lda) >= LIMIT || span(b_km, t.bn, ldb) >= LIMIT) continue;
+        const double cost = t.cost(((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1), nk);
+        if (!best || cost < best_cost) { best = &t; best_cost = cost; }
+    }
+    return best;
+}
+
 }  // namespace
 
 bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
                       int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, float *ws,
                       int splits, bool rowsum_accumulate) {
-    const int64_t kspan = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
-    // 32-bit buffer offsets: what one workgroup addresses of an operand has to lie within 1 GiB
-    auto span = [&](bool km, int64_t rows, int64_t ld) { return (km ? (kspan + 3 * BK) * ld : rows * ld + kspan + 3 * BK) * 2; };
-    constexpr int64_t LIMIT = (int64_t)1 << 30;
-    const Product p{s, a_km, b_km, M, N, K, (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid,
-                    ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate};
-    const int64_t nk = (kspan + BK - 1) / BK;
-    const TileChoice *best = nullptr;
-    double best_cost = 0;
-    for (const TileChoice &t : TILES) {
-        if (rowsum && !(a_km && b_km) && !(t.bm == 128 && t.bn == 128)) continue;
-        if (span(a_km, t.bm, lda) >= LIMIT || span(b_km, t.bn, ldb) >= LIMIT) continue;
-        const double cost = t.cost(((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1), nk);
-        if (!best || cost < best_cost) { best = &t; best_cost = cost; }
-    }
-    if (!best) return false;
-    best->launch(p);
+    const TileChoice *t = choose(a_km, b_km, M, N, K, lda, ldb, rowsum != nullptr, splits);
+    if (!t) return false;
+    t->launch(Product{s, a_km, b_km, M, N, K, (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid,
+                      ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate});
     return true;
+}
+
+void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits, int *rows,
+                    int *cols) {
+    const TileChoice *t = choose(a_km, b_km, M, N, K, lda, ldb, rowsum, splits);
+    *rows = t ? t->bm : 0;
+    *cols = t ? t->bn : 0;
 }
 
 }  // namespace k

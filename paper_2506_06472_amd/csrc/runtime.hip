@@ -864,6 +864,14 @@ int tio_op_gemm(void *stream, int32_t dtype, int32_t a_km, int32_t b_km, int64_t
     TIO_RT_END
 }
 
+int tio_op_gemm_tile(int32_t a_km, int32_t b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int32_t rowsum, int32_t splits,
+                     int32_t *out_rows, int32_t *out_cols) {
+    if (!out_rows || !out_cols) return fail(TIO_ERR_INVALID_ARG, "null argument");
+    if (M < 1 || N < 1 || K < 1 || splits < 1 || splits > 64) return fail(TIO_ERR_INVALID_ARG, "non-positive dimension, or splits not in 1..64");
+    k::gemm_bf16_tile(a_km != 0, b_km != 0, M, N, K, lda, ldb, rowsum != 0, N % 4 ? 1 : splits, out_rows, out_cols);
+    return TIO_OK;
+}
+
 // ---- split-contraction product for callers that cannot allocate ------------------------------------------------
 // The fp32 partial tiles go to a fixed array in device memory instead of a workspace from the caller.  In host
 // code the array's name is only a handle for hipGetSymbolAddress: every device has its own copy at its own address,

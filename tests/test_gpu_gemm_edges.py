@@ -6,11 +6,18 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+r8 = lambda n: (n + 7) // 8 * 8
+
+
+def _tile(M, N, K, a_km, b_km, rowsum, splits=1):
+    import paper_2506_06472_amd as tio
+    return tio.tio_op_gemm_tile(a_km, b_km, M, N, K, r8(M) if a_km else r8(K), r8(N) if b_km else r8(K), rowsum, splits)
+
+
 def _run(M, N, K, a_km, b_km, rowsum, splits=1):
     import torch
     import paper_2506_06472_amd as tio
     print(f"bf16 gemm M={M} N={N} K={K} a_km={a_km} b_km={b_km} rowsum={rowsum} splits={splits}", flush=True)
-    r8 = lambda n: (n + 7) // 8 * 8
     g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K + a_km + 2 * b_km)
     A = torch.randn((M, K), device="cuda", generator=g).bfloat16()
     B = torch.randn((N, K), device="cuda", generator=g).bfloat16()
@@ -56,3 +63,10 @@ def test_every_tile(M, N, K, a_km, b_km):
 @pytest.mark.parametrize("M,N,K,splits", [(256, 128, 1000, 3), (129, 68, 517, 2), (200, 136, 64, 8), (130, 64, 4097, 4)])
 def test_split_contraction_remainders(M, N, K, splits):
     _run(M, N, K, 1, 1, rowsum=True, splits=splits)
+
+
+@pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031)])
+def test_row_sums_of_the_large_tile_in_every_layout(M, N, K, a_km, b_km):
+    assert _tile(M, N, K, a_km, b_km, True) == (256, 256)
+    _run(M, N, K, a_km, b_km, rowsum=True)
