@@ -1,40 +1,45 @@
-"""GPU: the bf16 product kernel at the edges of its tiles: contractions of 1 to 4 tiles with every kind of remainder (whole,
-a multiple of 8, odd), outputs one short of and one over a tile, with and without row sums and split contraction, against
-float64; padding is NaN and must never leak."""
+"""GPU: the bf16 product kernels at the edges of their tiles: contractions of one to a dozen tiles with every kind of remainder
+(whole, a multiple of 8, odd), outputs one short of and one over a tile, every epilogue (plain, bias and residual on rows of 8k and
+8k + 4 elements, row sums, split contraction with short and empty ranges), against float64; padding is NaN and must never leak.  Every
+test states the output tile it is about and checks that the dispatch takes it."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-
+LAYOUTS = [(0, 0), (0, 1), (1, 1), (1, 0)]
 r8 = lambda n: (n + 7) // 8 * 8
 
 
-def _tile(M, N, K, a_km, b_km, rowsum, splits=1):
-    import paper_2506_06472_amd as tio
-    return tio.tio_op_gemm_tile(a_km, b_km, M, N, K, r8(M) if a_km else r8(K), r8(N) if b_km else r8(K), rowsum, splits)
-
-
-def _run(M, N, K, a_km, b_km, rowsum, splits=1):
+def _run(M, N, K, a_km, b_km, rowsum=False, splits=1, tile=None, epilogue=False, pad=0):
     import torch
     import paper_2506_06472_amd as tio
-    print(f"bf16 gemm M={M} N={N} K={K} a_km={a_km} b_km={b_km} rowsum={rowsum} splits={splits}", flush=True)
+    print(f"bf16 gemm M={M} N={N} K={K} a_km={a_km} b_km={b_km} rowsum={rowsum} splits={splits} tile={tile} epilogue={epilogue} pad={pad}",
+          flush=True)
+    lda, ldb, ldc = r8(M) if a_km else r8(K), r8(N) if b_km else r8(K), r8(N) + pad
+    if tile:
+        assert tio.tio_op_gemm_tile(a_km, b_km, M, N, K, lda, ldb, rowsum, splits) == tile
     g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K + a_km + 2 * b_km)
     A = torch.randn((M, K), device="cuda", generator=g).bfloat16()
     B = torch.randn((N, K), device="cuda", generator=g).bfloat16()
 
-    def stored(X, km):
-        X = X.t() if km else X
-        t = torch.full((X.shape[0], r8(X.shape[1])), float("nan"), device="cuda", dtype=torch.bfloat16)
+    def stored(X, ld):
+        t = torch.full((X.shape[0], ld), float("nan"), device="cuda", dtype=torch.bfloat16)
         t[:, :X.shape[1]] = X
         return t
-    dA, dB = stored(A, a_km), stored(B, b_km)
-    C = torch.full((M, r8(N)), 7.0, device="cuda", dtype=torch.bfloat16)
+    dA, dB = stored(A.t() if a_km else A, lda), stored(B.t() if b_km else B, ldb)
+    C = torch.full((M, ldc), 7.0, device="cuda", dtype=torch.bfloat16)
     rs = torch.full((r8(M) + 8,), 7.0, device="cuda", dtype=torch.bfloat16)
     ws = torch.full((splits * (M * N + M) + 64,), float("nan"), device="cuda") if splits > 1 else None
-    tio.tio_op_gemm(0, "bf16", a_km, b_km, M, N, K, dA.data_ptr(), dA.shape[1], dB.data_ptr(), dB.shape[1], 0, 0, 0, C.data_ptr(),
-                    r8(N), rs.data_ptr() if rowsum else 0, ws.data_ptr() if ws is not None else 0, splits)
-    torch.cuda.synchronize()
     ref, mag = A.double() @ B.double().t(), A.abs().double() @ B.abs().double().t()
+    bias = resid = None
+    if epilogue:
+        b, R = (torch.randn(n, device="cuda", generator=g).bfloat16() * 8 for n in ((1, N), (M, N)))
+        bias, resid = stored(b, r8(N)), stored(R, ldc)
+        ref, mag = ref + b.double() + R.double(), mag + b.abs().double() + R.abs().double()
+    tio.tio_op_gemm(0, "bf16", a_km, b_km, M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, bias.data_ptr() if epilogue else 0,
+                    resid.data_ptr() if epilogue else 0, ldc, C.data_ptr(), ldc, rs.data_ptr() if rowsum else 0,
+                    ws.data_ptr() if ws is not None else 0, splits)
+    torch.cuda.synchronize()
     # one fp32 rounding per addition of the chain, one bf16 rounding of the result
     bound = (K + 8) * 2.0 ** -24 * mag + 2.0 ** -8 * ref.abs()
     assert ((C[:, :N].double() - ref).abs() <= bound).all() and (C[:, N:] == 7.0).all()
@@ -46,27 +51,58 @@ def _run(M, N, K, a_km, b_km, rowsum, splits=1):
         assert torch.isnan(ws[splits * (M * N + M):]).all()
 
 
-@pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("a_km,b_km", LAYOUTS)
 @pytest.mark.parametrize("K", [1, 8, 31, 64, 65, 96, 127, 128, 129, 191, 192, 200, 256, 319])
 def test_contraction_remainders(K, a_km, b_km):
-    _run(127, 129, K, a_km, b_km, rowsum=K % 2 == 1)
+    rowsum = K % 2 == 1                              # with row sums only k-major operands have the 64x64 tile
+    _run(127, 129, K, a_km, b_km, rowsum, tile=(128, 128) if rowsum and not (a_km and b_km) else (64, 64))
 
 
-# output sizes that get each of the tiles: 256x256, 256x192, 128x192, 128x128, 64x64
-@pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 1), (1, 0)])
-@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031), (8192, 3072, 768), (8100, 3070, 777), (2047, 3072, 3000),
-                                   (4000, 1500, 640), (3100, 1000, 200), (2048, 2048, 300), (500, 700, 391), (1021, 768, 5025)])
-def test_every_tile(M, N, K, a_km, b_km):
-    _run(M, N, K, a_km, b_km, rowsum=a_km == b_km == 1)
+# one short of and one over whole tiles; contractions from one tile (less than the ring of tiles in LDS holds) to several, as short
+# as the dispatch gives each tile
+@pytest.mark.parametrize("a_km,b_km", LAYOUTS)
+@pytest.mark.parametrize("tile,M,N,K", [
+    *(((256, 256), 3990, 4010, K) for K in (1, 31, 64, 65, 127, 128, 129, 191, 319)),
+    *(((128, 128), 3100, 1010, K) for K in (1, 64, 65, 128, 129, 191, 391)),
+    *(((256, 192), 8100, 3010, K) for K in (513, 520, 639, 640)),
+    *(((128, 192), 2047, 3060, K) for K in (641, 648, 703, 705, 777))])
+def test_contraction_remainders_of_the_larger_tiles(tile, M, N, K, a_km, b_km):
+    _run(M, N, K, a_km, b_km, tile=tile)
+    if a_km and b_km:
+        _run(M, N, K, a_km, b_km, rowsum=True, tile=tile)
 
 
-@pytest.mark.parametrize("M,N,K,splits", [(256, 128, 1000, 3), (129, 68, 517, 2), (200, 136, 64, 8), (130, 64, 4097, 4)])
-def test_split_contraction_remainders(M, N, K, splits):
-    _run(M, N, K, 1, 1, rowsum=True, splits=splits)
+EVERY_TILE = [((256, 256), 4096, 4096, 1024), ((256, 256), 4095, 3841, 1031), ((256, 192), 8192, 3072, 768), ((256, 192), 8100, 3070, 777),
+              ((128, 192), 2047, 3072, 3000), ((128, 192), 2048, 3072, 704), ((128, 128), 4000, 1500, 640), ((128, 128), 3100, 1000, 200),
+              ((128, 128), 2048, 2048, 300), ((64, 64), 500, 700, 391), ((64, 64), 1021, 768, 5025), ((64, 64), 512, 640, 384)]
+
+
+@pytest.mark.parametrize("a_km,b_km", LAYOUTS)
+@pytest.mark.parametrize("tile,M,N,K", EVERY_TILE)
+def test_every_tile(tile, M, N, K, a_km, b_km):
+    _run(M, N, K, a_km, b_km, rowsum=a_km == b_km == 1, tile=tile)
+
+
+@pytest.mark.parametrize("a_km,b_km", LAYOUTS)
+@pytest.mark.parametrize("pad", [0, 4])              # rows of 8k + 4 elements: output and residual move element by element
+@pytest.mark.parametrize("tile,M,N,K", EVERY_TILE)
+def test_every_tile_with_bias_and_residual(tile, M, N, K, pad, a_km, b_km):
+    _run(M, N, K, a_km, b_km, tile=tile, epilogue=True, pad=pad)
+
+
+@pytest.mark.parametrize("tile,M,N,K,splits", [
+    ((64, 64), 256, 128, 1000, 3), ((64, 64), 129, 68, 517, 2), ((64, 64), 200, 136, 64, 8), ((64, 64), 130, 64, 4097, 4),
+    ((128, 128), 768, 768, 2048, 8), ((256, 256), 840, 6980, 500, 2), ((256, 256), 832, 6976, 128, 2), ((256, 192), 840, 4680, 2000, 2),
+    ((128, 192), 768, 3072, 8192, 2), ((128, 192), 3070, 764, 4161, 2), ((128, 192), 640, 836, 5121, 8),
+    # ranges of 640: the last of sixteen is one element long, or empty behind one of 257
+    ((128, 192), 250, 1148, 9601, 16), ((128, 192), 250, 1148, 9217, 16), ((256, 192), 380, 1324, 9601, 16),
+    ((256, 256), 500, 1544, 9217, 16)])
+@pytest.mark.parametrize("rowsum", [False, True])
+def test_split_contraction_remainders(tile, M, N, K, splits, rowsum):
+    _run(M, N, K, 1, 1, rowsum=rowsum, splits=splits, tile=tile)
 
 
 @pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 0)])
-@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031)])
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031), (3990, 4010, 65)])
 def test_row_sums_of_the_large_tile_in_every_layout(M, N, K, a_km, b_km):
-    assert _tile(M, N, K, a_km, b_km, True) == (256, 256)
-    _run(M, N, K, a_km, b_km, rowsum=True)
+    _run(M, N, K, a_km, b_km, rowsum=True, tile=(256, 256))

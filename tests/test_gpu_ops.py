@@ -76,14 +76,15 @@ def test_gemm_all_layouts(dtype, a_km, b_km, M, N, K, pad):
 
 @pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 1), (1, 0)])
 def test_gemm_large_tile_configuration(a_km, b_km):
-    """Enough 256x256 output tiles for the dispatch to pick the large-tile kernel; ragged in M, N and K."""
+    """Two rounds of 256x256 output tiles over the chip, with row sums; ragged in M, N and K."""
     import torch
     import paper_2506_06472_amd as tio
-    M, N, K = 5900, 5650, 200
+    M, N, K = 8100, 4010, 200
     print(f"large-tile gemm a_km={a_km} b_km={b_km}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(11 + 2 * a_km + b_km)
     r8 = lambda n: (n + 7) // 8 * 8
     lda, ldb, ldc = (r8(M) if a_km else r8(K)), (r8(N) if b_km else r8(K)), r8(N)
+    assert tio.tio_op_gemm_tile(a_km, b_km, M, N, K, lda, ldb, rowsum=True) == (256, 256)
     dA = torch.randn((K, lda) if a_km else (M, lda), device="cuda", generator=g).to(torch.bfloat16)
     dB = torch.randn((K, ldb) if b_km else (N, ldb), device="cuda", generator=g).to(torch.bfloat16)
     # padding must never leak into the result
