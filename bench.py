@@ -32,7 +32,7 @@ ATTN_OPS = (4, 17)
 HBM_CLASSES = {"norm": (1, 14, 15), "activation": (5, 6, 12, 13), "rope": (3, 18), "cross_entropy": (7,),
                "embedding": (0, 19, 20), "adamw": (21,)}
 PEAK_BF16_TFLOPS = 2500.0
-PEAK_FP32_VECTOR_TFLOPS = 157.3
+PEAK_FP32_TFLOPS = 157.3
 
 
 def gemm_traffic(workload):
@@ -423,7 +423,7 @@ def main():
     gemm_tflops = gemm_flops / gemm_ns / 1e3
     traffic = gemm_traffic(args.workload) if args.micro_batches == 1 else None
     bf16 = cfg["precision"] == "bf16"
-    gemm_peak = PEAK_BF16_TFLOPS if bf16 else PEAK_FP32_VECTOR_TFLOPS
+    gemm_peak = PEAK_BF16_TFLOPS if bf16 else PEAK_FP32_TFLOPS
     attn_tflops = flops[attn].sum() / ktimes[attn].sum() / 1e3
     comp_s = ktimes.sum() / 1e9
     mig_bound_s = (pe["bytes_per_direction"] * (2 if shared else 1) / bw) if bw else 0.0
@@ -463,9 +463,10 @@ def main():
         "attention_tflops": attn_tflops, "loss": loss,
         "hbm_kernels": {"peak_GBps": 8000.0, "bytes": "operand tensor sizes, counted once per read and once per write",
                         "classes": hbm},
-        # fp32 workloads (the tiny parity configurations) run the contractions on the fp32 vector ALU
+        # fp32 workloads (the tiny parity configurations) run the contractions on the fp32 matrix instruction, whose peak is that of
+        # the vector ALU ("alu")
         "roofline": {"bound": "mfma" if bf16 else "alu",
-                     "kernel": ("gemm_bf16_dl_k" if bf16 else "gemm_f32_k") + " (forward, dX and dW contractions)",
+                     "kernel": ("gemm_bf16_dl_k" if bf16 else "gemm_f32_mfma_k, gemm_f32_tiny_k") + " (forward, dX and dW contractions)",
                      "achieved": gemm_tflops, "peak": gemm_peak, "unit": "TFLOP/s",
                      "frac": gemm_tflops / gemm_peak, "traffic": (traffic or {}).get("bytes_per_launch"),
                      "traffic_unit": "bytes per launch missing the L2 (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated); "
