@@ -1072,7 +1072,8 @@ void ce_fwd_bwd(hipStream_t s, int dtype, void *logits, const int32_t *labels, f
     TIO_DISPATCH(dtype, {
         // 16-byte chunks per row; NT threads take NCH each.  Long rows are spread over 1024 threads: with 32 chunks in the
         // registers of each of 256, too few workgroups fit a compute unit for one row's exponentials to overlap another's loads
-        // (8192 rows of 50257 in bf16: 476 us, 3.5 TB/s; with 1024 threads 355 us, 4.6 TB/s)
+        // (8192 rows of 50257 in bf16: 486 us, 3.4 TB/s; with 1024 threads 353 us, 4.7 TB/s).  The order of the sum differs between
+        // the two, within fp32 rounding
         const int64_t chunks = ld / Vec16<T>::N;
         if (chunks <= 256 * 4) TIO_CE_REG(4, 256);
         else if (chunks <= 256 * 8) TIO_CE_REG(8, 256);

@@ -736,6 +736,9 @@ template <int D> void launch_small(const Product &p) {
 //    8192 x  768 x  3072   60 /  47 /  36 /  40 /  61      1021 x  768 x 50257  1097 / 1000 / 638 /  540 / 264
 //    8192 x 3072 x   768   48 /  44 /  54 /  43            1000 x 5120 x  5120    88 /   70 /  50 /   62 /  81
 //     768 x  768 x  8192  137 / 109 /  65 /  62 /  30      8192 x 22016 x 4096  1027 / 1101 / 1404 / 1381
+// The costs know neither where an operand's rows start in a cache line nor what the caches hold: for 1021 x 768 x 50257 they give the
+// 64x64 tile 161 us, which it takes (158) with warm operands in rows of whole 128-byte lines; rows of 100528 bytes make that 199, and
+// operands in no cache 264 (with whole lines 222).
 struct TileChoice {
     int bm, bn, per_cu;
     double tile, fixed, solo, solo_fixed;
