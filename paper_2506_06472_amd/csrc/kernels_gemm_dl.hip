@@ -210,104 +210,209 @@ __device__ __forceinline__ void store_rowsum(const floatx4 (&rs)[TM / 2], int la
     }
 }
 
-// A wavefront's part of the output tile through LDS, 16 rows at a time as fp32, so that a lane ends up with eight consecutive
-// columns of one row: bias, residual and output (or the fp32 partial tile of a split product) move as whole 16-byte chunks.
+// What a lane has of eight columns of a row of which the first n are there (rows start on 8-byte boundaries): whole groups of four,
+// and up to three elements behind them, which are put together only where they are used: doing so behind their loads would wait for
+// them.  Missing elements are zero.
+struct Piece {
+    uint2 lo, hi;
+    uint32_t t[3];
+    __device__ __forceinline__ void load(const uint16_t *p, int n) {
+        lo = hi = make_uint2(0, 0);
+        t[0] = t[1] = t[2] = 0;
+        if (n >= 4) lo = *reinterpret_cast<const uint2 *>(p);
+        if (n >= 8) hi = *reinterpret_cast<const uint2 *>(p + 4);
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < (n & 3)) t[e] = p[(n & 4) + e];
+    }
+    __device__ __forceinline__ uint4 get(int n) const {
+        const uint2 w = make_uint2(t[0] | (t[1] << 16), t[2]);
+        const uint2 a = n >= 4 ? lo : w, b = n >= 8 ? hi : n > 4 ? w : make_uint2(0, 0);
+        return make_uint4(a.x, a.y, b.x, b.y);
+    }
+    static __device__ __forceinline__ void store(uint16_t *p, const uint4 &v, int n) {
+        if (n >= 4) *reinterpret_cast<uint2 *>(p) = make_uint2(v.x, v.y);
+        if (n >= 8) *reinterpret_cast<uint2 *>(p + 4) = make_uint2(v.z, v.w);
+        const uint32_t w0 = n & 4 ? v.z : v.x, w1 = n & 4 ? v.w : v.y, u[3] = {w0 & 0xffffu, w0 >> 16, w1 & 0xffffu};
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < (n & 3)) p[(n & 4) + e] = (uint16_t)u[e];
+    }
+};
+__device__ __forceinline__ void add8(float (&v)[8], const uint4 &t) {
+    const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
+}
+
+// ---- epilogue: a wavefront's part of the output tile through LDS as fp32, 16 rows at a time, so that a lane ends up with eight
+// consecutive columns of one row: bias, residual and output (or the fp32 partial tile of a split product) move as whole 16-byte chunks.
+//
+// A part that lies wholly inside the output is straight-line code for the operands it has: tests of them between the blocks keep
+// the compiler from having one block's LDS reads and another's stores under way together, and with one wavefront per SIMD nothing
+// else hides them.  With a residual the next blocks' reads of it and of LDS are issued ahead as well.  Measured with 256x256 tiles and
+// operands in the caches, us, tests inside / straight-line: 8192 x 4096 x 64 24.1 / 21.9, with bias 27.4 / 21.8, with residual 39.0 /
+// 33.2; 8192 x 12288 x 768 149 / 142, with bias 164 / 146, with residual 211 / 193.
+template <int TM, int TN> struct Part {
+    static constexpr int WN = TN * 16, SPF = WN + 4, CPR = WN / 8, PASSES = 16 * CPR / 64;
+    static_assert((16 * CPR) % 64 == 0, "a 16-row block is a whole number of wavefront passes");
+    int row[PASSES], col[PASSES];                    // this lane's chunks of a block
+    __device__ __forceinline__ explicit Part(int lane) {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            row[p] = (p * 64 + lane) / CPR;
+            col[p] = (p * 64 + lane) % CPR * 8;
+        }
+    }
+    static __device__ __forceinline__ void to_lds(float *at, const floatx4 (&acc)[TN], int lane) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(at + (lane & 15) * SPF + j * 16 + (lane >> 4) * 4) = acc[j];
+    }
+    __device__ __forceinline__ void from_lds(float (&v)[PASSES][8], const float *at) const {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float4 t = *reinterpret_cast<const float4 *>(at + row[p] * SPF + col[p] + 4 * h);
+                v[p][4 * h] = t.x; v[p][4 * h + 1] = t.y; v[p][4 * h + 2] = t.z; v[p][4 * h + 3] = t.w;
+            }
+    }
+};
+template <int TM> constexpr int stage_rows() { return TM * 16 < 64 ? TM * 16 : 64; }
+template <int TM, int TN> constexpr int stage_floats() { return stage_rows<TM>() * Part<TM, TN>::SPF; }       // a wavefront's staging area
+__device__ __forceinline__ uint4 pack8(const float (&v)[8]) {
+    return make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+}
+__device__ __forceinline__ void store8(float *dst, const float (&v)[8], int n) {       // whole groups of four
+    *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    if (n > 4) *reinterpret_cast<float4 *>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
+}
+
+template <int TM, int TN, bool BIAS, bool RESID, bool WS>
+__device__ __forceinline__ void store_inside(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
+                                             const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
+                                             float *__restrict__ ws, int split) {
+    using P = Part<TM, TN>;
+    constexpr int PASSES = P::PASSES, AHEAD = RESID ? 1 : 0;         // blocks that pass through LDS ahead of the one being stored
+    const P part(lane);
+    const int64_t ldo = WS ? N : ldc;
+    int64_t out[PASSES], res[PASSES];
+    uint4 b[PASSES], r[PASSES];
+    float v[2][PASSES][8];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        out[p] = ((WS ? (int64_t)split * M : 0) + mw + part.row[p]) * ldo + nw + part.col[p];
+        if (RESID) res[p] = (mw + part.row[p]) * ldr + nw + part.col[p];
+        if (BIAS) b[p] = *reinterpret_cast<const uint4 *>(bias + nw + part.col[p]);
+        if (RESID) r[p] = *reinterpret_cast<const uint4 *>(resid + res[p]);
+    }
+    auto through_lds = [&](int i) __attribute__((always_inline)) {
+        float *at = stage + (i & AHEAD) * 16 * P::SPF;
+        P::to_lds(at, acc[i], lane);
+        __builtin_amdgcn_wave_barrier();
+        part.from_lds(v[i & AHEAD], at);
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (AHEAD) through_lds(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        uint4 now[PASSES];
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            if (!RESID) continue;
+            now[p] = r[p];
+            if (i + 1 < TM) r[p] = *reinterpret_cast<const uint4 *>(resid + res[p] + (int64_t)(i + 1) * 16 * ldr);
+        }
+        if (i + AHEAD < TM) through_lds(i + AHEAD);
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            float (&x)[8] = v[i & AHEAD][p];
+            if (WS) { store8(ws + out[p] + (int64_t)i * 16 * ldo, x, 8); continue; }
+            if (BIAS) add8(x, b[p]);
+            if (RESID) add8(x, now[p]);
+            *reinterpret_cast<uint4 *>(C + out[p] + (int64_t)i * 16 * ldo) = pack8(x);
+        }
+    }
+}
+
+// A part that reaches past the output's last row or column, or whose rows start on 8-byte boundaries (leading dimensions of 8k + 4):
+// up to eight columns of a row at a time, of which `cols` says how many there are; nothing at or past column N or row M is touched.
+// It is on the critical path of the last tiles of every row, so the residual is a block ahead here too, and a loop, since straight-line
+// code for what few wavefronts run has to be fetched by them alone.  One chunk after the other, each waiting for its residual, took
+// 101 us for 8192 x 4093 x 768 with residual, this 71 (256x256 tiles; operands in the caches).
+template <int TM, int TN>
+__device__ __forceinline__ void store_edge(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
+                                           const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
+                                           float *__restrict__ ws, int split) {
+    using P = Part<TM, TN>;
+    constexpr int PASSES = P::PASSES, BATCH = stage_rows<TM>() / 16;         // blocks in LDS at a time
+    static_assert(BATCH % 2 == 0 && (TM == BATCH || TM == 2 * BATCH), "blocks in pairs, one batch or two");
+    const P part(lane);
+    const int rows = M - mw < TM * 16 ? (int)(M - mw) : TM * 16;
+    const int64_t ldo = ws ? N : ldc;
+    int cols[PASSES];
+    int64_t out[PASSES], res[PASSES];
+    uint4 b[PASSES];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int64_t left = N - nw - part.col[p];
+        cols[p] = left >= 8 ? 8 : left > 0 ? (int)left : 0;
+        out[p] = ((ws ? (int64_t)split * M : 0) + mw + part.row[p]) * ldo + nw + part.col[p];
+        res[p] = (mw + part.row[p]) * ldr + nw + part.col[p];
+        if (bias) {
+            Piece t;
+            t.load(bias + nw + part.col[p], cols[p]);
+            b[p] = t.get(cols[p]);
+        }
+    }
+    auto load_resid = [&](int g, Piece (&r)[PASSES]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) r[p].load(resid + res[p] + (int64_t)g * 16 * ldr, g * 16 + part.row[p] < rows ? cols[p] : 0);
+    };
+    auto block = [&](int g, const Piece (&r)[PASSES], Piece (&ahead)[PASSES]) __attribute__((always_inline)) {
+        if (resid && g + 1 < TM) load_resid(g + 1, ahead);
+        float v[PASSES][8];
+        part.from_lds(v, stage + (g % BATCH) * 16 * P::SPF);
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            if (g * 16 + part.row[p] >= rows || cols[p] == 0) continue;
+            if (ws) { store8(ws + out[p] + (int64_t)g * 16 * ldo, v[p], cols[p]); continue; }
+            if (bias) add8(v[p], b[p]);
+            if (resid) add8(v[p], r[p].get(cols[p]));
+            Piece::store(C + out[p] + (int64_t)g * 16 * ldo, pack8(v[p]), cols[p]);
+        }
+    };
+    Piece r0[PASSES], r1[PASSES];
+    if (resid) load_resid(0, r0);
+    auto batch = [&](auto FIRST) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) P::to_lds(stage + i * 16 * P::SPF, acc[FIRST() + i], lane);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int g = FIRST(); g < FIRST() + BATCH; g += 2) {
+            block(g, r0, r1);
+            block(g + 1, r1, r0);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    batch(std::integral_constant<int, 0>{});
+    if constexpr (TM > BATCH) batch(std::integral_constant<int, BATCH>{});
+}
 template <int TM, int TN>
 __device__ __forceinline__ void store_tile(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
                                            const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
                                            float *__restrict__ ws, int split) {
-    constexpr int WN = TN * 16, SPF = WN + 4, CPR = WN / 8, PASSES = 16 * CPR / 64;
-    static_assert((16 * CPR) % 64 == 0, "a 16-row block is a whole number of wavefront passes");
-    const int l16 = lane & 15, lq = lane >> 4;
-    auto to_lds = [&](int i) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4 *>(stage + l16 * SPF + j * 16 + lq * 4) = acc[i][j];
-        __builtin_amdgcn_wave_barrier();
-    };
-    auto add8 = [](float (&v)[8], const uint4 &t) __attribute__((always_inline)) {
-        const uint32_t u[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { v[2 * e] += __uint_as_float(u[e] << 16); v[2 * e + 1] += __uint_as_float(u[e] & 0xffff0000u); }
-    };
-    if (mw + TM * 16 <= M && nw + WN <= N && (ws || ((ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0)))) {
-        // the whole part lies inside: no tests per chunk, the bias read once, the residual one 16-row block ahead
-        int64_t out[PASSES], res[PASSES];
-        uint4 b[PASSES], r[PASSES];
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-            const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
-            out[p] = ws ? ((int64_t)split * M + mw + row) * N + nw + ch * 8 : (mw + row) * ldc + nw + ch * 8;
-            res[p] = (mw + row) * ldr + nw + ch * 8;
-            if (bias) b[p] = *reinterpret_cast<const uint4 *>(bias + nw + ch * 8);
-            if (resid) r[p] = *reinterpret_cast<const uint4 *>(resid + res[p]);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            to_lds(i);
-            uint4 next[PASSES];
-            if (resid && i + 1 < TM) {
-#pragma unroll
-                for (int p = 0; p < PASSES; ++p) next[p] = *reinterpret_cast<const uint4 *>(resid + res[p] + (int64_t)(i + 1) * 16 * ldr);
-            }
-#pragma unroll
-            for (int p = 0; p < PASSES; ++p) {
-                const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
-                const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
-                const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
-                if (ws) {
-                    float *dst = ws + out[p] + (int64_t)i * 16 * N;
-                    *reinterpret_cast<float4 *>(dst) = x0;
-                    *reinterpret_cast<float4 *>(dst + 4) = x1;
-                } else {
-                    float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                    if (bias) add8(v, b[p]);
-                    if (resid) add8(v, r[p]);
-                    *reinterpret_cast<uint4 *>(C + out[p] + (int64_t)i * 16 * ldc) =
-                        make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
-                }
-            }
-            if (resid && i + 1 < TM) {
-#pragma unroll
-                for (int p = 0; p < PASSES; ++p) r[p] = next[p];
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        return;
-    }
-    const bool wide = (ldc % 8 == 0) && (resid == nullptr || ldr % 8 == 0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        to_lds(i);
-#pragma unroll 1
-        for (int p = 0; p < PASSES; ++p) {
-            const int c = p * 64 + lane, row = c / CPR, ch = c % CPR;
-            const float4 x0 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8);
-            const float4 x1 = *reinterpret_cast<const float4 *>(stage + row * SPF + ch * 8 + 4);
-            const int64_t m = mw + i * 16 + row, n = nw + ch * 8;
-            if (m >= M || n >= N) continue;
-            if (ws) {
-                float *dst = ws + ((int64_t)split * M + m) * N + n;
-                *reinterpret_cast<float4 *>(dst) = x0;
-                if (n + 4 < N) *reinterpret_cast<float4 *>(dst + 4) = x1;
-                continue;
-            }
-            float v[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            if (n + 8 <= N && wide) {
-                if (bias) add8(v, *reinterpret_cast<const uint4 *>(bias + n));
-                if (resid) add8(v, *reinterpret_cast<const uint4 *>(resid + m * ldr + n));
-                *reinterpret_cast<uint4 *>(C + m * ldc + n) =
-                    make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
-            } else {
-                for (int e = 0; e < 8 && n + e < N; ++e) {
-                    float x = v[e];
-                    if (bias) x += bf16_bits_to_f32(bias[n + e]);
-                    if (resid) x += bf16_bits_to_f32(resid[m * ldr + n + e]);
-                    C[m * ldc + n + e] = (uint16_t)f32_to_bf16_bits(x);
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
+    const bool inside = mw + TM * 16 <= M && nw + TN * 16 <= N;
+    const bool wide = ldc % 8 == 0 && (resid == nullptr || ldr % 8 == 0);
+#define TIO_STORE(BIAS, RESID, WS) store_inside<TM, TN, BIAS, RESID, WS>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split)
+    if (inside && ws) TIO_STORE(false, false, true);
+    else if (inside && wide) {
+        if (bias && resid) TIO_STORE(true, true, false);
+        else if (bias) TIO_STORE(true, false, false);
+        else if (resid) TIO_STORE(false, true, false);
+        else TIO_STORE(false, false, false);
+    } else if (mw < M && nw < N) store_edge<TM, TN>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split);
+#undef TIO_STORE
 }
 
 template <int BM, int BN, int WGM, int WGN, int D, bool AKM, bool BKM, bool ROWSUM>
@@ -499,9 +604,9 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     pin();
 
     if (do_rowsum) store_rowsum<TM>(rs, lane, wn, m0 + wm * WM, M, N, rowsum, rowsum_acc, ws, split, nsplit);
-    store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl) + wave * (16 * (WN + 4)), lane, m0 + wm * WM, n0 + wn * WN, M, N, bias, resid,
+    store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl) + wave * stage_floats<TM, TN>(), lane, m0 + wm * WM, n0 + wn * WN, M, N, bias, resid,
                        ldr, C, ldc, ws, split);      // the rings are free: the last barrier came after every fragment read
-    static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * 16 * (WN + 4) * 4, "the staging blocks fit the rings");
+    static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * stage_floats<TM, TN>() * 4, "the staging blocks fit the rings");
 }
 
 // 64x64 tiles for products with too few larger ones: eight wavefronts in two groups, each with one of the two contraction steps
@@ -661,8 +766,8 @@ __global__ void __launch_bounds__(512)
     rs[0][0] += red[TM * TN * 4 * 64];
     if (do_rowsum) store_rowsum<TM>(rs, lane, wn, m0 + wm * 32, M, N, rowsum, rowsum_acc, ws, split, nsplit);
     constexpr size_t RED = 4 * (TM * TN * 4 + 1) * 64 * 4;
-    static_assert(D * TILE >= RED + 4 * 16 * 36 * 4, "reduction and staging blocks fit the ring");
-    store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl + RED) + wave * (16 * 36), lane, m0 + wm * 32, n0 + wn * 32, M, N, bias, resid, ldr,
+    static_assert(D * TILE >= RED + 4 * stage_floats<TM, TN>() * 4, "reduction and staging blocks fit the ring");
+    store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl + RED) + wave * stage_floats<TM, TN>(), lane, m0 + wm * 32, n0 + wn * 32, M, N, bias, resid, ldr,
                        C, ldc, ws, split);
 }
 struct Product {
