@@ -833,14 +833,16 @@ template <int D> void launch_small(const Product &p) {
 
 // The tiles and what they take, in microseconds: `tile` per contraction tile of 64 with the chip full (the clock follows the
 // power drawn: 0.6 of it with few compute units busy), `fixed` per output tile (first loads, epilogue).  per_cu = 2: two
-// workgroups share a compute unit; `solo` / `solo_fixed` where there are no more workgroups than units.  Fitted to 37 products of
-// the GPT-2-small, Llama-7B and ragged shapes, every tile measured on each (operands in no cache); the choice below takes the
-// fastest tile or one within 4 % of it on 34 of them, 20 % slower on the worst.  Some of them, 256x256 / 256x192 / 128x192 / 128x128 /
-// 64x64, us (before, choosing between the first and the fourth by the fill of the last round: 8192 x 768 x 3072 40, head 1021 x 768
-// x 50257 540, 768 x 768 x 8192 62, 1024^3 11):
-//    8192 x  768 x  3072   60 /  47 /  36 /  40 /  61      1021 x  768 x 50257  1097 / 1000 / 638 /  540 / 264
-//    8192 x 3072 x   768   48 /  44 /  54 /  43            1000 x 5120 x  5120    88 /   70 /  50 /   62 /  81
-//     768 x  768 x  8192  137 / 109 /  65 /  62 /  30      8192 x 22016 x 4096  1027 / 1101 / 1404 / 1381
+// workgroups share a compute unit, so a round is 512 of them; `solo` / `solo_fixed` where there are no more workgroups than units.
+// Checked on 137 products (the GPT-2-small, Llama-7B and ragged shapes, contractions from 64, random sizes, layouts and epilogues;
+// operands in no cache): the choice is the fastest tile or one within 4 % of it on 125 of them, 16 % slower on the worst.  With small
+// products whose operands sit in the caches 128x128 is better than it is told for ragged outputs with a residual (by up to a third).
+// Some of them, 256x256 / 256x192 / 128x192 / 128x128 / 64x64, us (before, choosing between eight wavefronts on the first and the fourth by
+// the fill of the last round: 8192 x 768 x 3072 53, head 1021 x 768 x 50257 528 and 1021 x 50257 x 768 110, 1024^3 15, 8192 x 4096 x 128 30):
+//    8192 x  768 x  3072   62 /  55 /  41 /  49 /  72      1021 x   768 x 50257  1095 / 1008 / 642 /  543 / 262
+//    8192 x 3072 x   768   47 /  40 /  59 /  50 /  78      1021 x 50257 x   768   101 /  104 / 130 /  113 / 183
+//     768 x  768 x  8192  137 / 119 /  83 /  89 /  39      8192 x 22016 x  4096   984 / 1060 / 1360 / 1356
+//    8192 x 4096 x   128   26 /  32 /  42 /  31 /  56      1000 x  5120 x  5120   101 /   83 /  63 /   82 / 100
 // The costs know neither where an operand's rows start in a cache line nor what the caches hold: for 1021 x 768 x 50257 they give the
 // 64x64 tile 161 us, which it takes (158) with warm operands in rows of whole 128-byte lines; rows of 100528 bytes make that 199, and
 // operands in no cache 264 (with whole lines 222).
@@ -851,13 +853,13 @@ struct TileChoice {
     double cost(int64_t groups, int64_t nk) const {
         if (per_cu == 2 && groups <= 256) return (double)nk * solo + solo_fixed;
         const int64_t rounds = (groups + 255) / 256;
-        if (per_cu == 2) return 0.5 * (double)rounds * ((double)nk * tile + fixed);
+        if (per_cu == 2) return (double)((groups + 511) / 512) * ((double)nk * tile + fixed);
         const double busy = groups < 256 ? (double)groups / 256 : 1.0;
         return (double)rounds * ((double)nk * tile * (0.6 + 0.4 * busy) + fixed);
     }
 };
 const TileChoice TILES[] = {
-    {256, 256, 1, 1.33, 10, 0, 0, launch_dl<256, 256, 2>}, {256, 192, 1, 1.03, 10, 0, 0, launch_dl<256, 192, 2>},
+    {256, 256, 1, 1.33, 10.5, 0, 0, launch_dl<256, 256, 2>}, {256, 192, 1, 1.03, 10, 0, 0, launch_dl<256, 192, 2>},
     {128, 192, 1, 0.60, 8, 0, 0, launch_dl<128, 192, 3>},  {128, 128, 2, 0.88, 5, 0.5, 4, launch_dl<128, 128, 2>},
     {64, 64, 2, 0.42, 3, 0.2, 3.5, launch_small<4>},
 };
