@@ -835,14 +835,16 @@ template <int D> void launch_small(const Product &p) {
 // power drawn: 0.6 of it with few compute units busy), `fixed` per output tile (first loads, epilogue).  per_cu = 2: two
 // workgroups share a compute unit, so a round is 512 of them; `solo` / `solo_fixed` where there are no more workgroups than units.
 // Checked on 137 products (the GPT-2-small, Llama-7B and ragged shapes, contractions from 64, random sizes, layouts and epilogues;
-// operands in no cache): the choice is the fastest tile or one within 4 % of it on 125 of them, 16 % slower on the worst.  With small
-// products whose operands sit in the caches 128x128 is better than it is told for ragged outputs with a residual (by up to a third).
+// operands in no cache): the choice is the fastest tile or one within 4 % of it on 131 of them, 17 % slower on the worst.  A ragged
+// output costs a quarter of `fixed` once, because the parts that end inside the output are stored piece by piece and, in the last round,
+// behind nothing: without that term 3328 x 3904 x 128 with cached operands took 256x256 (15 us; 128x128 12).
 // Some of them, 256x256 / 256x192 / 128x192 / 128x128 / 64x64, us (before, choosing between eight wavefronts on the first and the fourth by
 // the fill of the last round: 8192 x 768 x 3072 53, head 1021 x 768 x 50257 528 and 1021 x 50257 x 768 110, 1024^3 15, 8192 x 4096 x 128 30):
 //    8192 x  768 x  3072   62 /  55 /  41 /  49 /  72      1021 x   768 x 50257  1095 / 1008 / 642 /  543 / 262
 //    8192 x 3072 x   768   47 /  40 /  59 /  50 /  78      1021 x 50257 x   768   101 /  104 / 130 /  113 / 183
 //     768 x  768 x  8192  137 / 119 /  83 /  89 /  39      8192 x 22016 x  4096   984 / 1060 / 1360 / 1356
 //    8192 x 4096 x   128   26 /  32 /  42 /  31 /  56      1000 x  5120 x  5120   101 /   83 /  63 /   82 / 100
+//     256 x 12055 x 11884 284 / 242 / 205 / 151 / 217     10624 x   832 x   101    16 /   14 /  15 /   11 /  18
 // The costs know neither where an operand's rows start in a cache line nor what the caches hold: for 1021 x 768 x 50257 they give the
 // 64x64 tile 161 us, which it takes (158) with warm operands in rows of whole 128-byte lines; rows of 100528 bytes make that 199, and
 // operands in no cache 264 (with whole lines 222).
@@ -850,17 +852,18 @@ struct TileChoice {
     int bm, bn, per_cu;
     double tile, fixed, solo, solo_fixed;
     void (*launch)(const Product &);
-    double cost(int64_t groups, int64_t nk) const {
-        if (per_cu == 2 && groups <= 256) return (double)nk * solo + solo_fixed;
-        const int64_t rounds = (groups + 255) / 256;
-        if (per_cu == 2) return (double)((groups + 511) / 512) * ((double)nk * tile + fixed);
-        const double busy = groups < 256 ? (double)groups / 256 : 1.0;
-        return (double)rounds * ((double)nk * tile * (0.6 + 0.4 * busy) + fixed);
+    double cost(int64_t M, int64_t N, int64_t nk, int splits) const {
+        const int64_t groups = ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
+        const double rounds = (double)((groups + 256 * per_cu - 1) / (256 * per_cu));
+        const double edge = M % (bm / 2) || N % (bn / 2) ? 0.25 * fixed / rounds : 0;      // less the more rounds: few end with one
+        if (per_cu == 2 && groups <= 256) return (double)nk * solo + solo_fixed + edge;
+        const double clock = per_cu == 1 && groups < 256 ? 0.6 + 0.4 * (double)groups / 256 : 1.0;
+        return rounds * ((double)nk * tile * clock + fixed) + edge;
     }
 };
 const TileChoice TILES[] = {
-    {256, 256, 1, 1.33, 10.5, 0, 0, launch_dl<256, 256, 2>}, {256, 192, 1, 1.03, 10, 0, 0, launch_dl<256, 192, 2>},
-    {128, 192, 1, 0.60, 8, 0, 0, launch_dl<128, 192, 3>},  {128, 128, 2, 0.88, 5, 0.5, 4, launch_dl<128, 128, 2>},
+    {256, 256, 1, 1.33, 10, 0, 0, launch_dl<256, 256, 2>}, {256, 192, 1, 1.03, 10, 0, 0, launch_dl<256, 192, 2>},
+    {128, 192, 1, 0.60, 8, 0, 0, launch_dl<128, 192, 3>},  {128, 128, 2, 0.88, 5, 0.49, 4, launch_dl<128, 128, 2>},
     {64, 64, 2, 0.42, 3, 0.2, 3.5, launch_small<4>},
 };
 
@@ -876,7 +879,7 @@ const TileChoice *choose(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, 
     for (const TileChoice &t : TILES) {
         if (rowsum && !(a_km && b_km) && !row_sums_in_every_layout(t.bm, t.bn)) continue;
         if (span(a_km, t.bm, lda) >= LIMIT || span(b_km, t.bn, ldb) >= LIMIT) continue;
-        const double cost = t.cost(((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * (splits > 1 ? splits : 1), nk);
+        const double cost = t.cost(M, N, nk, splits > 1 ? splits : 1);
         if (!best || cost < best_cost) { best = &t; best_cost = cost; }
     }
     return best;

@@ -62,17 +62,17 @@ def test_contraction_remainders(K, a_km, b_km):
 # as the dispatch gives each tile
 @pytest.mark.parametrize("a_km,b_km", LAYOUTS)
 @pytest.mark.parametrize("tile,M,N,K", [
-    *(((256, 256), 3990, 4010, K) for K in (65, 96, 127, 128, 129, 191, 319)),
+    *(((256, 256), 8100, 8170, K) for K in (65, 96, 127, 128, 129, 191)), *(((256, 256), 3990, 4010, K) for K in (257, 319, 385)),
     *(((128, 128), 3100, 1010, K) for K in (1, 31, 64, 65, 128, 129, 191, 391)),
-    *(((256, 192), 8100, 3010, K) for K in (513, 520, 639, 640)),
-    *(((128, 192), 2047, 3060, K) for K in (641, 648, 703, 705, 777))])
+    *(((256, 192), 8100, 3010, K) for K in (641, 648, 703, 704)),
+    *(((128, 192), 2047, 3070, K) for K in (833, 840, 896, 897, 959))])
 def test_contraction_remainders_of_the_larger_tiles(tile, M, N, K, a_km, b_km):
     _run(M, N, K, a_km, b_km, tile=tile)
     if a_km and b_km:
         _run(M, N, K, a_km, b_km, rowsum=True, tile=tile)
 
 
-EVERY_TILE = [((256, 256), 4096, 4096, 1024), ((256, 256), 4095, 3841, 1031), ((256, 256), 4095, 3841, 200),
+EVERY_TILE = [((256, 256), 4096, 4096, 1024), ((256, 256), 4095, 3841, 1031), ((256, 256), 8100, 8170, 200),
               ((256, 192), 8192, 3072, 768), ((256, 192), 8100, 3070, 777),
               ((128, 192), 2047, 3072, 3000), ((128, 192), 2048, 3072, 704), ((128, 128), 4000, 1500, 640), ((128, 128), 3100, 1000, 200),
               ((128, 128), 2048, 2048, 300), ((64, 64), 500, 700, 391), ((64, 64), 1021, 768, 5025), ((64, 64), 512, 640, 384)]
@@ -94,9 +94,9 @@ def test_every_tile_with_bias_and_residual(tile, M, N, K, pad, a_km, b_km):
 @pytest.mark.parametrize("tile,M,N,K,splits", [
     ((64, 64), 256, 128, 1000, 3), ((64, 64), 129, 68, 517, 2), ((64, 64), 200, 136, 64, 8), ((64, 64), 130, 64, 4097, 4),
     ((128, 128), 768, 768, 2048, 8), ((256, 256), 840, 6980, 500, 2), ((128, 128), 832, 6976, 128, 2), ((256, 192), 840, 4680, 2000, 2),
-    ((128, 192), 768, 3072, 8192, 2), ((128, 192), 3070, 764, 4161, 2), ((128, 192), 640, 836, 5121, 8),
+    ((128, 192), 768, 3072, 8192, 2), ((128, 192), 3070, 764, 4161, 2), ((128, 192), 200, 2068, 5121, 8),
     # ranges of 640: the last of sixteen is one element long, or empty behind one of 257
-    ((128, 192), 250, 1148, 9601, 16), ((128, 192), 250, 1148, 9217, 16), ((256, 192), 380, 1324, 9601, 16),
+    ((128, 192), 256, 1152, 9601, 16), ((128, 192), 256, 1152, 9217, 16), ((256, 192), 380, 1324, 9601, 16),
     ((256, 256), 500, 1544, 9601, 16), ((256, 256), 500, 1544, 9217, 16)])
 @pytest.mark.parametrize("rowsum", [False, True])
 def test_split_contraction_remainders(tile, M, N, K, splits, rowsum):
@@ -104,6 +104,6 @@ def test_split_contraction_remainders(tile, M, N, K, splits, rowsum):
 
 
 @pytest.mark.parametrize("a_km,b_km", [(0, 0), (0, 1), (1, 0)])
-@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031), (3990, 4010, 65)])
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031), (8100, 8170, 65)])
 def test_row_sums_of_the_large_tile_in_every_layout(M, N, K, a_km, b_km):
     _run(M, N, K, a_km, b_km, rowsum=True, tile=(256, 256))
