@@ -10,7 +10,7 @@ LAYOUTS = [(0, 0), (0, 1), (1, 1), (1, 0)]
 r8 = lambda n: (n + 7) // 8 * 8
 
 
-def _run(M, N, K, a_km, b_km, rowsum=False, splits=1, tile=None, epilogue=False, pad=0):
+def _run(M, N, K, a_km, b_km, rowsum=False, splits=1, tile=None, epilogue=(), pad=0):
     import torch
     import paper_2506_06472_amd as tio
     print(f"bf16 gemm M={M} N={N} K={K} a_km={a_km} b_km={b_km} rowsum={rowsum} splits={splits} tile={tile} epilogue={epilogue} pad={pad}",
@@ -34,10 +34,12 @@ def _run(M, N, K, a_km, b_km, rowsum=False, splits=1, tile=None, epilogue=False,
     bias = resid = None
     if epilogue:
         b, R = (torch.randn(n, device="cuda", generator=g).bfloat16() * 8 for n in ((1, N), (M, N)))
-        bias, resid = stored(b, r8(N)), stored(R, ldc)
-        ref, mag = ref + b.double() + R.double(), mag + b.abs().double() + R.abs().double()
-    tio.tio_op_gemm(0, "bf16", a_km, b_km, M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, bias.data_ptr() if epilogue else 0,
-                    resid.data_ptr() if epilogue else 0, ldc, C.data_ptr(), ldc, rs.data_ptr() if rowsum else 0,
+        if "bias" in epilogue:
+            bias, ref, mag = stored(b, r8(N)), ref + b.double(), mag + b.abs().double()
+        if "resid" in epilogue:
+            resid, ref, mag = stored(R, ldc), ref + R.double(), mag + R.abs().double()
+    tio.tio_op_gemm(0, "bf16", a_km, b_km, M, N, K, dA.data_ptr(), lda, dB.data_ptr(), ldb, bias.data_ptr() if bias is not None else 0,
+                    resid.data_ptr() if resid is not None else 0, ldc, C.data_ptr(), ldc, rs.data_ptr() if rowsum else 0,
                     ws.data_ptr() if ws is not None else 0, splits)
     torch.cuda.synchronize()
     # one fp32 rounding per addition of the chain, one bf16 rounding of the result
@@ -88,7 +90,13 @@ def test_every_tile(tile, M, N, K, a_km, b_km):
 @pytest.mark.parametrize("pad", [0, 4])              # rows of 8k + 4 elements: output and residual move element by element
 @pytest.mark.parametrize("tile,M,N,K", EVERY_TILE)
 def test_every_tile_with_bias_and_residual(tile, M, N, K, pad, a_km, b_km):
-    _run(M, N, K, a_km, b_km, tile=tile, epilogue=True, pad=pad)
+    _run(M, N, K, a_km, b_km, tile=tile, epilogue=("bias", "resid"), pad=pad)
+
+
+@pytest.mark.parametrize("epilogue", ["bias", "resid"])          # each set of operands has code of its own
+@pytest.mark.parametrize("tile,M,N,K", EVERY_TILE)
+def test_every_tile_with_bias_or_residual(tile, M, N, K, epilogue):
+    _run(M, N, K, 0, 0, tile=tile, epilogue=(epilogue,))
 
 
 @pytest.mark.parametrize("tile,M,N,K,splits", [
