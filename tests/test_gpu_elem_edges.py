@@ -41,3 +41,10 @@ def test_embedding_gradient_of_repeated_tokens(B, keep):
         t.ravel()[:keep] = tok.ravel()[:keep]
         return t
     _step_matches(dict(arch="gpt", L=1, d=64, H=2, f=128, V=300, T=64, B=B, precision="fp32", lr=1e-3), repeat)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("V", [16383, 16384])        # embedding and head of one row less than 2^20 parameters, and of 2^20
+def test_optimizer_where_its_accesses_become_non_temporal(V, precision):
+    from test_gpu_train import test_optimizer_state_follows_the_oracle_from_the_gpu_gradients as check
+    check(dict(arch="gpt", L=1, d=64, H=1 if precision == "bf16" else 2, f=128, V=V, T=24, B=1, precision=precision, lr=1e-3))
