@@ -19,6 +19,8 @@
 // Statistics are fp32, exp2 with the 1/sqrt(dh) scale folded into the exponent; the causal mask is
 // applied only on tiles that cross the diagonal; the backward pass recomputes P from the saved
 // log-sum-exp; dQ and dK/dV are separate launches, so every sum has a fixed order and no atomics.
+#include <type_traits>
+
 #include "../../include/teraio.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -68,6 +70,12 @@ __device__ __forceinline__ float sum_halves(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// the lane index, computed where it stands: not kept in a register over a loop
+__device__ __forceinline__ int lane_here() {
+    int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(l));
+    return l;
+}
 // row index inside a 32x32 accumulator tile of register r for lane half lhi
 __device__ __forceinline__ int acc_row(int r, int lhi) { return 8 * (r >> 2) + 4 * lhi + (r & 3); }
 
@@ -112,15 +120,15 @@ template <int DH> __device__ __forceinline__ int swz(int r) {
 template <int DH, bool LEAN = false> struct TileLanes {
     static constexpr int CPR = DH / 8, KS = DH / 16, DT = DH / 32;
     int roff[LEAN ? 1 : KS];          // row-wise fragment of contraction step ks: row lane%32, chunk 2 ks + lane/32
-    int troff[DT][2];      // transposing fragment of column block i: rows 4 (lane/32) + (lane%16)/4 (+ 8), columns by lane
+    int troff[LEAN ? 1 : DT][LEAN ? 1 : 2];      // transposing fragment of column block i: rows 4 (lane/32) + (lane%16)/4 (+ 8), columns by lane
     __device__ __forceinline__ TileLanes(int lane) {
         const int l32 = lane & 31, lhi = lane >> 5;
 #pragma unroll
         for (int ks = 0; ks < (LEAN ? 1 : KS); ++ks) roff[ks] = (l32 * CPR + ((ks * 2 + lhi) ^ swz<DH>(l32 & 15))) * 8;
 #pragma unroll
-        for (int i = 0; i < DT; ++i)
+        for (int i = 0; i < (LEAN ? 1 : DT); ++i)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < (LEAN ? 1 : 2); ++h) {
                 const int rl = 4 * lhi + ((lane & 15) >> 2) + 8 * h;
                 const int chunk = 4 * i + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
                 troff[i][h] = (rl * CPR + (chunk ^ swz<DH>(rl))) * 8 + 4 * (lane & 1);
@@ -136,8 +144,10 @@ template <int DH, bool LEAN = false> struct TileLanes {
     __device__ __forceinline__ bf16x8 tr(const uint16_t *lds, int r0, int i) const {
         typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
         union { s16x4 h[2]; bf16x8 v; } f;
-        f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + r0 * DH + troff[i][0]));
-        f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + r0 * DH + troff[i][1]));
+        // LEAN (head size 128): column block i moves bits 2 and 3 of the chunk index, eight rows further down bit 1
+        f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + r0 * DH + (LEAN ? troff[0][0] ^ (32 * i) : troff[LEAN ? 0 : i][0])));
+        f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4 *)(lds + r0 * DH + (LEAN ? (troff[0][0] ^ (32 * i + 16)) + 8 * DH : troff[LEAN ? 0 : i][LEAN ? 0 : 1])));
         return f.v;
     }
 };
@@ -343,11 +353,14 @@ __global__ void __launch_bounds__(NT, 2) attn_fwd_mfma_k(const uint16_t *__restr
 }
 
 // ------------------------------------------------------------------------------------------ dQ
+// Bound: vector work (exponentials, masks) and latency between the products; the tiles in front of the diagonal run through a loop of
+// their own, without mask and branch.  Three wavefronts per SIMD at head size 64, which a ring of three fragments leaves registers for.
+// 8 x 1024 tokens, 12 heads of 64: 45.9 -> 39.4 us (two wavefronts per SIMD 43.1); 4 x 2048, 32 heads of 128: 272 -> 252.
 template <int DH>
-__global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
+__global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
                                                          const float *__restrict__ lse, const float *__restrict__ delta,
                                                          uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale) {
-    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4;
+    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = DH == 64 ? 3 : 4;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];    // [2 buffers][K tile | V tile], filled as in the forward kernel
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int64_t d = H * DH, ld = 3 * d;
@@ -388,7 +401,8 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
     dma.load(rsV, 0, ldb, lds0 + TE * 2, wave);
     __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): this wavefront's part of tile 0 has landed
     __syncthreads();
-    for (int t = 0; t < ntiles; ++t) {
+    // DIAG: tiles that cross the diagonal of some row of this workgroup, the last ones; the others have no mask and no branch in them
+    auto tile = [&](int t, auto DIAG) __attribute__((always_inline)) {
         const int j0 = t * 64;
         const uint16_t *Ks = smem + (t & 1) * 2 * TE, *Vs = Ks + TE;
         if (t + 1 < ntiles) {                           // the other buffer is free since the barrier that ended tile t-1
@@ -396,7 +410,7 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
             dma.load(rsK, (uint32_t)j0 + 64, ldb, nx, wave);
             dma.load(rsV, (uint32_t)j0 + 64, ldb, nx + TE * 2, wave);
         }
-        if (j0 <= q0w + 31) {
+        if (!DIAG() || j0 <= q0w + 31) {
             floatx16 s[2], dp[2];
             {
                 // S = K.Q^T and dP = V.dO^T for both key groups; the K and V fragments run RING ahead of their products
@@ -421,14 +435,13 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
                 }
                 __builtin_amdgcn_sched_group_barrier(0x008, RING, 0);
             }
-            const bool diag = j0 + 63 > q0w;
             // per group of 32 keys: the element-wise part of one group overlaps the other group's products
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     float p = __builtin_amdgcn_exp2f(fmaf(s[kt][r], c, -lse2));
-                    if (diag && j0 + kt * 32 + acc_row(r, lhi) > q) p = 0.0f;
+                    if (DIAG() && kt * 32 + acc_row(r, 0) > q - j0 - 4 * lhi) p = 0.0f;
                     s[kt][r] = p * (dp[kt][r] - dl);          // the 1/sqrt(dh) factor is applied once, to the sums
                 }
                 const bf16x8 d0 = pack8<0>(s[kt]), d1 = pack8<8>(s[kt]);
@@ -441,7 +454,10 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0): this wavefront's part of tile t+1 has landed
         __syncthreads();
-    }
+    };
+    int t = 0;
+    for (; t < q0 / 64; ++t) tile(t, std::false_type{});
+    for (; t < ntiles; ++t) tile(t, std::true_type{});
     if (live) {
         uint16_t *orow = dqkv + (b * Tn + q) * ld + h * DH;
 #pragma unroll
@@ -464,17 +480,21 @@ __global__ void __launch_bounds__(NT, 2) attn_bwd_dq_mfma_k(const uint16_t *__re
 // products of two wavefronts per SIMD.  Measured at 4 x 2048 tokens, 32 heads of 128 (kernel trace): 393 us, where two launches with
 // four wavefronts each (dV, then dK) took 227 + 302; whole backward pass faster at every size tried, from 1 x 64 x 2 heads (forward and
 // backward 25.4 -> 21.5 us) to 1 x 4096 x 52 (1457 -> 1233).  Head size 64, 8 x 1024 tokens, 12 heads: 60 us.
+// The tiles behind the diagonal run through a loop of their own, without mask and branch: 4 x 2048, 32 heads of 128 444 -> 413 us.  At
+// head size 64 a second loop takes the registers of the third wavefront per SIMD and gains nothing over a mask of two instructions
+// (8 x 1024, 12 heads: 62 -> 56.3 us, 57.0 with two loops).
 // Every one of the 256 registers is in use at head size 128, and nothing may spill: a reload from scratch in the loop waits for the
-// tile loads in flight, and wavefront 0 with it keeps the other seven at the barrier (six spilled registers, and the statistics
-// multiplied where they are loaded: 418 us, and 70 at head size 64).  Transposed fragments four ahead in registers: slower by 9 %,
-// for want of the registers.
+// tile loads in flight, and the wavefront with it keeps the others at the barrier (six spilled registers, and the statistics multiplied
+// where they are loaded: 8 % of the kernel).  So the offsets of the transposing reads are one register and an exclusive or each, each of
+// two wavefronts fetches one of the statistics, and the lane index is computed where it is used.  Transposed fragments four ahead in
+// registers: slower by 9 %, for want of the registers.
 template <int DH> constexpr int dkv_waves() { return DH == 128 ? 8 : 4; }
 template <int DH>
-__global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
+__global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
     attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
                         const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale) {
     constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4, NW = dkv_waves<DH>(), KEYS = NW * 32;
-    constexpr bool VLDS = DH == 128;
+    constexpr bool VLDS = DH == 128, ONE_LOOP = DH == 64;
     constexpr int BUF = 2 * TE;                                          // Q tile | dO tile, filled as in the forward kernel
     // [2 buffers][Q | dO], [KEYS][DH] V rows if VLDS, then [2][64 lse | 64 delta] floats
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];
@@ -493,7 +513,6 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
     const i32x4 rsQ = make_rsrc(qb, head_bytes);
     const i32x4 rsG = make_rsrc(dO + b * Tn * d + h * DH, (uint32_t)(((Tn - 1) * d + DH) * 2));
     const float c = scale * LOG2E;
-    const bool live = kv < (int)Tn;
     const TileLanes<DH, VLDS> L(lane);
     const DmaTile<DH, NW> dmaQ(ldb, wave, lane), dmaG(ldg, wave, lane);
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
@@ -515,22 +534,17 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
     for (int i = 0; i < DT; ++i) { dk[i] = zero16(); dv[i] = zero16(); }
     const int ntiles = ((int)Tn - kv0 + 63) / 64;
 
-    // Statistics of row i0 + lane, one tile ahead, in wavefront 0: through descriptors of the head's rows (rows past the
-    // sequence read zero; no addresses to keep in registers), used only where they go to LDS, a tile after their fetch.
-    const __amdgpu_buffer_rsrc_t rsL = buffer_over(lse + bh * Tn, (uint32_t)Tn * 4), rsD = buffer_over(delta + bh * Tn, (uint32_t)Tn * 4);
-    float st_l = 0.f, st_d = 0.f;
+    // Statistics of row i0 + lane, one tile ahead, log-sum-exp in wavefront 0 and delta in wavefront 1: through descriptors of the head's
+    // rows (rows past the sequence read zero; no addresses to keep in registers), used only where they go to LDS, a tile after their fetch.
+    const __amdgpu_buffer_rsrc_t rsS = buffer_over((wave == 0 ? lse : delta) + bh * Tn, (uint32_t)Tn * 4);
+    const float to_lds = wave == 0 ? LOG2E : 1.f;
+    float st = 0.f;
     float *stats = reinterpret_cast<float *>(smem + 2 * BUF + (VLDS ? KEYS * DH : 0));
     auto load_stats = [&](int i0) {
-        if (wave == 0) {
-            st_l = buffer_load4(rsL, (uint32_t)(i0 + lane) * 4);
-            st_d = buffer_load4(rsD, (uint32_t)(i0 + lane) * 4);
-        }
+        if (wave < 2) st = buffer_load4(rsS, (uint32_t)(i0 + lane_here()) * 4);
     };
     auto store_stats = [&](int buf) {
-        if (wave == 0) {
-            stats[buf * 128 + lane] = st_l * LOG2E;
-            stats[buf * 128 + 64 + lane] = st_d;
-        }
+        if (wave < 2) stats[buf * 128 + wave * 64 + lane_here()] = st * to_lds;
     };
     auto load_tile = [&](int i0, int buf) {
         const uint32_t at = lds0 + (uint32_t)buf * BUF * 2;
@@ -543,7 +557,12 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
     if (ntiles > 1) load_stats(kv0 + 64);
     __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): this wavefront's part of tile 0 (and of V) has landed
     __syncthreads();
-    for (int t = 0; t < ntiles; ++t) {
+    // DIAG: tiles that cross the diagonal of some key of this workgroup, the first ones; the others have no mask and no branch in them
+    // (ONE_LOOP: every tile is taken for one).
+    // Rows past the sequence need none: their Q, dO and statistics are zero, so P is one, dP and dS are zero, and every product with
+    // them adds zero.
+    auto key_less_4half = []() __attribute__((always_inline)) { const int ln = lane_here(); return (ln & 31) - 4 * (ln >> 5); };
+    auto tile = [&](int t, auto DIAG) __attribute__((always_inline)) {
         const int i0 = kv0 + t * 64;
         const uint16_t *Qs = smem + (t & 1) * BUF, *Gs = Qs + TE;
         const float *L2s = stats + (t & 1) * 128, *Ds = L2s + 64;
@@ -555,10 +574,8 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
             load_tile(i0 + 64, (t + 1) & 1);
             if (t + 2 < ntiles) load_stats(i0 + 128);
         }
-        if (i0 + 63 >= kv0w) {
-            // masking is needed where some query of the tile precedes some key of this wavefront, and for
-            // rows past the end of the sequence (zero Q and dO, but a zero statistic too)
-            const bool edge = i0 < kv0w + 31 || i0 + 64 > (int)Tn;
+        if (!DIAG() || i0 + 63 >= kv0w) {
+            const int masked = DIAG() ? kv0w - i0 + key_less_4half() : 0;        // rows of the tile before this lane's key, less 4 lhi
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt) {
                 floatx16 s = zero16(), dp = zero16();
@@ -595,7 +612,7 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
                     for (int e = 0; e < 4; ++e) {
                         const int r = 4 * r4 + e;
                         float p = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lv[e]));
-                        if (edge && (i0 + ql + e < kv || i0 + ql + e >= (int)Tn)) p = 0.0f;
+                        if (DIAG() && qt * 32 + 8 * r4 + e < masked) p = 0.0f;
                         dp[r] = p * (dp[r] - dvv[e]);        // the 1/sqrt(dh) factor is applied once, to the sums
                         s[r] = p;
                     }
@@ -615,10 +632,17 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, 2)
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0): this wavefront's part of tile t+1 has landed
         __syncthreads();
+    };
+    int t = 0;
+    if constexpr (ONE_LOOP) {
+        for (; t < ntiles; ++t) tile(t, std::true_type{});
+    } else {
+        for (; t < KEYS / 64 && t < ntiles; ++t) tile(t, std::true_type{});
+        for (; t < ntiles; ++t) tile(t, std::false_type{});
     }
-    if (live) {
-        uint16_t *krow = dqkv + (b * Tn + kv) * ld + d + h * DH, *vrow = krow + d;
-        const int half = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) >> 5;      // lhi, not kept over the loop
+    const int last = lane_here(), half = last >> 5, key = kv0w + (last & 31);
+    if (key < (int)Tn) {
+        uint16_t *krow = dqkv + (b * Tn + key) * ld + d + h * DH, *vrow = krow + d;
 #pragma unroll
         for (int i = 0; i < DT; ++i)
 #pragma unroll

@@ -11,3 +11,10 @@ pytestmark = pytest.mark.gpu
                                       (1, 500, 1, 128), (1, 129, 9, 64), (1, 255, 2, 64)])
 def test_bf16_attention_edges(B, T, H, dh):
     check("bf16", B, T, H, dh, 1)
+
+
+# the loops over the tiles on the diagonal and the others: none of the others, one, a partial one
+@pytest.mark.parametrize("B,T,H,dh", [(1, 64, 3, 64), (1, 128, 9, 64), (1, 192, 2, 64), (2, 321, 1, 64), (1, 64, 1, 128), (1, 128, 2, 128),
+                                      (1, 320, 9, 128), (2, 321, 1, 128), (1, 577, 1, 128)])
+def test_bf16_attention_tiles_on_and_off_the_diagonal(B, T, H, dh):
+    check("bf16", B, T, H, dh, 1)
