@@ -92,14 +92,29 @@ __device__ __forceinline__ bf16x8 buf_frag(__amdgpu_buffer_rsrc_t rsrc, uint32_t
     return f.v;
 }
 
-// Workgroup index -> (batch*head, block of 128 rows).  Workgroups are dealt to the 8 XCDs round-robin and
-// each XCD has its own L2, so all row blocks of one head are given to one XCD (head = 8*i + xcd): the K and
-// V rows of a head are then fetched into one L2 only, and reused there by the head's other row blocks.
+// Workgroup -> (batch*head, block of rows).  Workgroups are dealt to the 8 XCDs round-robin and each XCD has its own L2, so all row
+// blocks of one head are given to one XCD (head = 8*i + xcd): the K and V rows of a head are then fetched into one L2 only, and reused
+// there by the head's other row blocks.  Under the causal mask a head's blocks differ in length by up to their number (block 0 is the
+// longest), and consecutive workgroups of an XCD go to its 32 compute units in turn.  In the order (head, block) a unit therefore gets
+// blocks of one length wherever the number of blocks divides 32: of 8 x 1024 tokens, 12 heads of 64, three of the longest (48 tiles; 27
+// on average) or three of the shortest.  So an XCD's heads are taken `heads` at a time, and within them all blocks 0 come first, then
+// all blocks 1: the longest first, the shorter ones where units become free.  Where all workgroups are resident from the start and none
+// becomes free, every other row of 32 is turned round (`turn`), which pairs long with short.  Forward / backward us, order (head,
+// block) / this: 8 x 1024, 12 heads of 64 31 / 23.5, 101 / 82; 4 x 2048, 32 of 128 181 / 170, 654 / 553; 1 x 4096, 32 of 64 125 / 82.5,
+// 344 / 274; 2 x 4096, 52 of 128 484 / 473, 1649 / 1570.
+struct Order {
+    int heads;
+    bool turn;
+};
 // Returns false for the padding workgroups when the head count is not a multiple of 8.
-__device__ __forceinline__ bool head_and_block(int64_t n_heads, int n_blocks, int64_t &bh, int &blk) {
-    const int id = (int)blockIdx.x, xcd = id & 7, slot = id >> 3;
-    bh = (int64_t)(slot / n_blocks) * 8 + xcd;
-    blk = slot % n_blocks;
+__device__ __forceinline__ bool head_and_block(int64_t n_heads, int n_blocks, Order order, int64_t &bh, int &blk) {
+    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+    const int of_xcd = (int)((n_heads + 7) / 8), first = slot / (order.heads * n_blocks) * order.heads;
+    const int here = of_xcd - first < order.heads ? of_xcd - first : order.heads;
+    int w = slot - first * n_blocks;
+    if (order.turn && (w & 32) && (w | 31) < here * n_blocks) w ^= 31;
+    bh = (int64_t)(first + w % here) * 8 + xcd;
+    blk = w / here;
     return bh < n_heads;
 }
 
@@ -187,7 +202,7 @@ template <int DH, int NW = NT / 64> struct DmaTile {
 // accumulate the first group's P.V.
 template <int DH>
 __global__ void __launch_bounds__(NT, 2) attn_fwd_mfma_k(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ o,
-                                                      float *__restrict__ lse, int64_t Bn, int64_t Tn, int64_t H, float scale) {
+                                                      float *__restrict__ lse, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
     constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];    // [2 buffers][K tile | V tile]
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
@@ -196,7 +211,7 @@ __global__ void __launch_bounds__(NT, 2) attn_fwd_mfma_k(const uint16_t *__restr
     const int nblk = (int)((Tn + 127) / 128);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, nblk, bh, blk)) return;
+    if (!head_and_block(Bn * H, nblk, order, bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
     const int q0 = (nblk - 1 - blk) * 128;                               // longest rows first
     const int q0w = q0 + wave * 32, q = q0w + l32;
@@ -359,7 +374,7 @@ __global__ void __launch_bounds__(NT, 2) attn_fwd_mfma_k(const uint16_t *__restr
 template <int DH>
 __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
                                                          const float *__restrict__ lse, const float *__restrict__ delta,
-                                                         uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale) {
+                                                         uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
     constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = DH == 64 ? 3 : 4;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];    // [2 buffers][K tile | V tile], filled as in the forward kernel
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
@@ -368,7 +383,7 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
     const int nblk = (int)((Tn + 127) / 128);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, nblk, bh, blk)) return;
+    if (!head_and_block(Bn * H, nblk, order, bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
     const int q0 = (nblk - 1 - blk) * 128;
     const int q0w = q0 + wave * 32, q = q0w + l32;
@@ -492,7 +507,7 @@ template <int DH> constexpr int dkv_waves() { return DH == 128 ? 8 : 4; }
 template <int DH>
 __global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
     attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
-                        const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale) {
+                        const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
     constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4, NW = dkv_waves<DH>(), KEYS = NW * 32;
     constexpr bool VLDS = DH == 128, ONE_LOOP = DH == 64;
     constexpr int BUF = 2 * TE;                                          // Q tile | dO tile, filled as in the forward kernel
@@ -503,7 +518,7 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
     const uint32_t ldb = (uint32_t)(ld * 2), ldg = (uint32_t)(d * 2);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, (int)((Tn + KEYS - 1) / KEYS), bh, blk)) return;
+    if (!head_and_block(Bn * H, (int)((Tn + KEYS - 1) / KEYS), order, bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
     const int kv0 = blk * KEYS;                                           // earliest keys see the most queries: first
     const int kv0w = kv0 + wave * 32, kv = kv0w + l32;
@@ -670,6 +685,21 @@ constexpr int64_t PAST = 192;
 static_assert(dkv_waves<64>() * 32 <= 2 * PAST && dkv_waves<128>() * 32 <= 2 * PAST && 128 <= 2 * PAST, "offsets past the sequence do not wrap");
 bool fits(int64_t Tn, int64_t H, int64_t dh) { return (Tn + PAST) * 3 * H * dh * 2 < ((int64_t)1 << 31); }
 
+// The order and the grid of a kernel whose workgroups take `rows` rows each and of which a compute unit holds per_cu.  Heads taken
+// together: all of them where that leaves nothing to wait for a free unit, otherwise as many as have 16 MiB of K and V (or Q and dO), so
+// that an XCD's 4 MiB L2 sees most of a tile's reuse by the other blocks (4 x 2048, 32 heads of 128, 2 / 4 / 8 / 16 heads, forward: 176 /
+// 169 / 167 / 171 us; 2 x 4096, 52 heads 486 / 487 / 473 / 483).
+struct Launch {
+    dim3 grid;
+    Order order;
+    Launch(int64_t n_heads, int64_t Tn, int64_t dh, int rows, int per_cu) {
+        const int64_t of_xcd = (n_heads + 7) / 8, blocks = (Tn + rows - 1) / rows, by_bytes = ((int64_t)16 << 20) / (Tn * dh * 4);
+        grid = dim3((unsigned)(blocks * of_xcd * 8));
+        order.turn = of_xcd * blocks <= 32 * per_cu;
+        order.heads = (int)(order.turn || by_bytes >= of_xcd ? of_xcd : by_bytes > 1 ? by_bytes : 1);
+    }
+};
+
 }  // namespace
 
 bool attn_mfma_supported(int dtype, int64_t Tn, int64_t H, int64_t dh) {
@@ -677,20 +707,19 @@ bool attn_mfma_supported(int dtype, int64_t Tn, int64_t H, int64_t dh) {
 }
 
 void attn_fwd_mfma(hipStream_t s, const void *qkv, void *o, float *lse, int64_t B, int64_t Tn, int64_t H, int64_t dh) {
-    const dim3 grid((unsigned)(((Tn + 127) / 128) * ((B * H + 7) / 8) * 8));
+    const Launch l(B * H, Tn, dh, 128, dh == 64 ? 4 : 2);
     const float scale = 1.0f / sqrtf((float)dh);
     static bool attr_set = false;
     if (!attr_set) {       // head dimension 128 needs more than the default 64 KiB of LDS
         (void)hipFuncSetAttribute((const void *)attn_fwd_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kv_smem<128>());
         attr_set = true;
     }
-    if (dh == 64) attn_fwd_mfma_k<64><<<grid, NT, kv_smem<64>(), s>>>((const uint16_t *)qkv, (uint16_t *)o, lse, B, Tn, H, scale);
-    else attn_fwd_mfma_k<128><<<grid, NT, kv_smem<128>(), s>>>((const uint16_t *)qkv, (uint16_t *)o, lse, B, Tn, H, scale);
+    if (dh == 64) attn_fwd_mfma_k<64><<<l.grid, NT, kv_smem<64>(), s>>>((const uint16_t *)qkv, (uint16_t *)o, lse, B, Tn, H, scale, l.order);
+    else attn_fwd_mfma_k<128><<<l.grid, NT, kv_smem<128>(), s>>>((const uint16_t *)qkv, (uint16_t *)o, lse, B, Tn, H, scale, l.order);
 }
 
 void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const float *lse, const float *delta, void *dqkv,
                    int64_t B, int64_t Tn, int64_t H, int64_t dh) {
-    const dim3 grid((unsigned)(((Tn + 127) / 128) * ((B * H + 7) / 8) * 8));
     const float scale = 1.0f / sqrtf((float)dh);
     static bool attr_set = false;
     if (!attr_set) {
@@ -698,15 +727,17 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const float *
         (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128>());
         attr_set = true;
     }
-    if (dh == 64) {
-        attn_bwd_dq_mfma_k<64><<<grid, NT, kv_smem<64>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
-        attn_bwd_dkv_mfma_k<64><<<grid, NT, dkv_smem<64>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
-    } else {
-        attn_bwd_dq_mfma_k<128><<<grid, NT, kv_smem<128>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
-        constexpr int KEYS = dkv_waves<128>() * 32;
-        const dim3 kgrid((unsigned)(((Tn + KEYS - 1) / KEYS) * ((B * H + 7) / 8) * 8));
-        attn_bwd_dkv_mfma_k<128><<<kgrid, dkv_waves<128>() * 64, dkv_smem<128>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale);
+#define TIO_ATTN_BWD(DH, DQ_PER_CU, DKV_PER_CU)                                                                                                \
+    {                                                                                                                                          \
+        const Launch q(B * H, Tn, DH, 128, DQ_PER_CU), kv(B * H, Tn, DH, dkv_waves<DH>() * 32, DKV_PER_CU);                                    \
+        attn_bwd_dq_mfma_k<DH><<<q.grid, NT, kv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, \
+                                                                 Tn, H, scale, q.order);                                                       \
+        attn_bwd_dkv_mfma_k<DH><<<kv.grid, dkv_waves<DH>() * 64, dkv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, \
+                                                                                      (uint16_t *)dqkv, B, Tn, H, scale, kv.order);            \
     }
+    if (dh == 64) TIO_ATTN_BWD(64, 3, 3)
+    else TIO_ATTN_BWD(128, 2, 1)
+#undef TIO_ATTN_BWD
 }
 
 }  // namespace k

@@ -18,3 +18,29 @@ def test_bf16_attention_edges(B, T, H, dh):
                                       (1, 320, 9, 128), (2, 321, 1, 128), (1, 577, 1, 128)])
 def test_bf16_attention_tiles_on_and_off_the_diagonal(B, T, H, dh):
     check("bf16", B, T, H, dh, 1)
+
+
+# orders of the workgroups: all resident with every other row of units turned round (whole rows only; a row short of one), not all
+# resident, heads taken eight and one at a time.  No result depends on the order: each sequence alone gives the same bits
+@pytest.mark.parametrize("B,T,H,dh", [(3, 300, 11, 64), (8, 520, 13, 64), (7, 1000, 5, 64), (8, 1025, 17, 64), (8, 520, 13, 128), (8, 4096, 9, 128)])
+def test_bf16_attention_does_not_depend_on_the_order_of_its_blocks(B, T, H, dh):
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"attention order B={B} T={T} H={H} dh={dh}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+    d = H * dh
+    qkv = torch.randn((B, T, 3 * d), device="cuda", generator=g).bfloat16()
+    dO = torch.randn((B, T, d), device="cuda", generator=g).bfloat16()
+
+    def run(qkv, dO):
+        n = qkv.shape[0]
+        o, dqkv = torch.full_like(dO, 7.0), torch.full_like(qkv, 7.0)
+        lse, delta = (torch.full((n, H, T), 7.0, device="cuda") for _ in range(2))
+        tio.tio_op_attention(0, "bf16", n, T, H, dh, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), delta.data_ptr(),
+                             dqkv.data_ptr())
+        torch.cuda.synchronize()
+        return o, lse, dqkv
+    whole = run(qkv, dO)
+    for b in range(B):
+        for name, w, one in zip(("o", "lse", "dqkv"), whole, run(qkv[b:b + 1].contiguous(), dO[b:b + 1].contiguous())):
+            assert torch.equal(w[b], one[0]), (name, b)
