@@ -58,7 +58,8 @@ void norm_bwd_params(hipStream_t s, int dtype, bool rms, const float *part, void
                      int64_t d, bool accumulate);
 void attn_bwd_pre(hipStream_t s, int dtype, const void *dO, const void *O, float *delta, int64_t B, int64_t T,
                   int64_t H, int64_t dh);
-void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const float *lse, const float *delta,
+// O: the forward pass's output, from which delta is then computed as well, or nullptr: delta comes from attn_bwd_pre
+void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const void *O, const float *lse, float *delta,
               void *dqkv, int64_t B, int64_t T, int64_t H, int64_t dh);
 void embed_bwd(hipStream_t s, int dtype, const void *dx, const int32_t *tok, void *dwte, int64_t S, int64_t d,
                int64_t V, bool accumulate);

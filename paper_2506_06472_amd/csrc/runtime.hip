@@ -303,7 +303,7 @@ void launch(tio_ctx *c, int k) {
         break;
     case OP_NORM_BWD_PARAMS: k::norm_bwd_params(s, dt, rms, (const float *)P(0), P(1), P(2), r.p[0], r.p[1], r.p[2] != 0); break;
     case OP_ATTN_BWD_PRE: k::attn_bwd_pre(s, dt, P(0), P(1), (float *)P(2), B, T, H, dh); break;
-    case OP_ATTN_BWD: k::attn_bwd(s, dt, P(0), P(1), (const float *)P(2), (const float *)P(3), P(4), B, T, H, dh); break;
+    case OP_ATTN_BWD: k::attn_bwd(s, dt, P(0), P(1), nullptr, (const float *)P(2), (float *)P(3), P(4), B, T, H, dh); break;
     case OP_EMBED_BWD: k::embed_bwd(s, dt, P(0), (const int32_t *)P(1), P(2), r.p[0], r.p[1], r.p[2], r.p[3] != 0); break;
     case OP_POSEMB_BWD: k::posemb_bwd(s, dt, P(0), P(1), r.p[0], r.p[1], r.p[2], r.p[3] != 0); break;
     case OP_ADAMW: {
@@ -937,8 +937,7 @@ int tio_op_attention(void *stream, int32_t dtype, int64_t B, int64_t T, int64_t 
     k::attn_fwd(s, dtype, qkv, o, lse, B, T, H, dh);
     if (dO) {
         if (!delta || !dqkv) return fail(TIO_ERR_INVALID_ARG, "backward needs delta and dqkv");
-        k::attn_bwd_pre(s, dtype, dO, o, delta, B, T, H, dh);
-        k::attn_bwd(s, dtype, dO, qkv, lse, delta, dqkv, B, T, H, dh);
+        k::attn_bwd(s, dtype, dO, qkv, o, lse, delta, dqkv, B, T, H, dh);
     }
     HIPCHK(hipGetLastError());
     return TIO_OK;

@@ -9,7 +9,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,B,T,H,dh", [
     ("fp32", 1, 1, 1, 32), ("fp32", 1, 31, 9, 32), ("fp32", 2, 32, 2, 64), ("fp32", 1, 33, 3, 128), ("fp32", 1, 128, 1, 32),
-    ("fp32", 1, 161, 3, 64), ("bf16", 1, 1, 1, 32), ("bf16", 3, 65, 3, 32), ("bf16", 1, 300, 2, 32)])
+    ("fp32", 1, 161, 3, 64), ("bf16", 1, 1, 1, 32), ("bf16", 3, 65, 3, 32), ("bf16", 1, 300, 2, 32),
+    # four and eight wavefronts to a block: up to four tiles, five, more than eight; more workgroups than eight are taken for
+    ("fp32", 1, 129, 8, 32), ("fp32", 2, 289, 4, 32), ("fp32", 8, 160, 8, 32), ("fp32", 3, 192, 1, 128)])
 def test_fp32_attention_edges(dtype, B, T, H, dh):
     check(dtype, B, T, H, dh, 1)
 
