@@ -466,7 +466,7 @@ def main():
         # fp32 workloads (the tiny parity configurations) run the contractions on the fp32 matrix instruction, whose peak is that of
         # the vector ALU ("alu")
         "roofline": {"bound": "mfma" if bf16 else "alu",
-                     "kernel": ("gemm_bf16_dl_k" if bf16 else "gemm_f32_mfma_k, gemm_f32_tiny_k") + " (forward, dX and dW contractions)",
+                     "kernel": ("gemm_bf16_dl_k" if bf16 else "gemm_f32_mfma_k") + " (forward, dX and dW contractions)",
                      "achieved": gemm_tflops, "peak": gemm_peak, "unit": "TFLOP/s",
                      "frac": gemm_tflops / gemm_peak, "traffic": (traffic or {}).get("bytes_per_launch"),
                      "traffic_unit": "bytes per launch missing the L2 (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated); "

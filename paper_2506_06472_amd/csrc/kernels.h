@@ -27,8 +27,23 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
 void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits, int *rows,
                     int *cols);
 // fp32 products on the fp32 matrix instruction (kernels_gemm_f32.hip); accumulate adds to rowsum (the caller passes C as resid)
-void gemm_f32(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
-              int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, bool accumulate);
+struct F32Product {
+    int64_t M, N, K;
+    const void *A;
+    int64_t lda;
+    const void *B;
+    int64_t ldb;
+    const void *bias, *resid;
+    int64_t ldr;
+    void *C;
+    int64_t ldc;
+    void *rowsum;
+    bool accumulate;
+};
+void gemm_f32(hipStream_t s, bool a_km, bool b_km, const F32Product &p);
+// dX = dY . W (B k-major) and dW = dY^T . X (both k-major) in one launch; only where gemm_f32_pairs says so (host only)
+bool gemm_f32_pairs(int64_t M_dx, int64_t N_dx, int64_t M_dw, int64_t N_dw);
+void gemm_f32_pair(hipStream_t s, const F32Product &dx, const F32Product &dw);
 void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A,
           int64_t lda, const void *B, int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C,
           int64_t ldc, void *rowsum, void *workspace, int splits, bool accumulate = false);
@@ -58,14 +73,24 @@ void norm_bwd_params(hipStream_t s, int dtype, bool rms, const float *part, void
                      int64_t d, bool accumulate);
 void attn_bwd_pre(hipStream_t s, int dtype, const void *dO, const void *O, float *delta, int64_t B, int64_t T,
                   int64_t H, int64_t dh);
+// whether attn_bwd computes delta in its own launch (host only)
+bool attn_bwd_has_delta(int dtype, int64_t T, int64_t H, int64_t dh);
 // O: the forward pass's output, from which delta is then computed as well, or nullptr: delta comes from attn_bwd_pre
 void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const void *O, const float *lse, float *delta,
               void *dqkv, int64_t B, int64_t T, int64_t H, int64_t dh);
 void embed_bwd(hipStream_t s, int dtype, const void *dx, const int32_t *tok, void *dwte, int64_t S, int64_t d,
                int64_t V, bool accumulate);
 void posemb_bwd(hipStream_t s, int dtype, const void *dx, void *dwpe, int64_t B, int64_t T, int64_t d, bool accumulate);
-void adamw(hipStream_t s, int dtype, const void *g, void *w, float *master, float *m, float *v, int64_t n,
-           float lr, float beta1, float beta2, float eps, float wd, float bc1, float bc2);
+// the update of up to kAdamwMax parameters in one launch
+constexpr int kAdamwMax = 8;
+struct AdamwTensor {
+    const void *g;
+    void *w;
+    float *master, *m, *v;       // master: nullptr in fp32
+    int64_t n;
+};
+void adamw(hipStream_t s, int dtype, const AdamwTensor *tensors, int count, float lr, float beta1, float beta2, float eps, float wd, float bc1,
+           float bc2);
 void fill_u32(hipStream_t s, void *p, uint32_t value, int64_t n_words);
 // fp32 <-> storage conversion helpers used when parameters are loaded and read back
 void convert_from_f32(hipStream_t s, int dtype, const float *src, void *dst, int64_t n);

@@ -886,11 +886,17 @@ template <bool STREAM, typename V> __device__ __forceinline__ void store_once(V 
     else *reinterpret_cast<V *>(p) = v;
 }
 constexpr int64_t ADAMW_STREAM = (int64_t)1 << 20;   // parameters
+struct AdamwBatch {
+    AdamwTensor t[kAdamwMax];
+    unsigned end[kAdamwMax];     // workgroups of tensors 0 .. i
+};
 template <typename T, bool STREAM>
-__global__ void __launch_bounds__(TPB) adamw_k(const T *__restrict__ g, T *__restrict__ w, float *__restrict__ master,
-                                               float *__restrict__ m, float *__restrict__ v, int64_t n, float lr,
-                                               float b1, float b2, float eps, float wd, float inv_bc1, float inv_bc2) {
-    const int64_t i0 = ((int64_t)blockIdx.x * TPB + threadIdx.x) * 4;
+__device__ __forceinline__ void adamw_at(const AdamwTensor &t, int64_t i0, float lr, float b1, float b2, float eps, float wd, float inv_bc1,
+                                         float inv_bc2) {
+    const T *__restrict__ g = (const T *)t.g;
+    T *__restrict__ w = (T *)t.w;
+    float *__restrict__ master = t.master, *__restrict__ m = t.m, *__restrict__ v = t.v;
+    const int64_t n = t.n;
     if (i0 >= n) return;
     float *theta = master ? master : reinterpret_cast<float *>(w);
     if (i0 + 4 <= n) {
@@ -926,6 +932,18 @@ __global__ void __launch_bounds__(TPB) adamw_k(const T *__restrict__ g, T *__res
             if (master) w[i] = from_f32<T>(ti);
         }
     }
+}
+// Parameters whose gradients one launch has completed (a weight and its bias, a norm's gain and bias) are updated by one launch: the
+// small ones take less time than a launch (2.2-3 us each in the tiny GPT step, 4.5-5 behind the GPT-2-small-width step's weights; 29
+// launches a step before, 16 now).
+template <typename T>
+__global__ void __launch_bounds__(TPB) adamw_k(const AdamwBatch b, float lr, float b1, float b2, float eps, float wd, float inv_bc1, float inv_bc2) {
+    int i = 0;
+    while (blockIdx.x >= b.end[i]) ++i;                       // the grid ends at the last tensor's end
+    const AdamwTensor t = b.t[i];
+    const int64_t i0 = ((int64_t)(blockIdx.x - (i ? b.end[i - 1] : 0u)) * TPB + threadIdx.x) * 4;
+    if (t.n >= ADAMW_STREAM) adamw_at<T, true>(t, i0, lr, b1, b2, eps, wd, inv_bc1, inv_bc2);
+    else adamw_at<T, false>(t, i0, lr, b1, b2, eps, wd, inv_bc1, inv_bc2);
 }
 
 // ---------------------------------------------------------------- utilities
@@ -1100,12 +1118,15 @@ void loss_reduce(hipStream_t s, const float *losses, float *loss, int64_t S, int
     loss_reduce_k<<<1, TPB, 0, s>>>(losses, loss, S, S_total, accumulate);
 }
 
-void adamw(hipStream_t s, int dtype, const void *g, void *w, float *master, float *m, float *v, int64_t n, float lr,
-           float beta1, float beta2, float eps, float wd, float bc1, float bc2) {
-    TIO_DISPATCH(dtype, {
-        const auto kernel = n >= ADAMW_STREAM ? adamw_k<T, true> : adamw_k<T, false>;
-        kernel<<<blocks_for(n, TPB * 4), TPB, 0, s>>>((const T *)g, (T *)w, master, m, v, n, lr, beta1, beta2, eps, wd, 1.0f / bc1, 1.0f / bc2);
-    });
+void adamw(hipStream_t s, int dtype, const AdamwTensor *tensors, int count, float lr, float beta1, float beta2, float eps, float wd, float bc1,
+           float bc2) {
+    AdamwBatch b{};
+    unsigned blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        b.t[i] = tensors[i];
+        b.end[i] = blocks += blocks_for(tensors[i].n, TPB * 4);
+    }
+    TIO_DISPATCH(dtype, { adamw_k<T><<<blocks, TPB, 0, s>>>(b, lr, beta1, beta2, eps, wd, 1.0f / bc1, 1.0f / bc2); });
 }
 
 void fill_u32(hipStream_t s, void *p, uint32_t value, int64_t n_words) {

@@ -280,7 +280,7 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
         // operands too large for 32-bit buffer offsets: plain kernel with 64-bit addressing
         launch_bf16<128, 128, 64, 2, 2, 1>(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, workspace, splits, accumulate);
     } else {
-        gemm_f32(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, accumulate);
+        gemm_f32(s, a_km, b_km, F32Product{M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, accumulate});
     }
 }
 

@@ -89,23 +89,36 @@ template <int ROWS, int BK, int NT, bool KM> struct F32Operand {
     static __device__ __forceinline__ float at(const float *lds, int row, int k) { return KM ? lds[k * PITCH + row] : lds[row * PITCH + k]; }
 };
 
+// operands of one product
+struct F32Args {
+    const float *A, *B, *bias, *resid;
+    float *C, *rowsum;
+    int64_t lda, ldb, ldr, ldc, M, N, K;
+    int tiles_m, tiles_n, rowsum_acc;
+};
+
+template <int BM, int BN, int BK, int WGM, int WGN, int KG, bool AKM, bool BKM> struct F32Tile {
+    static constexpr int NT = WGM * WGN * KG * 64;
+    using OpA = F32Operand<BM, BK, NT, AKM>;
+    using OpB = F32Operand<BN, BK, NT, BKM>;
+    static constexpr int STAGE = OpA::FLOATS + OpB::FLOATS, RED = (KG - 1) * BM * BN;
+    static constexpr int FLOATS = 2 * STAGE > RED ? 2 * STAGE : RED;      // of LDS
+    static unsigned blocks(int tiles_m, int tiles_n) { return 8 * (((unsigned)tiles_m * tiles_n + 7) / 8); }
+    static __device__ __forceinline__ void run(const F32Args &a, unsigned block, float *smem);
+};
+
 template <int BM, int BN, int BK, int WGM, int WGN, int KG, bool AKM, bool BKM>
-__global__ void __launch_bounds__(WGM *WGN *KG * 64)
-    gemm_f32_mfma_k(const float *__restrict__ A, int64_t lda, const float *__restrict__ B, int64_t ldb,
-                    const float *__restrict__ bias, const float *resid, int64_t ldr, float *C, int64_t ldc, int64_t M,
-                    int64_t N, int64_t K, int tiles_m, int tiles_n, float *__restrict__ rowsum, int rowsum_acc) {
-    constexpr int NT = WGM * WGN * KG * 64, TPR = NT / BM;
+__device__ __forceinline__ void F32Tile<BM, BN, BK, WGM, WGN, KG, AKM, BKM>::run(const F32Args &a, unsigned block, float *smem) {
+    const float *__restrict__ A = a.A, *__restrict__ B = a.B, *__restrict__ bias = a.bias, *resid = a.resid;
+    float *C = a.C, *__restrict__ rowsum = a.rowsum;
+    const int64_t lda = a.lda, ldb = a.ldb, ldr = a.ldr, ldc = a.ldc, M = a.M, N = a.N, K = a.K;
+    const int tiles_m = a.tiles_m, tiles_n = a.tiles_n, rowsum_acc = a.rowsum_acc;
+    constexpr int TPR = NT / BM;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
     constexpr int CH = BK / 8 / KG;                               // chunks of eight k per wavefront and tile
     static_assert(TPR <= 64 && (TPR & (TPR - 1)) == 0 && BK % TPR == 0 && CH >= 1, "row-sum mapping, chunks per wavefront");
-    using OpA = F32Operand<BM, BK, NT, AKM>;
-    using OpB = F32Operand<BN, BK, NT, BKM>;
-    constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
-    constexpr int RED = (KG - 1) * BM * BN;
-    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE > RED ? 2 * STAGE : RED];
-
     const int total = tiles_m * tiles_n;
-    const int bid = (int)(blockIdx.x % 8) * ((total + 7) / 8) + (int)(blockIdx.x / 8);      // neighbouring tiles on one XCD
+    const int bid = (int)(block % 8) * ((total + 7) / 8) + (int)(block / 8);      // neighbouring tiles on one XCD
     if (bid >= total) return;
     const int tm = bid % tiles_m, tn = bid / tiles_m;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
@@ -228,20 +241,24 @@ __global__ void __launch_bounds__(WGM *WGN *KG * 64)
 // 16x16 tiles on v_mfma_f32_16x16x4_f32 for outputs of a few thousand elements: four times the workgroups, and a quarter of the
 // chain of dependent products per contraction element (8 clocks against 32).  Four wavefronts split every contraction tile; lane
 // quarter q takes k = 16c + 4q + j in product j of chunk c.
-template <bool AKM, bool BKM>
-__global__ void __launch_bounds__(256)
-    gemm_f32_tiny_k(const float *__restrict__ A, int64_t lda, const float *__restrict__ B, int64_t ldb, const float *__restrict__ bias,
-                    const float *resid, int64_t ldr, float *C, int64_t ldc, int64_t M, int64_t N, int64_t K, int tiles_m,
-                    float *__restrict__ rowsum, int rowsum_acc) {
-    constexpr int T = 16, BK = 128, NT = 256, KG = 4, CH = BK / 16 / KG, TPR = NT / T;
-    typedef float floatx4 __attribute__((ext_vector_type(4)));
+template <bool AKM, bool BKM> struct F32Tiny {
+    static constexpr int T = 16, BK = 128, NT = 256, KG = 4;
     using OpA = F32Operand<T, BK, NT, AKM>;
     using OpB = F32Operand<T, BK, NT, BKM>;
-    constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
-    __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
-    __shared__ float red[KG - 1][4][64];
+    static constexpr int STAGE = OpA::FLOATS + OpB::FLOATS, FLOATS = 2 * STAGE;
+    static_assert(FLOATS >= (KG - 1) * 4 * 64, "the partial tiles fit the stages");
+    static unsigned blocks(int tiles_m, int tiles_n) { return (unsigned)(tiles_m * tiles_n); }
+    static __device__ __forceinline__ void run(const F32Args &a, unsigned block, float *smem);
+};
+template <bool AKM, bool BKM> __device__ __forceinline__ void F32Tiny<AKM, BKM>::run(const F32Args &a, unsigned block, float *smem) {
+    const float *__restrict__ A = a.A, *__restrict__ B = a.B, *__restrict__ bias = a.bias, *resid = a.resid;
+    float *C = a.C, *__restrict__ rowsum = a.rowsum;
+    const int64_t lda = a.lda, ldb = a.ldb, ldr = a.ldr, ldc = a.ldc, M = a.M, N = a.N, K = a.K;
+    const int tiles_m = a.tiles_m, rowsum_acc = a.rowsum_acc;
+    constexpr int CH = BK / 16 / KG, TPR = NT / T;
+    typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-    const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
+    const int tm = (int)block % tiles_m, tn = (int)block / tiles_m;
     const int64_t m0 = (int64_t)tm * T, n0 = (int64_t)tn * T;
     const int tid = threadIdx.x, kg = tid >> 6, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const float *baseA = AKM ? A + m0 : A + m0 * lda, *baseB = BKM ? B + n0 : B + n0 * ldb;
@@ -301,9 +318,10 @@ __global__ void __launch_bounds__(256)
         const int64_t m = m0 + tid / TPR;
         if (tid % TPR == 0 && m < M) rowsum[m] = rsum + (rowsum_acc ? rowsum[m] : 0.f);
     }
+    float *red = smem;                                // the last barrier came after every read of the stages
     if (kg > 0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[kg - 1][r][lane] = acc[r];
+        for (int r = 0; r < 4; ++r) red[((kg - 1) * 4 + r) * 64 + lane] = acc[r];
     }
     __syncthreads();
     if (kg > 0) return;
@@ -315,19 +333,28 @@ __global__ void __launch_bounds__(256)
         const int64_t m = m0 + 4 * lq + r;
         float x = acc[r];
 #pragma unroll
-        for (int g = 0; g < KG - 1; ++g) x += red[g][r][lane];
+        for (int g = 0; g < KG - 1; ++g) x += red[(g * 4 + r) * 64 + lane];
         if (m < M) C[m * ldc + n] = x + bn + (resid ? resid[m * ldr + n] : 0.f);
     }
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int KG>
-void launch(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const float *B,
-            int64_t ldb, const float *bias, const float *resid, int64_t ldr, float *C, int64_t ldc, float *rowsum, bool accumulate) {
-    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((N + BN - 1) / BN);
-    const unsigned grid = 8 * (((unsigned)tiles_m * tiles_n + 7) / 8);
-    constexpr int NT = WGM * WGN * KG * 64;
-#define TIO_F32(AKM, BKM) gemm_f32_mfma_k<BM, BN, BK, WGM, WGN, KG, AKM, BKM><<<grid, NT, 0, s>>>(A, lda, B, ldb, bias, resid, ldr, \
-                                                                                  C, ldc, M, N, K, tiles_m, tiles_n, rowsum, (int)accumulate)
+template <typename Tile> __global__ void __launch_bounds__(Tile::NT) gemm_f32_mfma_k(const F32Args a) {
+    __shared__ __attribute__((aligned(16))) float smem[Tile::FLOATS];
+    Tile::run(a, blockIdx.x, smem);
+}
+// two independent products in one launch
+template <typename T0, typename T1> __global__ void __launch_bounds__(T0::NT) gemm_f32_pair_k(const F32Args a0, unsigned blocks0, const F32Args a1) {
+    static_assert(T0::NT == T1::NT, "one workgroup size");
+    __shared__ __attribute__((aligned(16))) float smem[T0::FLOATS > T1::FLOATS ? T0::FLOATS : T1::FLOATS];
+    if (blockIdx.x < blocks0) T0::run(a0, blockIdx.x, smem);
+    else T1::run(a1, blockIdx.x - blocks0, smem);
+}
+
+template <bool AKM, bool BKM> using Tile64 = F32Tile<64, 64, 32, 2, 2, 1, AKM, BKM>;
+template <bool AKM, bool BKM> using Tile32 = F32Tile<32, 32, 64, 1, 1, 4, AKM, BKM>;
+
+template <template <bool, bool> class Tile> void launch(hipStream_t s, bool a_km, bool b_km, const F32Args &a) {
+#define TIO_F32(AKM, BKM) gemm_f32_mfma_k<Tile<AKM, BKM>><<<Tile<AKM, BKM>::blocks(a.tiles_m, a.tiles_n), Tile<AKM, BKM>::NT, 0, s>>>(a)
     if (!a_km && !b_km) TIO_F32(false, false);
     else if (!a_km && b_km) TIO_F32(false, true);
     else if (a_km && b_km) TIO_F32(true, true);
@@ -335,10 +362,8 @@ void launch(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K
 #undef TIO_F32
 }
 
-}  // namespace
-
-void gemm_f32(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
-              int64_t ldb, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, bool accumulate) {
+// edge of the output tile
+int tile_of(int64_t M, int64_t N) {
     // 32x32 tiles while 64x64 ones would leave compute units without work.  Microseconds, 32 / 64 / (not kept) 128 square, both
     // operands contraction-contiguous:
     //   128 x 512 x 128      5.5 /   7.2 /  20        1024 x  768 x 3072 (192 tiles of 64)   57 /  74 / 253
@@ -347,26 +372,48 @@ void gemm_f32(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N, int64_t
     //  2048 x 2048 x 2048  203   / 160   / 174        1024 x 1792 x 2048 (448)                96 /  80 / 172
     // The first kernel here (64x64 tiles on the vector ALU) took 62 us for 128 x 128 x 1024 and about 300 us for 1024 x 3072 x 768,
     // now 53.  128x128 tiles leave one wavefront per SIMD where the others leave three, and lose everywhere.
-#define TIO_F32_ARGS s, a_km, b_km, M, N, K, (const float *)A, lda, (const float *)B, ldb, (const float *)bias, (const float *)resid, ldr, \
-                     (float *)C, ldc, (float *)rowsum, accumulate
-    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64), tiles32 = ((M + 31) / 32) * ((N + 31) / 32);
     // 16x16 tiles up to 160 tiles of 32x32: 128 x 128 x 1024 (16 tiles) 12.5 -> 6.0 us, 256 x 512 x 512 (128) 8.5 -> 5.6,
     // 300 x 500 x 1000 (160) 13.2 -> 11.5, but 64 x 3000 x 512 (188) 8.7 -> 10.2 with a k-major operand
-    if (tiles32 <= 160) {
-        const int tiles_m = (int)((M + 15) / 16);
-        const unsigned grid = (unsigned)(tiles_m * ((N + 15) / 16));
-#define TIO_F32_TINY(AKM, BKM) gemm_f32_tiny_k<AKM, BKM><<<grid, 256, 0, s>>>((const float *)A, lda, (const float *)B, ldb, (const float *)bias, \
-                                   (const float *)resid, ldr, (float *)C, ldc, M, N, K, tiles_m, (float *)rowsum, (int)accumulate)
-        if (!a_km && !b_km) TIO_F32_TINY(false, false);
-        else if (!a_km && b_km) TIO_F32_TINY(false, true);
-        else if (a_km && b_km) TIO_F32_TINY(true, true);
-        else TIO_F32_TINY(true, false);
-#undef TIO_F32_TINY
-        return;
+    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64), tiles32 = ((M + 31) / 32) * ((N + 31) / 32);
+    return tiles32 <= 160 ? 16 : tiles64 >= 224 ? 64 : 32;
+}
+F32Args args_of(const F32Product &p, int tile) {
+    return F32Args{(const float *)p.A, (const float *)p.B, (const float *)p.bias, (const float *)p.resid, (float *)p.C, (float *)p.rowsum,
+                   p.lda, p.ldb, p.ldr, p.ldc, p.M, p.N, p.K, (int)((p.M + tile - 1) / tile), (int)((p.N + tile - 1) / tile), (int)p.accumulate};
+}
+
+}  // namespace
+
+void gemm_f32(hipStream_t s, bool a_km, bool b_km, const F32Product &p) {
+    const int tile = tile_of(p.M, p.N);
+    const F32Args a = args_of(p, tile);
+    if (tile == 16) launch<F32Tiny>(s, a_km, b_km, a);
+    else if (tile == 32) launch<Tile32>(s, a_km, b_km, a);
+    else launch<Tile64>(s, a_km, b_km, a);
+}
+
+// Both gradients of a linear layer in one launch, where the tiles of one of them are small (16 or 32 square): such products last
+// about as long as a launch, and neither fills the chip (4.2 + 4.5 us in the tiny GPT step, nine times: that step, with merged updates
+// and delta in the launch of attention backward as well, 332 -> 256 us).
+bool gemm_f32_pairs(int64_t M0, int64_t N0, int64_t M1, int64_t N1) { return tile_of(M0, N0) < 64 && tile_of(M1, N1) < 64; }
+
+void gemm_f32_pair(hipStream_t s, const F32Product &dx, const F32Product &dw) {
+    const int t0 = tile_of(dx.M, dx.N), t1 = tile_of(dw.M, dw.N);
+    const F32Args a0 = args_of(dx, t0), a1 = args_of(dw, t1);
+    using X16 = F32Tiny<false, true>;
+    using X32 = Tile32<false, true>;
+    using W16 = F32Tiny<true, true>;
+    using W32 = Tile32<true, true>;
+#define TIO_F32_PAIR(X, W)                                                                                          \
+    {                                                                                                               \
+        const unsigned n0 = X::blocks(a0.tiles_m, a0.tiles_n), n1 = W::blocks(a1.tiles_m, a1.tiles_n);              \
+        gemm_f32_pair_k<X, W><<<n0 + n1, X::NT, 0, s>>>(a0, n0, a1);                                                \
     }
-    if (tiles64 >= 224) launch<64, 64, 32, 2, 2, 1>(TIO_F32_ARGS);
-    else launch<32, 32, 64, 1, 1, 4>(TIO_F32_ARGS);
-#undef TIO_F32_ARGS
+    if (t0 == 16 && t1 == 16) TIO_F32_PAIR(X16, W16)
+    else if (t0 == 16) TIO_F32_PAIR(X16, W32)
+    else if (t1 == 16) TIO_F32_PAIR(X32, W16)
+    else TIO_F32_PAIR(X32, W32)
+#undef TIO_F32_PAIR
 }
 
 }  // namespace k

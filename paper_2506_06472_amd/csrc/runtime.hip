@@ -87,6 +87,7 @@ struct tio_ctx {
     std::vector<uint8_t> in_host1;                       // per persistent tensor: latest version is in a host-tier slot
     std::vector<uint64_t> host1_off;
     std::vector<std::vector<uint64_t>> ptrs;             // per kernel, per role: arena offset (UINT64_MAX = absent)
+    std::vector<int> merged;                             // per kernel: how many from it on go out in one launch (1: itself alone)
     std::vector<hipEvent_t> ev_kernel, ev_off, ev_pre, ev_t0, ev_t1;
     std::vector<uint8_t> rec_kernel, rec_off, rec_pre;
     int step = 0;
@@ -182,6 +183,44 @@ void gather_to_home(tio_ctx *c) {
     if (c->pool_dev) HIPCHK(hipDeviceSynchronize());
 }
 
+// ---- neighbours in the schedule that go out in one launch
+// Between kernels j - 1 and j nothing is issued, waited for or recorded.
+bool nothing_between(const Plan &p, int j) {
+    return p.entries_at[j].empty() && p.kernel_wait_pre[j].empty() && p.kernel_wait_off[j].empty() && !p.kernel_needs_event[j - 1];
+}
+// The kernels share no memory that one of them writes (a range may be taken over from a tensor that dies at k by one born at k + 1);
+// shared: a tensor that the merged launch hands from one to the other itself, or -1.
+bool independent(const tio_ctx *c, int k, int shared) {
+    const KernelRec &x = c->prog.kernels[k], &y = c->prog.kernels[k + 1];
+    for (int i = 0; i < kMaxRoles; ++i)
+        for (int j = 0; j < kMaxRoles; ++j) {
+            if (x.t[i] < 0 || y.t[j] < 0 || !((x.fl[i] | y.fl[j]) & 2) || (x.t[i] == shared && y.t[j] == shared)) continue;
+            const uint64_t a = c->ptrs[k][i], b = c->ptrs[k + 1][j];
+            if (a < b + c->prog.tensors[y.t[j]].bytes && b < a + c->prog.tensors[x.t[i]].bytes) return false;
+        }
+    return true;
+}
+// How many kernels from k on one launch does: updates in a row; the two gradients of a linear layer where both products are small; the
+// row products of attention's backward pass with that pass where its kernel computes them.
+int merged_from(const tio_ctx *c, int k) {
+    const int N = c->trace.n_kernels;
+    const KernelRec &r = c->prog.kernels[k];
+    auto next = [&](int j, int op) { return j < N && c->prog.kernels[j].op == op && nothing_between(c->plan, j); };
+    if (r.op == OP_ADAMW) {
+        int n = 1;
+        while (n < k::kAdamwMax && next(k + n, OP_ADAMW) && independent(c, k + n - 1, -1)) ++n;
+        return n;
+    }
+    if (r.op == OP_GEMM_DX && next(k + 1, OP_GEMM_DW) && c->cfg.precision == TIO_PREC_FP32) {
+        const KernelRec &w = c->prog.kernels[k + 1];
+        return k::gemm_f32_pairs(r.p[0], r.p[1], w.p[0], w.p[1]) && independent(c, k, -1) ? 2 : 1;
+    }
+    if (r.op == OP_ATTN_BWD_PRE && next(k + 1, OP_ATTN_BWD))
+        return k::attn_bwd_has_delta(c->cfg.precision, c->cfg.seq_len, c->cfg.n_heads, c->cfg.d_model / c->cfg.n_heads) &&
+               independent(c, k, r.t[2]) ? 2 : 1;
+    return 1;
+}
+
 void install_plan(tio_ctx *c, const Plan &p) {
     const int N = c->trace.n_kernels;
     if (p.structure_hash != c->trace.structure_hash || p.n_kernels != N)
@@ -252,6 +291,8 @@ void install_plan(tio_ctx *c, const Plan &p) {
     }
     if (c->pool_dev) HIPCHK(hipDeviceSynchronize());     // see gather_to_home
     c->ptrs = std::move(ptrs);
+    c->merged.assign(N, 1);
+    for (int k = 0; k < N; k += c->merged[k]) c->merged[k] = merged_from(c, k);
     make_events(c->ev_kernel, N, false);
     make_events(c->ev_off, p.pairs.size(), false);
     make_events(c->ev_pre, p.pairs.size(), false);
@@ -267,7 +308,8 @@ void install_plan(tio_ctx *c, const Plan &p) {
     c->params_dirty = false;
 }
 
-void launch(tio_ctx *c, int k) {
+// kernels k .. k + count - 1: one, or as many as merged_from says
+void launch(tio_ctx *c, int k, int count = 1) {
     const KernelRec &r = c->prog.kernels[k];
     const tio_model_cfg &m = c->cfg;
     auto P = [&](int role) -> void * { return c->ptrs[k][role] == UINT64_MAX ? nullptr : (void *)(c->arena + c->ptrs[k][role]); };
@@ -276,6 +318,7 @@ void launch(tio_ctx *c, int k) {
     // B: sequences of one micro-batch
     const int64_t B = m.batch / (m.micro_batches > 1 ? m.micro_batches : 1), T = m.seq_len, H = m.n_heads, dh = m.d_model / m.n_heads;
     hipStream_t s = c->sc;
+    auto Q = [&](int role) -> void * { return c->ptrs[k + 1][role] == UINT64_MAX ? nullptr : (void *)(c->arena + c->ptrs[k + 1][role]); };
     switch (r.op) {
     case OP_EMBED_FWD: k::embed_fwd(s, dt, (const int32_t *)P(0), P(1), P(2), P(3), r.p[0], r.p[1], r.p[2]); break;
     case OP_NORM_FWD: k::norm_fwd(s, dt, rms, P(0), P(1), P(2), P(3), (float *)P(4), r.p[0], r.p[1], m.norm_eps); break;
@@ -289,7 +332,16 @@ void launch(tio_ctx *c, int k) {
     case OP_SWIGLU_FWD: k::swiglu_fwd(s, dt, P(0), P(1), r.p[0], r.p[1]); break;
     case OP_CE_FWD_BWD: k::ce_fwd_bwd(s, dt, P(0), (const int32_t *)P(1), (float *)P(2), r.p[0], r.p[1], r.p[2], r.p[3]); break;
     case OP_LOSS_REDUCE: k::loss_reduce(s, (const float *)P(0), (float *)P(1), r.p[0], r.p[1], r.p[2] != 0); break;
-    case OP_GEMM_DX:   // dX[S,n_in] = dY[S,n_out] . W[n_out,n_in]: the weight has the contraction index slow
+    case OP_GEMM_DX:
+        if (count == 2) {
+            const KernelRec &w = c->prog.kernels[k + 1];
+            const bool more = w.p[5] != 0;             // a later micro-batch adds to the gradient
+            k::gemm_f32_pair(s, k::F32Product{r.p[0], r.p[1], r.p[2], P(0), r.p[3], P(1), r.p[1], nullptr, nullptr, 0, P(2), r.p[1], nullptr, false},
+                             k::F32Product{w.p[0], w.p[1], w.p[2], Q(0), w.p[3], Q(1), w.p[1], nullptr, more ? Q(2) : nullptr, more ? w.p[1] : 0,
+                                        Q(2), w.p[1], Q(3), more});
+            break;
+        }
+                       // dX[S,n_in] = dY[S,n_out] . W[n_out,n_in]: the weight has the contraction index slow
         k::gemm(s, dt, false, true, r.p[0], r.p[1], r.p[2], P(0), r.p[3], P(1), r.p[1], nullptr, nullptr, 0, P(2), r.p[1], nullptr, nullptr, 1);
         break;
     case OP_GEMM_DW:   // dW[n_out,n_in] = dY^T . X: both operands have the contraction index (tokens) slow;
@@ -302,15 +354,21 @@ void launch(tio_ctx *c, int k) {
         k::norm_bwd(s, dt, rms, P(0), P(1), (const float *)P(2), P(3), P(4), P(5), (float *)P(6), r.p[0], r.p[1], r.p[2]);
         break;
     case OP_NORM_BWD_PARAMS: k::norm_bwd_params(s, dt, rms, (const float *)P(0), P(1), P(2), r.p[0], r.p[1], r.p[2] != 0); break;
-    case OP_ATTN_BWD_PRE: k::attn_bwd_pre(s, dt, P(0), P(1), (float *)P(2), B, T, H, dh); break;
+    case OP_ATTN_BWD_PRE:
+        if (count == 2) { k::attn_bwd(s, dt, P(0), Q(1), P(1), (const float *)Q(2), (float *)P(2), Q(4), B, T, H, dh); break; }
+        k::attn_bwd_pre(s, dt, P(0), P(1), (float *)P(2), B, T, H, dh); break;
     case OP_ATTN_BWD: k::attn_bwd(s, dt, P(0), P(1), nullptr, (const float *)P(2), (float *)P(3), P(4), B, T, H, dh); break;
     case OP_EMBED_BWD: k::embed_bwd(s, dt, P(0), (const int32_t *)P(1), P(2), r.p[0], r.p[1], r.p[2], r.p[3] != 0); break;
     case OP_POSEMB_BWD: k::posemb_bwd(s, dt, P(0), P(1), r.p[0], r.p[1], r.p[2], r.p[3] != 0); break;
     case OP_ADAMW: {
         const double t = (double)(c->step + 1);
         const float bc1 = (float)(1.0 - std::pow((double)m.beta1, t)), bc2 = (float)(1.0 - std::pow((double)m.beta2, t));
-        k::adamw(s, dt, P(0), P(1), (float *)P(2), (float *)P(3), (float *)P(4), r.p[0], m.lr, m.beta1, m.beta2, m.adam_eps,
-                 m.weight_decay, bc1, bc2);
+        k::AdamwTensor u[k::kAdamwMax];
+        for (int i = 0; i < count; ++i) {
+            auto A = [&](int role) { return c->ptrs[k + i][role] == UINT64_MAX ? nullptr : (void *)(c->arena + c->ptrs[k + i][role]); };
+            u[i] = {A(0), A(1), (float *)A(2), (float *)A(3), (float *)A(4), c->prog.kernels[k + i].p[0]};
+        }
+        k::adamw(s, dt, u, count, m.lr, m.beta1, m.beta2, m.adam_eps, m.weight_decay, bc1, bc2);
         break;
     }
     default: throw PlanError{TIO_ERR_INVALID_ARG, "unknown operator"};
@@ -481,7 +539,10 @@ void run_step_body(tio_ctx *c, const int32_t *tokens, const int32_t *labels, boo
         }
         if (capture && c->prog.kernels[k].op == OP_ADAMW) capture_grad(c, k);
         if (timing) HIPCHK(hipEventRecord(c->ev_t0[k], c->sc));
-        launch(c, k);
+        // kernels are launched one by one where each is timed or its gradient read back
+        const int count = timing || capture ? 1 : c->merged[k];
+        launch(c, k, count);
+        k += count - 1;
         if (timing) HIPCHK(hipEventRecord(c->ev_t1[k], c->sc));
         // the scalar loss lives only until later kernels reuse its range: copy it out in stream order
         if (c->prog.kernels[k].op == OP_LOSS_REDUCE)

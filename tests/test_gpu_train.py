@@ -428,3 +428,26 @@ def test_optimizer_state_follows_the_oracle_from_the_gpu_gradients(cfg):
             assert np.array_equal(w, to_bf16_round(ctx.tio_params_read(n, 1).astype(np.float32)).reshape(-1)), n
     print("largest relative deviation of the optimizer state", worst, flush=True)
     ctx.close()
+
+
+@pytest.mark.parametrize("cfg", [
+    CONFIGS["tiny_gpt_fp32"], CONFIGS["tiny_llama_fp32"], SMALL_BF16,
+    # products of 32x32 beside 16x16 tiles, more than eight key tiles, odd sizes
+    dict(arch="gpt", L=1, d=160, H=5, f=520, V=1001, T=292, B=2, precision="fp32", lr=1e-3),
+    dict(arch="llama", L=2, d=96, H=3, f=264, V=500, T=72, B=3, precision="bf16", lr=3e-4),
+    dict(arch="gpt", L=1, d=128, H=4, f=512, V=700, T=64, B=4, precision="fp32", lr=1e-3, micro_batches=2)])
+def test_merged_launches_leave_the_bits_of_single_ones(cfg):
+    """A step whose gradients are read back launches every kernel by itself; the others merge neighbours."""
+    params, tok, lab = make_inputs(cfg, seed=1)
+    lt, ll, up, _, peak = plans_for(cfg)
+    out = []
+    for alone in (True, False):
+        ctx = _ctx(cfg, up.export())
+        ctx.tio_params_load(params)
+        losses = [ctx.tio_train_step(tok, lab, None, capture_grads=alone)["loss"] for _ in range(2)]
+        out.append((losses, {n: [ctx.tio_params_read(n, w) for w in (0, 2, 3)] for n, _, _ in ctx.params}))
+        ctx.close()
+    assert out[0][0] == out[1][0]
+    for n, tensors in out[0][1].items():
+        for a, b in zip(tensors, out[1][1][n]):
+            assert np.array_equal(a, b), n
