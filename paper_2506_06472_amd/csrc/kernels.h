@@ -26,6 +26,11 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
 // the output tile gemm_bf16_direct takes, 0 x 0 where it refuses; host only
 void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits, int *rows,
                     int *cols);
+// contraction ranges a product without a workspace from its caller is worth cutting into (1: none), with partials of at most `bytes`;
+// host only
+int gemm_bf16_splits(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t bytes);
+// the fp32 partials of a split product: `splits` tiles of M rows of partial_ld(N), then `splits` row sums of M
+constexpr int64_t partial_ld(int64_t N) { return (N + 3) / 4 * 4; }
 // fp32 products on the fp32 matrix instruction (kernels_gemm_f32.hip); accumulate adds to rowsum (the caller passes C as resid)
 struct F32Product {
     int64_t M, N, K;

@@ -14,6 +14,8 @@
 // fp32: kernels_gemm_f32.hip.
 #include <stdexcept>
 
+#include <mutex>
+
 #include "../../include/teraio.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -189,37 +191,137 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     }
 }
 
-// adds the split-K partials in split order and rounds once; also finishes the fused row sums
-__global__ void __launch_bounds__(256) splitk_reduce_k(const float *__restrict__ ws, uint16_t *__restrict__ C, int64_t ldc,
-                                                       uint16_t *__restrict__ rowsum, int64_t M, int64_t N, int splits,
-                                                       int accumulate) {
+// Adds the split-K partials in split order, then bias and residual, and rounds once; also finishes the fused row sums.  A thread has four
+// columns of a row (the last ones of a row: up to four), and the partials of eight ranges on their way at a time.
+__global__ void __launch_bounds__(256) splitk_reduce_k(const float *__restrict__ ws, const uint16_t *__restrict__ bias, const uint16_t *resid,
+                                                       int64_t ldr, uint16_t *C, int64_t ldc, uint16_t *__restrict__ rowsum, int64_t M, int64_t N,
+                                                       int splits, int accumulate) {
+    constexpr int AHEAD = 8;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t nq = N / 4, total = M * nq;
+    const int64_t ld = partial_ld(N), nq = ld / 4, total = M * nq;
     if (idx < total) {
         const int64_t m = idx / nq, n = (idx % nq) * 4;
-        float4 a = *reinterpret_cast<const float4 *>(ws + m * N + n);
-        for (int sp = 1; sp < splits; ++sp) {
-            const float4 b = *reinterpret_cast<const float4 *>(ws + ((int64_t)sp * M + m) * N + n);
-            a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+        const float *at = ws + m * ld + n;
+        const int cols = N - n < 4 ? (int)(N - n) : 4;
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int sp = 0; sp < splits; sp += AHEAD) {
+            float4 part[AHEAD];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i)
+                if (sp + i < splits) part[i] = *reinterpret_cast<const float4 *>(at + (int64_t)(sp + i) * M * ld);
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i)
+                if (sp + i < splits) { a[0] += part[i].x; a[1] += part[i].y; a[2] += part[i].z; a[3] += part[i].w; }
         }
-        if (accumulate) {          // earlier micro-batches' sum is in C
-            const uint2 t = *reinterpret_cast<const uint2 *>(C + m * ldc + n);
-            a.x += __uint_as_float(t.x << 16); a.y += __uint_as_float(t.x & 0xffff0000u);
-            a.z += __uint_as_float(t.y << 16); a.w += __uint_as_float(t.y & 0xffff0000u);
+        uint16_t *c = C + m * ldc + n;
+        const uint16_t *extra[2] = {bias ? bias + n : nullptr, accumulate ? c : resid ? resid + m * ldr + n : nullptr};   // accumulate: earlier micro-batches' sum is in C
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (!extra[k]) continue;
+            if (cols == 4) {
+                const uint2 t = *reinterpret_cast<const uint2 *>(extra[k]);
+                a[0] += __uint_as_float(t.x << 16); a[1] += __uint_as_float(t.x & 0xffff0000u);
+                a[2] += __uint_as_float(t.y << 16); a[3] += __uint_as_float(t.y & 0xffff0000u);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < cols) a[e] += bf16_bits_to_f32(extra[k][e]);
+            }
         }
-        uint2 o;
-        o.x = pack_bf16x2(a.x, a.y);
-        o.y = pack_bf16x2(a.z, a.w);
-        *reinterpret_cast<uint2 *>(C + m * ldc + n) = o;
+        if (cols == 4) {
+            *reinterpret_cast<uint2 *>(c) = make_uint2(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (e < cols) c[e] = (uint16_t)f32_to_bf16_bits(a[e]);
+        }
     } else if (rowsum != nullptr && idx - total < M) {
         const int64_t m = idx - total;
-        const float *r = ws + (int64_t)splits * M * N;
+        const float *r = ws + (int64_t)splits * M * ld;
         float a = r[m];
         for (int sp = 1; sp < splits; ++sp) a += r[(int64_t)sp * M + m];
         if (accumulate) a += bf16_bits_to_f32(rowsum[m]);
         rowsum[m] = (uint16_t)f32_to_bf16_bits(a);
     }
 }
+void splitk_reduce(hipStream_t s, const void *ws, const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, int64_t M,
+                   int64_t N, int splits, bool accumulate) {
+    const int64_t n = M * (partial_ld(N) / 4) + (rowsum ? M : 0);
+    splitk_reduce_k<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const float *)ws, (const uint16_t *)bias, (const uint16_t *)resid, ldr, (uint16_t *)C,
+                                                                 ldc, (uint16_t *)rowsum, M, N, splits, (int)accumulate);
+}
+
+// ---- scratch space of products that are split without a workspace from their caller
+// A fixed array on every device, in SLOTS parts.  A product takes a part for its two launches: the stream first waits for the event
+// that the part's last user recorded behind its own, and the lock is held from the choice of the part to the recording, so that two
+// threads' launches on one stream do not mix.  A stream gets the part it had before, if it is still the last one there, so that
+// up to SLOTS streams do not wait for each other.  No allocation, and no waiting on the host.  (An allocation from a stream-ordered pool for
+// each product took 18 us of host time.)
+constexpr int SLOTS = 4, DEVICES = 64;
+constexpr int64_t SLOT_BYTES = (int64_t)32 << 20;
+__device__ __align__(256) unsigned char split_partials[SLOTS * SLOT_BYTES];
+
+struct Slot {
+    hipEvent_t free = nullptr;
+    hipStream_t user = nullptr;
+    uint64_t used = 0;           // number of its last use; 0: never
+};
+struct SlotsOfDevice {
+    unsigned char *base = nullptr;
+    bool failed = false;
+    uint64_t uses = 0;
+    Slot slot[SLOTS];
+};
+std::mutex slots_mu;
+SlotsOfDevice slots_of[DEVICES];
+
+class SplitScratch {
+    std::unique_lock<std::mutex> lock;
+    hipStream_t s;
+    Slot *mine = nullptr;
+    unsigned char *at = nullptr;
+
+public:
+    // partials() is nullptr where there is no part to be had: a stream under capture (a replay would not wait for the part's other
+    // users), or a device that refuses the array or an event
+    explicit SplitScratch(hipStream_t stream) : s(stream) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); return; }
+        int dev = -1;
+        if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= DEVICES) return;
+        lock = std::unique_lock<std::mutex>(slots_mu);
+        SlotsOfDevice &d = slots_of[dev];
+        if (!d.base && !d.failed) prepare(d);
+        if (d.failed) { lock.unlock(); return; }
+        Slot *best = &d.slot[0];
+        for (Slot &x : d.slot) {
+            if (x.used && x.user == s) { best = &x; break; }
+            if (x.used < best->used) best = &x;
+        }
+        if (best->used && hipStreamWaitEvent(s, best->free, 0) != hipSuccess) { (void)hipGetLastError(); lock.unlock(); return; }
+        mine = best;
+        mine->user = s;
+        mine->used = ++d.uses;
+        at = d.base + (mine - d.slot) * SLOT_BYTES;
+    }
+    ~SplitScratch() {
+        if (mine) (void)hipEventRecord(mine->free, s);
+    }
+    float *partials() const { return reinterpret_cast<float *>(at); }
+
+private:
+    // once per device; another thread's capture in global mode must not see these calls as its own
+    static void prepare(SlotsOfDevice &d) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        bool ok = hipGetSymbolAddress(&p, HIP_SYMBOL(split_partials)) == hipSuccess && p;
+        for (Slot &x : d.slot) ok = ok && hipEventCreateWithFlags(&x.free, hipEventDisableTiming) == hipSuccess;
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (ok) d.base = (unsigned char *)p;
+        else { (void)hipGetLastError(); d.failed = true; }
+    }
+};
 
 }  // namespace
 
@@ -248,10 +350,7 @@ static void launch_bf16(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t 
     else if (a_km && b_km) gemm_bf16_k<BM, BN, BK, WGM, WGN, NBUF, true, true><<<grid, block, lds, s>>>(TIO_GEMM_ARGS);
     else gemm_bf16_k<BM, BN, BK, WGM, WGN, NBUF, true, false><<<grid, block, lds, s>>>(TIO_GEMM_ARGS);
 #undef TIO_GEMM_ARGS
-    if (ws) {
-        const int64_t n = M * (N / 4) + (rowsum ? M : 0);
-        splitk_reduce_k<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(ws, (uint16_t *)C, ldc, (uint16_t *)rowsum, M, N, splits, (int)accumulate);
-    }
+    if (ws) splitk_reduce(s, ws, nullptr, nullptr, 0, C, ldc, rowsum, M, N, splits, accumulate);
 }
 
 void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
@@ -260,6 +359,17 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
     if (M <= 0 || N <= 0 || K <= 0) return;
     // split-K needs the fp32 workspace, no epilogue operands and whole float4 rows
     if (dtype != TIO_PREC_BF16 || !workspace || bias || resid || (N % 4) || splits < 2) splits = 1;
+    if (dtype == TIO_PREC_BF16 && splits == 1) {
+        const int own = gemm_bf16_splits(a_km, b_km, M, N, K, lda, ldb, rowsum != nullptr, SLOT_BYTES);
+        if (own > 1) {
+            const SplitScratch scratch(s);
+            float *const ws = scratch.partials();
+            if (ws && gemm_bf16_direct(s, a_km, b_km, M, N, K, A, lda, B, ldb, nullptr, nullptr, 0, C, ldc, rowsum, ws, own, accumulate)) {
+                splitk_reduce(s, ws, bias, resid, ldr, C, ldc, rowsum, M, N, own, accumulate);
+                return;
+            }
+        }
+    }
     // accumulate: C += A.B^T and rowsum += row sums (gradient accumulation over micro-batches).  In a single
     // pass the old C is the residual operand (every element is read and then written by the same lane); with
     // split-K the reduction launch adds it.
@@ -271,10 +381,7 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
     if (dtype == TIO_PREC_BF16) {
         float *const wsp = splits > 1 ? (float *)workspace : nullptr;
         if (gemm_bf16_direct(s, a_km, b_km, M, N, K, A, lda, B, ldb, bias, resid, ldr, C, ldc, rowsum, wsp, splits, accumulate)) {
-            if (splits > 1) {
-                const int64_t n = M * (N / 4) + (rowsum ? M : 0);
-                splitk_reduce_k<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const float *)workspace, (uint16_t *)C, ldc, (uint16_t *)rowsum, M, N, splits, (int)accumulate);
-            }
+            if (splits > 1) splitk_reduce(s, workspace, nullptr, nullptr, 0, C, ldc, rowsum, M, N, splits, accumulate);
             return;
         }
         // operands too large for 32-bit buffer offsets: plain kernel with 64-bit addressing

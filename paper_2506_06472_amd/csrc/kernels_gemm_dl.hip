@@ -204,7 +204,7 @@ __device__ __forceinline__ void store_rowsum(const floatx4 (&rs)[TM / 2], int la
     for (int u = 0; u < TM / 2; ++u) {
         const int64_t m = mw + (2 * u + wn) * 16 + lane;
         if (lane < 16 && m < M) {
-            if (ws) ws[(int64_t)nsplit * M * N + (int64_t)split * M + m] = rs[u][0];
+            if (ws) ws[(int64_t)nsplit * M * partial_ld(N) + (int64_t)split * M + m] = rs[u][0];
             else rowsum[m] = (uint16_t)f32_to_bf16_bits(rs[u][0] + (accumulate ? bf16_bits_to_f32(rowsum[m]) : 0.f));
         }
     }
@@ -295,7 +295,7 @@ __device__ __forceinline__ void store_inside(const floatx4 (&acc)[TM][TN], float
     using P = Part<TM, TN>;
     constexpr int PASSES = P::PASSES, AHEAD = RESID ? 1 : 0;         // blocks that pass through LDS ahead of the one being stored
     const P part(lane);
-    const int64_t ldo = WS ? N : ldc;
+    const int64_t ldo = WS ? partial_ld(N) : ldc;
     int64_t out[PASSES], res[PASSES];
     uint4 b[PASSES], r[PASSES];
     float v[2][PASSES][8];
@@ -349,7 +349,7 @@ __device__ __forceinline__ void store_edge(const floatx4 (&acc)[TM][TN], float *
     static_assert(BATCH % 2 == 0 && (TM == BATCH || TM == 2 * BATCH), "blocks in pairs, one batch or two");
     const P part(lane);
     const int rows = M - mw < TM * 16 ? (int)(M - mw) : TM * 16;
-    const int64_t ldo = ws ? N : ldc;
+    const int64_t ldo = ws ? partial_ld(N) : ldc;
     int cols[PASSES];
     int64_t out[PASSES], res[PASSES];
     uint4 b[PASSES];
@@ -868,7 +868,8 @@ const TileChoice TILES[] = {
 };
 
 // the tile with the lowest cost among those that can address the operands and have the layout; nullptr: none can
-const TileChoice *choose(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits) {
+const TileChoice *choose(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits,
+                         double *its_cost = nullptr) {
     const int64_t kspan = splits > 1 ? ((K + splits - 1) / splits + BK - 1) / BK * BK : K;
     // 32-bit buffer offsets: what one workgroup addresses of an operand has to lie within 1 GiB
     auto span = [&](bool km, int64_t rows, int64_t ld) { return (km ? (kspan + 3 * BK) * ld : rows * ld + kspan + 3 * BK) * 2; };
@@ -882,6 +883,7 @@ const TileChoice *choose(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, 
         const double cost = t.cost(M, N, nk, splits > 1 ? splits : 1);
         if (!best || cost < best_cost) { best = &t; best_cost = cost; }
     }
+    if (its_cost) *its_cost = best_cost;
     return best;
 }
 
@@ -895,6 +897,27 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
     t->launch(Product{s, a_km, b_km, M, N, K, (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid,
                       ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate});
     return true;
+}
+
+// A long contraction with a small output leaves most compute units without a tile, and the small tiles that keep more of them busy fetch
+// more than a unit can load.  Cut into ranges it costs the partials' way to memory and back, a launch and the events around the
+// scratch space, and has to promise a seventh for that (the launch and the events take host time too).  us, in one range / cut:
+//   1021 x 768 x 50257 264 / 107 (eight)    64 x 1024 x 22016 99 / 25     200 x 300 x 15000 68 / 17     300 x 300 x 8000 36 / 15
+// and left alone, though a cut with a workspace at hand gains something: 128 x 2000 x 4000 19.0 / 12.6 + 3, 1024 x 2048 x 8192 54 / 44 + 3,
+// 1000 x 1000 x 10000 45 / 37 + 3; 768 x 768 x 1900 10.8 / 14.3 + 3.
+int gemm_bf16_splits(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t bytes) {
+    double whole = 0;
+    if (!choose(a_km, b_km, M, N, K, lda, ldb, rowsum, 1, &whole)) return 1;
+    int best = 1;
+    double best_cost = 0.85 * whole;
+    for (int s = 2; s <= 8 && K >= 256 * s; s *= 2) {
+        const int64_t partials = s * (M * partial_ld(N) + M) * 4;
+        double cost = 0;
+        if (partials > bytes || !choose(a_km, b_km, M, N, K, lda, ldb, rowsum, s, &cost)) break;
+        cost += 7.5 + 2e-6 * (double)partials / 6;                // us; the partials go through the caches at 6 TB/s
+        if (cost < best_cost) { best = s; best_cost = cost; }
+    }
+    return best;
 }
 
 void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int splits, int *rows,
