@@ -32,16 +32,16 @@ template <int ROWS, int BK, int NT, bool KM> struct F32Operand {
     static_assert(PER >= 1 && PER * NT * 4 == ROWS * BK, "chunks divide over the threads");
     const float *p[PER];
     int64_t step;                                                // floats from one contraction tile to the next
-    int rows, slow_rows;                                          // rows of the operand in this tile; some chunk holds both valid and other rows
+    int rows, part_rows;                                          // rows of the operand in this tile; some chunk holds both valid and other rows
     __device__ __forceinline__ void init(const float *base, int64_t ld, int rows_valid, int tid) {
         rows = rows_valid;
-        slow_rows = KM && rows_valid < ROWS && (rows_valid & 3);
+        part_rows = KM && rows_valid < ROWS && (rows_valid & 3);
         step = KM ? (int64_t)BK * ld : BK;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int c = i * NT + tid, o = c / CPR, q = c % CPR;
-            // rows past the end read a valid row: what comes out of them is never stored
-            if (KM) p[i] = base + (int64_t)o * ld + (q * 4 + 4 <= rows_valid ? q * 4 : 0);
+            // rows past the end read a valid row, or with KM the padding up to the leading dimension: what comes out of them is never stored
+            if (KM) p[i] = base + (int64_t)o * ld + (q * 4 < rows_valid ? q * 4 : 0);
             else p[i] = base + (int64_t)(o < rows_valid ? o : rows_valid - 1) * ld + q * 4;
         }
     }
@@ -49,9 +49,10 @@ template <int ROWS, int BK, int NT, bool KM> struct F32Operand {
 #pragma unroll
         for (int i = 0; i < PER; ++i) r[i] = *reinterpret_cast<const float4 *>(p[i] + kt * step);
     }
-    // the last tile of a contraction that is no multiple of BK, and tiles with a partly valid chunk: whole chunks as such, a partly
-    // valid one element by element, nothing at or past the end is read (all of them element by element: 128 x 2496 x 50 6.9 us, now
-    // 6.0; 1021 x 1019 x 256 with B k-major 16.4, now 13.2; 128 x 2496 x 16 6.1, now 5.8)
+    // the last tile of a contraction, where it is no multiple of BK or has partly valid chunks: whole chunks as such, a partly valid one
+    // element by element, nothing at or past the end is read (all of them element by element: 128 x 2496 x 50 6.9 us, now 6.0; 128 x
+    // 2496 x 16 6.1, now 5.8).  In the tiles before, what follows a partly valid chunk of a k-row is that row's padding (every tile this
+    // way: 768 x 1307 x 717 with both operands k-major 33 us, now 22; 167 x 429 x 1920 23, now 15.4)
     __device__ void load_edge(float4 (&r)[PER], const float *base, int64_t ld, int kt, int kvalid, int tid) const {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
@@ -131,11 +132,11 @@ __device__ __forceinline__ void F32Tile<BM, BN, BK, WGM, WGN, KG, AKM, BKM>::run
     oa.init(baseA, lda, (int)(M - m0 < BM ? M - m0 : BM), tid);
     ob.init(baseB, ldb, (int)(N - n0 < BN ? N - n0 : BN), tid);
     const int nk = (int)((K + BK - 1) / BK), nkf = (int)(K / BK), rem = (int)(K - (int64_t)nkf * BK);
-    const bool edge_rows = oa.slow_rows || ob.slow_rows;
+    const int fast = nk - nkf || !(oa.part_rows || ob.part_rows) ? nkf : nkf - 1;      // tiles without edges
 
     float4 ra[2][OpA::PER], rb[2][OpB::PER];
     auto load = [&](int set, int kt) {
-        if (kt < nkf && !edge_rows) {
+        if (kt < fast) {
             oa.load(ra[set], kt);
             ob.load(rb[set], kt);
         } else {
@@ -267,10 +268,10 @@ template <bool AKM, bool BKM> __device__ __forceinline__ void F32Tiny<AKM, BKM>:
     oa.init(baseA, lda, (int)(M - m0 < T ? M - m0 : T), tid);
     ob.init(baseB, ldb, (int)(N - n0 < T ? N - n0 : T), tid);
     const int nk = (int)((K + BK - 1) / BK), nkf = (int)(K / BK), rem = (int)(K - (int64_t)nkf * BK);
-    const bool edge_rows = oa.slow_rows || ob.slow_rows;
+    const int fast = nk - nkf || !(oa.part_rows || ob.part_rows) ? nkf : nkf - 1;      // tiles without edges
     float4 ra[2][OpA::PER], rb[2][OpB::PER];
     auto load = [&](int set, int kt) {
-        if (kt < nkf && !edge_rows) {
+        if (kt < fast) {
             oa.load(ra[set], kt);
             ob.load(rb[set], kt);
         } else {
@@ -351,6 +352,7 @@ template <typename T0, typename T1> __global__ void __launch_bounds__(T0::NT) ge
 }
 
 template <bool AKM, bool BKM> using Tile64 = F32Tile<64, 64, 32, 2, 2, 1, AKM, BKM>;
+template <bool AKM, bool BKM> using Tile64x32 = F32Tile<64, 32, 32, 2, 1, 2, AKM, BKM>;
 template <bool AKM, bool BKM> using Tile32 = F32Tile<32, 32, 64, 1, 1, 4, AKM, BKM>;
 
 template <template <bool, bool> class Tile> void launch(hipStream_t s, bool a_km, bool b_km, const F32Args &a) {
@@ -362,43 +364,55 @@ template <template <bool, bool> class Tile> void launch(hipStream_t s, bool a_km
 #undef TIO_F32
 }
 
-// edge of the output tile
-int tile_of(int64_t M, int64_t N) {
-    // 32x32 tiles while 64x64 ones would leave compute units without work.  Microseconds, 32 / 64 / (not kept) 128 square, both
-    // operands contraction-contiguous:
-    //   128 x 512 x 128      5.5 /   7.2 /  20        1024 x  768 x 3072 (192 tiles of 64)   57 /  74 / 253
-    //   128 x 128 x 1024    12.4 /  27   /  91         896 x 1024 x 2048 (224)                55 /  52 / 173
-    //   512 x 512 x 512      8.7 /  15.7 /  50        1024 x 1280 x 2048 (320)                75 /  79 / 172
-    //  2048 x 2048 x 2048  203   / 160   / 174        1024 x 1792 x 2048 (448)                96 /  80 / 172
-    // The first kernel here (64x64 tiles on the vector ALU) took 62 us for 128 x 128 x 1024 and about 300 us for 1024 x 3072 x 768,
-    // now 53.  128x128 tiles leave one wavefront per SIMD where the others leave three, and lose everywhere.
-    // 16x16 tiles up to 160 tiles of 32x32: 128 x 128 x 1024 (16 tiles) 12.5 -> 6.0 us, 256 x 512 x 512 (128) 8.5 -> 5.6,
-    // 300 x 500 x 1000 (160) 13.2 -> 11.5, but 64 x 3000 x 512 (188) 8.7 -> 10.2 with a k-major operand
-    const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64), tiles32 = ((M + 31) / 32) * ((N + 31) / 32);
-    return tiles32 <= 160 ? 16 : tiles64 >= 224 ? 64 : 32;
+// The output tile.  All workgroups of these products are on the chip at once, so that its time is that of the compute unit with the most
+// tiles: `rate` us per 64 x 64 x 768 of work, which falls with the number of tiles there are to cover each other's latencies.  us, 64x64 /
+// 64x32 / 32x32, tiles on that unit in brackets:
+//   1024 x 3072 x  768  47 ( 3) / 57 ( 6) /  63 (12)      1024 x  768 x 3072  75 ( 1) / 71 ( 2) /  53 ( 3)
+//   3072 x  768 x 1024  58 ( 3) / 56 ( 5) /  62 ( 9)      2048 x  768 x 3072 114 ( 2) / 96 ( 3) / 113 ( 6)
+//   1500 x  900 x 2000  79 ( 2) / 65 ( 3) /  73 ( 6)       512 x 1024 x 1024  28 ( 1) / 22 ( 1) /  17 ( 2)
+//   1024 x 1024 x 1024  28 ( 1) / 27 ( 2) /  28 ( 4)       300 x 2000 x 2500  63 ( 1) / 62 ( 2) /  45 ( 3)
+// 128x128 tiles leave one wavefront per SIMD where the others leave three, and lose everywhere (2048^3: 174, 160 with 64x64).
+// 16x16 tiles up to 160 tiles of 32x32: 128 x 128 x 1024 (16 tiles) 12.5 -> 6.0 us, 256 x 512 x 512 (128) 8.5 -> 5.6,
+// 300 x 500 x 1000 (160) 13.2 -> 11.5, but 64 x 3000 x 512 (188) 8.7 -> 10.2 with a k-major operand.
+struct TileShape {
+    int rows, cols;
+};
+constexpr TileShape T16{16, 16}, T32{32, 32}, T64x32{64, 32}, T64{64, 64};
+TileShape tile_of(int64_t M, int64_t N) {
+    auto tiles = [&](TileShape t) { return ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols); };
+    if (tiles(T32) <= 160) return T16;
+    auto cost = [&](TileShape t, double one, double two, double more) {
+        const int64_t n = (tiles(t) + 255) / 256;
+        return (double)n * (t.rows * t.cols / 4096.0) * (n == 1 ? one : n == 2 ? two : more);
+    };
+    const double c64 = cost(T64, 18, 14.3, 14.3), c64x32 = cost(T64x32, 27.5, 17, 15.5), c32 = cost(T32, 33, 20.7, 18);
+    return c64 <= c64x32 && c64 <= c32 ? T64 : c64x32 <= c32 ? T64x32 : T32;
 }
-F32Args args_of(const F32Product &p, int tile) {
+bool small(TileShape t) { return t.rows <= 32; }
+F32Args args_of(const F32Product &p, TileShape t) {
     return F32Args{(const float *)p.A, (const float *)p.B, (const float *)p.bias, (const float *)p.resid, (float *)p.C, (float *)p.rowsum,
-                   p.lda, p.ldb, p.ldr, p.ldc, p.M, p.N, p.K, (int)((p.M + tile - 1) / tile), (int)((p.N + tile - 1) / tile), (int)p.accumulate};
+                   p.lda, p.ldb, p.ldr, p.ldc, p.M, p.N, p.K, (int)((p.M + t.rows - 1) / t.rows), (int)((p.N + t.cols - 1) / t.cols),
+                   (int)p.accumulate};
 }
 
 }  // namespace
 
 void gemm_f32(hipStream_t s, bool a_km, bool b_km, const F32Product &p) {
-    const int tile = tile_of(p.M, p.N);
+    const TileShape tile = tile_of(p.M, p.N);
     const F32Args a = args_of(p, tile);
-    if (tile == 16) launch<F32Tiny>(s, a_km, b_km, a);
-    else if (tile == 32) launch<Tile32>(s, a_km, b_km, a);
+    if (tile.rows == 16) launch<F32Tiny>(s, a_km, b_km, a);
+    else if (tile.rows == 32) launch<Tile32>(s, a_km, b_km, a);
+    else if (tile.cols == 32) launch<Tile64x32>(s, a_km, b_km, a);
     else launch<Tile64>(s, a_km, b_km, a);
 }
 
-// Both gradients of a linear layer in one launch, where the tiles of one of them are small (16 or 32 square): such products last
+// Both gradients of a linear layer in one launch, where the tiles of both are small (16 or 32 square): such products last
 // about as long as a launch, and neither fills the chip (4.2 + 4.5 us in the tiny GPT step, nine times: that step, with merged updates
 // and delta in the launch of attention backward as well, 332 -> 256 us).
-bool gemm_f32_pairs(int64_t M0, int64_t N0, int64_t M1, int64_t N1) { return tile_of(M0, N0) < 64 && tile_of(M1, N1) < 64; }
+bool gemm_f32_pairs(int64_t M0, int64_t N0, int64_t M1, int64_t N1) { return small(tile_of(M0, N0)) && small(tile_of(M1, N1)); }
 
 void gemm_f32_pair(hipStream_t s, const F32Product &dx, const F32Product &dw) {
-    const int t0 = tile_of(dx.M, dx.N), t1 = tile_of(dw.M, dw.N);
+    const TileShape t0 = tile_of(dx.M, dx.N), t1 = tile_of(dw.M, dw.N);
     const F32Args a0 = args_of(dx, t0), a1 = args_of(dw, t1);
     using X16 = F32Tiny<false, true>;
     using X32 = Tile32<false, true>;
@@ -409,9 +423,9 @@ void gemm_f32_pair(hipStream_t s, const F32Product &dx, const F32Product &dw) {
         const unsigned n0 = X::blocks(a0.tiles_m, a0.tiles_n), n1 = W::blocks(a1.tiles_m, a1.tiles_n);              \
         gemm_f32_pair_k<X, W><<<n0 + n1, X::NT, 0, s>>>(a0, n0, a1);                                                \
     }
-    if (t0 == 16 && t1 == 16) TIO_F32_PAIR(X16, W16)
-    else if (t0 == 16) TIO_F32_PAIR(X16, W32)
-    else if (t1 == 16) TIO_F32_PAIR(X32, W16)
+    if (t0.rows == 16 && t1.rows == 16) TIO_F32_PAIR(X16, W16)
+    else if (t0.rows == 16) TIO_F32_PAIR(X16, W32)
+    else if (t1.rows == 16) TIO_F32_PAIR(X32, W16)
     else TIO_F32_PAIR(X32, W32)
 #undef TIO_F32_PAIR
 }

@@ -1,4 +1,4 @@
-"""GPU: fp32 products at the sizes where the dispatch changes its tile (16, 32 or 64 square) and at the edges of tiles and of
+"""GPU: fp32 products at the sizes where the dispatch changes its tile (16 or 32 square, 64x32, 64 square) and at the edges of tiles and of
 contraction tiles, against numpy in 64 bits."""
 import numpy as np
 import pytest
@@ -9,6 +9,8 @@ CASES = [  # M, N, K: 16x16, 32x32, then 64x64 tiles; whole, one short, one over
     (32, 32, 128), (1, 1, 1), (31, 33, 127), (65, 97, 300), (17, 15, 129),
     (512, 512, 64), (509, 423, 63), (64, 3000, 200),
     (896, 1024, 32), (1024, 1024, 64), (1021, 1019, 97),
+    # 64x32 tiles; 64x64 ones; k-major rows that end inside a chunk, contractions of whole tiles and of one more
+    (1024, 1024, 65), (1021, 1022, 31), (1023, 1021, 96), (1500, 901, 33), (1022, 3070, 64), (1021, 3071, 129), (717, 1307, 128),
 ]
 
 
