@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd_k(const T *__restrict__ qkv,
 
 // ---------------------------------------------------------------- backward
 // delta[b,h,t] = sum_e dO[s,h,e] * O[s,h,e].  dh / (elements per 16 bytes) consecutive lanes share one (s, h):
-// the wavefront reads consecutive 16-byte chunks, and the partial sums (of four elements) meet in a fixed order, that of row_dot.
+// the wavefront reads consecutive 16-byte chunks, and the partial sums meet in a fixed xor-shuffle order, that of row_dot.
 template <typename T>
 __global__ void __launch_bounds__(TPB) attn_bwd_pre_k(const T *__restrict__ dO, const T *__restrict__ O,
                                                       float *__restrict__ delta, int64_t Bn, int64_t Tn, int64_t H, int64_t dh) {
@@ -227,14 +227,8 @@ __global__ void __launch_bounds__(TPB) attn_bwd_pre_k(const T *__restrict__ dO, 
     if (ok) {
         Vec16<T> x, y; x.load(dO + idx * V); y.load(O + idx * V);
         float fx[V], fy[V]; x.get(fx); y.get(fy);
-        float four[V / 4];
 #pragma unroll
-        for (int j = 0; j < V / 4; ++j) {
-            four[j] = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) four[j] = fmaf(fx[4 * j + i], fy[4 * j + i], four[j]);
-        }
-        sum = V == 4 ? four[0] : four[0] + four[V / 4 - 1];
+        for (int i = 0; i < V; ++i) sum = fmaf(fx[i], fy[i], sum);
     }
     for (int o = 1; o < G; o <<= 1) sum += __shfl_xor(sum, o, 64);
     if (ok && idx % G == 0) {
@@ -256,15 +250,19 @@ template <typename T> struct BwdArgs {
 };
 // sum over the head dimension of g * x, for the row a lane pair holds; the same in both lanes, and the bits of attn_bwd_pre_k, so that a
 // step does not depend on whether delta has a launch of its own
-template <int DH> __device__ __forceinline__ float row_dot(const RowFrag<DH> &g, const RowFrag<DH> &x) {
+template <typename T, int DH> __device__ __forceinline__ float row_dot(const RowFrag<DH> &g, const RowFrag<DH> &x, int lane) {
     static_assert(DH == 32, "the order of the sum");
     float p[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        p[c] = 0.f;
+        auto four = [&](float sum) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) p[c] = fmaf(g.f[4 * c + i], x.f[4 * c + i], p[c]);
-        p[c] = sum_halves(p[c]);
+            for (int i = 0; i < 4; ++i) sum = fmaf(g.f[4 * c + i], x.f[4 * c + i], sum);
+            return sum;
+        };
+        const float first = four(0.f);
+        // 16 bytes of the row, one chain of that kernel, are four elements, or eight: this half's behind the other half's
+        p[c] = sizeof(T) == 4 ? sum_halves(first) : __shfl(four(__shfl(first, lane & 31, 64)), lane | 32, 64);
     }
     return (p[0] + p[1]) + (p[2] + p[3]);
 }
@@ -288,7 +286,7 @@ __device__ __forceinline__ void dq_rows(const BwdArgs<T> &a, unsigned block, flo
     if constexpr (OWN_DELTA) {
         RowFrag<DH> of;
         of.load(Rows<T>(a.O + b * Tn * d + h * DH, d, q0, a.Tn, DH), lane);
-        di = row_dot(gf, of);
+        di = row_dot<T>(gf, of, lane);
         if (wave == 0 && lhi == 0 && q < a.Tn) a.delta[bh * Tn + q] = di;
     } else {
         di = a.delta[bh * Tn + qc];
@@ -352,7 +350,7 @@ __device__ __forceinline__ void dkv_rows(const BwdArgs<T> &a, unsigned block, fl
         if constexpr (OWN_DELTA) {
             RowFrag<DH> of;
             of.load(Rows<T>(a.O + b * Tn * d + h * DH, d, i0, a.Tn, DH), lane);
-            delta_row = row_dot(gf, of);
+            delta_row = row_dot<T>(gf, of, lane);
         } else {
             delta_row = dl[row];
         }
@@ -396,7 +394,7 @@ unsigned grid_for(int64_t heads, int64_t Tn) { return (unsigned)((Tn + ROWS - 1)
 // 200, 8 heads 18.5 / 18.2, 8 x 512, 8 heads 121 / 161.  The forward kernel gains less (4 x 333: 8.9 / 8.3; 1 x 512: 10.5 / 9.8).
 bool eight_wavefronts(int64_t blocks, int64_t Tn, int64_t dh) { return dh == 32 && Tn > 4 * ROWS && blocks <= 512; }
 
-template <int DH> constexpr bool own_delta() { return DH == 32; }    // what attn_bwd_has_delta says; at 64 it does not fit the registers, and delta has a launch of its own
+template <int DH> constexpr bool own_delta() { return DH == 32; }    // at 64 it does not fit the registers, and delta has a launch of its own
 template <typename T, int DH> void launch_bwd(hipStream_t s, const BwdArgs<T> &a) {
     const unsigned blocks = grid_for(a.heads, a.Tn);
     if constexpr (own_delta<DH>()) {
@@ -447,12 +445,12 @@ void attn_bwd_pre(hipStream_t s, int dtype, const void *dO, const void *O, float
         attn_bwd_pre_k<float><<<(unsigned)((n + TPB - 1) / TPB), TPB, 0, s>>>((const float *)dO, (const float *)O, delta, B, Tn, H, dh);
 }
 
-bool attn_bwd_has_delta(int, int64_t, int64_t, int64_t dh) { return dh == 32; }
+bool attn_bwd_has_delta(int dtype, int64_t Tn, int64_t H, int64_t dh) { return dh == 32 || attn_mfma_supported(dtype, Tn, H, dh); }
 
 void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const void *O, const float *lse, float *delta, void *dqkv,
               int64_t B, int64_t Tn, int64_t H, int64_t dh) {
     if (O && !attn_bwd_has_delta(dtype, Tn, H, dh)) attn_bwd_pre(s, dtype, dO, O, delta, B, Tn, H, dh);
-    if (attn_mfma_supported(dtype, Tn, H, dh)) { attn_bwd_mfma(s, dO, qkv, lse, delta, dqkv, B, Tn, H, dh); return; }
+    if (attn_mfma_supported(dtype, Tn, H, dh)) { attn_bwd_mfma(s, dO, qkv, O, lse, delta, dqkv, B, Tn, H, dh); return; }
     const float scale = 1.0f / sqrtf((float)dh);
     TIO_ATTN_DISPATCH(dtype, dh, {
         const BwdArgs<T> a{(const T *)dO, (const T *)qkv, (const T *)O, lse, delta, (T *)dqkv, B * H, H, (int)Tn, scale};

@@ -368,12 +368,39 @@ __global__ void __launch_bounds__(NT, 2) attn_fwd_mfma_k(const uint16_t *__restr
 }
 
 // ------------------------------------------------------------------------------------------ dQ
+// Sum over the head dimension of two rows of which a lane pair has the fragments, the same in both lanes: in the order of
+// attn_bwd_pre_k, whose bits these are (chains of eight elements, then pairs).
+template <int KS> __device__ __forceinline__ float row_dot(const bf16x8 (&g)[KS], const bf16x8 (&o)[KS]) {
+    float p[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        Frag a, b;
+        a.v = g[ks];
+        b.v = o[ks];
+        const uint32_t x[4] = {a.u.x, a.u.y, a.u.z, a.u.w}, y[4] = {b.u.x, b.u.y, b.u.z, b.u.w};
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sum = fmaf(__uint_as_float(x[i] << 16), __uint_as_float(y[i] << 16), sum);
+            sum = fmaf(__uint_as_float(x[i] & 0xffff0000u), __uint_as_float(y[i] & 0xffff0000u), sum);
+        }
+        p[ks] = sum_halves(sum);
+    }
+#pragma unroll
+    for (int o2 = 1; o2 < KS; o2 *= 2)
+#pragma unroll
+        for (int ks = 0; ks < KS; ks += 2 * o2) p[ks] += p[ks + o2];
+    return p[0];
+}
+
 // Bound: vector work (exponentials, masks) and latency between the products; the tiles in front of the diagonal run through a loop of
 // their own, without mask and branch.  Three wavefronts per SIMD at head size 64, which a ring of three fragments leaves registers for.
 // 8 x 1024 tokens, 12 heads of 64: 45.9 -> 39.4 us (two wavefronts per SIMD 43.1); 4 x 2048, 32 heads of 128: 272 -> 252.
+// O: nullptr, or the forward pass's output: delta is then computed here, from the rows of dO that are in registers anyway, and
+// written for the dK/dV kernel, in place of a launch that reads both tensors (forward and backward 100.8 -> 97.2 us and 708 -> 687).
 template <int DH>
 __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
-                                                         const float *__restrict__ lse, const float *__restrict__ delta,
+                                                         const uint16_t *__restrict__ O, const float *__restrict__ lse, float *__restrict__ delta,
                                                          uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
     constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = DH == 64 ? 3 : 4;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];    // [2 buffers][K tile | V tile], filled as in the forward kernel
@@ -405,7 +432,17 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
         gf[ks] = buf_frag(rsG, (uint32_t)q * (uint32_t)(d * 2) + (ks * 16 + lhi * 8) * 2);
     }
     const float lse2 = live ? lse[bh * Tn + q] * LOG2E : 0.f;
-    const float dl = live ? delta[bh * Tn + q] : 0.f;
+    float dl;
+    if (O) {
+        const __amdgpu_buffer_rsrc_t rsO = head_rsrc(O + b * Tn * d + h * DH, Tn, d, DH);
+        bf16x8 of[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) of[ks] = buf_frag(rsO, (uint32_t)q * (uint32_t)(d * 2) + (ks * 16 + lhi * 8) * 2);
+        dl = row_dot<KS>(gf, of);
+        if (live && lhi == 0) delta[bh * Tn + q] = dl;
+    } else {
+        dl = live ? delta[bh * Tn + q] : 0.f;
+    }
     floatx16 dq[DT];
 #pragma unroll
     for (int i = 0; i < DT; ++i) dq[i] = zero16();
@@ -718,7 +755,7 @@ void attn_fwd_mfma(hipStream_t s, const void *qkv, void *o, float *lse, int64_t 
     else attn_fwd_mfma_k<128><<<l.grid, NT, kv_smem<128>(), s>>>((const uint16_t *)qkv, (uint16_t *)o, lse, B, Tn, H, scale, l.order);
 }
 
-void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const float *lse, const float *delta, void *dqkv,
+void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O, const float *lse, float *delta, void *dqkv,
                    int64_t B, int64_t Tn, int64_t H, int64_t dh) {
     const float scale = 1.0f / sqrtf((float)dh);
     static bool attr_set = false;
@@ -730,8 +767,8 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const float *
 #define TIO_ATTN_BWD(DH, DQ_PER_CU, DKV_PER_CU)                                                                                                \
     {                                                                                                                                          \
         const Launch q(B * H, Tn, DH, 128, DQ_PER_CU), kv(B * H, Tn, DH, dkv_waves<DH>() * 32, DKV_PER_CU);                                    \
-        attn_bwd_dq_mfma_k<DH><<<q.grid, NT, kv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, \
-                                                                 Tn, H, scale, q.order);                                                       \
+        attn_bwd_dq_mfma_k<DH><<<q.grid, NT, kv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, (const uint16_t *)O, lse, delta, \
+                                                                 (uint16_t *)dqkv, B, Tn, H, scale, q.order);                                  \
         attn_bwd_dkv_mfma_k<DH><<<kv.grid, dkv_waves<DH>() * 64, dkv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, \
                                                                                       (uint16_t *)dqkv, B, Tn, H, scale, kv.order);            \
     }

@@ -431,7 +431,7 @@ def test_optimizer_state_follows_the_oracle_from_the_gpu_gradients(cfg):
 
 
 @pytest.mark.parametrize("cfg", [
-    CONFIGS["tiny_gpt_fp32"], CONFIGS["tiny_llama_fp32"], SMALL_BF16,
+    CONFIGS["tiny_gpt_fp32"], CONFIGS["tiny_llama_fp32"], SMALL_BF16, SMALL_LLAMA_BF16,
     # products of 32x32 beside 16x16 tiles, more than eight key tiles, odd sizes
     dict(arch="gpt", L=1, d=160, H=5, f=520, V=1001, T=292, B=2, precision="fp32", lr=1e-3),
     dict(arch="llama", L=2, d=96, H=3, f=264, V=500, T=72, B=3, precision="bf16", lr=3e-4),
