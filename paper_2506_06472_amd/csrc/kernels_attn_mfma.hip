@@ -18,7 +18,7 @@
 // ring of registers a few fragments ahead of the products that use them.
 // Statistics are fp32, exp2 with the 1/sqrt(dh) scale folded into the exponent; the causal mask is
 // applied only on tiles that cross the diagonal; the backward pass recomputes P from the saved
-// log-sum-exp; dQ and dK/dV are separate launches, so every sum has a fixed order and no atomics.
+// log-sum-exp; dQ and dK/dV come from workgroups of their own, so every sum has a fixed order and no atomics.
 #include <type_traits>
 
 #include "../../include/teraio.h"
@@ -107,8 +107,8 @@ struct Order {
     bool turn;
 };
 // Returns false for the padding workgroups when the head count is not a multiple of 8.
-__device__ __forceinline__ bool head_and_block(int64_t n_heads, int n_blocks, Order order, int64_t &bh, int &blk) {
-    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+__device__ __forceinline__ bool head_and_block(unsigned block, int64_t n_heads, int n_blocks, Order order, int64_t &bh, int &blk) {
+    const int xcd = (int)(block & 7), slot = (int)(block >> 3);
     const int of_xcd = (int)((n_heads + 7) / 8), first = slot / (order.heads * n_blocks) * order.heads;
     const int here = of_xcd - first < order.heads ? of_xcd - first : order.heads;
     int w = slot - first * n_blocks;
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(NT, 2) attn_fwd_mfma_k(const uint16_t *__restr
     const int nblk = (int)((Tn + 127) / 128);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, nblk, order, bh, blk)) return;
+    if (!head_and_block(blockIdx.x, Bn * H, nblk, order, bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
     const int q0 = (nblk - 1 - blk) * 128;                               // longest rows first
     const int q0w = q0 + wave * 32, q = q0w + l32;
@@ -398,21 +398,21 @@ template <int KS> __device__ __forceinline__ float row_dot(const bf16x8 (&g)[KS]
 // 8 x 1024 tokens, 12 heads of 64: 45.9 -> 39.4 us (two wavefronts per SIMD 43.1); 4 x 2048, 32 heads of 128: 272 -> 252.
 // O: nullptr, or the forward pass's output: delta is then computed here, from the rows of dO that are in registers anyway, and
 // written for the dK/dV kernel, in place of a launch that reads both tensors (forward and backward 100.8 -> 97.2 us and 708 -> 687).
-template <int DH>
-__global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
-                                                         const uint16_t *__restrict__ O, const float *__restrict__ lse, float *__restrict__ delta,
-                                                         uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
-    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = DH == 64 ? 3 : 4;
+template <int DH, int NW>
+__device__ __forceinline__ void dq_rows(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const uint16_t *__restrict__ O,
+                                        const float *__restrict__ lse, float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn,
+                                        int64_t Tn, int64_t H, float scale, Order order, unsigned block) {
+    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = DH == 64 ? 3 : 4, ROWS = NW * 32;
     extern __shared__ __attribute__((aligned(1024))) uint16_t smem[];    // [2 buffers][K tile | V tile], filled as in the forward kernel
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int64_t d = H * DH, ld = 3 * d;
     const uint32_t ldb = (uint32_t)(ld * 2);
-    const int nblk = (int)((Tn + 127) / 128);
+    const int nblk = (int)((Tn + ROWS - 1) / ROWS);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, nblk, order, bh, blk)) return;
+    if (!head_and_block(block, Bn * H, nblk, order, bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
-    const int q0 = (nblk - 1 - blk) * 128;
+    const int q0 = (nblk - 1 - blk) * ROWS;
     const int q0w = q0 + wave * 32, q = q0w + l32;
     const uint16_t *qb = qkv + b * Tn * ld + h * DH;
     const __amdgpu_buffer_rsrc_t rsQ = head_rsrc(qb, Tn, ld, DH);
@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
     const float c = scale * LOG2E;
     const bool live = q < Tn;
     const TileLanes<DH> L(lane);
-    const DmaTile<DH> dma(ldb, wave, lane);
+    const DmaTile<DH, NW> dma(ldb, wave, lane);
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
 
     bf16x8 qf[KS], gf[KS];
@@ -446,7 +446,7 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
     floatx16 dq[DT];
 #pragma unroll
     for (int i = 0; i < DT; ++i) dq[i] = zero16();
-    const int kv_end = q0 + 128 < (int)Tn ? q0 + 128 : (int)Tn;
+    const int kv_end = q0 + ROWS < (int)Tn ? q0 + ROWS : (int)Tn;
     const int ntiles = (kv_end + 63) / 64;
 
     dma.load(rsK, 0, ldb, lds0, wave);
@@ -524,6 +524,13 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
     }
 }
 
+template <int DH>
+__global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv,
+                                                         const uint16_t *__restrict__ O, const float *__restrict__ lse, float *__restrict__ delta,
+                                                         uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
+    dq_rows<DH, NT / 64>(dO, qkv, O, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
+}
+
 // ------------------------------------------------------------------------------------------ dK, dV
 // Both gradients in one launch: S and dP are computed once for the two of them, and the Q and dO tiles are loaded once.  A
 // wavefront's accumulators and K fragments take 160 of the 256 registers that two wavefronts per SIMD allow at head size 128,
@@ -541,11 +548,11 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
 // two wavefronts fetches one of the statistics, and the lane index is computed where it is used.  Transposed fragments four ahead in
 // registers: slower by 9 %, for want of the registers.
 template <int DH> constexpr int dkv_waves() { return DH == 128 ? 8 : 4; }
-template <int DH>
-__global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
-    attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
-                        const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
-    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4, NW = dkv_waves<DH>(), KEYS = NW * 32;
+template <int DH, int NW>
+__device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
+                                         const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H,
+                                         float scale, Order order, unsigned block) {
+    constexpr int KS = DH / 16, DT = DH / 32, TE = 64 * DH, RING = 4, KEYS = NW * 32;
     constexpr bool VLDS = DH == 128, ONE_LOOP = DH == 64;
     constexpr int BUF = 2 * TE;                                          // Q tile | dO tile, filled as in the forward kernel
     // [2 buffers][Q | dO], [KEYS][DH] V rows if VLDS, then [2][64 lse | 64 delta] floats
@@ -555,7 +562,7 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
     const uint32_t ldb = (uint32_t)(ld * 2), ldg = (uint32_t)(d * 2);
     int64_t bh;
     int blk;
-    if (!head_and_block(Bn * H, (int)((Tn + KEYS - 1) / KEYS), order, bh, blk)) return;
+    if (!head_and_block(block, Bn * H, (int)((Tn + KEYS - 1) / KEYS), order, bh, blk)) return;
     const int64_t b = bh / H, h = bh % H;
     const int kv0 = blk * KEYS;                                           // earliest keys see the most queries: first
     const int kv0w = kv0 + wave * 32, kv = kv0w + l32;
@@ -710,9 +717,29 @@ __global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
     }
 }
 
+template <int DH>
+__global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
+    attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
+                        const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
+    dkv_rows<DH, dkv_waves<DH>()>(dO, qkv, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
+}
+
+// Both kernels' blocks in one launch, those of key rows first: for sequences whose blocks leave the chip room, where each of the two
+// kernels lasts as long as its longest chain of tiles.  The same rows to a block on either side; delta comes from a launch of its own, and
+// every output has the bits of the two launches.  At head size 128 with four wavefronts a workgroup has a compute unit to itself (its
+// V rows in LDS), and its wavefronts all registers of their SIMD.
+template <int DH, int NW>
+__global__ void __launch_bounds__(NW * 64, DH == 64 ? 3 : NW == 4 ? 1 : 2)
+    attn_bwd_both_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
+                         float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order,
+                         unsigned blocks) {
+    if (blockIdx.x < blocks) dkv_rows<DH, NW>(dO, qkv, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
+    else dq_rows<DH, NW>(dO, qkv, nullptr, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x - blocks);
+}
+
 template <int DH> constexpr size_t kv_smem() { return (size_t)2 * 2 * 64 * DH * 2; }       // two buffers of two tiles
-template <int DH> constexpr size_t dkv_smem() {         // tiles, V rows, then statistics
-    return (size_t)2 * 2 * 64 * DH * 2 + (DH == 128 ? (size_t)dkv_waves<DH>() * 32 * DH * 2 : 0) + 2 * 128 * 4;
+template <int DH, int NW> constexpr size_t dkv_smem() {         // tiles, V rows, then statistics
+    return (size_t)2 * 2 * 64 * DH * 2 + (DH == 128 ? (size_t)NW * 32 * DH * 2 : 0) + 2 * 128 * 4;
 }
 
 // Unsigned 32-bit buffer offsets: one head's rows, and PAST more, span less than 2 GiB.  A block's rows past the sequence (up to
@@ -761,19 +788,44 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void *)attn_bwd_dq_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kv_smem<128>());
-        (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, dkv_waves<128>()>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 4>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 8>());
         attr_set = true;
+    }
+    // One launch for both gradients while its workgroups, which a unit holds three of at head size 64 and one of at 128, are at most a
+    // little more than the chip holds at once.  Forward and backward, us, two launches / one (workgroups):
+    //   heads of 64:  1 x 1024, 12 heads  65 /  50 (256)     8 x 512, 12 47 / 41 (768)       8 x 300, 20 37.4 / 35.4 (960)
+    //                 1 x 4096,  8       213 / 169 (512)     8 x 192,  7 22.7 / 19.6 (224)   8 x 1024, 12 90.8 / 91.5 (1536)
+    //   of 128, four wavefronts, eight in brackets:  1 x 2048, 8 178 / 126 [137] (256 [128])   4 x 512, 16 68 / 58 [56] (512 [256])
+    //                 4 x 333, 6 52 / 37 [42] (144 [96])     3 x 700, 25 90 / - [87] (960 [480])   8 x 1024, 16 217 / - [225] (- [1024])
+#define TIO_ATTN_BOTH(DH, NW, WORKGROUPS)                                                                                                      \
+    {                                                                                                                                          \
+        const Launch l(B * H, Tn, DH, NW * 32, DH == 64 ? 3 : 1);                                                                              \
+        if (2 * (int64_t)l.grid.x <= WORKGROUPS) {                                                                                             \
+            if (O) attn_bwd_pre(s, TIO_PREC_BF16, dO, O, delta, B, Tn, H, DH);                                                                 \
+            attn_bwd_both_mfma_k<DH, NW><<<2 * l.grid.x, NW * 64, dkv_smem<DH, NW>(), s>>>(                                                    \
+                (const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale, l.order, l.grid.x);                \
+            return;                                                                                                                            \
+        }                                                                                                                                      \
     }
 #define TIO_ATTN_BWD(DH, DQ_PER_CU, DKV_PER_CU)                                                                                                \
     {                                                                                                                                          \
         const Launch q(B * H, Tn, DH, 128, DQ_PER_CU), kv(B * H, Tn, DH, dkv_waves<DH>() * 32, DKV_PER_CU);                                    \
         attn_bwd_dq_mfma_k<DH><<<q.grid, NT, kv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, (const uint16_t *)O, lse, delta, \
                                                                  (uint16_t *)dqkv, B, Tn, H, scale, q.order);                                  \
-        attn_bwd_dkv_mfma_k<DH><<<kv.grid, dkv_waves<DH>() * 64, dkv_smem<DH>(), s>>>((const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, \
-                                                                                      (uint16_t *)dqkv, B, Tn, H, scale, kv.order);            \
+        attn_bwd_dkv_mfma_k<DH><<<kv.grid, dkv_waves<DH>() * 64, dkv_smem<DH, dkv_waves<DH>()>(), s>>>(                                        \
+            (const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale, kv.order);                             \
     }
-    if (dh == 64) TIO_ATTN_BWD(64, 3, 3)
-    else TIO_ATTN_BWD(128, 2, 1)
+    if (dh == 64) {
+        TIO_ATTN_BOTH(64, 4, 1024)
+        TIO_ATTN_BWD(64, 3, 3)
+    } else {
+        TIO_ATTN_BOTH(128, 4, 256)
+        TIO_ATTN_BOTH(128, 8, 512)
+        TIO_ATTN_BWD(128, 2, 1)
+    }
+#undef TIO_ATTN_BOTH
 #undef TIO_ATTN_BWD
 }
 

@@ -20,6 +20,12 @@ def test_bf16_attention_tiles_on_and_off_the_diagonal(B, T, H, dh):
     check("bf16", B, T, H, dh, 1)
 
 
+# one launch for both gradients (head size 128: four wavefronts, eight) and two, beside the sizes above
+@pytest.mark.parametrize("B,T,H,dh", [(2, 257, 9, 64), (4, 333, 6, 128), (1, 1025, 3, 128), (7, 300, 16, 128), (5, 129, 9, 128), (8, 261, 21, 64)])
+def test_bf16_attention_gradients_in_one_launch_or_two(B, T, H, dh):
+    check("bf16", B, T, H, dh, 1)
+
+
 # orders of the workgroups: all resident with every other row of units turned round (whole rows only; a row short of one), not all
 # resident, heads taken eight and one at a time.  No result depends on the order: each sequence alone gives the same bits
 @pytest.mark.parametrize("B,T,H,dh", [(3, 300, 11, 64), (8, 520, 13, 64), (7, 1000, 5, 64), (8, 1025, 17, 64), (8, 520, 13, 128), (8, 4096, 9, 128)])
