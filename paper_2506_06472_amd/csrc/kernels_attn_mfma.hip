@@ -798,6 +798,8 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
     //   heads of 64:  1 x 1024, 12 heads  65 /  50 (256)     8 x 512, 12 47 / 41 (768)       8 x 300, 20 37.4 / 35.4 (960)
     //                 1 x 4096,  8       213 / 169 (512)     8 x 192,  7 22.7 / 19.6 (224)   8 x 1024, 12 90.8 / 91.5 (1536)
     //   of 128, four wavefronts, eight in brackets:  1 x 2048, 8 178 / 126 [137] (256 [128])   4 x 512, 16 68 / 58 [56] (512 [256])
+    //                 (two rounds of four wavefronts are better with long chains: 1 x 4096, 4 heads 330 / 230 [255], 2 x 1024, 16 105 / 81
+    //                 [84], but 8 x 256, 16 49 / 46 [43])
     //                 4 x 333, 6 52 / 37 [42] (144 [96])     3 x 700, 25 90 / - [87] (960 [480])   8 x 1024, 16 217 / - [225] (- [1024])
 #define TIO_ATTN_BOTH(DH, NW, WORKGROUPS)                                                                                                      \
     {                                                                                                                                          \
@@ -821,7 +823,7 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
         TIO_ATTN_BOTH(64, 4, 1024)
         TIO_ATTN_BWD(64, 3, 3)
     } else {
-        TIO_ATTN_BOTH(128, 4, 256)
+        TIO_ATTN_BOTH(128, 4, (Tn < 1024 ? 256 : 512))
         TIO_ATTN_BOTH(128, 8, 512)
         TIO_ATTN_BWD(128, 2, 1)
     }
