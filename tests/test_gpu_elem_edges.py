@@ -43,6 +43,14 @@ def test_embedding_gradient_of_repeated_tokens(B, keep):
     _step_matches(dict(arch="gpt", L=1, d=64, H=2, f=128, V=300, T=64, B=B, precision="fp32", lr=1e-3), repeat)
 
 
+# partial rows of the norm's gradients around 128 (eight groups of rows, 32) and 256 (a whole round of loads), and losses around 2048
+# (256 threads, 1024) and past a whole round of loads
+@pytest.mark.parametrize("T", [1016, 1024, 2048, 2056, 2064, 8200])
+def test_sums_over_many_tokens(T):
+    print(f"tokens {T}", flush=True)
+    _step_matches(dict(arch="gpt", L=1, d=64, H=2, f=128, V=300, T=8, B=T // 8, precision="fp32", lr=1e-3))
+
+
 @pytest.mark.parametrize("precision", ["fp32", "bf16"])
 @pytest.mark.parametrize("V", [16383, 16384])        # embedding and head of one row less than 2^20 parameters, and of 2^20
 def test_optimizer_where_its_accesses_become_non_temporal(V, precision):
