@@ -906,6 +906,8 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
 // and left alone, though a cut with a workspace at hand gains something: 128 x 2000 x 4000 19.0 / 12.6 + 3, 1024 x 2048 x 8192 54 / 44 + 3,
 // 1000 x 1000 x 10000 45 / 37 + 3; 768 x 768 x 1900 10.8 / 14.3 + 3.
 int gemm_bf16_splits(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t bytes) {
+    if (K < 2048) return 1;              // 32 tiles of the smallest kind take less than the cut costs; the small products that are quick to
+                                         // run are not kept waiting for the comparison
     double whole = 0;
     if (!choose(a_km, b_km, M, N, K, lda, ldb, rowsum, 1, &whole)) return 1;
     int best = 1;
