@@ -3,6 +3,7 @@
 // 16-byte coalesced accesses, fp32 arithmetic, wavefront (64-lane) reductions, fixed summation
 // orders (no floating-point atomics) so that results do not depend on timing or addresses.
 #include <stdexcept>
+#include <type_traits>
 
 #include <cstdlib>
 #include "../../include/teraio.h"
@@ -527,34 +528,42 @@ __global__ void __launch_bounds__(NT) norm_bwd_block_k(const T *__restrict__ dy,
     }
 }
 
-// Column sums of the per-workgroup partial rows: 32 columns x G row groups per workgroup, each thread adds its rows in order and the
-// groups are combined in order.  Bound: memory latency, since a gradient has few columns and so few workgroups (24 for d = 768): with
-// many rows 32 groups keep four times the loads of 8 on their way (1024 rows, d = 768: 9.6 -> 6.8 us; RMS, d = 4096: 8.7 -> 5.7).
-template <typename T, bool RMS, int G>
-__global__ void __launch_bounds__(G * 32) norm_bwd_params_k(const float *__restrict__ part, T *__restrict__ dg,
+// Column sums of the per-workgroup partial rows: 32 columns x 8 row groups per workgroup, each thread adds its rows in order and the
+// eight groups are combined in order, whatever the number of rows.  Bound: memory latency, since a gradient has few columns and so few
+// workgroups (24 for d = 768): with many rows a thread has 32 loads of a sum on their way at a time.  us, eight loads / 32, the rows not in
+// the caches: 1024 rows, d = 768 13.2 / 11.1; RMS: 1024 rows, d = 4096 11.7 / 7.1, 2048, d = 2048 21.9 / 11.6.  (32 row groups take 9.8,
+// 7.3 and 10.1, in an order of the sum that depends on the number of rows.)
+template <typename T, bool RMS>
+__global__ void __launch_bounds__(TPB) norm_bwd_params_k(const float *__restrict__ part, T *__restrict__ dg,
                                                          T *__restrict__ db, int64_t nb, int64_t d, bool accumulate) {
-    constexpr int NP = RMS ? 1 : 2;
+    constexpr int NP = RMS ? 1 : 2, G = 8;
     __shared__ float red[2][G][33];
     const int c = threadIdx.x & 31, rg = threadIdx.x >> 5;
     const int64_t col = (int64_t)blockIdx.x * 32 + c;
     float sg = 0.f, sb = 0.f;
     if (col < d) {
-        // eight loads in flight per sum; the additions stay in row order
+        // the loads of U rows first, then the additions, in row order; the last round: up to eight rows, zeros behind them
         int64_t b = rg;
-        for (; b + 7 * G < nb; b += 8 * G) {
-            float tg[8], tb[8];
+        auto rows = [&](auto U, auto LAST) __attribute__((always_inline)) {
+            for (; LAST() ? b < nb : b + (U() - 1) * G < nb; b += U() * G) {
+                float tg[U()], tb[U()];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                tg[u] = part[(b + G * u) * NP * d + col];
-                tb[u] = RMS ? 0.f : part[(b + G * u) * NP * d + d + col];
+                for (int u = 0; u < U(); ++u) {
+                    const int64_t row = LAST() && b + G * u >= nb ? b : b + G * u;
+                    tg[u] = part[row * NP * d + col];
+                    tb[u] = RMS ? 0.f : part[row * NP * d + d + col];
+                }
+#pragma unroll
+                for (int u = 0; u < U(); ++u) {
+                    const bool valid = !LAST() || b + G * u < nb;
+                    sg += valid ? tg[u] : 0.f;
+                    sb += valid ? tb[u] : 0.f;
+                }
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) { sg += tg[u]; sb += tb[u]; }
-        }
-        for (; b < nb; b += G) {
-            sg += part[b * NP * d + col];
-            if (!RMS) sb += part[b * NP * d + d + col];
-        }
+        };
+        rows(std::integral_constant<int, 32>{}, std::false_type{});
+        rows(std::integral_constant<int, 8>{}, std::false_type{});
+        rows(std::integral_constant<int, 8>{}, std::true_type{});
     }
     red[0][rg][c] = sg;
     red[1][rg][c] = sb;
@@ -859,23 +868,26 @@ __global__ void __launch_bounds__(NT) ce_reg_k(T *__restrict__ logits, const int
     }
 }
 
-// One workgroup (the sum has one order), eight loads of a thread on their way at a time: one after the other they took 13.7 us for 8192
-// tokens, 5.0 now.
-template <int NT>
-__global__ void __launch_bounds__(NT) loss_reduce_k(const float *__restrict__ losses, float *__restrict__ loss, int64_t S,
-                                                    int64_t S_total, bool accumulate) {
-    __shared__ float red[NT / 64];
+// One workgroup of 256 threads (the sum has one order, whatever the number of tokens), 32 loads of a thread on their way at a time: 8192
+// tokens 13.9 us with one load after the other, 3.5 now.
+__global__ void __launch_bounds__(TPB) loss_reduce_k(const float *__restrict__ losses, float *__restrict__ loss, int64_t S,
+                                                     int64_t S_total, bool accumulate) {
+    __shared__ float red[TPB / 64];
     float s = 0.f;
     int64_t i = threadIdx.x;
-    for (; i + 7 * NT < S; i += 8 * NT) {
-        float t[8];
+    auto rounds = [&](auto U) __attribute__((always_inline)) {
+        for (; i + (U() - 1) * TPB < S; i += U() * TPB) {
+            float t[U()];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = losses[i + u * NT];
+            for (int u = 0; u < U(); ++u) t[u] = losses[i + u * TPB];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += t[u];
-    }
-    for (; i < S; i += NT) s += losses[i];
-    const float t = block_sum<NT / 64>(s, red);
+            for (int u = 0; u < U(); ++u) s += t[u];
+        }
+    };
+    rounds(std::integral_constant<int, 32>{});
+    rounds(std::integral_constant<int, 8>{});
+    rounds(std::integral_constant<int, 1>{});
+    const float t = block_sum<TPB / 64>(s, red);
     if (threadIdx.x == 0) loss[0] = (accumulate ? loss[0] : 0.f) + t / (float)S_total;
 }
 
@@ -1067,12 +1079,9 @@ void norm_bwd(hipStream_t s, int dtype, bool rms, const void *dy, const void *x,
 void norm_bwd_params(hipStream_t s, int dtype, bool rms, const float *part, void *dg, void *db, int64_t nb, int64_t d,
                      bool accumulate) {
     TIO_DISPATCH(dtype, {
-        // from 128 rows on the 32 groups have four rows and more each
         const unsigned blocks = blocks_for(d, 32);
-        if (rms && nb >= 128) norm_bwd_params_k<T, true, 32><<<blocks, 1024, 0, s>>>(part, (T *)dg, nullptr, nb, d, accumulate);
-        else if (rms) norm_bwd_params_k<T, true, 8><<<blocks, 256, 0, s>>>(part, (T *)dg, nullptr, nb, d, accumulate);
-        else if (nb >= 128) norm_bwd_params_k<T, false, 32><<<blocks, 1024, 0, s>>>(part, (T *)dg, (T *)db, nb, d, accumulate);
-        else norm_bwd_params_k<T, false, 8><<<blocks, 256, 0, s>>>(part, (T *)dg, (T *)db, nb, d, accumulate);
+        if (rms) norm_bwd_params_k<T, true><<<blocks, TPB, 0, s>>>(part, (T *)dg, nullptr, nb, d, accumulate);
+        else norm_bwd_params_k<T, false><<<blocks, TPB, 0, s>>>(part, (T *)dg, (T *)db, nb, d, accumulate);
     });
 }
 
@@ -1131,9 +1140,7 @@ void ce_fwd_bwd(hipStream_t s, int dtype, void *logits, const int32_t *labels, f
 }
 
 void loss_reduce(hipStream_t s, const float *losses, float *loss, int64_t S, int64_t S_total, bool accumulate) {
-    // 256 threads up to where each has eight rows
-    if (S > 2048) loss_reduce_k<1024><<<1, 1024, 0, s>>>(losses, loss, S, S_total, accumulate);
-    else loss_reduce_k<256><<<1, 256, 0, s>>>(losses, loss, S, S_total, accumulate);
+    loss_reduce_k<<<1, TPB, 0, s>>>(losses, loss, S, S_total, accumulate);
 }
 
 void adamw(hipStream_t s, int dtype, const AdamwTensor *tensors, int count, float lr, float beta1, float beta2, float eps, float wd, float bc1,
