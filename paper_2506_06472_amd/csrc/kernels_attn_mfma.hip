@@ -617,15 +617,19 @@ __device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const 
     __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): this wavefront's part of tile 0 (and of V) has landed
     __syncthreads();
     // DIAG: tiles that cross the diagonal of some key of this workgroup, the first ones; the others have no mask and no branch in them
-    // (ONE_LOOP: every tile is taken for one).
-    // Rows past the sequence need none: their Q, dO and statistics are zero, so P is one, dP and dS are zero, and every product with
-    // them adds zero.
+    // (ONE_LOOP: every tile is taken for one).  END: the last tile where the sequence ends inside it, in code of its own.  Its rows past the
+    // sequence are masked too: their Q, dO and statistics are zero, which adds nothing while K is finite, but with an infinite component
+    // of a key their scores are not numbers.
+    using Plain = std::integral_constant<int, 0>;
+    using Diag = std::integral_constant<int, 1>;
+    using End = std::integral_constant<int, 2>;
     auto key_less_4half = []() __attribute__((always_inline)) { const int ln = lane_here(); return (ln & 31) - 4 * (ln >> 5); };
-    auto tile = [&](int t, auto DIAG) __attribute__((always_inline)) {
+    auto tile = [&](int t, auto KIND) __attribute__((always_inline)) {
+        constexpr bool DIAG = KIND() == Diag(), END = KIND() == End();
         const int i0 = kv0 + t * 64;
         const uint16_t *Qs = smem + (t & 1) * BUF, *Gs = Qs + TE;
         const float *L2s = stats + (t & 1) * 128, *Ds = L2s + 64;
-        if (t + 1 < ntiles) {                           // the other buffer is free since the barrier that ended tile t-1
+        if (!END && t + 1 < ntiles) {                           // the other buffer is free since the barrier that ended tile t-1
             // The statistics fetched a tile ago go to LDS before the tile loads are issued: the write waits for every
             // outstanding vector memory operation of the wavefront, and behind the tile loads that would be their
             // whole latency, at the start of every tile.
@@ -633,8 +637,8 @@ __device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const 
             load_tile(i0 + 64, (t + 1) & 1);
             if (t + 2 < ntiles) load_stats(i0 + 128);
         }
-        if (!DIAG() || i0 + 63 >= kv0w) {
-            const int masked = DIAG() ? kv0w - i0 + key_less_4half() : 0;        // rows of the tile before this lane's key, less 4 lhi
+        if (KIND() == Plain() || i0 + 63 >= kv0w) {
+            const int masked = DIAG ? kv0w - i0 + key_less_4half() : 0;        // rows of the tile before this lane's key, less 4 lhi
 #pragma unroll
             for (int qt = 0; qt < 2; ++qt) {
                 floatx16 s = zero16(), dp = zero16();
@@ -664,14 +668,16 @@ __device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const 
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     // rows 8*r4 + 4*lhi + 0..3 of this 32-row group: their statistics are 16 contiguous bytes
-                    const int ql = qt * 32 + 8 * r4 + 4 * lhi;
+                    const int half4 = 4 * (END ? lane_here() >> 5 : lhi), ql = qt * 32 + 8 * r4 + half4;
                     const float4 l4 = *reinterpret_cast<const float4 *>(L2s + ql), d4 = *reinterpret_cast<const float4 *>(Ds + ql);
+                    const int first = END ? kv0w - i0 + key_less_4half() : 0, end = (int)Tn - i0 - half4;
                     const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dvv[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int r = 4 * r4 + e;
                         float p = __builtin_amdgcn_exp2f(fmaf(s[r], c, -lv[e]));
-                        if (DIAG() && qt * 32 + 8 * r4 + e < masked) p = 0.0f;
+                        if (DIAG && qt * 32 + 8 * r4 + e < masked) p = 0.0f;
+                        if (END && (qt * 32 + 8 * r4 + e < first || qt * 32 + 8 * r4 + e >= end)) p = 0.0f;
                         dp[r] = p * (dp[r] - dvv[e]);        // the 1/sqrt(dh) factor is applied once, to the sums
                         s[r] = p;
                     }
@@ -692,13 +698,12 @@ __device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const 
         __builtin_amdgcn_s_waitcnt(0x0F70);             // vmcnt(0): this wavefront's part of tile t+1 has landed
         __syncthreads();
     };
+    const int whole = ((int)Tn - kv0) / 64, diag = ONE_LOOP || whole < KEYS / 64 ? whole : KEYS / 64;
     int t = 0;
-    if constexpr (ONE_LOOP) {
-        for (; t < ntiles; ++t) tile(t, std::true_type{});
-    } else {
-        for (; t < KEYS / 64 && t < ntiles; ++t) tile(t, std::true_type{});
-        for (; t < ntiles; ++t) tile(t, std::false_type{});
-    }
+    for (; t < diag; ++t) tile(t, Diag());
+    if constexpr (!ONE_LOOP)
+        for (; t < whole; ++t) tile(t, Plain());
+    if (t < ntiles) tile(t, End());
     const int last = lane_here(), half = last >> 5, key = kv0w + (last & 31);
     if (key < (int)Tn) {
         uint16_t *krow = dqkv + (b * Tn + key) * ld + d + h * DH, *vrow = krow + d;

@@ -50,3 +50,35 @@ def test_bf16_attention_does_not_depend_on_the_order_of_its_blocks(B, T, H, dh):
     for b in range(B):
         for name, w, one in zip(("o", "lse", "dqkv"), whole, run(qkv[b:b + 1].contiguous(), dO[b:b + 1].contiguous())):
             assert torch.equal(w[b], one[0]), (name, b)
+
+
+# one launch for both gradients (head size 128: four wavefronts, eight) and two; sequences that end inside a tile of 64 rows and inside a
+# workgroup's first tiles, and a whole one
+@pytest.mark.parametrize("B,T,H,dh", [(2, 333, 3, 64), (1, 50, 2, 64), (8, 1000, 9, 64), (2, 320, 1, 64), (2, 333, 3, 128), (1, 50, 2, 128),
+                                      (4, 300, 16, 128), (8, 1000, 20, 128), (2, 384, 1, 128)])
+def test_gradients_of_keys_at_minus_infinity(B, T, H, dh):
+    """A key whose scores are all -inf takes part in nothing: dK and dV are those of a key far below every other.  The forward pass
+    rescales at other tiles then, which changes the rounding of probabilities, their gradients and the outputs to bf16: 2^-8 each."""
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"attention, infinite keys B={B} T={T} H={H} dh={dh}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+    x = torch.randn((B, T, 3, H, dh), device="cuda", generator=g)
+    x[:, :, 0, :, 5] = x[:, :, 0, :, 5].abs() + 0.25
+    keys = sorted({1, T // 2, T - 2})
+    dO = torch.randn((B, T, H * dh), device="cuda", generator=g).bfloat16()
+
+    def run(value):
+        q = x.clone()
+        q[:, keys, 1, :, 5] = value
+        q = q.bfloat16().contiguous()
+        o, dqkv = torch.full_like(dO, 7.0), torch.full_like(q, 7.0)
+        lse, delta = (torch.full((B, H, T), 7.0, device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        tio.tio_op_attention(0, "bf16", B, T, H, dh, q.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), delta.data_ptr(), dqkv.data_ptr())
+        torch.cuda.synchronize()
+        return o, lse, dqkv[:, :, 1:]
+    for name, a, b in zip(("o", "lse", "dk, dv"), run(float("-inf")), run(-1e30)):
+        assert torch.isfinite(a).all(), name
+        a, b = a.double(), b.double()
+        assert ((a - b).norm() <= 3 * 2.0 ** -8 * b.norm()).item(), name
