@@ -35,8 +35,9 @@ constexpr int ROWS = 32;         // own rows of a wavefront, and rows of a tile 
 // Up to 32 rows of one head from a row r0 on, behind a buffer descriptor: rows past the sequence read as zeros.  An element's address is
 // one register that the lane keeps for the whole kernel, a uniform offset and a constant; with 64-bit addresses per row and the clamp
 // to the last row the address arithmetic was most of the instructions of a kernel whose code runs once or twice, and reading
-// the code took longer than running it.  32 rows span less than 4 GiB up to 2^23 columns of q, k and v.
+// the code took longer than running it.
 template <typename T> struct Rows {
+    static constexpr bool WIDE = false;
     __amdgpu_buffer_rsrc_t rsrc;
     uint32_t pitch;
     __device__ __forceinline__ Rows(const T *head, int64_t ld, int r0, int Tn, int dh) {
@@ -45,6 +46,24 @@ template <typename T> struct Rows {
         pitch = (uint32_t)(ld * (int64_t)sizeof(T));
     }
 };
+// The same where 32 rows span 4 GiB and more, which 32-bit offsets do not reach: 64-bit addresses, rows past the sequence read its last.
+template <typename T> struct WideRows {
+    static constexpr bool WIDE = true;
+    const T *head;
+    int64_t ld;
+    int n;
+    __device__ __forceinline__ WideRows(const T *head, int64_t ld, int r0, int Tn, int) : head(head + r0 * ld), ld(ld), n(Tn - r0) {}
+    __device__ __forceinline__ const T *row(int r) const { return head + (r < n ? r : n - 1) * ld; }
+};
+__device__ __forceinline__ void load4(float *f, const float *p) {
+    const float4 v = *reinterpret_cast<const float4 *>(p);
+    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+}
+__device__ __forceinline__ void load4(float *f, const bf16_t *p) {
+    const uint2 v = *reinterpret_cast<const uint2 *>(p);
+    f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
+    f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
+}
 __device__ __forceinline__ void load4(float *f, const Rows<float> &x, uint32_t off) {
     const auto v = __builtin_amdgcn_raw_buffer_load_b128(x.rsrc, (int)off, 0, 0);
     f[0] = __uint_as_float(v[0]); f[1] = __uint_as_float(v[1]); f[2] = __uint_as_float(v[2]); f[3] = __uint_as_float(v[3]);
@@ -80,6 +99,11 @@ __device__ __forceinline__ floatx16 mfma(float a, float b, floatx16 c) { return 
 // holds elements 8 c + 4 half .. + 3 of chunk c, on both operands of a product alike.
 template <int DH> struct RowFrag {
     float f[DH / 2];
+    template <typename T> __device__ __forceinline__ void load(const WideRows<T> &x, int lane) {
+        const T *row = x.row(lane & 31) + 4 * (lane >> 5);
+#pragma unroll
+        for (int c = 0; c < DH / 8; ++c) load4(f + 4 * c, row + 8 * c);
+    }
     template <typename T> __device__ __forceinline__ void load(const Rows<T> &x, int lane) {
         const uint32_t off = (uint32_t)(lane & 31) * x.pitch + (uint32_t)(lane >> 5) * (4 * sizeof(T));
 #pragma unroll
@@ -95,6 +119,14 @@ template <int DH> __device__ __forceinline__ floatx16 dot_rows(const RowFrag<DH>
 // A 32-row tile whose rows are the contraction index: register (i, r) is column 32 i + lane % 32 of row acc_row(r).
 template <int DH> struct ColFrag {
     float f[DH / 32][16];
+    template <typename T> __device__ __forceinline__ void load(const WideRows<T> &x, int lane) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const T *row = x.row(acc_row(r, lane >> 5)) + (lane & 31);
+#pragma unroll
+            for (int i = 0; i < DH / 32; ++i) f[i][r] = to_f32(row[32 * i]);
+        }
+    }
     template <typename T> __device__ __forceinline__ void load(const Rows<T> &x, int lane) {
         const uint32_t off = (uint32_t)(4 * (lane >> 5)) * x.pitch + (uint32_t)(lane & 31) * (uint32_t)sizeof(T);
 #pragma unroll
@@ -150,7 +182,7 @@ __device__ __forceinline__ void merge_store(const floatx16 (&acc)[DH / 32], floa
 }
 
 // ---------------------------------------------------------------- forward
-template <typename T, int DH, int NW>
+template <template <typename> class R, typename T, int DH, int NW>
 __global__ void __launch_bounds__(NW * 64) attn_fwd_k(const T *__restrict__ qkv, T *__restrict__ o, float *__restrict__ lse,
                                                   int64_t heads, int Tn, int64_t H, float scale) {
     __shared__ float part[merge_floats<NW>()];
@@ -164,7 +196,7 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd_k(const T *__restrict__ qkv,
     const int q = q0 + l32;
     const T *base = qkv + b * Tn * ld + h * DH;
     RowFrag<DH> qf;
-    qf.load(Rows<T>(base, ld, q0, Tn, DH), lane);
+    qf.load(R<T>(base, ld, q0, Tn, DH), lane);
     floatx16 acc[DH / 32];
 #pragma unroll
     for (int i = 0; i < DH / 32; ++i) acc[i] = zero16();
@@ -174,8 +206,8 @@ __global__ void __launch_bounds__(NW * 64) attn_fwd_k(const T *__restrict__ qkv,
         const int j0 = t * ROWS;
         RowFrag<DH> kf;
         ColFrag<DH> vf;
-        kf.load(Rows<T>(base + d, ld, j0, Tn, DH), lane);
-        vf.load(Rows<T>(base + 2 * d, ld, j0, Tn, DH), lane);
+        kf.load(R<T>(base + d, ld, j0, Tn, DH), lane);
+        vf.load(R<T>(base + 2 * d, ld, j0, Tn, DH), lane);
         floatx16 s = dot_rows(kf, qf);
         const float m_old = m;
         float tmax = -INFINITY;
@@ -268,7 +300,7 @@ template <typename T, int DH> __device__ __forceinline__ float row_dot(const Row
 }
 
 // dQ: own query rows, keys and values stream
-template <typename T, int DH, int NW, bool OWN_DELTA>
+template <template <typename> class R, typename T, int DH, int NW, bool OWN_DELTA>
 __device__ __forceinline__ void dq_rows(const BwdArgs<T> &a, unsigned block, float *part) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l32 = lane & 31, lhi = lane >> 5;
     const int64_t H = a.H, d = H * DH, ld = 3 * d, Tn = a.Tn;
@@ -279,13 +311,13 @@ __device__ __forceinline__ void dq_rows(const BwdArgs<T> &a, unsigned block, flo
     const int q = q0 + l32, qc = min(q, a.Tn - 1);
     const T *base = a.qkv + b * Tn * ld + h * DH;
     RowFrag<DH> qf, gf;
-    qf.load(Rows<T>(base, ld, q0, a.Tn, DH), lane);
-    gf.load(Rows<T>(a.dO + b * Tn * d + h * DH, d, q0, a.Tn, DH), lane);
+    qf.load(R<T>(base, ld, q0, a.Tn, DH), lane);
+    gf.load(R<T>(a.dO + b * Tn * d + h * DH, d, q0, a.Tn, DH), lane);
     const float li = a.lse[bh * Tn + qc];
     float di;
     if constexpr (OWN_DELTA) {
         RowFrag<DH> of;
-        of.load(Rows<T>(a.O + b * Tn * d + h * DH, d, q0, a.Tn, DH), lane);
+        of.load(R<T>(a.O + b * Tn * d + h * DH, d, q0, a.Tn, DH), lane);
         di = row_dot<T>(gf, of, lane);
         if (wave == 0 && lhi == 0 && q < a.Tn) a.delta[bh * Tn + q] = di;
     } else {
@@ -297,7 +329,7 @@ __device__ __forceinline__ void dq_rows(const BwdArgs<T> &a, unsigned block, flo
     const int ntiles = q0 / ROWS + 1;
     for (int t = wave; t < ntiles; t += NW) {
         const int j0 = t * ROWS;
-        const Rows<T> k(base + d, ld, j0, a.Tn, DH), v(base + 2 * d, ld, j0, a.Tn, DH);
+        const R<T> k(base + d, ld, j0, a.Tn, DH), v(base + 2 * d, ld, j0, a.Tn, DH);
         RowFrag<DH> kf, vf;
         ColFrag<DH> kc;
         kf.load(k, lane);
@@ -319,7 +351,7 @@ __device__ __forceinline__ void dq_rows(const BwdArgs<T> &a, unsigned block, flo
 }
 
 // dK, dV: own key rows, queries and output gradients stream
-template <typename T, int DH, int NW, bool OWN_DELTA>
+template <template <typename> class R, typename T, int DH, int NW, bool OWN_DELTA>
 __device__ __forceinline__ void dkv_rows(const BwdArgs<T> &a, unsigned block, float *part) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l32 = lane & 31, lhi = lane >> 5;
     const int64_t H = a.H, d = H * DH, ld = 3 * d, Tn = a.Tn;
@@ -331,13 +363,13 @@ __device__ __forceinline__ void dkv_rows(const BwdArgs<T> &a, unsigned block, fl
     const T *base = a.qkv + b * Tn * ld + h * DH, *gbase = a.dO + b * Tn * d + h * DH;
     const float *ls = a.lse + bh * Tn, *dl = a.delta + bh * Tn;
     RowFrag<DH> kf, vf;
-    kf.load(Rows<T>(base + d, ld, kv0, a.Tn, DH), lane);
-    vf.load(Rows<T>(base + 2 * d, ld, kv0, a.Tn, DH), lane);
+    kf.load(R<T>(base + d, ld, kv0, a.Tn, DH), lane);
+    vf.load(R<T>(base + 2 * d, ld, kv0, a.Tn, DH), lane);
     floatx16 dk[DH / 32], dv[DH / 32];
 #pragma unroll
     for (int i = 0; i < DH / 32; ++i) { dk[i] = zero16(); dv[i] = zero16(); }
     for (int i0 = kv0 + wave * ROWS; i0 < a.Tn; i0 += NW * ROWS) {
-        const Rows<T> qr(base, ld, i0, a.Tn, DH), gr(gbase, d, i0, a.Tn, DH);
+        const R<T> qr(base, ld, i0, a.Tn, DH), gr(gbase, d, i0, a.Tn, DH);
         const int row = min(i0 + l32, a.Tn - 1);
         RowFrag<DH> qf, gf;
         ColFrag<DH> qc, gc;
@@ -349,7 +381,7 @@ __device__ __forceinline__ void dkv_rows(const BwdArgs<T> &a, unsigned block, fl
         float delta_row;
         if constexpr (OWN_DELTA) {
             RowFrag<DH> of;
-            of.load(Rows<T>(a.O + b * Tn * d + h * DH, d, i0, a.Tn, DH), lane);
+            of.load(R<T>(a.O + b * Tn * d + h * DH, d, i0, a.Tn, DH), lane);
             delta_row = row_dot<T>(gf, of, lane);
         } else {
             delta_row = dl[row];
@@ -378,12 +410,13 @@ __device__ __forceinline__ void dkv_rows(const BwdArgs<T> &a, unsigned block, fl
 
 // The blocks of key rows come first, they are the longer ones; then the blocks of query rows.  One launch for both: the sequences that
 // this path is for fill neither the chip with one of them, nor the time of a launch.  Two wavefronts per SIMD at head size 64 (235
-// registers; left to itself the compiler takes 288 and there is one), three at 32.
-template <typename T, int DH, int NW, bool OWN_DELTA>
-__global__ void __launch_bounds__(NW * 64, DH == 128 ? 1 : DH == 64 || NW == 8 ? 2 : 3) attn_bwd_k(const BwdArgs<T> a, unsigned blocks) {
+// registers; left to itself the compiler takes 288 and there is one), three at 32; one with 64-bit addresses.
+template <bool WIDE, int DH, int NW> constexpr int waves_per_simd() { return DH == 128 || WIDE ? 1 : DH == 64 || NW == 8 ? 2 : 3; }
+template <template <typename> class R, typename T, int DH, int NW, bool OWN_DELTA>
+__global__ void __launch_bounds__(NW * 64, (waves_per_simd<R<T>::WIDE, DH, NW>())) attn_bwd_k(const BwdArgs<T> a, unsigned blocks) {
     __shared__ float part[merge_floats<NW>()];
-    if (blockIdx.x < blocks) dkv_rows<T, DH, NW, OWN_DELTA>(a, blockIdx.x, part);
-    else dq_rows<T, DH, NW, OWN_DELTA>(a, blockIdx.x - blocks, part);
+    if (blockIdx.x < blocks) dkv_rows<R, T, DH, NW, OWN_DELTA>(a, blockIdx.x, part);
+    else dq_rows<R, T, DH, NW, OWN_DELTA>(a, blockIdx.x - blocks, part);
 }
 
 unsigned grid_for(int64_t heads, int64_t Tn) { return (unsigned)((Tn + ROWS - 1) / ROWS * ((heads + 7) / 8) * 8); }
@@ -395,16 +428,20 @@ unsigned grid_for(int64_t heads, int64_t Tn) { return (unsigned)((Tn + ROWS - 1)
 bool eight_wavefronts(int64_t blocks, int64_t Tn, int64_t dh) { return dh == 32 && Tn > 4 * ROWS && blocks <= 512; }
 
 template <int DH> constexpr bool own_delta() { return DH == 32; }    // at 64 it does not fit the registers, and delta has a launch of its own
-template <typename T, int DH> void launch_bwd(hipStream_t s, const BwdArgs<T> &a) {
+// whether 32 rows of q, k and v are too wide for Rows
+bool wide(int dtype, int64_t H, int64_t dh) { return ROWS * 3 * H * dh * (dtype == TIO_PREC_BF16 ? 2 : 4) >= ((int64_t)1 << 32); }
+template <typename T, int DH> void launch_bwd(hipStream_t s, const BwdArgs<T> &a, bool wide) {
     const unsigned blocks = grid_for(a.heads, a.Tn);
-    if constexpr (own_delta<DH>()) {
+    if (wide) {
+        attn_bwd_k<WideRows, T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
+    } else if constexpr (own_delta<DH>()) {
         const bool eight = eight_wavefronts(2 * blocks, a.Tn, DH);
-        if (a.O && eight) attn_bwd_k<T, DH, 8, true><<<2 * blocks, 512, 0, s>>>(a, blocks);
-        else if (a.O) attn_bwd_k<T, DH, 4, true><<<2 * blocks, 256, 0, s>>>(a, blocks);
-        else if (eight) attn_bwd_k<T, DH, 8, false><<<2 * blocks, 512, 0, s>>>(a, blocks);
-        else attn_bwd_k<T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
+        if (a.O && eight) attn_bwd_k<Rows, T, DH, 8, true><<<2 * blocks, 512, 0, s>>>(a, blocks);
+        else if (a.O) attn_bwd_k<Rows, T, DH, 4, true><<<2 * blocks, 256, 0, s>>>(a, blocks);
+        else if (eight) attn_bwd_k<Rows, T, DH, 8, false><<<2 * blocks, 512, 0, s>>>(a, blocks);
+        else attn_bwd_k<Rows, T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
     } else {
-        attn_bwd_k<T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
+        attn_bwd_k<Rows, T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
     }
 }
 
@@ -431,8 +468,9 @@ void attn_fwd(hipStream_t s, int dtype, const void *qkv, void *o, float *lse, in
     TIO_ATTN_DISPATCH(dtype, dh, {
         const unsigned grid = grid_for(B * H, Tn);
         constexpr int MANY = DH == 32 ? 8 : 4;
-        if (eight_wavefronts(grid, Tn, DH)) attn_fwd_k<T, DH, MANY><<<grid, MANY * 64, 0, s>>>((const T *)qkv, (T *)o, lse, B * H, (int)Tn, H, scale);
-        else attn_fwd_k<T, DH, 4><<<grid, 256, 0, s>>>((const T *)qkv, (T *)o, lse, B * H, (int)Tn, H, scale);
+        if (wide(dtype, H, dh)) attn_fwd_k<WideRows, T, DH, 4><<<grid, 256, 0, s>>>((const T *)qkv, (T *)o, lse, B * H, (int)Tn, H, scale);
+        else if (eight_wavefronts(grid, Tn, DH)) attn_fwd_k<Rows, T, DH, MANY><<<grid, MANY * 64, 0, s>>>((const T *)qkv, (T *)o, lse, B * H, (int)Tn, H, scale);
+        else attn_fwd_k<Rows, T, DH, 4><<<grid, 256, 0, s>>>((const T *)qkv, (T *)o, lse, B * H, (int)Tn, H, scale);
     });
 }
 
@@ -445,7 +483,9 @@ void attn_bwd_pre(hipStream_t s, int dtype, const void *dO, const void *O, float
         attn_bwd_pre_k<float><<<(unsigned)((n + TPB - 1) / TPB), TPB, 0, s>>>((const float *)dO, (const float *)O, delta, B, Tn, H, dh);
 }
 
-bool attn_bwd_has_delta(int dtype, int64_t Tn, int64_t H, int64_t dh) { return dh == 32 || attn_mfma_supported(dtype, Tn, H, dh); }
+bool attn_bwd_has_delta(int dtype, int64_t Tn, int64_t H, int64_t dh) {
+    return (dh == 32 && !wide(dtype, H, dh)) || attn_mfma_supported(dtype, Tn, H, dh);
+}
 
 void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const void *O, const float *lse, float *delta, void *dqkv,
               int64_t B, int64_t Tn, int64_t H, int64_t dh) {
@@ -454,7 +494,7 @@ void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const v
     const float scale = 1.0f / sqrtf((float)dh);
     TIO_ATTN_DISPATCH(dtype, dh, {
         const BwdArgs<T> a{(const T *)dO, (const T *)qkv, (const T *)O, lse, delta, (T *)dqkv, B * H, H, (int)Tn, scale};
-        launch_bwd<T, DH>(s, a);
+        launch_bwd<T, DH>(s, a, wide(dtype, H, dh));
     });
 }
 

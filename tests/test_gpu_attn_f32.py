@@ -33,3 +33,37 @@ def test_scores_of_minus_infinity():
     p = torch.softmax(s[40:], -1)
     assert (o[40:] - p @ v).abs().max() < 1e-5 and (lse[40:] - torch.logsumexp(s[40:], -1)).abs().max() < 1e-5
     assert not torch.isfinite(o[:40]).any() and (lse[:40] == float("-inf")).all()
+
+
+@pytest.mark.parametrize("dtype,T,H,dh", [("fp32", 33, 365000, 32), ("bf16", 40, 730000, 32), ("fp32", 32, 182500, 64), ("bf16", 33, 365000, 64)])
+def test_rows_whose_tile_spans_more_than_4_GiB(dtype, T, H, dh):
+    """So many heads that 32-bit offsets do not reach over a tile of 32 rows: the first and the last heads have the bits they have in
+    a layer of their own (bf16 with heads of 64 runs on other kernels then: fp32-rounded probabilities against bf16 ones, 2^-8 each
+    for them, their gradients and the outputs)."""
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"wide attention {dtype} T={T} H={H} dh={dh}", flush=True)
+    t = torch.float32 if dtype == "fp32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(T)
+    qkv, dO = torch.zeros((T, 3, H, dh), device="cuda", dtype=t), torch.zeros((T, H, dh), device="cuda", dtype=t)
+    ends = [slice(0, 3), slice(H // 2, H // 2 + 3), slice(H - 3, H)]
+    for s in ends:
+        qkv[:, :, s] = torch.randn((T, 3, 3, dh), device="cuda", generator=g).to(t)
+        dO[:, s] = torch.randn((T, 3, dh), device="cuda", generator=g).to(t)
+
+    def run(qkv, dO):
+        n = dO.shape[1]
+        o, dqkv = torch.full_like(dO, 7.0), torch.full_like(qkv, 7.0)
+        lse, delta = (torch.full((n, T), 7.0, device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        tio.tio_op_attention(0, dtype, 1, T, n, dh, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), delta.data_ptr(),
+                             dqkv.data_ptr())
+        torch.cuda.synchronize()
+        return o, lse, delta, dqkv
+    o, lse, delta, dqkv = run(qkv, dO)
+    same = dtype == "fp32" or dh == 32
+    for s in ends:
+        alone = run(qkv[:, :, s].contiguous(), dO[:, s].contiguous())
+        for name, a, b in zip(("o", "lse", "delta", "dqkv"), (o[:, s], lse[s], delta[s], dqkv[:, :, s]), alone):
+            a, b = a.double(), b.double()
+            assert torch.equal(a, b) if same else ((a - b).norm() <= 3 * 2.0 ** -8 * b.norm()).item(), (name, s)
