@@ -67,3 +67,31 @@ def test_rows_whose_tile_spans_more_than_4_GiB(dtype, T, H, dh):
         for name, a, b in zip(("o", "lse", "delta", "dqkv"), (o[:, s], lse[s], delta[s], dqkv[:, :, s]), alone):
             a, b = a.double(), b.double()
             assert torch.equal(a, b) if same else ((a - b).norm() <= 3 * 2.0 ** -8 * b.norm()).item(), (name, s)
+
+
+@pytest.mark.parametrize("dtype,T,H,dh", [("fp32", 1, 2, 32), ("fp32", 7, 3, 32), ("fp32", 33, 2, 32), ("fp32", 129, 2, 32), ("fp32", 1, 2, 64),
+                                          ("fp32", 65, 1, 64), ("fp32", 5, 1, 128), ("fp32", 97, 2, 128), ("bf16", 1, 2, 32), ("bf16", 33, 3, 32),
+                                          ("bf16", 161, 1, 32)])
+def test_what_lies_behind_the_buffers_does_not_matter(dtype, T, H, dh):
+    """Tiles of 32 rows reach up to 31 rows past a sequence: behind qkv, dO and the rows of o lie zeros in one run and NaN in the other, in
+    the same allocations, and every output has to be finite and the same to the bit."""
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"attention behind the buffer {dtype} T={T} H={H} dh={dh}", flush=True)
+    t, d = torch.float32 if dtype == "fp32" else torch.bfloat16, H * dh
+    g = torch.Generator(device="cuda").manual_seed(T + dh)
+    qkv, dO = torch.randn((T, 3 * d), device="cuda", generator=g).to(t), torch.randn((T, d), device="cuda", generator=g).to(t)
+    outs = []
+    for fill in (0.0, float("nan")):
+        big_q, big_g, big_o = (torch.full((T + 64, n), fill, device="cuda", dtype=t) for n in (3 * d, d, d))
+        big_q[:T], big_g[:T] = qkv, dO
+        dqkv = torch.full((T, 3 * d), 7.0, device="cuda", dtype=t)
+        lse, delta = (torch.full((H * T + 64,), fill, device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        tio.tio_op_attention(0, dtype, 1, T, H, dh, big_q.data_ptr(), big_o.data_ptr(), lse.data_ptr(), big_g.data_ptr(), delta.data_ptr(),
+                             dqkv.data_ptr())
+        torch.cuda.synchronize()
+        outs.append([big_o[:T], lse[:H * T], delta[:H * T], dqkv])
+        assert torch.equal(big_o[T:].isnan(), torch.full_like(big_o[T:], fill).isnan())
+    for name, a, b in zip(("o", "lse", "delta", "dqkv"), *outs):
+        assert torch.isfinite(b).all() and torch.equal(a, b), name
