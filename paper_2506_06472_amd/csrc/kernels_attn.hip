@@ -413,10 +413,11 @@ __device__ __forceinline__ void dkv_rows(const BwdArgs<T> &a, unsigned block, fl
 // registers; left to itself the compiler takes 288 and there is one), three at 32; one with 64-bit addresses.
 template <bool WIDE, int DH, int NW> constexpr int waves_per_simd() { return DH == 128 || WIDE ? 1 : DH == 64 || NW == 8 ? 2 : 3; }
 template <template <typename> class R, typename T, int DH, int NW, bool OWN_DELTA>
-__global__ void __launch_bounds__(NW * 64, (waves_per_simd<R<T>::WIDE, DH, NW>())) attn_bwd_k(const BwdArgs<T> a, unsigned blocks) {
+__global__ void __launch_bounds__(NW * 64, (waves_per_simd<R<T>::WIDE, DH, NW>())) attn_bwd_k(const BwdArgs<T> a, unsigned blocks, unsigned first) {
     __shared__ float part[merge_floats<NW>()];
-    if (blockIdx.x < blocks) dkv_rows<R, T, DH, NW, OWN_DELTA>(a, blockIdx.x, part);
-    else dq_rows<R, T, DH, NW, OWN_DELTA>(a, blockIdx.x - blocks, part);
+    const unsigned block = first + blockIdx.x;
+    if (block < blocks) dkv_rows<R, T, DH, NW, OWN_DELTA>(a, block, part);
+    else dq_rows<R, T, DH, NW, OWN_DELTA>(a, block - blocks, part);
 }
 
 unsigned grid_for(int64_t heads, int64_t Tn) { return (unsigned)((Tn + ROWS - 1) / ROWS * ((heads + 7) / 8) * 8); }
@@ -430,18 +431,26 @@ bool eight_wavefronts(int64_t blocks, int64_t Tn, int64_t dh) { return dh == 32 
 template <int DH> constexpr bool own_delta() { return DH == 32; }    // at 64 it does not fit the registers, and delta has a launch of its own
 // whether 32 rows of q, k and v are too wide for Rows
 bool wide(int dtype, int64_t H, int64_t dh) { return ROWS * 3 * H * dh * (dtype == TIO_PREC_BF16 ? 2 : 4) >= ((int64_t)1 << 32); }
+template <template <typename> class R, typename T, int DH, int NW, bool OWN_DELTA> void launch_both(hipStream_t s, const BwdArgs<T> &a, unsigned blocks) {
+    if ((uint64_t)2 * blocks * NW * 64 < ((uint64_t)1 << 32)) {
+        attn_bwd_k<R, T, DH, NW, OWN_DELTA><<<2 * blocks, NW * 64, 0, s>>>(a, blocks, 0);
+    } else {                     // a grid has fewer than 2^32 threads
+        attn_bwd_k<R, T, DH, NW, OWN_DELTA><<<blocks, NW * 64, 0, s>>>(a, blocks, 0);
+        attn_bwd_k<R, T, DH, NW, OWN_DELTA><<<blocks, NW * 64, 0, s>>>(a, blocks, blocks);
+    }
+}
 template <typename T, int DH> void launch_bwd(hipStream_t s, const BwdArgs<T> &a, bool wide) {
     const unsigned blocks = grid_for(a.heads, a.Tn);
     if (wide) {
-        attn_bwd_k<WideRows, T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
+        launch_both<WideRows, T, DH, 4, false>(s, a, blocks);
     } else if constexpr (own_delta<DH>()) {
-        const bool eight = eight_wavefronts(2 * blocks, a.Tn, DH);
-        if (a.O && eight) attn_bwd_k<Rows, T, DH, 8, true><<<2 * blocks, 512, 0, s>>>(a, blocks);
-        else if (a.O) attn_bwd_k<Rows, T, DH, 4, true><<<2 * blocks, 256, 0, s>>>(a, blocks);
-        else if (eight) attn_bwd_k<Rows, T, DH, 8, false><<<2 * blocks, 512, 0, s>>>(a, blocks);
-        else attn_bwd_k<Rows, T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
+        const bool eight = eight_wavefronts(2 * (int64_t)blocks, a.Tn, DH);
+        if (a.O && eight) launch_both<Rows, T, DH, 8, true>(s, a, blocks);
+        else if (a.O) launch_both<Rows, T, DH, 4, true>(s, a, blocks);
+        else if (eight) launch_both<Rows, T, DH, 8, false>(s, a, blocks);
+        else launch_both<Rows, T, DH, 4, false>(s, a, blocks);
     } else {
-        attn_bwd_k<Rows, T, DH, 4, false><<<2 * blocks, 256, 0, s>>>(a, blocks);
+        launch_both<Rows, T, DH, 4, false>(s, a, blocks);
     }
 }
 

@@ -95,3 +95,24 @@ def test_what_lies_behind_the_buffers_does_not_matter(dtype, T, H, dh):
         assert torch.equal(big_o[T:].isnan(), torch.full_like(big_o[T:], fill).isnan())
     for name, a, b in zip(("o", "lse", "delta", "dqkv"), *outs):
         assert torch.isfinite(b).all() and torch.equal(a, b), name
+
+
+def test_more_heads_than_one_grid_has_room_for():
+    """Sequences of one token, so that o = v and dV = dO but for the rounding of a probability of one: 8.4 million blocks of dK/dV and as many of dQ, of 256 threads, where
+    a grid has fewer than 2^32 of them."""
+    import torch
+    import paper_2506_06472_amd as tio
+    B, H, dh = 1 << 13, 1032, 32
+    print(f"attention B={B} T=1 H={H}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    qkv, dO = torch.randn((B, 3, H, dh), device="cuda", generator=g), torch.randn((B, H, dh), device="cuda", generator=g)
+    o, dqkv = torch.full_like(dO, 7.0), torch.full_like(qkv, 7.0)
+    lse, delta = (torch.full((B, H), 7.0, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    tio.tio_op_attention(0, "fp32", B, 1, H, dh, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), delta.data_ptr(), dqkv.data_ptr())
+    torch.cuda.synchronize()
+    # exp(s - max) and exp(s - lse) of |s| < 16: its rounding, 2^-21, and a few more
+    assert ((o - qkv[:, 2]).abs() <= 2.0 ** -20 * qkv[:, 2].abs()).all() and ((dqkv[:, 2] - dO).abs() <= 2.0 ** -20 * dO.abs()).all()
+    # P (dP - delta) is the difference of two sums of 32 products, of v and of o; dK and dQ that times q / sqrt(32) and k / sqrt(32)
+    bound = (2 * 32 * 2.0 ** -24 + 2.0 ** -20) * (dO * o).abs().sum(-1, keepdim=True) / 32 ** 0.5
+    assert (dqkv[:, 0].abs() <= bound * qkv[:, 1].abs() + 1e-30).all() and (dqkv[:, 1].abs() <= bound * qkv[:, 0].abs() + 1e-30).all()
