@@ -382,6 +382,7 @@ TileShape tile_of(int64_t M, int64_t N) {
     auto tiles = [&](TileShape t) { return ((M + t.rows - 1) / t.rows) * ((N + t.cols - 1) / t.cols); };
     if (tiles(T32) <= 160) return T16;
     auto cost = [&](TileShape t, double one, double two, double more) {
+        if (t.rows * t.cols < 4096 && tiles(t) > ((int64_t)1 << 24) - 8) return 1e300;     // a grid has fewer than 2^32 threads
         const int64_t n = (tiles(t) + 255) / 256;
         return (double)n * (t.rows * t.cols / 4096.0) * (n == 1 ? one : n == 2 ? two : more);
     };

@@ -46,3 +46,21 @@ def test_fp32_products(M, N, K, a_km, b_km):
     sums = rs.cpu().numpy().astype(np.float64)
     assert np.all(np.abs(sums[:M] - A.double().sum(1).cpu().numpy()) <= (K + 3) * 2.0 ** -24 * A.abs().double().sum(1).cpu().numpy() + 1e-30)
     assert np.all(sums[M:] == 7.0)
+
+
+@pytest.mark.parametrize("M,N", [(1, (1 << 29) + 5), (1, (1 << 29) - 261), ((1 << 29) + 5, 1)])
+def test_more_small_tiles_than_one_grid_has_room_for(M, N):
+    """2^24 tiles of 256 threads and more are one grid too many; a contraction of one element is rounded once."""
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"fp32 gemm M={M} N={N} K=1", flush=True)
+    r8 = lambda n: (n + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(1)
+    A, B = torch.randn((1, r8(M)), device="cuda", generator=g), torch.randn((1, r8(N)), device="cuda", generator=g)
+    C = torch.full((M, r8(N)) if M == 1 else (M, 4), 7.0, device="cuda")
+    torch.cuda.synchronize()
+    tio.tio_op_gemm(0, "fp32", 1, 1, M, N, 1, A.data_ptr(), A.shape[1], B.data_ptr(), B.shape[1], 0, 0, 0, C.data_ptr(), C.shape[1])
+    torch.cuda.synchronize()
+    want = A[0, 0] * B[0, :N] if M == 1 else A[0, :M] * B[0, 0]
+    assert torch.equal(C[0, :N] if M == 1 else C[:, 0], want)
+    assert (C[0, N:] == 7.0).all()
