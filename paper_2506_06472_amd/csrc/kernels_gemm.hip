@@ -359,6 +359,14 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
     if (M <= 0 || N <= 0 || K <= 0) return;
     // split-K needs the fp32 workspace, no epilogue operands and whole float4 rows
     if (dtype != TIO_PREC_BF16 || !workspace || bias || resid || (N % 4) || splits < 2) splits = 1;
+    // accumulate: C += A.B^T and rowsum += row sums (gradient accumulation over micro-batches).  In a single
+    // pass the old C is the residual operand (every element is read and then written by the same lane); with
+    // split-K, the caller's or the cut made here, the reduction launch adds it.
+    if (accumulate && splits == 1) {
+        if (resid) throw std::invalid_argument("gemm: accumulate cannot be combined with a residual operand");
+        resid = C;
+        ldr = ldc;
+    }
     if (dtype == TIO_PREC_BF16 && splits == 1) {
         const int own = gemm_bf16_splits(a_km, b_km, M, N, K, lda, ldb, rowsum != nullptr, SLOT_BYTES);
         if (own > 1) {
@@ -369,14 +377,6 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
                 return;
             }
         }
-    }
-    // accumulate: C += A.B^T and rowsum += row sums (gradient accumulation over micro-batches).  In a single
-    // pass the old C is the residual operand (every element is read and then written by the same lane); with
-    // split-K the reduction launch adds it.
-    if (accumulate && splits == 1) {
-        if (resid) throw std::invalid_argument("gemm: accumulate cannot be combined with a residual operand");
-        resid = C;
-        ldr = ldc;
     }
     if (dtype == TIO_PREC_BF16) {
         float *const wsp = splits > 1 ? (float *)workspace : nullptr;

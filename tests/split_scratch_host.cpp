@@ -1,0 +1,118 @@
+// The host side of products that the library cuts by itself, on a stand-in for the HIP runtime: this program defines the runtime calls of
+// that path, so that the library's calls come here and nothing reaches a GPU.  A stream and an event carry clocks (which operations of
+// each stream lie before them); a part of the scratch space must only be taken up by a stream that comes after its last user.
+// The argument names the test; exit status 0: passed.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include <exception>
+#include <map>
+#include <vector>
+
+namespace tio {
+namespace k {
+void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
+          const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum, void *workspace, int splits, bool accumulate);
+}
+}  // namespace tio
+
+namespace {
+constexpr int BF16 = 1, STREAMS = 8;
+using Clock = std::map<hipStream_t, int>;            // stream -> number of its operations that lie before
+std::map<hipStream_t, Clock> streams;
+std::map<hipEvent_t, Clock> events;
+std::map<hipStream_t, int> device_of;
+int launches = 0, event_calls = 0, records_to_fail = 0;
+void *last_first_arg = nullptr;
+struct Config { dim3 grid, block; size_t lds; hipStream_t stream; } config;
+alignas(256) unsigned char image[64];                // stands for the array of the device image: never read or written
+
+hipStream_t stream(int i) { return reinterpret_cast<hipStream_t>(static_cast<uintptr_t>(0x1000 * (i + 1))); }
+void merge(Clock &into, const Clock &from) {
+    for (auto &[s, n] : from)
+        if (into[s] < n) into[s] = n;
+}
+}  // namespace
+
+extern "C" {
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *status) { *status = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipGetDevice(int *dev) { *dev = 0; return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *dev) { *dev = device_of[s]; return hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) { *p = image; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    static uintptr_t next = 0x100000;
+    *e = reinterpret_cast<hipEvent_t>(next += 16);
+    events[*e];
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    ++event_calls;
+    if (records_to_fail) { --records_to_fail; return hipErrorUnknown; }
+    events[e] = streams[s];
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { ++event_calls; merge(streams[s], events[e]); return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) { config = {grid, block, lds, s}; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s) {
+    *grid = config.grid; *block = config.block; *lds = config.lds; *s = config.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **args, size_t, hipStream_t s) {
+    ++launches;
+    ++streams[s][s];
+    last_first_arg = *static_cast<void **>(args[0]);
+    return hipSuccess;
+}
+}
+
+namespace {
+struct Use { hipStream_t stream; int operations; };
+std::map<void *, Use> parts;                         // part of the scratch space -> its last user and that stream's operations so far
+
+// a product of 200 x 300 x 15000, which the library cuts: two launches, of which the second reads the partials (its first argument)
+bool product(hipStream_t s, bool accumulate = false, const void *resid = nullptr) {
+    void *const operand = image;
+    launches = 0;
+    tio::k::gemm(s, BF16, false, false, 200, 300, 15000, operand, 15000, operand, 15000, nullptr, resid, 304, operand, 304, nullptr, nullptr, 1,
+                 accumulate);
+    if (launches != 2) return launches == 1;
+    const auto last = parts.find(last_first_arg);
+    if (last != parts.end() && streams[s][last->second.stream] < last->second.operations) {
+        std::printf("a part of the scratch space is taken up while another stream may be using it\n");
+        return false;
+    }
+    parts[last_first_arg] = {s, streams[s][s]};
+    return true;
+}
+
+bool cuts_and_waits() {
+    for (int i = 0; i < 40; ++i)
+        if (!product(stream(i * 5 % STREAMS)) || launches != 2) return false;
+    return parts.size() > 1;
+}
+
+// accumulate adds to C in place of a residual: both together are refused before anything is launched, whatever the size
+bool refuses_accumulate_with_residual() {
+    try {
+        product(stream(0), true, image);
+    } catch (const std::exception &) {
+        return launches == 0;
+    }
+    std::printf("accepted, %d launches\n", launches);
+    return false;
+}
+}  // namespace
+
+int main(int argc, char **argv) {
+    const char *name = argc > 1 ? argv[1] : "";
+    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual};
+    const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual"};
+    for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
+        if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
+    return 2;
+}
