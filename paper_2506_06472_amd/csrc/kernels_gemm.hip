@@ -278,12 +278,13 @@ SlotsOfDevice slots_of[DEVICES];
 class SplitScratch {
     std::unique_lock<std::mutex> lock;
     hipStream_t s;
+    SlotsOfDevice *owner = nullptr;
     Slot *mine = nullptr;
     unsigned char *at = nullptr;
 
 public:
     // partials() is nullptr where there is no part to be had: a stream under capture (a replay would not wait for the part's other
-    // users), or a device that refuses the array or an event
+    // users), or a device that refuses the array or an event, or has refused to record one: nobody could wait for the part's user then
     explicit SplitScratch(hipStream_t stream) : s(stream) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); return; }
@@ -299,13 +300,14 @@ public:
             if (x.used < best->used) best = &x;
         }
         if (best->used && hipStreamWaitEvent(s, best->free, 0) != hipSuccess) { (void)hipGetLastError(); lock.unlock(); return; }
+        owner = &d;
         mine = best;
         mine->user = s;
         mine->used = ++d.uses;
         at = d.base + (mine - d.slot) * SLOT_BYTES;
     }
     ~SplitScratch() {
-        if (mine) (void)hipEventRecord(mine->free, s);
+        if (mine && hipEventRecord(mine->free, s) != hipSuccess) owner->failed = true;      // the caller reports the error
     }
     float *partials() const { return reinterpret_cast<float *>(at); }
 

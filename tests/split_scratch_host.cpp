@@ -106,12 +106,21 @@ bool refuses_accumulate_with_residual() {
     std::printf("accepted, %d launches\n", launches);
     return false;
 }
+// A part whose last use has left no event behind is not handed out again
+bool a_failed_record_ends_the_sharing() {
+    if (!product(stream(0)) || !product(stream(1))) return false;
+    records_to_fail = 1;
+    if (!product(stream(2)) || records_to_fail) return false;
+    for (int i = 0; i < 40; ++i)
+        if (!product(stream(3 + i % (STREAMS - 3)))) return false;
+    return true;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
-    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual};
-    const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual"};
+    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing};
+    const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing"};
     for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
         if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
     return 2;
