@@ -284,12 +284,16 @@ class SplitScratch {
 
 public:
     // partials() is nullptr where there is no part to be had: a stream under capture (a replay would not wait for the part's other
-    // users), or a device that refuses the array or an event, or has refused to record one: nobody could wait for the part's user then
+    // users), one of another device than the current one (the array's address and the events are the current one's), or a device that
+    // refuses the array or an event, or has refused to record one: nobody could wait for the part's user then
     explicit SplitScratch(hipStream_t stream) : s(stream) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); return; }
         int dev = -1;
         if (capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= DEVICES) return;
+        hipDevice_t of_stream = dev;
+        if (s && hipStreamGetDevice(s, &of_stream) != hipSuccess) { (void)hipGetLastError(); return; }
+        if (of_stream != dev) return;
         lock = std::unique_lock<std::mutex>(slots_mu);
         SlotsOfDevice &d = slots_of[dev];
         if (!d.base && !d.failed) prepare(d);

@@ -115,12 +115,21 @@ bool a_failed_record_ends_the_sharing() {
         if (!product(stream(3 + i % (STREAMS - 3)))) return false;
     return true;
 }
+// The scratch space and its events are those of the current device: a stream of another one takes its products in one range
+bool leaves_streams_of_other_devices_alone() {
+    device_of[stream(1)] = 1;
+    if (!product(stream(0)) || launches != 2) return false;
+    const int before = event_calls;
+    if (!product(stream(1)) || launches != 1) { std::printf("%d launches\n", launches); return false; }
+    return event_calls == before && product(nullptr) && launches == 2;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
-    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing};
-    const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing"};
+    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing, leaves_streams_of_other_devices_alone};
+    const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
+                                 "leaves_streams_of_other_devices_alone"};
     for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
         if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
     return 2;

@@ -21,7 +21,8 @@ def program(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("name", ["cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing"])
+@pytest.mark.parametrize("name", ["cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
+                                  "leaves_streams_of_other_devices_alone"])
 def test_split_scratch(program, name):
     r = subprocess.run([program, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
