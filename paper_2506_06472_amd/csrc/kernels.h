@@ -46,6 +46,8 @@ struct F32Product {
     bool accumulate;
 };
 void gemm_f32(hipStream_t s, bool a_km, bool b_km, const F32Product &p);
+// the output tile gemm_f32 takes; host only
+void gemm_f32_tile(int64_t M, int64_t N, int *rows, int *cols);
 // dX = dY . W (B k-major) and dW = dY^T . X (both k-major) in one launch; only where gemm_f32_pairs says so (host only)
 bool gemm_f32_pairs(int64_t M_dx, int64_t N_dx, int64_t M_dw, int64_t N_dw);
 void gemm_f32_pair(hipStream_t s, const F32Product &dx, const F32Product &dw);

@@ -407,6 +407,12 @@ void gemm_f32(hipStream_t s, bool a_km, bool b_km, const F32Product &p) {
     else launch<Tile64>(s, a_km, b_km, a);
 }
 
+void gemm_f32_tile(int64_t M, int64_t N, int *rows, int *cols) {
+    const TileShape t = tile_of(M, N);
+    *rows = t.rows;
+    *cols = t.cols;
+}
+
 // Both gradients of a linear layer in one launch, where the tiles of both are small (16 or 32 square): such products last
 // about as long as a launch, and neither fills the chip (4.2 + 4.5 us in the tiny GPT step, nine times: that step, with merged updates
 // and delta in the launch of attention backward as well, 332 -> 256 us).

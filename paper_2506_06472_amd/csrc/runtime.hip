@@ -29,6 +29,7 @@
 #include "file_tier.h"
 #include "handles.h"
 #include "kernels.h"
+#include "merge.h"
 #include "paced_pool.h"
 
 using namespace tio;
@@ -183,44 +184,6 @@ void gather_to_home(tio_ctx *c) {
     if (c->pool_dev) HIPCHK(hipDeviceSynchronize());
 }
 
-// ---- neighbours in the schedule that go out in one launch
-// Between kernels j - 1 and j nothing is issued, waited for or recorded.
-bool nothing_between(const Plan &p, int j) {
-    return p.entries_at[j].empty() && p.kernel_wait_pre[j].empty() && p.kernel_wait_off[j].empty() && !p.kernel_needs_event[j - 1];
-}
-// The kernels share no memory that one of them writes (a range may be taken over from a tensor that dies at k by one born at k + 1);
-// shared: a tensor that the merged launch hands from one to the other itself, or -1.
-bool independent(const tio_ctx *c, int k, int shared) {
-    const KernelRec &x = c->prog.kernels[k], &y = c->prog.kernels[k + 1];
-    for (int i = 0; i < kMaxRoles; ++i)
-        for (int j = 0; j < kMaxRoles; ++j) {
-            if (x.t[i] < 0 || y.t[j] < 0 || !((x.fl[i] | y.fl[j]) & 2) || (x.t[i] == shared && y.t[j] == shared)) continue;
-            const uint64_t a = c->ptrs[k][i], b = c->ptrs[k + 1][j];
-            if (a < b + c->prog.tensors[y.t[j]].bytes && b < a + c->prog.tensors[x.t[i]].bytes) return false;
-        }
-    return true;
-}
-// How many kernels from k on one launch does: updates in a row; the two gradients of a linear layer where both products are small; the
-// row products of attention's backward pass with that pass where its kernel computes them.
-int merged_from(const tio_ctx *c, int k) {
-    const int N = c->trace.n_kernels;
-    const KernelRec &r = c->prog.kernels[k];
-    auto next = [&](int j, int op) { return j < N && c->prog.kernels[j].op == op && nothing_between(c->plan, j); };
-    if (r.op == OP_ADAMW) {
-        int n = 1;
-        while (n < k::kAdamwMax && next(k + n, OP_ADAMW) && independent(c, k + n - 1, -1)) ++n;
-        return n;
-    }
-    if (r.op == OP_GEMM_DX && next(k + 1, OP_GEMM_DW) && c->cfg.precision == TIO_PREC_FP32) {
-        const KernelRec &w = c->prog.kernels[k + 1];
-        return k::gemm_f32_pairs(r.p[0], r.p[1], w.p[0], w.p[1]) && independent(c, k, -1) ? 2 : 1;
-    }
-    if (r.op == OP_ATTN_BWD_PRE && next(k + 1, OP_ATTN_BWD))
-        return k::attn_bwd_has_delta(c->cfg.precision, c->cfg.seq_len, c->cfg.n_heads, c->cfg.d_model / c->cfg.n_heads) &&
-               independent(c, k, r.t[2]) ? 2 : 1;
-    return 1;
-}
-
 void install_plan(tio_ctx *c, const Plan &p) {
     const int N = c->trace.n_kernels;
     if (p.structure_hash != c->trace.structure_hash || p.n_kernels != N)
@@ -291,8 +254,7 @@ void install_plan(tio_ctx *c, const Plan &p) {
     }
     if (c->pool_dev) HIPCHK(hipDeviceSynchronize());     // see gather_to_home
     c->ptrs = std::move(ptrs);
-    c->merged.assign(N, 1);
-    for (int k = 0; k < N; k += c->merged[k]) c->merged[k] = merged_from(c, k);
+    c->merged = merged_launches(c->prog, c->plan, c->ptrs);
     make_events(c->ev_kernel, N, false);
     make_events(c->ev_off, p.pairs.size(), false);
     make_events(c->ev_pre, p.pairs.size(), false);
@@ -308,7 +270,7 @@ void install_plan(tio_ctx *c, const Plan &p) {
     c->params_dirty = false;
 }
 
-// kernels k .. k + count - 1: one, or as many as merged_from says
+// kernels k .. k + count - 1: one, or as many as merged_launches says
 void launch(tio_ctx *c, int k, int count = 1) {
     const KernelRec &r = c->prog.kernels[k];
     const tio_model_cfg &m = c->cfg;
