@@ -78,7 +78,8 @@ def test_streams_and_threads_do_not_share_partials():
 
 
 def test_under_graph_capture():
-    """A captured product keeps to one range, so that its replays use no scratch space that others may be using."""
+    """A captured product keeps to one range, so that its replays use no scratch space that others may be using: it does not have the
+    bits of the cut (eager) product, and has the same ones in every replay while cut products of six other streams are under way."""
     import torch
     p = _Product(torch, 200, 304, 15000, 5)
     ref = p.A[:, :p.K].double() @ p.B[:, :p.K].double().t()
@@ -90,10 +91,28 @@ def test_under_graph_capture():
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         p.run(out, torch.cuda.current_stream().cuda_stream)
-    for _ in range(3):
+    others = [_Product(torch, 200 + 8 * i, 304, 15000, 10 + i) for i in range(6)]
+    want = [q.out() for q in others]
+    for q, w in zip(others, want):
+        q.run(w)
+    got = [q.out() for q in others]
+    streams = [torch.cuda.Stream() for _ in others]
+    first = None
+    for _ in range(4):
         out.zero_()
-        graph.replay()
-        p.run(eager, torch.cuda.current_stream().cuda_stream)
+        for g in got:
+            g.zero_()
+        torch.cuda.synchronize()
+        for when in (0, 1):
+            for q, g, s in zip(others, got, streams):
+                q.run(g, s.cuda_stream)
+            if when == 0:
+                graph.replay()
+                p.run(eager, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         for o in (out, eager):
             assert ((o[:, :304].double() - ref).abs() <= bound).all()
+        first = out.clone() if first is None else first
+        assert torch.equal(out, first)
+        assert not torch.equal(out, eager)
+        assert all(torch.equal(w, g) for w, g in zip(want, got))

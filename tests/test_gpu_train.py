@@ -430,12 +430,18 @@ def test_optimizer_state_follows_the_oracle_from_the_gpu_gradients(cfg):
     ctx.close()
 
 
-@pytest.mark.parametrize("cfg", [
+# test_merged_launches.py checks what of each is merged
+MERGED = [
     CONFIGS["tiny_gpt_fp32"], CONFIGS["tiny_llama_fp32"], SMALL_BF16, SMALL_LLAMA_BF16,
     # products of 32x32 beside 16x16 tiles, more than eight key tiles, odd sizes
     dict(arch="gpt", L=1, d=160, H=5, f=520, V=1001, T=292, B=2, precision="fp32", lr=1e-3),
     dict(arch="llama", L=2, d=96, H=3, f=264, V=500, T=72, B=3, precision="bf16", lr=3e-4),
-    dict(arch="gpt", L=1, d=128, H=4, f=512, V=700, T=64, B=4, precision="fp32", lr=1e-3, micro_batches=2)])
+    dict(arch="gpt", L=1, d=128, H=4, f=512, V=700, T=64, B=4, precision="fp32", lr=1e-3, micro_batches=2),
+    # 16x16 tiles of dX beside 32x32 ones of dW, 32x32 for both
+    dict(arch="gpt", L=1, d=256, H=8, f=904, V=3001, T=208, B=4, precision="fp32", lr=1e-3, micro_batches=2)]
+
+
+@pytest.mark.parametrize("cfg", MERGED)
 def test_merged_launches_leave_the_bits_of_single_ones(cfg):
     """A step whose gradients are read back launches every kernel by itself; the others merge neighbours."""
     params, tok, lab = make_inputs(cfg, seed=1)
