@@ -57,7 +57,9 @@ typedef struct tio_model_cfg {
 } tio_model_cfg;
 
 typedef struct tio_runtime_cfg {
-    void *arena;                     /* device, 256-byte aligned; every tensor lives here */
+    void *arena;                     /* device, 256-byte aligned; every tensor lives here.  The library's device image takes 192 MiB
+                                        more on every GPU it runs on, which no cap counts: the arrays of tio_op_gemm (128) and
+                                        tio_op_gemm_static_ws (64) */
     uint64_t arena_bytes;
     void *host_pool;                 /* slow tier, stands in for the paper's SSD tier: pinned host memory, or
                                         (pool_on_device) a second device buffer outside the capped arena */
@@ -211,7 +213,8 @@ void tio_trace_free(tio_trace *trace);
 
 /* Runs iterations of the real kernels (uncapped layout: the arena must hold the whole
  * iteration), marks every operand of every launch active and times each launch with HIP events;
- * tau = median of three iterations.  tokens/labels: host int32 [batch, seq_len].
+ * tau = median of three iterations, of every kernel in a launch of its own (see TIO_STEP_TIME_KERNELS).
+ * tokens/labels: host int32 [batch, seq_len].
  * mode TIO_PROFILE_MODELLED skips the GPU and equals tio_trace_build.
  * mode TIO_PROFILE_OFFLOADED is for iterations that need more memory than the arena has (Section 2 of the
  * paper profiles such models by offloading tensors the current kernel does not need): the library plans
@@ -302,7 +305,9 @@ int tio_engine_choose(const uint8_t *ready, const uint8_t *urgent, int32_t n, in
  * flags: TIO_STEP_CAPTURE_GRADS keeps a host copy of every parameter gradient (debug: it
  * synchronises before each optimizer launch); TIO_STEP_TIME_KERNELS brackets every launch with HIP
  * events on the compute stream (see tio_kernel_times); TIO_STEP_TIMELINE additionally stamps every
- * migration (see tio_step_timeline).
+ * migration (see tio_step_timeline).  With any of them every kernel of the trace is a launch of its own; a step without
+ * them does some neighbours in one launch (the updates of a weight and its bias, the two gradients of a small fp32
+ * layer, the row products of attention's backward pass with that pass), with the same bits in less time.
  * Blocks until the compute stream has finished the iteration (copies may still be in flight).
  * Errors found before the first launch (null or out-of-vocabulary ids, a parameter never loaded, a plan that is
  * stale, invalid or too large for the arena or the pools) leave the context as it was.  TIO_ERR_HIP or TIO_ERR_IO
@@ -312,7 +317,8 @@ enum { TIO_STEP_CAPTURE_GRADS = 1, TIO_STEP_TIME_KERNELS = 2, TIO_STEP_TIMELINE 
 int tio_train_step(tio_ctx *ctx, const int32_t *tokens, const int32_t *labels,
                    const tio_plan *plan, int32_t flags, tio_step_stats *out);
 /* Per-launch durations (ns, HIP events) of the last step run with TIO_STEP_TIME_KERNELS;
- * n must equal the kernel count of the trace. */
+ * n must equal the kernel count of the trace.  Of small kernels they can add up to more than a step without the flag
+ * takes, which does some of them in one launch. */
 int tio_kernel_times(tio_ctx *ctx, int64_t *out_ns, int32_t n);
 /* Timeline of the last step run with TIO_STEP_TIMELINE (it synchronises all streams before and
  * after the step): begin and end of every kernel and of every plan entry's copy, in ns from the
@@ -330,7 +336,8 @@ int tio_step_timeline(tio_ctx *ctx, int64_t *kernel_begin, int64_t *kernel_end, 
  * workspace (device, fp32, splits*(M*N+M) floats) receives the partial tiles and a second launch
  * adds them in range order; splits = 1 ignores workspace.  With splits = 1 the library itself cuts a bf16 product with a long
  * contraction and a small output, of any operands and sizes, into 2, 4 or 8 ranges: the partial tiles go to an array of its device
- * image (128 MiB on every GPU it runs on, shared safely between streams and threads); on a stream under graph capture it does not. */
+ * image (128 MiB on every GPU it runs on, shared safely between streams and threads).  On a stream under graph capture, or of
+ * another device than the current one, it does not: such a call has the bits of one range, and takes the time of one. */
 int tio_op_gemm(void *stream, int32_t dtype, int32_t a_kmajor, int32_t b_kmajor,
                 int64_t M, int64_t N, int64_t K,
                 const void *A, int64_t lda, const void *B, int64_t ldb,
@@ -356,7 +363,7 @@ int tio_op_gemm_static_ws(void *stream, int32_t dtype, int32_t a_kmajor, int32_t
 /* Causal self-attention on a packed qkv buffer [B*T, 3*H*dh] (q | k | v, heads side by side):
  * o [B*T, H*dh] = softmax(q k^T / sqrt(dh)) v per head, lse [B*H*T] fp32 = log-sum-exp of the scaled
  * scores.  With dO != NULL also the backward pass: delta [B*H*T] fp32 (work buffer, receives
- * rowsum(dO * o)) and dqkv [B*T, 3*H*dh].  Device pointers, 16-byte aligned; dh in {32, 64, 128}. */
+ * rowsum(dO * o)) and dqkv [B*T, 3*H*dh], which may lie over o.  Device pointers, 16-byte aligned; dh in {32, 64, 128}. */
 int tio_op_attention(void *stream, int32_t dtype, int64_t B, int64_t T, int64_t H, int64_t dh,
                      const void *qkv, void *o, float *lse, const void *dO, float *delta, void *dqkv);
 /* Measuring aid: launch number kernel_index of the schedule, repeated reps times on the compute stream with the

@@ -80,9 +80,11 @@ void norm_bwd_params(hipStream_t s, int dtype, bool rms, const float *part, void
                      int64_t d, bool accumulate);
 void attn_bwd_pre(hipStream_t s, int dtype, const void *dO, const void *O, float *delta, int64_t B, int64_t T,
                   int64_t H, int64_t dh);
-// whether attn_bwd computes delta in its own launch (host only)
+// whether attn_bwd takes care of delta where it is cheapest: in its gradients' launch, or in attn_bwd_pre's in front of the one launch for
+// both gradients; otherwise O only adds that launch to it (host only)
 bool attn_bwd_has_delta(int dtype, int64_t T, int64_t H, int64_t dh);
-// O: the forward pass's output, from which delta is then computed as well, or nullptr: delta comes from attn_bwd_pre
+// O: the forward pass's output, from which delta is then computed as well, or nullptr: delta comes from attn_bwd_pre.  dqkv must not lie
+// over O
 void attn_bwd(hipStream_t s, int dtype, const void *dO, const void *qkv, const void *O, const float *lse, float *delta,
               void *dqkv, int64_t B, int64_t T, int64_t H, int64_t dh);
 void embed_bwd(hipStream_t s, int dtype, const void *dx, const int32_t *tok, void *dwte, int64_t S, int64_t d,

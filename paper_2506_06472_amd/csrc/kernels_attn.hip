@@ -16,7 +16,7 @@
 // 218 / 257, 4 x 2048 x 12 x 64 1580 / 2155): the shared form has four times the workgroups of a quarter the length, and the
 // last rows of a causal mask end sooner.  With a row per lane on the vector ALU the first of these took 446.
 // Since then, with delta, dQ and dK/dV in one launch, tiles behind buffer descriptors, row statistics handed round the lanes, and a
-// merge that all wavefronts take part in: 4 x 333 x 4 x 32 43.1 -> 25.0, 2 x 64 x 4 x 32 21.7 -> 10.7, 8 x 512 x 8 x 64 218 -> 165.
+// merge that four wavefronts share: 4 x 333 x 4 x 32 43.1 -> 25.0, 2 x 64 x 4 x 32 21.7 -> 10.7, 8 x 512 x 8 x 64 218 -> 165.
 // Statistics are fp32 (log-sum-exp saved for the backward pass, which recomputes the probabilities from it); every sum has a
 // fixed order; the blocks of dQ and those of dK/dV are workgroups of their own, so that no atomics are needed.
 #include "../../include/teraio.h"
@@ -155,8 +155,8 @@ __device__ __forceinline__ bool place(int64_t heads, int Tn, bool long_last, uns
 }
 // LDS of the merge: the wavefronts' accumulators of one 32-column block
 template <int NW> constexpr int merge_floats() { return NW * 16 * 64; }
-// Sums of the wavefronts' accumulators, in wavefront order, stored to the rows the lanes hold (nullptr: no such row).  Every wavefront
-// sums and stores its share of the groups of four consecutive columns: with all of it in wavefront 0 the others stood idle for the
+// Sums of the wavefronts' accumulators, in wavefront order, stored to the rows the lanes hold (nullptr: no such row).  Wavefronts 0 to 3
+// sum and store one of the four groups of four consecutive columns each: with all of it in wavefront 0 the others stood idle for the
 // longest serial part of a short sequence.  weight[w] is applied to wavefront w's accumulators, scale to the sum.
 template <typename T, int DH, int NW>
 __device__ __forceinline__ void merge_store(const floatx16 (&acc)[DH / 32], float *lds, int wave, int lane, const float (&weight)[NW], float scale,

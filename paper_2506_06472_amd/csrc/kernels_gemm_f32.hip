@@ -13,7 +13,7 @@
 //  * small outputs have too few tiles to fill 256 compute units and too short a contraction to hide a memory latency, so
 //    their tile is 32x32 and the four wavefronts of a workgroup split every contraction tile between them; the four
 //    partial tiles are added in wavefront order.
-// Measured figures stand at the choice of the tile in gemm_f32.
+// Measured figures stand at the choice of the tile, tile_of.
 #include "../../include/teraio.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -364,9 +364,9 @@ template <template <bool, bool> class Tile> void launch(hipStream_t s, bool a_km
 #undef TIO_F32
 }
 
-// The output tile.  All workgroups of these products are on the chip at once, so that its time is that of the compute unit with the most
-// tiles: `rate` us per 64 x 64 x 768 of work, which falls with the number of tiles there are to cover each other's latencies.  us, 64x64 /
-// 64x32 / 32x32, tiles on that unit in brackets:
+// The output tile.  A unit holds three or four workgroups at a time, and these products have few more for it, so that the time is taken
+// as that of the compute unit with the most tiles: us per 64 x 64 x 768 of work (cost's last arguments: one tile on that unit, two, more),
+// which fall with the number of tiles there are to cover each other's latencies.  us, 64x64 / 64x32 / 32x32, tiles on that unit in brackets:
 //   1024 x 3072 x  768  47 ( 3) / 57 ( 6) /  63 (12)      1024 x  768 x 3072  75 ( 1) / 71 ( 2) /  53 ( 3)
 //   3072 x  768 x 1024  58 ( 3) / 56 ( 5) /  62 ( 9)      2048 x  768 x 3072 114 ( 2) / 96 ( 3) / 113 ( 6)
 //   1500 x  900 x 2000  79 ( 2) / 65 ( 3) /  73 ( 6)       512 x 1024 x 1024  28 ( 1) / 22 ( 1) /  17 ( 2)

@@ -960,7 +960,11 @@ int tio_op_attention(void *stream, int32_t dtype, int64_t B, int64_t T, int64_t 
     k::attn_fwd(s, dtype, qkv, o, lse, B, T, H, dh);
     if (dO) {
         if (!delta || !dqkv) return fail(TIO_ERR_INVALID_ARG, "backward needs delta and dqkv");
-        k::attn_bwd(s, dtype, dO, qkv, o, lse, delta, dqkv, B, T, H, dh);
+        // a caller that has no more use for o may have dqkv written over it: its last reader is then the launch of delta alone
+        const uint64_t bytes = (uint64_t)B * T * H * dh * (dtype == TIO_PREC_BF16 ? 2 : 4);
+        const bool over_o = (uintptr_t)o < (uintptr_t)dqkv + 3 * bytes && (uintptr_t)dqkv < (uintptr_t)o + bytes;
+        if (over_o) k::attn_bwd_pre(s, dtype, dO, o, delta, B, T, H, dh);
+        k::attn_bwd(s, dtype, dO, qkv, over_o ? nullptr : o, lse, delta, dqkv, B, T, H, dh);
     }
     HIPCHK(hipGetLastError());
     return TIO_OK;

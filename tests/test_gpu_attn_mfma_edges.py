@@ -82,3 +82,29 @@ def test_gradients_of_keys_at_minus_infinity(B, T, H, dh):
         assert torch.isfinite(a).all(), name
         a, b = a.double(), b.double()
         assert ((a - b).norm() <= 3 * 2.0 ** -8 * b.norm()).item(), name
+
+
+# one launch for both gradients and two, delta in the launch of dQ, of both, in one of its own; o at the start, the end and across
+@pytest.mark.parametrize("dtype,B,T,H,dh", [("bf16", 2, 333, 3, 64), ("bf16", 8, 1000, 9, 64), ("bf16", 4, 300, 16, 128), ("bf16", 8, 1000, 20, 128),
+                                            ("bf16", 2, 200, 3, 32), ("fp32", 2, 333, 3, 32), ("fp32", 2, 200, 3, 64)])
+@pytest.mark.parametrize("at", [0, 2, "across"])
+def test_gradients_written_over_the_output(dtype, B, T, H, dh, at):
+    """o may lie where dqkv goes: the backward pass has the bits that it has with buffers of their own."""
+    import torch
+    import paper_2506_06472_amd as tio
+    print(f"attention, dqkv over o {dtype} B={B} T={T} H={H} dh={dh}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + H)
+    t, n = torch.float32 if dtype == "fp32" else torch.bfloat16, B * T * H * dh
+    qkv, dO = torch.randn(3 * n, device="cuda", generator=g).to(t), torch.randn(n, device="cuda", generator=g).to(t)
+    outs = []
+    for alone in (True, False):
+        buf = torch.full((4 * n,), 7.0, device="cuda", dtype=t)
+        dqkv = buf[:3 * n]
+        o = buf[3 * n:] if alone else buf[n * at:] if at != "across" else buf[3 * n - 64:]
+        lse, delta = (torch.full((B * H * T,), 7.0, device="cuda") for _ in range(2))
+        torch.cuda.synchronize()
+        tio.tio_op_attention(0, dtype, B, T, H, dh, qkv.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), delta.data_ptr(), dqkv.data_ptr())
+        torch.cuda.synchronize()
+        outs.append((dqkv.clone(), lse, delta))
+    for name, a, b in zip(("dqkv", "lse", "delta"), *outs):
+        assert torch.equal(a, b), name
