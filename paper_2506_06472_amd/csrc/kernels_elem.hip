@@ -923,6 +923,12 @@ __device__ __forceinline__ void adamw_at(const AdamwTensor &t, int64_t i0, float
     const int64_t n = t.n;
     if (i0 >= n) return;
     float *theta = master ? master : reinterpret_cast<float *>(w);
+    // which product of each sum is rounded by itself is written out: left to the compiler it changed with the code around it
+    auto update = [&](float &th, float &mj, float &vj, float gj) __attribute__((always_inline)) {
+        mj = fmaf(1.0f - b1, gj, b1 * mj);
+        vj = fmaf((1.0f - b2) * gj, gj, b2 * vj);
+        th = fmaf(-lr, fmaf(wd, th, mj * inv_bc1 / (sqrtf(vj * inv_bc2) + eps)), th);
+    };
     if (i0 + 4 <= n) {
         float gg[4];
         if (sizeof(T) == 4) {
@@ -938,9 +944,9 @@ __device__ __forceinline__ void adamw_at(const AdamwTensor &t, int64_t i0, float
               vv = load_once<STREAM, f32x4>(v + i0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            mm[j] = b1 * mm[j] + (1.0f - b1) * gg[j];
-            vv[j] = b2 * vv[j] + (1.0f - b2) * gg[j] * gg[j];
-            th[j] = th[j] - lr * (mm[j] * inv_bc1 / (sqrtf(vv[j] * inv_bc2) + eps) + wd * th[j]);
+            float t = th[j], mj = mm[j], vj = vv[j];
+            update(t, mj, vj, gg[j]);
+            th[j] = t; mm[j] = mj; vv[j] = vj;
         }
         store_once<STREAM>(th, theta + i0);
         store_once<STREAM>(mm, m + i0);
@@ -948,10 +954,8 @@ __device__ __forceinline__ void adamw_at(const AdamwTensor &t, int64_t i0, float
         if (master) store_once<STREAM>((u32x2){pack_bf16x2(th[0], th[1]), pack_bf16x2(th[2], th[3])}, w + i0);
     } else {
         for (int64_t i = i0; i < n; ++i) {
-            const float gi = to_f32(g[i]);
-            const float mi = b1 * m[i] + (1.0f - b1) * gi;
-            const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-            const float ti = theta[i] - lr * (mi * inv_bc1 / (sqrtf(vi * inv_bc2) + eps) + wd * theta[i]);
+            float ti = theta[i], mi = m[i], vi = v[i];
+            update(ti, mi, vi, to_f32(g[i]));
             m[i] = mi; v[i] = vi; theta[i] = ti;
             if (master) w[i] = from_f32<T>(ti);
         }
