@@ -415,7 +415,7 @@ void gemm_f32_tile(int64_t M, int64_t N, int *rows, int *cols) {
 
 // Both gradients of a linear layer in one launch, where the tiles of both are small (16 or 32 square): such products last
 // about as long as a launch, and neither fills the chip (4.2 + 4.5 us in the tiny GPT step, nine times: that step, with merged updates
-// and delta in the launch of attention backward as well, 332 -> 256 us).
+// and delta in the launch of attention backward as well, 344 -> 268 us).
 bool gemm_f32_pairs(int64_t M0, int64_t N0, int64_t M1, int64_t N1) { return small(tile_of(M0, N0)) && small(tile_of(M1, N1)); }
 
 void gemm_f32_pair(hipStream_t s, const F32Product &dx, const F32Product &dw) {
