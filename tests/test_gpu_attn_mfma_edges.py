@@ -26,6 +26,15 @@ def test_bf16_attention_gradients_in_one_launch_or_two(B, T, H, dh):
     check("bf16", B, T, H, dh, 1)
 
 
+# sixteen rows to a wavefront (few workgroups of 64 rows) and thirty-two, in the forward pass and in the backward one: sequences that end in
+# the first, second and last row of a wavefront's group, in either half of a tile of 32 keys, and tiles of which only later wavefronts have use
+@pytest.mark.parametrize("B,T,H,dh", [(1, 16, 2, 64), (1, 17, 1, 64), (3, 31, 2, 64), (1, 81, 2, 64), (1, 97, 9, 64), (2, 176, 1, 64), (1, 16, 1, 128),
+                                      (1, 17, 2, 128), (1, 47, 2, 128), (2, 81, 1, 128), (1, 113, 9, 128), (1, 240, 1, 128), (8, 177, 54, 64),
+                                      (8, 273, 32, 64), (8, 257, 21, 128), (8, 145, 32, 128)])
+def test_bf16_attention_rows_of_a_wavefront(B, T, H, dh):
+    check("bf16", B, T, H, dh, 1)
+
+
 # orders of the workgroups: all resident with every other row of units turned round (whole rows only; a row short of one), not all
 # resident, heads taken eight and one at a time.  No result depends on the order: each sequence alone gives the same bits
 @pytest.mark.parametrize("B,T,H,dh", [(3, 300, 11, 64), (8, 520, 13, 64), (7, 1000, 5, 64), (8, 1025, 17, 64), (8, 520, 13, 128), (8, 4096, 9, 128)])
