@@ -790,21 +790,33 @@ __global__ void __launch_bounds__(TPB) ce_k(T *__restrict__ logits, const int32_
 
 // Same contract as ce_k, for rows of at most NT*NCH 16-byte chunks: the workgroup keeps its row in registers, so
 // the logits are read once with all of a thread's loads in flight together, and maximum, sum and gradient are three
-// passes over registers.
-template <typename T, int NCH, int NT>
-__global__ void __launch_bounds__(NT) ce_reg_k(T *__restrict__ logits, const int32_t *__restrict__ labels,
+// passes over registers.  Bound: HBM (one read, one write; 5.8 TB/s), as long as one row's exponentials run under another's loads: bf16 rows stay
+// packed between the passes (the compiler would keep them converted, in twice the registers) and are addressed through a descriptor, so
+// that two workgroups of 1024 threads fit a compute unit: 8192 x 50257 344 -> 283 us, 8192 x 32000 (256 threads) 183 -> 171.
+constexpr int NON_TEMPORAL = 2;          // cache policy bit of a buffer access
+template <typename T, int NCH, int NT, bool STREAM, bool PACKED = sizeof(T) == 2>
+__global__ void __launch_bounds__(NT, PACKED && NT == 1024 ? 8 : 1) ce_reg_k(T *__restrict__ logits, const int32_t *__restrict__ labels,
                                                 float *__restrict__ losses, int64_t S, int64_t Vn, int64_t ld, int64_t S_total) {
     constexpr int V = Vec16<T>::N;
     __shared__ float red[NT / 64];
     const int64_t row = blockIdx.x;
     T *xr = logits + row * ld;
     const int nchunk = (int)(ld / V), nv = (int)Vn;
+    const __amdgpu_buffer_rsrc_t r = buffer_over(xr, (uint32_t)(nchunk * 16));
+    const int at = threadIdx.x * 16;
     Vec16<T> a[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
-        const int c = threadIdx.x + NT * i;
-        if (c < nchunk) a[i].load(xr + (int64_t)c * V);
+        a[i].raw = __builtin_bit_cast(decltype(a[i].raw), __builtin_amdgcn_raw_buffer_load_b128(r, at, NT * 16 * i, STREAM ? NON_TEMPORAL : 0));
     }
+    auto keep_packed = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < (PACKED ? NCH : 0); ++i) {
+            tio_u32x4 w = __builtin_bit_cast(tio_u32x4, a[i].raw);
+            asm volatile("" : "+v"(w));
+            a[i].raw = __builtin_bit_cast(decltype(a[i].raw), w);
+        }
+    };
     const int32_t lab = labels[row];
     const float x_lab = threadIdx.x == 0 ? to_f32(xr[lab]) : 0.f;      // read long before the row is overwritten
     // only the last chunk that holds logits can be partly padding: the others take the paths without column tests
@@ -825,6 +837,7 @@ __global__ void __launch_bounds__(NT) ce_reg_k(T *__restrict__ logits, const int
         }
     }
     const float M = block_max<NT / 64>(m, red);
+    keep_packed();
     const float kM = -M * L2E;
     float sum = 0.f;
 #pragma unroll
@@ -842,6 +855,7 @@ __global__ void __launch_bounds__(NT) ce_reg_k(T *__restrict__ logits, const int
         }
     }
     const float tot = block_sum<NT / 64>(sum, red);
+    keep_packed();
     const float lse = M + logf(tot);
     if (threadIdx.x == 0) losses[row] = lse - x_lab;
     // gradient of the mean loss over the whole batch: exp(x - lse) / S_total as one exponential, the 1/S_total folded
@@ -863,7 +877,8 @@ __global__ void __launch_bounds__(NT) ce_reg_k(T *__restrict__ logits, const int
 #pragma unroll
                 for (int j = 0; j < V; ++j) if (c * V + j >= nv) f[j] = 0.f;
             }
-            a[i].set(f); a[i].store(xr + (int64_t)c * V);
+            a[i].set(f);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(tio_u32x4, a[i].raw), r, at, NT * 16 * i, STREAM ? NON_TEMPORAL : 0);
         }
     }
 }
@@ -1127,17 +1142,20 @@ void rope(hipStream_t s, int dtype, void *qkv, int64_t B, int64_t Tn, int64_t H,
 
 void ce_fwd_bwd(hipStream_t s, int dtype, void *logits, const int32_t *labels, float *losses, int64_t S, int64_t V,
                 int64_t ld, int64_t S_total) {
-#define TIO_CE_REG(NCH, NT) ce_reg_k<T, NCH, NT><<<(unsigned)S, NT, 0, s>>>((T *)logits, labels, losses, S, V, ld, S_total)
+#define TIO_CE_REG(NCH, NT, STREAM) ce_reg_k<T, NCH, NT, STREAM><<<(unsigned)S, NT, 0, s>>>((T *)logits, labels, losses, S, V, ld, S_total)
     TIO_DISPATCH(dtype, {
         // 16-byte chunks per row; NT threads take NCH each.  Long rows are spread over 1024 threads: with 32 chunks in the
         // registers of each of 256, too few workgroups fit a compute unit for one row's exponentials to overlap another's loads
-        // (8192 rows of 50257 in bf16: 486 us, 3.4 TB/s; with 1024 threads 353 us, 4.7 TB/s).  The order of the sum differs between
-        // the two, within fp32 rounding
+        // (8192 rows of 50257 in bf16, before the rows stayed packed: 486 us; with 1024 threads 353).  The order of the sum differs between
+        // the two, within fp32 rounding.  Long rows of 256 MiB together go past the caches, which would not hold them until they are
+        // used again: this launch takes the same time, the product that reads them 593 -> 567 us (with rows of 32000, 8192 of them, it
+        // gains nothing and this launch loses 4 %)
         const int64_t chunks = ld / Vec16<T>::N;
-        if (chunks <= 256 * 4) TIO_CE_REG(4, 256);
-        else if (chunks <= 256 * 8) TIO_CE_REG(8, 256);
-        else if (chunks <= 256 * 16) TIO_CE_REG(16, 256);
-        else if (chunks <= 1024 * 8) TIO_CE_REG(8, 1024);
+        if (chunks <= 256 * 4) TIO_CE_REG(4, 256, false);
+        else if (chunks <= 256 * 8) TIO_CE_REG(8, 256, false);
+        else if (chunks <= 256 * 16) TIO_CE_REG(16, 256, false);
+        else if (chunks <= 1024 * 8 && S * chunks >= (int64_t)1 << 24) TIO_CE_REG(8, 1024, true);
+        else if (chunks <= 1024 * 8) TIO_CE_REG(8, 1024, false);
         else ce_k<T><<<(unsigned)S, TPB, 0, s>>>((T *)logits, labels, losses, S, V, ld, S_total);
     });
 #undef TIO_CE_REG

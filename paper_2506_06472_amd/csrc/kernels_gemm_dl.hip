@@ -288,7 +288,7 @@ __device__ __forceinline__ void store8(float *dst, const float (&v)[8], int n) {
     if (n > 4) *reinterpret_cast<float4 *>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
 
-template <int TM, int TN, bool BIAS, bool RESID, bool WS>
+template <int TM, int TN, bool BIAS, bool RESID, bool WS, bool STREAM>
 __device__ __forceinline__ void store_inside(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
                                              const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
                                              float *__restrict__ ws, int split) {
@@ -330,7 +330,10 @@ __device__ __forceinline__ void store_inside(const floatx4 (&acc)[TM][TN], float
             if (WS) { store8(ws + out[p] + (int64_t)i * 16 * ldo, x, 8); continue; }
             if (BIAS) add8(x, b[p]);
             if (RESID) add8(x, now[p]);
-            *reinterpret_cast<uint4 *>(C + out[p] + (int64_t)i * 16 * ldo) = pack8(x);
+            const uint4 w = pack8(x);
+            uint16_t *to = C + out[p] + (int64_t)i * 16 * ldo;
+            if (STREAM) __builtin_nontemporal_store((tio_u32x4){w.x, w.y, w.z, w.w}, reinterpret_cast<tio_u32x4 *>(to));
+            else *reinterpret_cast<uint4 *>(to) = w;
         }
     }
 }
@@ -398,19 +401,24 @@ __device__ __forceinline__ void store_edge(const floatx4 (&acc)[TM][TN], float *
     batch(std::integral_constant<int, 0>{});
     if constexpr (TM > BATCH) batch(std::integral_constant<int, BATCH>{});
 }
+// An output larger than the memory-side cache (256 MiB) is stored past the caches: nothing of it would be found there, and dirty lines
+// take the operands' place.  us: 8192 x 50176 x 768 608 -> 557, 8192 x 50257 x 768 667 -> 588, 8192 x 22016 x 4096 1011 -> 996, 8192 x 32000 x
+// 4096 1482 both; with 100 MB (1021 x 50257 x 768) it would be 101 -> 104.
+constexpr int64_t STREAMED = (int64_t)1 << 27;          // elements
 template <int TM, int TN>
 __device__ __forceinline__ void store_tile(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
                                            const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
                                            float *__restrict__ ws, int split) {
     const bool inside = mw + TM * 16 <= M && nw + TN * 16 <= N;
     const bool wide = ldc % 8 == 0 && (resid == nullptr || ldr % 8 == 0);
-#define TIO_STORE(BIAS, RESID, WS) store_inside<TM, TN, BIAS, RESID, WS>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split)
-    if (inside && ws) TIO_STORE(false, false, true);
+#define TIO_STORE(BIAS, RESID, WS, STREAM) store_inside<TM, TN, BIAS, RESID, WS, STREAM>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split)
+    if (inside && ws) TIO_STORE(false, false, true, false);
     else if (inside && wide) {
-        if (bias && resid) TIO_STORE(true, true, false);
-        else if (bias) TIO_STORE(true, false, false);
-        else if (resid) TIO_STORE(false, true, false);
-        else TIO_STORE(false, false, false);
+        if (bias && resid) TIO_STORE(true, true, false, false);
+        else if (bias) TIO_STORE(true, false, false, false);
+        else if (resid) TIO_STORE(false, true, false, false);
+        else if (M * N >= STREAMED) TIO_STORE(false, false, false, true);
+        else TIO_STORE(false, false, false, false);
     } else if (mw < M && nw < N) store_edge<TM, TN>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split);
 #undef TIO_STORE
 }

@@ -115,3 +115,9 @@ def test_split_contraction_remainders(tile, M, N, K, splits, rowsum):
 @pytest.mark.parametrize("M,N,K", [(4096, 4096, 1024), (4095, 3841, 1031), (8100, 8170, 65)])
 def test_row_sums_of_the_large_tile_in_every_layout(M, N, K, a_km, b_km):
     _run(M, N, K, a_km, b_km, rowsum=True, tile=(256, 256))
+
+
+# an output of just under 2^27 elements, and of as many, which is stored past the caches: parts inside it and at its ragged ends
+@pytest.mark.parametrize("M,N", [(4095, 32776), (4096, 32768), (4099, 32777)])
+def test_outputs_larger_than_the_caches(M, N):
+    _run(M, N, 72, 0, 0)
