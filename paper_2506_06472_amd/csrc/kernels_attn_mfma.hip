@@ -416,24 +416,26 @@ __global__ void __launch_bounds__(NT, DH == 64 || NG == 1 ? 4 : 3) attn_fwd_mfma
 }
 
 // ------------------------------------------------------------------------------------------ dQ
+// Sum of the products of eight elements, in order.
+__device__ __forceinline__ float chunk_dot(const bf16x8 &g, const bf16x8 &o) {
+    Frag a, b;
+    a.v = g;
+    b.v = o;
+    const uint32_t x[4] = {a.u.x, a.u.y, a.u.z, a.u.w}, y[4] = {b.u.x, b.u.y, b.u.z, b.u.w};
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        sum = fmaf(__uint_as_float(x[i] << 16), __uint_as_float(y[i] << 16), sum);
+        sum = fmaf(__uint_as_float(x[i] & 0xffff0000u), __uint_as_float(y[i] & 0xffff0000u), sum);
+    }
+    return sum;
+}
 // Sum over the head dimension of two rows of which the four lane groups have the fragments, the same in all of them: in the order of
 // attn_bwd_pre_k, whose bits these are (chains of eight elements, then pairs).
 template <int KS> __device__ __forceinline__ float row_dot(const bf16x8 (&g)[KS], const bf16x8 (&o)[KS]) {
     float p[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        Frag a, b;
-        a.v = g[ks];
-        b.v = o[ks];
-        const uint32_t x[4] = {a.u.x, a.u.y, a.u.z, a.u.w}, y[4] = {b.u.x, b.u.y, b.u.z, b.u.w};
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sum = fmaf(__uint_as_float(x[i] << 16), __uint_as_float(y[i] << 16), sum);
-            sum = fmaf(__uint_as_float(x[i] & 0xffff0000u), __uint_as_float(y[i] & 0xffff0000u), sum);
-        }
-        p[ks] = sum_halves(sum_neighbours(sum));
-    }
+    for (int ks = 0; ks < KS; ++ks) p[ks] = sum_halves(sum_neighbours(chunk_dot(g[ks], o[ks])));
 #pragma unroll
     for (int o2 = 1; o2 < KS; o2 *= 2)
 #pragma unroll
@@ -613,12 +615,27 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
 // exclusive or each at head size 128, each of two wavefronts fetches one of the statistics, and the lane index is computed where it is used.
 // The tiles behind the diagonal run through a loop of their own, without mask and branch; at head size 64 a second loop gains nothing
 // over a mask of two instructions.
+// The same sum with a row spread over four neighbouring lanes, CH chunks of eight elements each, the same in all of them.
+template <int CH> __device__ __forceinline__ float quad_dot(const bf16x8 (&g)[CH], const bf16x8 (&o)[CH]) {
+    float p[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) p[c] = chunk_dot(g[c], o[c]);
+#pragma unroll
+    for (int o2 = 1; o2 < CH; o2 *= 2)
+#pragma unroll
+        for (int c = 0; c < CH; c += 2 * o2) p[c] += p[c + o2];
+    auto add_from = [](float x, auto LANES) {
+        return x + __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), LANES(), 0xf, 0xf, true));
+    };
+    const float pair = add_from(p[0], std::integral_constant<int, 0xB1>{});         // lanes 1 0 3 2
+    return add_from(pair, std::integral_constant<int, 0x4E>{});                    // lanes 2 3 0 1
+}
 // V rows in LDS instead of registers (NG: groups of 16 key rows of a wavefront)
 template <int DH, int NG> constexpr bool dkv_v_in_lds() { return DH == 128 && NG == 2; }
 template <int DH> constexpr int dkv_waves() { return DH == 128 ? 8 : 4; }
-template <int DH, int NW, int NG>
-__device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
-                                         const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H,
+template <int DH, int NW, int NG, bool DELTA>
+__device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const uint16_t *__restrict__ O,
+                                         const float *__restrict__ lse, const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H,
                                          float scale, Order order, unsigned block) {
     constexpr int KS = DH / 32, DT = DH / 16, TE = 64 * DH, RING = 4, TR = 4, KEYS = NW * 16 * NG;
     constexpr bool VLDS = dkv_v_in_lds<DH, NG>(), ONE_LOOP = DH == 64;
@@ -666,15 +683,34 @@ __device__ __forceinline__ void dkv_rows(const uint16_t *__restrict__ dO, const 
 
     // Statistics of row i0 + lane, one tile ahead, log-sum-exp in wavefront 0 and delta in wavefront 1: through descriptors of the head's
     // rows (rows past the sequence read zero; no addresses to keep in registers), used only where they go to LDS, a tile after their fetch.
-    const __amdgpu_buffer_rsrc_t rsS = buffer_over((wave == 0 ? lse : delta) + bh * Tn, (uint32_t)Tn * 4);
-    const float to_lds = wave == 0 ? LOG2E : 1.f;
+    // DELTA: four lanes to a row fetch its dO and O instead and multiply them.
+    const __amdgpu_buffer_rsrc_t rsS = buffer_over((DELTA || wave == 0 ? lse : delta) + bh * Tn, (uint32_t)Tn * 4);
+    const float to_lds = DELTA || wave == 0 ? LOG2E : 1.f;
+    constexpr int STATS = DELTA ? 1 : 2, CH = DH / 32;                    // wavefronts that fetch statistics; chunks of a row to a lane
+    static_assert(!DELTA || NW == 4, "four lanes to each of 64 rows");
     float st = 0.f;
+    bf16x8 go[DELTA ? CH : 1], oo[DELTA ? CH : 1];
+    const __amdgpu_buffer_rsrc_t rsD = head_rsrc(dO + b * Tn * d + h * DH, Tn, d, DH), rsO = head_rsrc((DELTA ? O : dO) + b * Tn * d + h * DH, Tn, d, DH);
     float *stats = reinterpret_cast<float *>(smem + 2 * BUF + (VLDS ? KEYS * DH : 0));
     auto load_stats = [&](int i0) {
-        if (wave < 2) st = buffer_load4(rsS, (uint32_t)(i0 + lane_here()) * 4);
+        if (wave < STATS) st = buffer_load4(rsS, (uint32_t)(i0 + lane_here()) * 4);
+        if (DELTA) {
+            const int ln = lane_here();
+            const uint32_t at = (uint32_t)(i0 + wave * 16 + (ln >> 2)) * ldg + (ln & 3) * CH * 16;
+#pragma unroll
+            for (int c = 0; c < (DELTA ? CH : 0); ++c) {
+                go[c] = buf_frag(rsD, at + c * 16);
+                oo[c] = buf_frag(rsO, at + c * 16);
+            }
+        }
     };
     auto store_stats = [&](int buf) {
-        if (wave < 2) stats[buf * 128 + wave * 64 + lane_here()] = st * to_lds;
+        if (wave < STATS) stats[buf * 128 + wave * 64 + lane_here()] = st * to_lds;
+        if (DELTA) {
+            const float sum = quad_dot<DELTA ? CH : 1>(go, oo);
+            const int ln = lane_here();
+            if ((ln & 3) == 0) stats[buf * 128 + 64 + wave * 16 + (ln >> 2)] = sum;
+        }
     };
     auto load_tile = [&](int i0, int buf) {
         const uint32_t at = lds0 + (uint32_t)buf * BUF * 2;
@@ -823,19 +859,20 @@ template <int DH>
 __global__ void __launch_bounds__(dkv_waves<DH>() * 64, DH == 64 ? 3 : 2)
     attn_bwd_dkv_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
                         const float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order) {
-    dkv_rows<DH, dkv_waves<DH>(), 2>(dO, qkv, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
+    dkv_rows<DH, dkv_waves<DH>(), 2, false>(dO, qkv, nullptr, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
 }
 
 // Both kernels' blocks in one launch, those of key rows first: for sequences whose blocks leave the chip room, where each of the two
-// kernels lasts as long as its longest chain of tiles.  The same rows to a block on either side; delta comes from a launch of its own, and
-// every output has the bits of the two launches.
-template <int DH, int NW, int NG>
+// kernels lasts as long as its longest chain of tiles.  The same rows to a block on either side; every output has the bits of the two
+// launches.  Delta comes from a launch of its own, or (DELTA) both kinds of blocks multiply dO and O themselves: the blocks of query rows
+// theirs, which they write, and those of key rows all that they meet, a tile ahead.
+template <int DH, int NW, int NG, bool DELTA>
 __global__ void __launch_bounds__(NW * 64, NG == 1 ? 2 : DH == 64 ? 3 : 2)
-    attn_bwd_both_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const float *__restrict__ lse,
+    attn_bwd_both_mfma_k(const uint16_t *__restrict__ dO, const uint16_t *__restrict__ qkv, const uint16_t *__restrict__ O, const float *__restrict__ lse,
                          float *__restrict__ delta, uint16_t *__restrict__ dqkv, int64_t Bn, int64_t Tn, int64_t H, float scale, Order order,
                          unsigned blocks) {
-    if (blockIdx.x < blocks) dkv_rows<DH, NW, NG>(dO, qkv, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
-    else dq_rows<DH, NW, NG>(dO, qkv, nullptr, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x - blocks);
+    if (blockIdx.x < blocks) dkv_rows<DH, NW, NG, DELTA>(dO, qkv, O, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x);
+    else dq_rows<DH, NW, NG>(dO, qkv, DELTA ? O : nullptr, lse, delta, dqkv, Bn, Tn, H, scale, order, blockIdx.x - blocks);
 }
 
 template <int DH> constexpr size_t fwd_smem() { return (size_t)3 * 2 * 32 * DH * 2; }      // three pairs of tiles
@@ -901,8 +938,9 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
     if (!attr_set) {
         (void)hipFuncSetAttribute((const void *)attn_bwd_dq_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kv_smem<128>());
         (void)hipFuncSetAttribute((const void *)attn_bwd_dkv_mfma_k<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, dkv_waves<128>(), 2>());
-        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 8, 2>());
-        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 4, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 4, 1>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 8, 2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 8, 2>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 4, 1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 4, 1>());
+        (void)hipFuncSetAttribute((const void *)attn_bwd_both_mfma_k<128, 4, 1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dkv_smem<128, 4, 1>());
         attr_set = true;
     }
     // One launch for both gradients while its workgroups are at most a little more than the chip holds at once, with 16 rows to a
@@ -916,13 +954,23 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
     //   32 rows, two launches / one
     //     heads of 64:  1 x 4096, 16 203 / 182           8 x 1024, 8 62.4 / 57.9          4 x 500, 31 41.1 / 39.5
     //     of 128:       4 x 1024, 16 112 / 104           1 x 4096, 16 362 / 304           2 x 2000, 15 191 / 165
+    // Delta inside that launch while the tiles are few: the products are done over by every block of keys, the launch they replace
+    // takes 3 us and two more between launches.  us, a launch of its own / inside: 5 x 145, 22 heads of 64 16.3 / 13.6, 8 x 512, 12 37.9 / 35.0,
+    // 1 x 1024, 12 35.8 / 35.1, 1 x 4096, 8 123 / 131; 4 x 100, 6 heads of 128 14.9 / 12.8, 4 x 512, 16 47.5 / 44.8, 1 x 1024, 5 42.5 / 45.9.
+    constexpr int64_t OWN_DELTA = 65536;                  // sequence length times head size
+#define TIO_ATTN_BOTH_AS(DH, NW, NG, DELTA)                                                                                                    \
+    attn_bwd_both_mfma_k<DH, NW, NG, DELTA><<<2 * l.grid.x, NW * 64, dkv_smem<DH, NW, NG>(), s>>>(                                             \
+        (const uint16_t *)dO, (const uint16_t *)qkv, (const uint16_t *)O, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale, l.order, l.grid.x)
 #define TIO_ATTN_BOTH(DH, NW, NG, WORKGROUPS)                                                                                                  \
     {                                                                                                                                          \
         const Launch l(B * H, Tn, DH, NW * 16 * NG, NG == 1 ? 2 : DH == 64 ? 3 : 1);                                                           \
         if (2 * (int64_t)l.grid.x <= WORKGROUPS) {                                                                                             \
+            if (NG == 1 && O && Tn * DH <= OWN_DELTA) {                                                                                        \
+                TIO_ATTN_BOTH_AS(DH, NW, NG, (NG == 1));                                                                                       \
+                return;                                                                                                                        \
+            }                                                                                                                                  \
             if (O) attn_bwd_pre(s, TIO_PREC_BF16, dO, O, delta, B, Tn, H, DH);                                                                 \
-            attn_bwd_both_mfma_k<DH, NW, NG><<<2 * l.grid.x, NW * 64, dkv_smem<DH, NW, NG>(), s>>>(                                            \
-                (const uint16_t *)dO, (const uint16_t *)qkv, lse, delta, (uint16_t *)dqkv, B, Tn, H, scale, l.order, l.grid.x);                \
+            TIO_ATTN_BOTH_AS(DH, NW, NG, false);                                                                                               \
             return;                                                                                                                            \
         }                                                                                                                                      \
     }
@@ -944,6 +992,7 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
         TIO_ATTN_BWD(128, 2, 1)
     }
 #undef TIO_ATTN_BOTH
+#undef TIO_ATTN_BOTH_AS
 #undef TIO_ATTN_BWD
 }
 
