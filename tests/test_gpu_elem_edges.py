@@ -70,3 +70,21 @@ def test_sums_over_many_tokens(T):
 def test_optimizer_where_its_accesses_become_non_temporal(V, precision):
     from test_gpu_train import test_optimizer_state_follows_the_oracle_from_the_gpu_gradients as check
     check(dict(arch="gpt", L=1, d=64, H=1 if precision == "bf16" else 2, f=128, V=V, T=24, B=1, precision=precision, lr=1e-3))
+
+
+# rotations where a thread takes one row, two (from 1023 rows), four, and sixteen (from 8177), whole groups of rows and not
+@pytest.mark.parametrize("B", [1, 127, 128, 255, 256, 257, 1023, 1025])
+def test_rotations_of_few_and_many_rows(B):
+    import paper_2506_06472_amd as tio
+    print(f"rotations, {8 * B} rows", flush=True)
+    cfg = dict(arch="llama", L=1, d=64, H=2, f=128, V=300, T=8, B=B, precision="fp32", lr=1e-3)
+    params, tok, lab = make_inputs(cfg, seed=1)
+    pe = plans_for(cfg)[2].export()
+    ctx = tio.tio_ctx_create(cfg, pe["arena_needed"], pe["host_needed"] + (1 << 20), 0)
+    ctx.tio_params_load(params)
+    loss = ctx.tio_train_step(tok, lab, None, capture_grads=True)["loss"]
+    ref, grads = om.forward_backward(cfg, params, tok, lab)
+    assert abs(loss - ref) <= 1e-5 * abs(ref), (loss, ref)
+    g, r = ctx.tio_grads_read("l0.w_qkv").astype(np.float64).ravel(), grads["l0.w_qkv"].ravel()
+    assert np.abs(g - r).max() <= 1e-4 * np.abs(r).max(), np.abs(g - r).max() / np.abs(r).max()
+    ctx.close()
