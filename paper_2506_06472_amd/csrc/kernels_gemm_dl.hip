@@ -911,8 +911,12 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
 
 // A long contraction with a small output leaves most compute units without a tile, and the small tiles that keep more of them busy fetch
 // more than a unit can load.  Cut into ranges it costs the partials' way to memory and back, a launch and the events around the
-// scratch space, and has to promise a seventh for that (the launch and the events take host time too).  us, in one range / cut:
+// scratch space, and has to promise a seventh for that (the launch and the events take host time too), or a twentieth of a product of
+// 100 us and more: there the costs above, made from shorter ones, promise too little (they know 480 us of the first one's 653).  us, in
+// one range / cut:
 //   1021 x 768 x 50257 264 / 107 (eight)    64 x 1024 x 22016 99 / 25     200 x 300 x 15000 68 / 17     300 x 300 x 8000 36 / 15
+//   8192 x 768 x 50257 653 / 562 (two)      8192 x 1024 x 32000 503 / 379 (two)    4096 x 1024 x 32000 343 / 206 (four)    8192 x 512 x 20000 202 / 146
+//   4096 x 2048 x 32000 494 / 374 (two)     4096 x 1792 x 12940 187 / 150 (two); left alone 8192 x 1280 x 16000 260 / 301, 8192 x 768 x 8192 85 / 89
 // and left alone, though a cut with a workspace at hand gains something: 128 x 2000 x 4000 19.0 / 12.6 + 3, 1024 x 2048 x 8192 54 / 44 + 3,
 // 1000 x 1000 x 10000 45 / 37 + 3; 768 x 768 x 1900 10.8 / 14.3 + 3.
 int gemm_bf16_splits(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t bytes) {
@@ -921,7 +925,7 @@ int gemm_bf16_splits(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int6
     double whole = 0;
     if (!choose(a_km, b_km, M, N, K, lda, ldb, rowsum, 1, &whole)) return 1;
     int best = 1;
-    double best_cost = 0.85 * whole;
+    double best_cost = (whole < 100 ? 0.85 : 0.95) * whole;
     for (int s = 2; s <= 8 && K >= 256 * s; s *= 2) {
         const int64_t partials = s * (M * partial_ld(N) + M) * 4;
         double cost = 0;

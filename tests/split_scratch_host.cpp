@@ -123,13 +123,40 @@ bool leaves_streams_of_other_devices_alone() {
     if (!product(stream(1)) || launches != 1) { std::printf("%d launches\n", launches); return false; }
     return event_calls == before && product(nullptr) && launches == 2;
 }
+// Products whose partials take one, two and all four parts: every part that one takes up has been left by its last user
+bool large_products_take_several_parts() {
+    constexpr int64_t PART = (int64_t)32 << 20;
+    struct Shape { int64_t M, N, K; int parts; };
+    const Shape shapes[] = {{200, 300, 15000, 1}, {8192, 768, 50257, 2}, {4096, 1024, 32000, 4}, {300, 300, 8000, 1}, {4096, 1792, 12940, 2}};
+    Use last[4] = {};
+    unsigned seen = 0;
+    for (int i = 0; i < 200; ++i) {
+        const Shape &p = shapes[i * 7 % 5];
+        const hipStream_t s = stream(i * 5 % STREAMS);
+        launches = 0;
+        tio::k::gemm(s, BF16, false, true, p.M, p.N, p.K, image, (p.K + 7) / 8 * 8, image, p.N + 8, nullptr, nullptr, 0, image, p.N, nullptr, nullptr, 1, false);
+        if (launches != 2) { std::printf("%d launches\n", launches); return false; }
+        const int64_t first = (static_cast<unsigned char *>(last_first_arg) - image) / PART;
+        if (first % p.parts || first + p.parts > 4) { std::printf("part %d of %d\n", (int)first, p.parts); return false; }
+        for (int64_t k = first; k < first + p.parts; ++k) {
+            if (last[k].stream && streams[s][last[k].stream] < last[k].operations) {
+                std::printf("part %d is taken up while another stream may be using it\n", (int)k);
+                return false;
+            }
+            last[k] = {s, streams[s][s]};
+            seen |= 1u << k;
+        }
+    }
+    return seen == 15;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
-    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing, leaves_streams_of_other_devices_alone};
+    bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing, leaves_streams_of_other_devices_alone,
+                              large_products_take_several_parts};
     const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
-                                 "leaves_streams_of_other_devices_alone"};
+                                 "leaves_streams_of_other_devices_alone", "large_products_take_several_parts"};
     for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
         if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
     return 2;

@@ -17,6 +17,14 @@ def test_long_contractions(M, N, K, a_km, b_km, rowsum, epilogue, pad):
     _run(M, N, K, a_km, b_km, rowsum=rowsum, epilogue=epilogue, pad=pad)
 
 
+# partials of two parts of the scratch space and of all four, ragged and not
+@pytest.mark.parametrize("M,N,K,a_km,b_km,rowsum,epilogue", [
+    (4096, 1792, 12940, 0, 1, False, ()), (4093, 1790, 12941, 0, 1, False, ("bias", "resid")), (4096, 1024, 32000, 0, 1, False, ()),
+    (2050, 2047, 16001, 1, 1, True, ())])
+def test_large_partials(M, N, K, a_km, b_km, rowsum, epilogue):
+    _run(M, N, K, a_km, b_km, rowsum=rowsum, epilogue=epilogue)
+
+
 class _Product:
     def __init__(self, torch, M, N, K, seed):
         g = torch.Generator(device="cuda").manual_seed(seed)
@@ -116,3 +124,21 @@ def test_under_graph_capture():
         assert torch.equal(out, first)
         assert not torch.equal(out, eager)
         assert all(torch.equal(w, g) for w, g in zip(want, got))
+
+
+def test_products_of_one_part_and_of_several_on_many_streams():
+    import torch
+    products = [_Product(torch, M, N, K, i) for i, (M, N, K) in enumerate(
+        [(200, 304, 15000), (4096, 1792, 12940), (216, 304, 15000), (4096, 1024, 32000), (232, 304, 15000), (2048, 1792, 12940)])]
+    want = [p.out() for p in products]
+    for p, w in zip(products, want):
+        p.run(w)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in products]
+    got = [[p.out() for _ in range(3)] for p in products]
+    for j in range(3):
+        for i, p in enumerate(products):
+            p.run(got[i][j], streams[(i + j) % 6].cuda_stream)
+    torch.cuda.synchronize()
+    for w, outs in zip(want, got):
+        assert all(torch.equal(w, o) for o in outs)
