@@ -121,3 +121,12 @@ def test_row_sums_of_the_large_tile_in_every_layout(M, N, K, a_km, b_km):
 @pytest.mark.parametrize("M,N", [(4095, 32776), (4096, 32768), (4099, 32777)])
 def test_outputs_larger_than_the_caches(M, N):
     _run(M, N, 72, 0, 0)
+
+
+# products in two launches, whole rounds of tiles and what is left: cut by columns and by rows, what is left ragged and less than a tile
+@pytest.mark.parametrize("M,N,K,a_km,b_km,rowsum,epilogue,pad", [
+    (1021, 50257, 768, 0, 0, False, ("bias", "resid"), 0), (1021, 50261, 770, 0, 0, False, ("resid",), 4), (1792, 9664, 1000, 0, 1, False, ("bias",), 0),
+    (50257, 768, 1021, 1, 1, True, (), 0), (16001, 3130, 1161, 1, 1, True, (), 0), (4224, 12277, 1200, 0, 0, False, (), 4),
+    (6200, 8449, 1000, 1, 0, False, ("bias", "resid"), 0), (2508, 6720, 3968, 0, 1, False, ("bias", "resid"), 0)])
+def test_products_in_two_launches(M, N, K, a_km, b_km, rowsum, epilogue, pad):
+    _run(M, N, K, a_km, b_km, rowsum=rowsum, epilogue=epilogue, pad=pad)
