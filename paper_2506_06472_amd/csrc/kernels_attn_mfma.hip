@@ -917,12 +917,13 @@ void attn_fwd_mfma(hipStream_t s, const void *qkv, void *o, float *lse, int64_t 
         attn_fwd_mfma_k<DH, NG><<<l.grid, NT, fwd_smem<DH>(), s>>>((const uint16_t *)qkv, (uint16_t *)o, lse, B, Tn, H, scale, l.order);       \
     }
     // Sixteen rows to a wavefront while the chip holds about all workgroups of 64 rows at once: half the work in a tile, where the chain
-    // of a wavefront's tiles is what counts; more of them would load K and V twice as often.  us, 32 / 16 rows (workgroups of 64):
-    //   heads of 64:  8 x  192,  7  5.6 /  5.0 (168)    1 x 4096,  8 53.6 / 41.2 (512)    4 x 1024, 12 17.9 / 14.3 (768)
-    //                 2 x 2048, 20 34.4 / 33.0 (1280)   8 x 1024, 12 21.2 / 22.2 (1536)   8 x  256, 52 13.4 / 14.6 (1664)
-    //   of 128:       4 x  333,  6 10.3 /  7.8 (144)    1 x 2048,  8 39.8 / 28.5 (256)    8 x  512, 10 16.8 / 13.9 (640)
-    //                 8 x  256, 26 13.5 / 15.1 (832)    8 x  400, 16 16.0 / 16.4 (896)    4 x 1024, 16 27.2 / 29.0 (1024)
-    const bool one = B * H * ((Tn + 63) / 64) <= (dh == 64 ? 1280 : 768);
+    // of a wavefront's tiles is what counts; more of them would load K and V twice as often.  us, 32 / 16 rows (workgroups of 64, the heads
+    // rounded up to the XCDs: one with a head more than the others decides):
+    //   heads of 64:  8 x  192,  7  5.6 /  5.0 (168)    1 x 4096,  9 54.5 / 44.1 (1024)   3 x 2000, 13 29.9 / 29.7 (1280)
+    //                 2 x 2048, 20 34.4 / 33.0 (1280)   4 x 3904,  5 57.8 / 59.3 (1464)   8 x 1024, 12 21.2 / 22.2 (1536)
+    //   of 128:       4 x  333,  6 10.3 /  7.8 (144)    1 x 2048,  8 39.8 / 28.5 (256)    7 x  868,  8 23.3 / 19.6 (784)
+    //                 8 x  256, 26 13.5 / 15.1 (832)    4 x 1024, 16 27.2 / 29.0 (1024)   1 x 4000,  9 72.7 / 65.1 (1008)
+    const bool one = Launch(B * H, Tn, dh, 64, 1).grid.x <= (dh == 64 ? 1280 : Tn < 2048 ? 800 : 1024);
     if (dh == 64) {
         if (one) TIO_ATTN_FWD(64, 1) else TIO_ATTN_FWD(64, 2)
     } else {
