@@ -335,7 +335,7 @@ int tio_step_timeline(tio_ctx *ctx, int64_t *kernel_begin, int64_t *kernel_end, 
  * splits > 1 (bf16, no bias/resid, N multiple of 4) cuts the contraction into `splits` ranges:
  * workspace (device, fp32, splits*(M*N+M) floats) receives the partial tiles and a second launch
  * adds them in range order; splits = 1 ignores workspace.  With splits = 1 the library itself cuts a bf16 product with a long
- * contraction and a small output, of any operands and sizes, into 2, 4 or 8 ranges: the partial tiles go to an array of its device
+ * contraction, of any operands and sizes whose partial tiles fit, into 2, 4 or 8 ranges: the partial tiles go to an array of its device
  * image (128 MiB on every GPU it runs on, shared safely between streams and threads).  On a stream under graph capture, or of
  * another device than the current one, it does not: such a call has the bits of one range, and takes the time of one. */
 int tio_op_gemm(void *stream, int32_t dtype, int32_t a_kmajor, int32_t b_kmajor,
@@ -344,7 +344,8 @@ int tio_op_gemm(void *stream, int32_t dtype, int32_t a_kmajor, int32_t b_kmajor,
                 const void *bias, const void *resid, int64_t ldr, void *C, int64_t ldc, void *rowsum,
                 void *workspace, int32_t splits);
 /* Measuring aid, host only: the output tile (rows x columns) that tio_op_gemm takes for a bf16 product, with or without row sums and
- * with its contraction in `splits` ranges (workspace given, no bias / resid; 1: taken in one range); 0 x 0: the kernel with 64-bit addressing. */
+ * with its contraction in `splits` ranges (workspace given, no bias / resid; 1: taken in one range), of a product in two launches that of the
+ * first; 0 x 0: the kernel with 64-bit addressing. */
 int tio_op_gemm_tile(int32_t a_kmajor, int32_t b_kmajor, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int32_t rowsum,
                      int32_t splits, int32_t *out_rows, int32_t *out_cols);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses

@@ -1,7 +1,8 @@
 // Building blocks shared by the MFMA kernels (GEMM, attention): vector types of the
-// v_mfma_f32_32x32x16_bf16 operands and the staging of operand tiles global -> registers -> LDS.
+// bf16 operands and the staging of operand tiles global -> registers -> LDS.
 //
-// Operand layout of the instruction D[32x32] += A[32x16] . B[16x32]: lane l supplies row (A) or column (B)
+// Operand layout of v_mfma_f32_32x32x16_bf16, D[32x32] += A[32x16] . B[16x32] (v_mfma_f32_16x16x32_bf16 beside the kernels that
+// take it): lane l supplies row (A) or column (B)
 // l%32 and the eight contraction slots 8*(l/32) .. +7; D: lane l owns column l%32 and rows
 // 8*(r/4) + 4*(l/32) + r%4 for register r = 0..15.  Any assignment of contraction elements to slots is
 // valid as long as A and B use the same one.
