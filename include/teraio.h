@@ -335,8 +335,9 @@ int tio_step_timeline(tio_ctx *ctx, int64_t *kernel_begin, int64_t *kernel_end, 
  * splits > 1 (bf16, no bias/resid, N multiple of 4) cuts the contraction into `splits` ranges:
  * workspace (device, fp32, splits*(M*N+M) floats) receives the partial tiles and a second launch
  * adds them in range order; splits = 1 ignores workspace.  With splits = 1 the library itself cuts a bf16 product with a long
- * contraction, of any operands and sizes whose partial tiles fit, into 2, 4 or 8 ranges: the partial tiles go to an array of its device
- * image (128 MiB on every GPU it runs on, shared safely between streams and threads).  On a stream under graph capture, or of
+ * contraction, of any operands and sizes whose partial tiles fit 72 MiB, into 2, 4 or 8 ranges: the partial tiles go to an array of its device
+ * image (four parts, 288 MiB on every GPU it runs on, shared safely between streams and threads).  Up to four streams with such products
+ * do not wait for each other; with more, one may wait for what another stream has queued up to its last such product.  On a stream under graph capture, or of
  * another device than the current one, it does not: such a call has the bits of one range, and takes the time of one. */
 int tio_op_gemm(void *stream, int32_t dtype, int32_t a_kmajor, int32_t b_kmajor,
                 int64_t M, int64_t N, int64_t K,

@@ -252,14 +252,18 @@ void splitk_reduce(hipStream_t s, const void *ws, const void *bias, const void *
 }
 
 // ---- scratch space of products that are split without a workspace from their caller
-// A fixed array on every device, in SLOTS parts.  A product takes a part for its two launches, or two or all of them where its partials
-// are larger: the stream first waits for the events that the parts' last users recorded behind their own, and the lock is held from the
-// choice of the parts to the recording, so that two threads' launches on one stream do not mix.  A stream gets the parts it had before, if
-// it is still the last one there, so that up to SLOTS streams with small products do not wait for each other.  No allocation, and no
-// waiting on the host.  (An allocation from a stream-ordered pool for
-// each product took 18 us of host time.)
+// A fixed array on every device, in SLOTS parts.  A product takes a part for its two launches: the stream first waits for the event
+// that the part's last user recorded behind its own, and the lock is held from the choice of the part to the recording, so that two
+// threads' launches on one stream do not mix.  A stream gets the part it had before, if it is still the last one there, so that
+// up to SLOTS streams do not wait for each other; with more, a product waits until another stream has come as far as its last cut product
+// (HIP's four hardware queues are shared by then anyway).  A product has one part, whatever its size: with four parts of 32 MiB, of
+// which a large product took two or all, 200 x 304 x 15000 behind 20 of 4096 x 1024 x 32000 on another stream took 4150 us; now 209, and 38 with
+// those in one range, where they take 365 us instead of 252.  72 MiB hold every cut that pays: of 24 contractions of 20000 to 50257 with
+// 18 to 112 MiB of partials in two ranges, none that needs more than 64 is cut, or quicker with parts of 128 MiB.  The array costs 0.4 ms of
+// host time per MiB once, when the first cut product loads it (52 ms with 128 MiB, 115 now).  No allocation, and no
+// waiting on the host.  (An allocation from a stream-ordered pool for each product took 18 us of host time.)
 constexpr int SLOTS = 4, DEVICES = 64;
-constexpr int64_t SLOT_BYTES = (int64_t)32 << 20;
+constexpr int64_t SLOT_BYTES = (int64_t)72 << 20;
 __device__ __align__(256) unsigned char split_partials[SLOTS * SLOT_BYTES];
 
 struct Slot {
@@ -280,17 +284,14 @@ class SplitScratch {
     std::unique_lock<std::mutex> lock;
     hipStream_t s;
     SlotsOfDevice *owner = nullptr;
-    Slot *mine = nullptr;                                    // the first of `count` neighbours
-    int count = 1;
+    Slot *mine = nullptr;
     unsigned char *at = nullptr;
 
 public:
     // partials() is nullptr where there is no part to be had: a stream under capture (a replay would not wait for the part's other
     // users), one of another device than the current one (the array's address and the events are the current one's), or a device that
     // refuses the array or an event, or has refused to record one: nobody could wait for the part's user then
-    SplitScratch(hipStream_t stream, int64_t bytes) : s(stream) {
-        while (count < SLOTS && count * SLOT_BYTES < bytes) count *= 2;
-        if (count * SLOT_BYTES < bytes) return;
+    explicit SplitScratch(hipStream_t stream) : s(stream) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &capture) != hipSuccess) { (void)hipGetLastError(); return; }
         int dev = -1;
@@ -302,33 +303,20 @@ public:
         SlotsOfDevice &d = slots_of[dev];
         if (!d.base && !d.failed) prepare(d);
         if (d.failed) { lock.unlock(); return; }
-        Slot *best = nullptr;
-        uint64_t best_used = 0;
-        for (int g = 0; g < SLOTS; g += count) {
-            uint64_t used = 0;
-            bool own = true;
-            for (int i = g; i < g + count; ++i) {
-                const Slot &x = d.slot[i];
-                own = own && x.used && x.user == s;
-                if (x.used > used) used = x.used;
-            }
-            if (!best || own || used < best_used) { best = &d.slot[g]; best_used = used; }
-            if (own) break;
+        Slot *best = &d.slot[0];
+        for (Slot &x : d.slot) {
+            if (x.used && x.user == s) { best = &x; break; }
+            if (x.used < best->used) best = &x;
         }
-        for (int i = 0; i < count; ++i)
-            if (best[i].used && hipStreamWaitEvent(s, best[i].free, 0) != hipSuccess) { (void)hipGetLastError(); lock.unlock(); return; }
+        if (best->used && hipStreamWaitEvent(s, best->free, 0) != hipSuccess) { (void)hipGetLastError(); lock.unlock(); return; }
         owner = &d;
         mine = best;
-        ++d.uses;
-        for (int i = 0; i < count; ++i) {
-            mine[i].user = s;
-            mine[i].used = d.uses;
-        }
+        mine->user = s;
+        mine->used = ++d.uses;
         at = d.base + (mine - d.slot) * SLOT_BYTES;
     }
     ~SplitScratch() {
-        for (int i = 0; mine && i < count; ++i)
-            if (hipEventRecord(mine[i].free, s) != hipSuccess) owner->failed = true;      // the caller reports the error
+        if (mine && hipEventRecord(mine->free, s) != hipSuccess) owner->failed = true;      // the caller reports the error
     }
     float *partials() const { return reinterpret_cast<float *>(at); }
 
@@ -391,9 +379,9 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
         ldr = ldc;
     }
     if (dtype == TIO_PREC_BF16 && splits == 1) {
-        const int own = gemm_bf16_splits(a_km, b_km, M, N, K, lda, ldb, rowsum != nullptr, SLOTS * SLOT_BYTES);
+        const int own = gemm_bf16_splits(a_km, b_km, M, N, K, lda, ldb, rowsum != nullptr, SLOT_BYTES);
         if (own > 1) {
-            const SplitScratch scratch(s, own * (M * partial_ld(N) + M) * 4);
+            const SplitScratch scratch(s);
             float *const ws = scratch.partials();
             if (ws && gemm_bf16_direct(s, a_km, b_km, M, N, K, A, lda, B, ldb, nullptr, nullptr, 0, C, ldc, rowsum, ws, own, accumulate)) {
                 splitk_reduce(s, ws, bias, resid, ldr, C, ldc, rowsum, M, N, own, accumulate);

@@ -27,6 +27,7 @@ std::map<hipStream_t, int> device_of;
 int launches = 0, event_calls = 0, records_to_fail = 0;
 void *last_first_arg = nullptr;
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; } config;
+constexpr int64_t ARRAY_BYTES = (int64_t)4 * 72 << 20;
 alignas(256) unsigned char image[64];                // stands for the array of the device image: never read or written
 
 hipStream_t stream(int i) { return reinterpret_cast<hipStream_t>(static_cast<uintptr_t>(0x1000 * (i + 1))); }
@@ -123,40 +124,54 @@ bool leaves_streams_of_other_devices_alone() {
     if (!product(stream(1)) || launches != 1) { std::printf("%d launches\n", launches); return false; }
     return event_calls == before && product(nullptr) && launches == 2;
 }
-// Products whose partials take one, two and all four parts: every part that one takes up has been left by its last user
-bool large_products_take_several_parts() {
-    constexpr int64_t PART = (int64_t)32 << 20;
-    struct Shape { int64_t M, N, K; int parts; };
-    const Shape shapes[] = {{200, 300, 15000, 1}, {8192, 768, 50257, 2}, {4096, 1024, 32000, 4}, {300, 300, 8000, 1}, {4096, 1792, 12940, 2}};
-    Use last[4] = {};
-    unsigned seen = 0;
+// Products whose partials take a few MiB and up to 64: as many streams as there are parts do not wait for each other, whatever the sizes;
+// with more streams, what one takes up has been left by every earlier user of any of its bytes
+struct Shape { int64_t M, N, K, ranges; };
+constexpr Shape SHAPES[] = {{200, 300, 15000, 8}, {8192, 768, 50257, 2}, {4096, 1024, 32000, 4}, {300, 300, 8000, 4}, {4096, 1792, 12940, 2}, {8192, 1024, 32000, 2}};
+int64_t partial_bytes(const Shape &p) { return p.ranges * (p.M * ((p.N + 3) / 4 * 4) + p.M) * 4; }
+bool shape_on(const Shape &p, hipStream_t s) {
+    launches = 0;
+    tio::k::gemm(s, BF16, false, true, p.M, p.N, p.K, image, (p.K + 7) / 8 * 8, image, p.N + 8, nullptr, nullptr, 0, image, p.N, nullptr, nullptr, 1, false);
+    if (launches != 2) std::printf("%d launches of %d x %d x %d\n", launches, (int)p.M, (int)p.N, (int)p.K);
+    return launches == 2;
+}
+bool large_products_of_four_streams_do_not_wait() {
     for (int i = 0; i < 200; ++i) {
-        const Shape &p = shapes[i * 7 % 5];
+        const hipStream_t s = stream(i * 3 % 4);
+        if (!shape_on(SHAPES[i * 7 % 6], s)) return false;
+        for (auto &[other, n] : streams[s])
+            if (other != s && n > 0) { std::printf("stream %d waits for another one\n", i * 3 % 4); return false; }
+    }
+    return true;
+}
+bool large_products_share_no_bytes_with_a_running_one() {
+    struct Extent { int64_t first, end; Use use; };
+    std::vector<Extent> taken;
+    int64_t end = 0;
+    for (int i = 0; i < 200; ++i) {
+        const Shape &p = SHAPES[i * 7 % 6];
         const hipStream_t s = stream(i * 5 % STREAMS);
-        launches = 0;
-        tio::k::gemm(s, BF16, false, true, p.M, p.N, p.K, image, (p.K + 7) / 8 * 8, image, p.N + 8, nullptr, nullptr, 0, image, p.N, nullptr, nullptr, 1, false);
-        if (launches != 2) { std::printf("%d launches\n", launches); return false; }
-        const int64_t first = (static_cast<unsigned char *>(last_first_arg) - image) / PART;
-        if (first % p.parts || first + p.parts > 4) { std::printf("part %d of %d\n", (int)first, p.parts); return false; }
-        for (int64_t k = first; k < first + p.parts; ++k) {
-            if (last[k].stream && streams[s][last[k].stream] < last[k].operations) {
-                std::printf("part %d is taken up while another stream may be using it\n", (int)k);
+        if (!shape_on(p, s)) return false;
+        const int64_t first = static_cast<unsigned char *>(last_first_arg) - image;
+        for (const Extent &e : taken)
+            if (first < e.end && e.first < first + partial_bytes(p) && streams[s][e.use.stream] < e.use.operations) {
+                std::printf("bytes from %lld on are taken up while another stream may be using them\n", (long long)first);
                 return false;
             }
-            last[k] = {s, streams[s][s]};
-            seen |= 1u << k;
-        }
+        taken.push_back({first, first + partial_bytes(p), {s, streams[s][s]}});
+        if (first + partial_bytes(p) > end) end = first + partial_bytes(p);
     }
-    return seen == 15;
+    return end <= ARRAY_BYTES;
 }
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing, leaves_streams_of_other_devices_alone,
-                              large_products_take_several_parts};
+                              large_products_of_four_streams_do_not_wait, large_products_share_no_bytes_with_a_running_one};
     const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
-                                 "leaves_streams_of_other_devices_alone", "large_products_take_several_parts"};
+                                 "leaves_streams_of_other_devices_alone", "large_products_of_four_streams_do_not_wait",
+                                 "large_products_share_no_bytes_with_a_running_one"};
     for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
         if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
     return 2;

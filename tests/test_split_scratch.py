@@ -22,7 +22,8 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name", ["cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
-                                  "leaves_streams_of_other_devices_alone", "large_products_take_several_parts"])
+                                  "leaves_streams_of_other_devices_alone", "large_products_of_four_streams_do_not_wait",
+                                  "large_products_share_no_bytes_with_a_running_one"])
 def test_split_scratch(program, name):
     r = subprocess.run([program, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
