@@ -402,13 +402,16 @@ __device__ __forceinline__ void store_edge(const floatx4 (&acc)[TM][TN], float *
     if constexpr (TM > BATCH) batch(std::integral_constant<int, BATCH>{});
 }
 // An output larger than the memory-side cache (256 MiB) is stored past the caches: nothing of it would be found there, and dirty lines
-// take the operands' place.  us: 8192 x 50176 x 768 608 -> 557, 8192 x 50257 x 768 667 -> 588, 8192 x 22016 x 4096 1011 -> 996, 8192 x 32000 x
-// 4096 1482 both; with 100 MB (1021 x 50257 x 768) it would be 101 -> 104.
+// take the operands' place.  That is decided by the size of the product, for both of its launches where it has two, and holds for the parts
+// inside plain outputs; those with bias or residual, the ragged ends and the sums of cut contractions are stored as ever.
+// us: 8192 x 50176 x 768 608 -> 557, 8192 x 50257 x 768 667 -> 588, 8192 x 22016 x 4096 1011 -> 996, 8192 x 32000 x
+// 4096 1482 both; with 100 MB (1021 x 50257 x 768) it would be 101 -> 104; in two launches 8176 x 16470 x 3143 747 -> 665, whose first has
+// just under 256 MiB.
 constexpr int64_t STREAMED = (int64_t)1 << 27;          // elements
 template <int TM, int TN>
 __device__ __forceinline__ void store_tile(const floatx4 (&acc)[TM][TN], float *stage, int lane, int64_t mw, int64_t nw, int64_t M, int64_t N,
                                            const uint16_t *__restrict__ bias, const uint16_t *resid, int64_t ldr, uint16_t *C, int64_t ldc,
-                                           float *__restrict__ ws, int split) {
+                                           float *__restrict__ ws, int split, int streamed) {
     const bool inside = mw + TM * 16 <= M && nw + TN * 16 <= N;
     const bool wide = ldc % 8 == 0 && (resid == nullptr || ldr % 8 == 0);
 #define TIO_STORE(BIAS, RESID, WS, STREAM) store_inside<TM, TN, BIAS, RESID, WS, STREAM>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split)
@@ -417,7 +420,7 @@ __device__ __forceinline__ void store_tile(const floatx4 (&acc)[TM][TN], float *
         if (bias && resid) TIO_STORE(true, true, false, false);
         else if (bias) TIO_STORE(true, false, false, false);
         else if (resid) TIO_STORE(false, true, false, false);
-        else if (M * N >= STREAMED) TIO_STORE(false, false, false, true);
+        else if (streamed) TIO_STORE(false, false, false, true);
         else TIO_STORE(false, false, false, false);
     } else if (mw < M && nw < N) store_edge<TM, TN>(acc, stage, lane, mw, nw, M, N, bias, resid, ldr, C, ldc, ws, split);
 #undef TIO_STORE
@@ -428,7 +431,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
     gemm_bf16_dl_k(const uint16_t *__restrict__ A, int64_t lda, const uint16_t *__restrict__ B, int64_t ldb,
                    const uint16_t *__restrict__ bias, const uint16_t *__restrict__ resid, int64_t ldr,
                    uint16_t *__restrict__ C, int64_t ldc, int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n,
-                   uint16_t *__restrict__ rowsum, float *__restrict__ ws, int64_t k_chunk, int rowsum_acc, int xsplits) {
+                   uint16_t *__restrict__ rowsum, float *__restrict__ ws, int64_t k_chunk, int rowsum_acc, int xsplits, int streamed) {
     constexpr int NT = WGM * WGN * 64;
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
     static_assert(TM <= 8 && TN <= 8 && BK == 64, "two contraction steps of 32 per tile");
@@ -617,7 +620,7 @@ __global__ void __launch_bounds__(WGM *WGN * 64)
 
     if (do_rowsum) store_rowsum<TM>(rs, lane, wn, m0 + wm * WM, M, N, rowsum, rowsum_acc, ws, split, nsplit);
     store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl) + wave * stage_floats<TM, TN>(), lane, m0 + wm * WM, n0 + wn * WN, M, N, bias, resid,
-                       ldr, C, ldc, ws, split);      // the rings are free: the last barrier came after every fragment read
+                       ldr, C, ldc, ws, split, streamed);      // the rings are free: the last barrier came after every fragment read
     static_assert((size_t)RINGA + RINGB >= (size_t)WGM * WGN * stage_floats<TM, TN>() * 4, "the staging blocks fit the rings");
 }
 
@@ -629,7 +632,7 @@ __global__ void __launch_bounds__(512)
     gemm_bf16_small_k(const uint16_t *__restrict__ A, int64_t lda, const uint16_t *__restrict__ B, int64_t ldb,
                       const uint16_t *__restrict__ bias, const uint16_t *__restrict__ resid, int64_t ldr,
                       uint16_t *__restrict__ C, int64_t ldc, int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n,
-                      uint16_t *__restrict__ rowsum, float *__restrict__ ws, int64_t k_chunk, int rowsum_acc, int xsplits) {
+                      uint16_t *__restrict__ rowsum, float *__restrict__ ws, int64_t k_chunk, int rowsum_acc, int xsplits, int streamed) {
     constexpr int BM = 64, BN = 64, NT = 512, TM = 2, TN = 2;
     using OpA = DlOperand<BM, NT, AKM>;
     using OpB = DlOperand<BN, NT, BKM>;
@@ -780,7 +783,7 @@ __global__ void __launch_bounds__(512)
     constexpr size_t RED = 4 * (TM * TN * 4 + 1) * 64 * 4;
     static_assert(D * TILE >= RED + 4 * stage_floats<TM, TN>() * 4, "reduction and staging blocks fit the ring");
     store_tile<TM, TN>(acc, reinterpret_cast<float *>(smem_dl + RED) + wave * stage_floats<TM, TN>(), lane, m0 + wm * 32, n0 + wn * 32, M, N, bias, resid, ldr,
-                       C, ldc, ws, split);
+                       C, ldc, ws, split, streamed);
 }
 struct Product {
     hipStream_t s;
@@ -796,7 +799,7 @@ struct Product {
     int64_t ldc;
     uint16_t *rowsum;
     float *ws;
-    int splits, rowsum_acc;
+    int splits, rowsum_acc, streamed;
 };
 
 template <auto *KERNEL> void launch(const Product &p, int BM, int BN, int threads, size_t lds) {
@@ -808,7 +811,7 @@ template <auto *KERNEL> void launch(const Product &p, int BM, int BN, int thread
     const dim3 grid = xsplits ? dim3((unsigned)(8 * ((tiles + 8 / xsplits - 1) / (8 / xsplits))))
                               : dim3((unsigned)(8 * ((tiles + 7) / 8)), (unsigned)(p.splits > 1 ? p.splits : 1));
     KERNEL<<<grid, threads, lds, p.s>>>(p.A, p.lda, p.B, p.ldb, p.bias, p.resid, p.ldr, p.C, p.ldc, p.M, p.N, p.K, tiles_m, tiles_n,
-                                        p.rowsum, p.ws, k_chunk, p.rowsum_acc, xsplits);
+                                        p.rowsum, p.ws, k_chunk, p.rowsum_acc, xsplits, p.streamed);
 }
 
 // With row sums the layout of a weight gradient (both operands k-major) has every tile, the others the two square ones above 64:
@@ -954,7 +957,7 @@ bool gemm_bf16_direct(hipStream_t s, bool a_km, bool b_km, int64_t M, int64_t N,
     const Plan plan(Choice(a_km, b_km, K, lda, ldb, rowsum != nullptr, splits), M, N);
     if (!plan.first) return false;
     Product p{s, a_km, b_km, M, N, K, (const uint16_t *)A, lda, (const uint16_t *)B, ldb, (const uint16_t *)bias, (const uint16_t *)resid,
-              ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate};
+              ldr, (uint16_t *)C, ldc, (uint16_t *)rowsum, ws, splits, (int)rowsum_accumulate, (int)(M * N >= STREAMED)};
     if (!plan.rest) {
         plan.first->launch(p);
         return true;

@@ -26,6 +26,9 @@ std::map<hipEvent_t, Clock> events;
 std::map<hipStream_t, int> device_of;
 int launches = 0, event_calls = 0, records_to_fail = 0;
 void *last_first_arg = nullptr;
+struct Launched { int64_t M, N; int streamed; };
+bool keep_launches = false;                          // launches of the product kernels alone: their arguments are read by position
+std::vector<Launched> launched;
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; } config;
 constexpr int64_t ARRAY_BYTES = (int64_t)4 * 72 << 20;
 alignas(256) unsigned char image[64];                // stands for the array of the device image: never read or written
@@ -67,6 +70,7 @@ hipError_t hipLaunchKernel(const void *, dim3, dim3, void **args, size_t, hipStr
     ++launches;
     ++streams[s][s];
     last_first_arg = *static_cast<void **>(args[0]);
+    if (keep_launches) launched.push_back({*static_cast<int64_t *>(args[9]), *static_cast<int64_t *>(args[10]), *static_cast<int *>(args[19])});
     return hipSuccess;
 }
 }
@@ -163,15 +167,36 @@ bool large_products_share_no_bytes_with_a_running_one() {
     }
     return end <= ARRAY_BYTES;
 }
+// An output of 256 MiB and more goes past the caches whole, in whichever launches it is made
+bool streams_outputs_by_the_size_of_the_product() {
+    struct Output { int64_t M, N, K; size_t launches; bool streamed; };
+    constexpr Output OUTPUTS[] = {{8176, 16470, 3143, 2, true}, {7727, 17374, 4540, 2, true}, {8192, 50257, 768, 1, true}, {4096, 32768, 72, 1, true},
+                                  {4095, 32776, 72, 1, false}, {1021, 50257, 768, 2, false}};
+    keep_launches = true;
+    for (const Output &o : OUTPUTS) {
+        launched.clear();
+        tio::k::gemm(stream(0), BF16, false, false, o.M, o.N, o.K, image, (o.K + 7) / 8 * 8, image, (o.K + 7) / 8 * 8, nullptr, nullptr, 0, image,
+                     (o.N + 7) / 8 * 8, nullptr, nullptr, 1, false);
+        if (launched.size() != o.launches) { std::printf("%d x %d x %d: %d launches\n", (int)o.M, (int)o.N, (int)o.K, (int)launched.size()); return false; }
+        int64_t elements = 0;
+        for (const Launched &l : launched) {
+            elements += l.M * l.N;
+            if (l.streamed != o.streamed) { std::printf("%d x %d of %d x %d: %d\n", (int)l.M, (int)l.N, (int)o.M, (int)o.N, l.streamed); return false; }
+        }
+        if (elements != o.M * o.N) { std::printf("%lld elements of %d x %d\n", (long long)elements, (int)o.M, (int)o.N); return false; }
+    }
+    return true;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing, leaves_streams_of_other_devices_alone,
-                              large_products_of_four_streams_do_not_wait, large_products_share_no_bytes_with_a_running_one};
+                              large_products_of_four_streams_do_not_wait, large_products_share_no_bytes_with_a_running_one,
+                              streams_outputs_by_the_size_of_the_product};
     const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
                                  "leaves_streams_of_other_devices_alone", "large_products_of_four_streams_do_not_wait",
-                                 "large_products_share_no_bytes_with_a_running_one"};
+                                 "large_products_share_no_bytes_with_a_running_one", "streams_outputs_by_the_size_of_the_product"};
     for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
         if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
     return 2;

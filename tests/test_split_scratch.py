@@ -23,7 +23,7 @@ def program(tmp_path_factory):
 
 @pytest.mark.parametrize("name", ["cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
                                   "leaves_streams_of_other_devices_alone", "large_products_of_four_streams_do_not_wait",
-                                  "large_products_share_no_bytes_with_a_running_one"])
+                                  "large_products_share_no_bytes_with_a_running_one", "streams_outputs_by_the_size_of_the_product"])
 def test_split_scratch(program, name):
     r = subprocess.run([program, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
