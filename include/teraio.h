@@ -349,6 +349,10 @@ int tio_op_gemm(void *stream, int32_t dtype, int32_t a_kmajor, int32_t b_kmajor,
  * first; 0 x 0: the kernel with 64-bit addressing. */
 int tio_op_gemm_tile(int32_t a_kmajor, int32_t b_kmajor, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int32_t rowsum,
                      int32_t splits, int32_t *out_rows, int32_t *out_cols);
+/* Measuring aid, host only: how tio_op_gemm takes a bf16 product without a workspace.  out_ranges: the ranges it cuts the contraction into by
+ * itself (1: none); out_rows / out_cols: of a product in two launches the rows or the columns of the first (the other is 0; both: one launch). */
+int tio_op_gemm_route(int32_t a_kmajor, int32_t b_kmajor, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int32_t rowsum,
+                      int32_t *out_ranges, int64_t *out_rows, int64_t *out_cols);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): tio_op_gemm without bias / residual, whose split-contraction partial tiles go to a
  * fixed 64 MiB (67108864-byte) array in the library's device image instead of a caller workspace.  It allocates

@@ -458,6 +458,14 @@ def tio_op_gemm_tile(a_kmajor, b_kmajor, M, N, K, lda, ldb, rowsum=False, splits
     return rows.value, cols.value
 
 
+def tio_op_gemm_route(a_kmajor, b_kmajor, M, N, K, lda, ldb, rowsum=False):
+    """(ranges of the contraction, rows, columns of the first of two launches or 0, 0) of a bf16 product without a workspace; host only."""
+    ranges, rows, cols = C.c_int32(), C.c_int64(), C.c_int64()
+    _check(lib().tio_op_gemm_route(int(a_kmajor), int(b_kmajor), C.c_int64(M), C.c_int64(N), C.c_int64(K), C.c_int64(lda),
+                                   C.c_int64(ldb), int(rowsum), C.byref(ranges), C.byref(rows), C.byref(cols)))
+    return ranges.value, rows.value, cols.value
+
+
 def tio_op_gemm_static_ws(stream_handle, dtype, a_kmajor, b_kmajor, M, N, K, A_ptr, lda, B_ptr, ldb, C_ptr, ldc,
                           rowsum_ptr=0, splits=1):
     """tio_op_gemm with the split-contraction partials in the library's fixed device array; allocates nothing."""

@@ -29,6 +29,12 @@ void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64
 // contraction ranges a product without a workspace from its caller is worth cutting into (1: none), with partials of at most `bytes`;
 // host only
 int gemm_bf16_splits(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t bytes);
+// rows or columns of the first launch of a product in two (both 0: one launch); host only
+void gemm_bf16_first_launch(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t *rows,
+                            int64_t *cols);
+// the two together for a product without a workspace: the ranges it is cut into, or how it is launched in one range; host only
+void gemm_bf16_route(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int *ranges, int64_t *rows,
+                     int64_t *cols);
 // the fp32 partials of a split product: `splits` tiles of M rows of partial_ld(N), then `splits` row sums of M
 constexpr int64_t partial_ld(int64_t N) { return (N + 3) / 4 * 4; }
 // fp32 products on the fp32 matrix instruction (kernels_gemm_f32.hip); accumulate adds to rowsum (the caller passes C as resid)

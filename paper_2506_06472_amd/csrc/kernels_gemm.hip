@@ -402,5 +402,12 @@ void gemm(hipStream_t s, int dtype, bool a_km, bool b_km, int64_t M, int64_t N, 
     }
 }
 
+void gemm_bf16_route(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int *ranges, int64_t *rows,
+                     int64_t *cols) {
+    *ranges = gemm_bf16_splits(a_km, b_km, M, N, K, lda, ldb, rowsum, SLOT_BYTES);
+    *rows = *cols = 0;
+    if (*ranges == 1) gemm_bf16_first_launch(a_km, b_km, M, N, K, lda, ldb, rowsum, rows, cols);
+}
+
 }  // namespace k
 }  // namespace tio

@@ -1018,5 +1018,12 @@ void gemm_bf16_tile(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64
     *cols = t ? t->bn : 0;
 }
 
+void gemm_bf16_first_launch(bool a_km, bool b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool rowsum, int64_t *rows,
+                            int64_t *cols) {
+    const Plan plan(Choice(a_km, b_km, K, lda, ldb, rowsum, 1), M, N);
+    *rows = plan.rest ? plan.rows : 0;
+    *cols = plan.rest ? plan.cols : 0;
+}
+
 }  // namespace k
 }  // namespace tio

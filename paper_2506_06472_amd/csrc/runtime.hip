@@ -895,6 +895,14 @@ int tio_op_gemm_tile(int32_t a_km, int32_t b_km, int64_t M, int64_t N, int64_t K
     return TIO_OK;
 }
 
+int tio_op_gemm_route(int32_t a_km, int32_t b_km, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int32_t rowsum,
+                      int32_t *out_ranges, int64_t *out_rows, int64_t *out_cols) {
+    if (!out_ranges || !out_rows || !out_cols) return fail(TIO_ERR_INVALID_ARG, "null argument");
+    if (M < 1 || N < 1 || K < 1) return fail(TIO_ERR_INVALID_ARG, "non-positive dimension");
+    k::gemm_bf16_route(a_km != 0, b_km != 0, M, N, K, lda, ldb, rowsum != 0, out_ranges, out_rows, out_cols);
+    return TIO_OK;
+}
+
 // ---- split-contraction product for callers that cannot allocate ------------------------------------------------
 // The fp32 partial tiles go to a fixed array in device memory instead of a workspace from the caller.  In host
 // code the array's name is only a handle for hipGetSymbolAddress: every device has its own copy at its own address,

@@ -1,7 +1,7 @@
-// The host side of products that the library cuts by itself, on a stand-in for the HIP runtime: this program defines the runtime calls of
-// that path, so that the library's calls come here and nothing reaches a GPU.  A stream and an event carry clocks (which operations of
-// each stream lie before them); a part of the scratch space must only be taken up by a stream that comes after its last user.
-// The argument names the test; exit status 0: passed.
+// The host side of products that the library cuts by itself, in their contraction or into two launches, on a stand-in for the HIP runtime:
+// this program defines the runtime calls of that path, so that the library's calls come here and nothing reaches a GPU.  A stream and an
+// event carry clocks (which operations of each stream lie before them); a part of the scratch space must only be taken up by a stream
+// that comes after its last user.  The argument names the test; exit status 0: passed.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdint>
@@ -26,7 +26,7 @@ std::map<hipEvent_t, Clock> events;
 std::map<hipStream_t, int> device_of;
 int launches = 0, event_calls = 0, records_to_fail = 0;
 void *last_first_arg = nullptr;
-struct Launched { int64_t M, N; int streamed; };
+struct Launched { int64_t M, N; int streamed; uintptr_t A, B, bias, resid, C, rowsum; int64_t ldr, ldc; int rowsum_acc; };
 bool keep_launches = false;                          // launches of the product kernels alone: their arguments are read by position
 std::vector<Launched> launched;
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; } config;
@@ -70,7 +70,11 @@ hipError_t hipLaunchKernel(const void *, dim3, dim3, void **args, size_t, hipStr
     ++launches;
     ++streams[s][s];
     last_first_arg = *static_cast<void **>(args[0]);
-    if (keep_launches) launched.push_back({*static_cast<int64_t *>(args[9]), *static_cast<int64_t *>(args[10]), *static_cast<int *>(args[19])});
+    auto number = [&](int i) { return *static_cast<int64_t *>(args[i]); };
+    auto address = [&](int i) { return *static_cast<uintptr_t *>(args[i]); };
+    if (keep_launches)
+        launched.push_back({number(9), number(10), *static_cast<int *>(args[19]), address(0), address(2), address(4), address(5), address(7), address(14),
+                            number(6), number(8), *static_cast<int *>(args[17])});
     return hipSuccess;
 }
 }
@@ -131,7 +135,7 @@ bool leaves_streams_of_other_devices_alone() {
 // Products whose partials take a few MiB and up to 64: as many streams as there are parts do not wait for each other, whatever the sizes;
 // with more streams, what one takes up has been left by every earlier user of any of its bytes
 struct Shape { int64_t M, N, K, ranges; };
-constexpr Shape SHAPES[] = {{200, 300, 15000, 8}, {8192, 768, 50257, 2}, {4096, 1024, 32000, 4}, {300, 300, 8000, 4}, {4096, 1792, 12940, 2}, {8192, 1024, 32000, 2}};
+constexpr Shape SHAPES[] = {{200, 300, 15000, 8}, {8192, 768, 50257, 2}, {4096, 1024, 32000, 4}, {300, 300, 8000, 8}, {4096, 1792, 12940, 2}, {8192, 1024, 32000, 2}};
 int64_t partial_bytes(const Shape &p) { return p.ranges * (p.M * ((p.N + 3) / 4 * 4) + p.M) * 4; }
 bool shape_on(const Shape &p, hipStream_t s) {
     launches = 0;
@@ -187,16 +191,50 @@ bool streams_outputs_by_the_size_of_the_product() {
     }
     return true;
 }
+// A product in two launches: the second has the operands' next rows or columns, with bias, residual, row sums and C beside them; where C is
+// accumulated it is the residual of both, and the row sums of both add
+bool a_second_launch_goes_on_where_the_first_ends() {
+    struct Cut { int64_t M, N, K; bool a_km, b_km, rowsum, by_rows; };
+    constexpr Cut CUTS[] = {{50257, 768, 1021, true, true, true, true},   {6200, 8449, 1000, true, false, false, true}, {4224, 12277, 1200, false, false, false, true},
+                            {16001, 3130, 1161, true, true, true, false}, {1792, 9664, 1000, false, true, false, false}, {1021, 50257, 768, false, false, false, false}};
+    constexpr uintptr_t A = 0x10000000000, B = 0x20000000000, C = 0x30000000000, BIAS = 0x40000000000, RESID = 0x50000000000, ROWSUM = 0x60000000000;
+    auto at = [](uintptr_t p) { return reinterpret_cast<void *>(p); };
+    auto up8 = [](int64_t n) { return (n + 7) / 8 * 8; };
+    keep_launches = true;
+    for (const Cut &c : CUTS)
+        for (const bool accumulate : {false, true}) {
+            const int64_t lda = up8(c.a_km ? c.M : c.K), ldb = up8(c.b_km ? c.N : c.K), ldc = up8(c.N) + 16, ldr = accumulate ? ldc : up8(c.N);
+            launched.clear();
+            tio::k::gemm(stream(0), BF16, c.a_km, c.b_km, c.M, c.N, c.K, at(A), lda, at(B), ldb, at(BIAS), accumulate ? nullptr : at(RESID),
+                         accumulate ? 0 : ldr, at(C), ldc, c.rowsum ? at(ROWSUM) : nullptr, nullptr, 1, accumulate);
+            if (launched.size() != 2) { std::printf("%d launches\n", (int)launched.size()); return false; }
+            const Launched &f = launched[0], &s = launched[1];
+            const int64_t rows = c.by_rows ? f.M : 0, cols = c.by_rows ? 0 : f.N;
+            const uintptr_t resid = accumulate ? C : RESID, rowsum = c.rowsum ? ROWSUM : 0;
+            const bool first = f.A == A && f.B == B && f.bias == BIAS && f.resid == resid && f.C == C && f.rowsum == rowsum;
+            const bool sizes = c.by_rows ? f.N == c.N && s.N == c.N && f.M + s.M == c.M : f.M == c.M && s.M == c.M && f.N + s.N == c.N;
+            const bool second = s.A == A + 2 * rows * (c.a_km ? 1 : lda) && s.B == B + 2 * cols * (c.b_km ? 1 : ldb) && s.bias == BIAS + 2 * cols &&
+                                s.resid == resid + 2 * (rows * ldr + cols) && s.C == C + 2 * (rows * ldc + cols) &&
+                                s.rowsum == (c.by_rows && c.rowsum ? ROWSUM + 2 * rows : 0);
+            const bool same = f.ldr == ldr && s.ldr == ldr && f.ldc == ldc && s.ldc == ldc && f.rowsum_acc == accumulate && s.rowsum_acc == accumulate;
+            if (!first || !sizes || !second || !same) {
+                std::printf("%d x %d x %d, accumulate %d: first %d sizes %d second %d same %d\n", (int)c.M, (int)c.N, (int)c.K, accumulate, first, sizes, second, same);
+                return false;
+            }
+        }
+    return true;
+}
 }  // namespace
 
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     bool (*const tests[])() = {cuts_and_waits, refuses_accumulate_with_residual, a_failed_record_ends_the_sharing, leaves_streams_of_other_devices_alone,
                               large_products_of_four_streams_do_not_wait, large_products_share_no_bytes_with_a_running_one,
-                              streams_outputs_by_the_size_of_the_product};
+                              streams_outputs_by_the_size_of_the_product, a_second_launch_goes_on_where_the_first_ends};
     const char *const names[] = {"cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
                                  "leaves_streams_of_other_devices_alone", "large_products_of_four_streams_do_not_wait",
-                                 "large_products_share_no_bytes_with_a_running_one", "streams_outputs_by_the_size_of_the_product"};
+                                 "large_products_share_no_bytes_with_a_running_one", "streams_outputs_by_the_size_of_the_product",
+                                 "a_second_launch_goes_on_where_the_first_ends"};
     for (size_t i = 0; i < sizeof names / sizeof *names; ++i)
         if (!std::strcmp(name, names[i])) return tests[i]() ? 0 : 1;
     return 2;

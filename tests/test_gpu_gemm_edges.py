@@ -1,13 +1,20 @@
 """GPU: the bf16 product kernels at the edges of their tiles: contractions of one to a dozen tiles with every kind of remainder
 (whole, a multiple of 8, odd), outputs one short of and one over a tile, every epilogue (plain, bias and residual on rows of 8k and
 8k + 4 elements, row sums, split contraction with short and empty ranges), against float64; padding is NaN and must never leak.  Every
-test states the output tile it is about and checks that the dispatch takes it."""
+test states the output tile or the route (ranges of the contraction, one launch or two) it is about and checks that the dispatch takes it."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 LAYOUTS = [(0, 0), (0, 1), (1, 1), (1, 0)]
 r8 = lambda n: (n + 7) // 8 * 8
+
+
+def route(M, N, K, a_km, b_km, rowsum=False):
+    """"rows" / "columns": two launches, the first with whole rows or columns; otherwise the ranges the contraction is cut into."""
+    import paper_2506_06472_amd as tio
+    ranges, rows, cols = tio.tio_op_gemm_route(a_km, b_km, M, N, K, r8(M) if a_km else r8(K), r8(N) if b_km else r8(K), rowsum)
+    return "rows" if rows else "columns" if cols else ranges
 
 
 def _run(M, N, K, a_km, b_km, rowsum=False, splits=1, tile=None, epilogue=(), pad=0):
@@ -120,13 +127,22 @@ def test_row_sums_of_the_large_tile_in_every_layout(M, N, K, a_km, b_km):
 # an output of just under 2^27 elements, and of as many, which is stored past the caches: parts inside it and at its ragged ends
 @pytest.mark.parametrize("M,N", [(4095, 32776), (4096, 32768), (4099, 32777)])
 def test_outputs_larger_than_the_caches(M, N):
+    assert route(M, N, 72, 0, 0) == 1
     _run(M, N, 72, 0, 0)
 
 
+# the same in two launches, of which the first alone is under that size
+def test_outputs_larger_than_the_caches_in_two_launches():
+    assert route(8176, 16470, 1211, 0, 0) == "columns"
+    _run(8176, 16470, 1211, 0, 0)
+
+
 # products in two launches, whole rounds of tiles and what is left: cut by columns and by rows, what is left ragged and less than a tile
-@pytest.mark.parametrize("M,N,K,a_km,b_km,rowsum,epilogue,pad", [
-    (1021, 50257, 768, 0, 0, False, ("bias", "resid"), 0), (1021, 50261, 770, 0, 0, False, ("resid",), 4), (1792, 9664, 1000, 0, 1, False, ("bias",), 0),
-    (50257, 768, 1021, 1, 1, True, (), 0), (16001, 3130, 1161, 1, 1, True, (), 0), (4224, 12277, 1200, 0, 0, False, (), 4),
-    (6200, 8449, 1000, 1, 0, False, ("bias", "resid"), 0), (2508, 6720, 3968, 0, 1, False, ("bias", "resid"), 0)])
-def test_products_in_two_launches(M, N, K, a_km, b_km, rowsum, epilogue, pad):
+@pytest.mark.parametrize("M,N,K,a_km,b_km,rowsum,epilogue,pad,cut", [
+    (1021, 50257, 768, 0, 0, False, ("bias", "resid"), 0, "columns"), (1021, 50261, 770, 0, 0, False, ("resid",), 4, "columns"),
+    (1792, 9664, 1000, 0, 1, False, ("bias",), 0, "columns"), (50257, 768, 1021, 1, 1, True, (), 0, "rows"),
+    (16001, 3130, 1161, 1, 1, True, (), 0, "columns"), (4224, 12277, 1200, 0, 0, False, (), 4, "rows"),
+    (6200, 8449, 1000, 1, 0, False, ("bias", "resid"), 0, "rows"), (2508, 6720, 3968, 0, 1, False, ("bias", "resid"), 0, "columns")])
+def test_products_in_two_launches(M, N, K, a_km, b_km, rowsum, epilogue, pad, cut):
+    assert route(M, N, K, a_km, b_km, rowsum) == cut
     _run(M, N, K, a_km, b_km, rowsum=rowsum, epilogue=epilogue, pad=pad)

@@ -4,7 +4,7 @@ workspace, and the scratch space under more streams than it has parts, under thr
 import threading
 
 import pytest
-from test_gpu_gemm_edges import _run, r8
+from test_gpu_gemm_edges import _run, r8, route
 
 pytestmark = pytest.mark.gpu
 
@@ -14,14 +14,17 @@ pytestmark = pytest.mark.gpu
     (1, 1, 20000, 0, 0, False, ("bias",), 0), (3, 7, 16385, 1, 0, False, ("bias", "resid"), 4), (300, 301, 15999, 1, 1, True, (), 0),
     (512, 130, 30011, 1, 1, True, (), 0), (1021, 768, 50257, 0, 1, False, (), 0)])
 def test_long_contractions(M, N, K, a_km, b_km, rowsum, epilogue, pad):
+    assert route(M, N, K, a_km, b_km, rowsum) == 8
     _run(M, N, K, a_km, b_km, rowsum=rowsum, epilogue=epilogue, pad=pad)
 
 
-# partials of two parts of the scratch space and of all four, ragged and not
-@pytest.mark.parametrize("M,N,K,a_km,b_km,rowsum,epilogue", [
-    (4096, 1792, 12940, 0, 1, False, ()), (4093, 1790, 12941, 0, 1, False, ("bias", "resid")), (4096, 1024, 32000, 0, 1, False, ()),
-    (2050, 2047, 16001, 1, 1, True, ())])
-def test_large_partials(M, N, K, a_km, b_km, rowsum, epilogue):
+# two, four and eight ranges with 45 to 64 MiB of partials, ragged and not, row sums behind them; the last is next to the line and not cut
+@pytest.mark.parametrize("M,N,K,a_km,b_km,rowsum,epilogue,ranges", [
+    (4096, 1792, 12940, 0, 1, False, (), 2), (4093, 1790, 12941, 0, 1, False, ("bias", "resid"), 2), (4096, 1024, 32000, 0, 1, False, (), 4),
+    (3330, 1791, 16001, 1, 1, True, (), 2), (2300, 1791, 24001, 1, 1, True, (), 4), (1536, 1280, 24001, 1, 1, True, (), 8),
+    (2050, 2047, 16001, 1, 1, True, (), 1)])
+def test_large_partials(M, N, K, a_km, b_km, rowsum, epilogue, ranges):
+    assert route(M, N, K, a_km, b_km, rowsum) == ranges
     _run(M, N, K, a_km, b_km, rowsum=rowsum, epilogue=epilogue)
 
 
@@ -126,10 +129,11 @@ def test_under_graph_capture():
         assert all(torch.equal(w, g) for w, g in zip(want, got))
 
 
-def test_products_of_one_part_and_of_several_on_many_streams():
+def test_cut_products_of_all_sizes_on_many_streams():
     import torch
     products = [_Product(torch, M, N, K, i) for i, (M, N, K) in enumerate(
-        [(200, 304, 15000), (4096, 1792, 12940), (216, 304, 15000), (4096, 1024, 32000), (232, 304, 15000), (2048, 1792, 12940)])]
+        [(200, 304, 15000), (4096, 1792, 12940), (216, 304, 15000), (4096, 1024, 32000), (232, 304, 15000), (2304, 1280, 16000)])]
+    assert all(route(p.M, p.N, p.K, 0, 0) > 1 for p in products)
     want = [p.out() for p in products]
     for p, w in zip(products, want):
         p.run(w)

@@ -1,5 +1,5 @@
-"""The host side of products that the library cuts by itself (which stream may use which part of the scratch space, what is refused),
-without a GPU: split_scratch_host.cpp runs it on a stand-in for the HIP runtime."""
+"""The host side of products that the library cuts by itself (which stream may use which part of the scratch space, what is refused, what
+each of two launches is given), without a GPU: split_scratch_host.cpp runs it on a stand-in for the HIP runtime."""
 import os
 import subprocess
 
@@ -23,7 +23,8 @@ def program(tmp_path_factory):
 
 @pytest.mark.parametrize("name", ["cuts_and_waits", "refuses_accumulate_with_residual", "a_failed_record_ends_the_sharing",
                                   "leaves_streams_of_other_devices_alone", "large_products_of_four_streams_do_not_wait",
-                                  "large_products_share_no_bytes_with_a_running_one", "streams_outputs_by_the_size_of_the_product"])
+                                  "large_products_share_no_bytes_with_a_running_one", "streams_outputs_by_the_size_of_the_product",
+                                  "a_second_launch_goes_on_where_the_first_ends"])
 def test_split_scratch(program, name):
     r = subprocess.run([program, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
