@@ -36,7 +36,7 @@ PEAK_FP32_TFLOPS = 157.3
 
 
 def gemm_traffic(workload):
-    """Bytes per GEMM launch that cross between the L2s and the fabric, measured offline with rocprofv3 --pmc
+    """Bytes per product (one kernel launch or two) that cross between the L2s and the fabric, measured offline with rocprofv3 --pmc
     FETCH_SIZE / WRITE_SIZE runs of this command and kept with their provenance in profiles/gemm_traffic.json
     (workload -> bytes_per_launch, profile file, commit of the kernels measured).  None where no such run exists."""
     try:
@@ -469,7 +469,7 @@ def main():
                      "kernel": ("gemm_bf16_dl_k" if bf16 else "gemm_f32_mfma_k") + " (forward, dX and dW contractions)",
                      "achieved": gemm_tflops, "peak": gemm_peak, "unit": "TFLOP/s",
                      "frac": gemm_tflops / gemm_peak, "traffic": (traffic or {}).get("bytes_per_launch"),
-                     "traffic_unit": "bytes per launch missing the L2 (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated); "
+                     "traffic_unit": "bytes per product missing the L2 (rocprofv3 FETCH_SIZE + WRITE_SIZE, calibrated); "
                                      "measured offline, not in this run",
                      "traffic_provenance": ({k: traffic[k] for k in ("profile", "kernels_as_of_commit")} if traffic else None),
                      "algorithmic_bytes_per_launch": gemm_bytes / n_gemm,

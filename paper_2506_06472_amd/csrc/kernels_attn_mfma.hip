@@ -11,9 +11,11 @@
 // transposed copies.
 //
 // All products are v_mfma_f32_16x16x32_bf16, D[16x16] += A[16x32] . B[32x16]: lane l supplies row (A) or column (B) l%16 and eight
-// contraction slots of lane group l/16; of D it holds column l%16 and rows 4 (l/16) + 0..3.  These kernels run into the power limit (the
-// clock stands at 1.5 to 1.8 GHz of 2.4 in them), and at that limit a loop of nothing but products on normal values does 2060 TFLOP/s with
-// this instruction and 1800 with v_mfma_f32_32x32x16_bf16, on zeros both 2440.  Consecutive products share one operand (the order of
+// contraction slots of lane group l/16; of D it holds column l%16 and rows 4 (l/16) + 0..3.  At head size 128 these kernels run into
+// the power limit (the clock stands at 1.5 to 1.8 GHz of 2.4 in the forward kernel, by card; on zeros, which draw less, it takes a fifth to a
+// quarter less; at head size 64 2.2 GHz and 6 %), and at that limit a loop of nothing but products on normal values does 2000 to 2060 TFLOP/s with
+// this instruction and 1750 to 1800 with v_mfma_f32_32x32x16_bf16, on zeros both 2440.  Of a SIMD's time the matrix cores work 51 to 57 % at head
+// size 128 and 35 to 43 at 64, the vector ALU 37 to 60 and 57 to 68.  Consecutive products share one operand (the order of
 // the second index turns round with every step of the first), 2 % of the same loop.  With 32x32x16 products, two wavefronts per SIMD
 // in the forward kernel and no fragments of the transposed operand ahead, forward / forward and backward, us, before and now:
 //   4 x 2048, 32 heads of 128 158 / 685 -> 143 / 600    2 x 4096, 52 of 128 457 / 1935 -> 412 / 1745    8 x 1024, 12 of 64 22.9 / 95 -> 21 / 86
@@ -443,7 +445,8 @@ template <int KS> __device__ __forceinline__ float row_dot(const bf16x8 (&g)[KS]
     return p[0];
 }
 
-// Bound: power, then latency between the products; the tiles in front of the diagonal run through a loop of their own, without mask and
+// Bound: the matrix cores and the vector ALU, which work for 57 and 48 % of the time at head size 128 (39 and 57 at 64) and for a fifth to a third
+// of the products' time together, and power; the tiles in front of the diagonal run through a loop of their own, without mask and
 // branch.  Three wavefronts per SIMD at head size 64, two at 128.  With fragments of the transposed K tile four ahead in registers, where
 // the compiler read each right before its products, 4 x 2048 tokens, 32 heads of 128, forward and backward 634 -> 614 us (dK/dV too).
 // O: nullptr, or the forward pass's output: delta is then computed here, from the rows of dO that are in registers anyway, and
@@ -609,8 +612,8 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
 // Both gradients in one launch: S and dP are computed once for the two of them, and the Q and dO tiles are loaded once.  The
 // accumulators and K fragments of 32 key rows take 160 of the 256 registers that two wavefronts per SIMD allow at head size 128,
 // so the V fragments are not kept in registers there but read from LDS (the workgroup's V rows, loaded once); to have room for
-// them, and half the tile loads per product, a workgroup is eight wavefronts with 256 key rows.  Bound: power, then latency between the
-// products of two wavefronts per SIMD (three at head size 64).  Nothing may spill: a reload from scratch in the loop waits for the tile
+// them, and half the tile loads per product, a workgroup is eight wavefronts with 256 key rows.  Bound: latency between the
+// products of two wavefronts per SIMD (three at head size 64), a third of their cycles, and power.  Nothing may spill: a reload from scratch in the loop waits for the tile
 // loads in flight, and the wavefront with it keeps the others at the barrier.  So the offsets of the reads are one register and an
 // exclusive or each at head size 128, each of two wavefronts fetches one of the statistics, and the lane index is computed where it is used.
 // The tiles behind the diagonal run through a loop of their own, without mask and branch; at head size 64 a second loop gains nothing
@@ -918,7 +921,9 @@ void attn_fwd_mfma(hipStream_t s, const void *qkv, void *o, float *lse, int64_t 
     }
     // Sixteen rows to a wavefront while the chip holds about all workgroups of 64 rows at once: half the work in a tile, where the chain
     // of a wavefront's tiles is what counts; more of them would load K and V twice as often.  us, 32 / 16 rows (workgroups of 64, the heads
-    // rounded up to the XCDs: one with a head more than the others decides):
+    // rounded up to the XCDs: one with a head more than the others decides).  At head size 128 the line is where all of them are resident, four to
+    // a unit, for long sequences: with as many workgroups of fewer heads, the longest chain of tiles is more of the launch, and half the work in
+    // its tiles counts for more than twice the loads; for short ones it is lower.
     //   heads of 64:  8 x  192,  7  5.6 /  5.0 (168)    1 x 4096,  9 54.5 / 44.1 (1024)   3 x 2000, 13 29.9 / 29.7 (1280)
     //                 2 x 2048, 20 34.4 / 33.0 (1280)   4 x 3904,  5 57.8 / 59.3 (1464)   8 x 1024, 12 21.2 / 22.2 (1536)
     //   of 128:       4 x  333,  6 10.3 /  7.8 (144)    1 x 2048,  8 39.8 / 28.5 (256)    7 x  868,  8 23.3 / 19.6 (784)
@@ -945,8 +950,8 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
         attr_set = true;
     }
     // One launch for both gradients while its workgroups are at most a little more than the chip holds at once, with 16 rows to a
-    // wavefront as in the forward pass while it holds about twice the workgroups of 64 rows (and for short sequences, of whose blocks of
-    // more rows much is empty).  Forward and backward, us (workgroups of 64 rows on either side):
+    // wavefront as in the forward pass while it holds about twice the workgroups of 64 rows (and up to 256 rows of a sequence nearly twice as
+    // many of them: a block of 128 or 256 rows is a whole sequence or half of one there, most of whose products the mask throws away).  Forward and backward, us (workgroups of 64 rows on either side):
     //   32 rows, as in the launches below them / 16 rows
     //     heads of 64:  5 x 145, 22 19.1 / 16.1 (330)    8 x 512, 12 38.9 / 34.2 (768)    1 x 4096, 8 150 / 120 (512)    8 x 300, 20 34.4 / 30.7 (800)
     //                   8 x 256, 52 59.0 / 56.0 (1664)   6 x 512, 24 52.1 / 53.0 (1152)   8 x 1024, 8 64.1 / 66.1 (1024)
