@@ -916,8 +916,9 @@ struct Choice {
 // fifteenth, and 3 us for the second launch: the costs are good to 4 %.  Products under 40 us are left alone (and not kept waiting for
 // the comparison).  Of 40 products of random sizes that are cut, the slowest against one launch takes 1 % more, the quickest 17 % less, 6.6 %
 // less on average.  us, one launch / two, each product repeated by itself: 1021 x 50257 x 768 103 / 90 (among the other products of its
-// layer, with nothing of its operands in the caches, 106 / 104, and 50257 x 768 x 1021 93 / 87), 50257 x 768 x 8192 524 / 489 (both operands k-major), 4224 x 12277 x 4778
-// 463 / 394, 6208 x 2880 x 19392 650 / 536, 16000 x 3136 x 2319 216 / 184, 1792 x 9664 x 704 34.8 / 30.4; 4340 x 9232 x 1970 148.7 / 150.0.
+// layer, with nothing of its operands in the caches, 106 / 104, and 50257 x 768 x 1021 93 / 87), 50257 x 768 x 8192 524 / 489 (both operands
+// k-major), 4224 x 12277 x 4778 463 / 394, 6208 x 2880 x 19392 650 / 536, 16000 x 3136 x 2319 216 / 184, 1792 x 9664 x 704 34.8 / 30.4; 4340 x
+// 9232 x 1970 148.7 / 150.0.
 struct Plan {
     const TileChoice *first, *rest = nullptr;
     int64_t rows = 0, cols = 0;
