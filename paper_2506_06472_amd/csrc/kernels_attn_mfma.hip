@@ -613,8 +613,8 @@ __global__ void __launch_bounds__(NT, DH == 64 ? 3 : 2) attn_bwd_dq_mfma_k(const
 // accumulators and K fragments of 32 key rows take 160 of the 256 registers that two wavefronts per SIMD allow at head size 128,
 // so the V fragments are not kept in registers there but read from LDS (the workgroup's V rows, loaded once); to have room for
 // them, and half the tile loads per product, a workgroup is eight wavefronts with 256 key rows.  Bound: latency between the
-// products of two wavefronts per SIMD (three at head size 64), a third of their cycles, and power.  Nothing may spill: a reload from scratch in the loop waits for the tile
-// loads in flight, and the wavefront with it keeps the others at the barrier.  So the offsets of the reads are one register and an
+// products of two wavefronts per SIMD (three at head size 64), a third of their cycles, and power.  Nothing may spill: a reload from
+// scratch in the loop waits for the tile loads in flight, and the wavefront with it keeps the others at the barrier.  So the offsets of the reads are one register and an
 // exclusive or each at head size 128, each of two wavefronts fetches one of the statistics, and the lane index is computed where it is used.
 // The tiles behind the diagonal run through a loop of their own, without mask and branch; at head size 64 a second loop gains nothing
 // over a mask of two instructions.
@@ -951,7 +951,8 @@ void attn_bwd_mfma(hipStream_t s, const void *dO, const void *qkv, const void *O
     }
     // One launch for both gradients while its workgroups are at most a little more than the chip holds at once, with 16 rows to a
     // wavefront as in the forward pass while it holds about twice the workgroups of 64 rows (and up to 256 rows of a sequence nearly twice as
-    // many of them: a block of 128 or 256 rows is a whole sequence or half of one there, most of whose products the mask throws away).  Forward and backward, us (workgroups of 64 rows on either side):
+    // many of them: a block of 128 or 256 rows is a whole sequence or half of one there, most of whose products the mask throws away).
+    // Forward and backward, us (workgroups of 64 rows on either side):
     //   32 rows, as in the launches below them / 16 rows
     //     heads of 64:  5 x 145, 22 19.1 / 16.1 (330)    8 x 512, 12 38.9 / 34.2 (768)    1 x 4096, 8 150 / 120 (512)    8 x 300, 20 34.4 / 30.7 (800)
     //                   8 x 256, 52 59.0 / 56.0 (1664)   6 x 512, 24 52.1 / 53.0 (1152)   8 x 1024, 8 64.1 / 66.1 (1024)
